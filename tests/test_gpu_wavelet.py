@@ -110,3 +110,34 @@ def test_denoise_levels_and_thin_cubes_bitwise(dev, shape, levels):
         y, _ = ig.wavelet_denoise(torch.from_numpy(cube).to(dev), name, levels, t, rms=rms)
         ref = Wv.denoise(cube, kind, levels, t, rms=rms, dtype=np.float32)
         assert np.array_equal(y.cpu().numpy(), ref), (name, shape, levels)
+
+
+# the one-launch Haar kernel: cubes at and around its tiles (128 x 8 x 8 above
+# 64 voxels in x and up to three levels, else 32 x 16 x 16), axes shorter than
+# a block, every level count it serves and the first that it does not
+@pytest.mark.parametrize("levels", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("shape", [(8, 8, 128), (9, 7, 129), (17, 16, 127), (16, 17, 64), (15, 33, 65), (33, 31, 33),
+                                   (1, 40, 259), (2, 1, 31), (19, 3, 1)])
+def test_haar_one_launch_bitwise(dev, shape, levels):
+    import torch
+    import paper_1609_03782_amd as ig
+    x = igsynth.random_cube(shape, seed=levels + sum(shape))
+    xt = torch.from_numpy(x).to(dev)
+    t = (0.4, 0.7, 0.9, 1.2, 1.3)[:levels]
+    c = ig.wavelet_forward(xt, "haar", levels)
+    ref = Wv.forward(x, Wv.HAAR, levels, np.float32)
+    assert np.array_equal(c.cpu().numpy(), ref)
+    assert np.array_equal(ig.wavelet_inverse(c, "haar", levels).cpu().numpy(),
+                          Wv.inverse(ref, Wv.HAAR, levels, np.float32))
+    # in place the transforms run the axis passes: the same values
+    p = xt.clone()
+    ig.wavelet_forward(p, "haar", levels, out=p)
+    assert torch.equal(p, c)
+    ig.wavelet_inverse(p, "haar", levels, out=p)
+    assert torch.equal(p, ig.wavelet_inverse(c, "haar", levels))
+    want = Wv.denoise(x, Wv.HAAR, levels, t, rms=0.8, dtype=np.float32)
+    y, _ = ig.wavelet_denoise(xt, "haar", levels, t, rms=0.8)
+    assert np.array_equal(y.cpu().numpy(), want)
+    assert np.array_equal(xt.cpu().numpy(), x)
+    ig.wavelet_denoise(xt, "haar", levels, t, rms=0.8, out=xt)
+    assert np.array_equal(xt.cpu().numpy(), want)
