@@ -39,7 +39,10 @@ extern "C" int64_t ig_debug_set_infer_piece_limit(int64_t voxels) {
 
 namespace {
 
-constexpr long kWgradGroups = 512;   // workgroups of the weight-gradient kernel (at most)
+// Workgroups of the weight-gradient kernels (at most): one per compute unit of
+// the 32-channel kernel (108 KB of LDS each), two of the 1-channel one.  Fixed,
+// so a gradient does not depend on the device it was computed on.
+constexpr long kWgradGroups32 = 256, kWgradGroups1 = 512;
 
 struct Dev {
     void* p = nullptr;
@@ -60,8 +63,22 @@ struct Dev {
     template <typename T> T* as() const { return static_cast<T*>(p); }
 };
 
-long wgrad_units(long nx, long ny, long nz) { return ((nx + TX - 1) / TX) * ((ny + TY - 1) / TY) * nz; }
-long wgrad_groups(long nx, long ny, long nz) { return std::min(kWgradGroups, wgrad_units(nx, ny, nz)); }
+// Weight-gradient partials: workgroups and floats of one (weights, then biases).
+struct WgradPlan {
+    int ntx, nty;
+    long groups, stride, lenw, len;
+};
+WgradPlan wgrad_plan(int cin, int cout, long nx, long ny, long nz) {
+    WgradPlan w;
+    w.ntx = (int)((nx + kWgX - 1) / kWgX);
+    w.nty = (int)((ny + kWgY - 1) / kWgY);
+    const bool both = cin == 32 && cout == 32;
+    w.groups = std::min(both ? kWgradGroups32 : kWgradGroups1, (long)w.ntx * w.nty * nz);
+    w.lenw = 27L * cin * cout;
+    w.len = w.lenw + cout;
+    w.stride = both ? w.len : 28L * std::max(cin, cout);
+    return w;
+}
 
 // Grid of the z-streaming kernels (tiles of xw voxels by kZsRows rows, one
 // workgroup per (tile, z chunk)): the z chunk that minimises the slowest
@@ -172,38 +189,33 @@ size_t packed_count(int cin, int cout, int mode) {
 }
 
 // weight gradient of a conv with cin (1 or 32) inputs and cout (1 or 32)
-// outputs: per-workgroup partials, then a fixed-order fold into dW [27*cin][COUTP]
-// and db [COUTP] (COUTP = 32, or 16 for one output: column 0 is the gradient)
-hipError_t launch_wgrad(int cin, int cout, const void* a, const void* dz, Dev& part, Dev& partb, float* dW, float* db,
+// outputs: per-workgroup partials, then a fixed-order fold into dW [27][cin][cout]
+// and db [cout]
+hipError_t launch_wgrad(int cin, int cout, const void* a, const void* dz, Dev& part, float* dW, float* db,
                         int accumulate, long nx, long ny, long nz, hipStream_t s) {
-    const long units = wgrad_units(nx, ny, nz);
-    const long nwg = wgrad_groups(nx, ny, nz);
-    const int ntx = (int)((nx + TX - 1) / TX), nty = (int)((ny + TY - 1) / TY);
-    const dim3 g((unsigned)nwg);
-    const int NB = cout > 16 ? 2 : 1, COUTP = 16 * NB;
-    hipError_t e = part.ensure((size_t)nwg * 27 * cin * COUTP * sizeof(float));
-    if (e == hipSuccess) e = partb.ensure((size_t)nwg * COUTP * sizeof(float));
+    const WgradPlan w = wgrad_plan(cin, cout, nx, ny, nz);
+    hipError_t e = part.ensure((size_t)w.groups * w.stride * sizeof(float));
     if (e != hipSuccess) return e;
     const u16* A = static_cast<const u16*>(a);
     const u16* D = static_cast<const u16*>(dz);
-    if (cin == 32 && NB == 2) hipLaunchKernelGGL((k_wgrad<32, 2>), g, dim3(256), 0, s, A, D, cout, part.as<float>(), partb.as<float>(), (int)nx, (int)ny, (int)nz, ntx, nty, units);
-    else if (cin == 32) hipLaunchKernelGGL((k_wgrad<32, 1>), g, dim3(256), 0, s, A, D, cout, part.as<float>(), partb.as<float>(), (int)nx, (int)ny, (int)nz, ntx, nty, units);
-    else if (NB == 2) hipLaunchKernelGGL((k_wgrad<1, 2>), g, dim3(256), 0, s, A, D, cout, part.as<float>(), partb.as<float>(), (int)nx, (int)ny, (int)nz, ntx, nty, units);
-    else hipLaunchKernelGGL((k_wgrad<1, 1>), g, dim3(256), 0, s, A, D, cout, part.as<float>(), partb.as<float>(), (int)nx, (int)ny, (int)nz, ntx, nty, units);
+    const dim3 g((unsigned)w.groups), b(kWgThreads);
+    const int x = (int)nx, y = (int)ny, z = (int)nz;
+    if (cin == 32 && cout == 32) {
+        e = hipFuncSetAttribute((const void*)k_wgrad32, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kWgLds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_wgrad32, g, b, kWgLds, s, A, D, part.as<float>(), x, y, z, w.ntx, w.nty);
+    } else if (cin == 32) {
+        hipLaunchKernelGGL(k_wgrad1<32>, g, b, 0, s, A, D, 1, part.as<float>(), x, y, z, w.ntx, w.nty);
+    } else if (cout == 32) {
+        hipLaunchKernelGGL(k_wgrad1<32>, g, b, 0, s, D, A, 0, part.as<float>(), x, y, z, w.ntx, w.nty);
+    } else {
+        hipLaunchKernelGGL(k_wgrad1<1>, g, b, 0, s, D, A, 0, part.as<float>(), x, y, z, w.ntx, w.nty);
+    }
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const long len = 27L * cin * COUTP;
-    hipLaunchKernelGGL(k_wgrad_fold, dim3((len + 63) / 64), dim3(256), 0, s, part.as<float>(), nwg, len, dW, accumulate);
-    hipLaunchKernelGGL(k_wgrad_fold, dim3(1), dim3(256), 0, s, partb.as<float>(), nwg, (long)COUTP, db, accumulate);
+    hipLaunchKernelGGL(k_wgrad_fold, dim3((unsigned)((w.len + 63) / 64)), dim3(1024), 0, s, part.as<float>(), w.groups,
+                       w.stride, w.lenw, w.len, dW, db, accumulate);
     return hipGetLastError();
-}
-
-__global__ void k_unpad(const float* __restrict__ src, int rows, int colsp, int cols, float* __restrict__ dst,
-                        int accumulate) {
-    const int q = blockIdx.x * 256 + threadIdx.x;
-    if (q >= rows * cols) return;
-    const int r = q / cols, c = q % cols;
-    dst[q] = accumulate ? dst[q] + src[r * colsp + c] : src[r * colsp + c];
 }
 
 __global__ void k_fill(float* __restrict__ p, long n, float v) {
@@ -264,7 +276,7 @@ struct ig_surrogate {
     // activations, sized for the largest cube seen
     long cap = 0;
     std::vector<Dev> act, pre;          // act[0] 1 channel, act[1..L-1] 32; pre[1..L-1]
-    Dev y, dy, dzA, dzB, part, partb, parts, sub_x, sub_y, tmp;
+    Dev y, dy, dzA, dzB, part, parts, sub_x, sub_y, tmp;
     // inference: the bf16 input and two 32-channel buffers used in turn
     long icap = 0;
     Dev iact0, iact[2];
@@ -457,18 +469,16 @@ extern "C" ig_status ig_surrogate_train_step(ig_surrogate* s, const float* const
     }
     ig_status rc = ensure_acts(s, n);
     if (rc != IG_OK) return rc;
-    {   // weight-gradient partials for the largest layer, sized before any launch
-        const long nwg = wgrad_groups(nx, ny, nz);
-        HIP_TRY(s->part.ensure((size_t)nwg * 27 * 32 * 32 * sizeof(float)));
-        HIP_TRY(s->partb.ensure((size_t)nwg * 32 * sizeof(float)));
+    for (int l = 0; l < s->L; ++l) {   // weight-gradient partials for the largest layer, sized before any launch
+        const WgradPlan w = wgrad_plan(s->cin[l], s->cout[l], nx, ny, nz);
+        HIP_TRY(s->part.ensure((size_t)w.groups * w.stride * sizeof(float)));
     }
     const long np = (long)s->nparam;
     hipLaunchKernelGGL(k_fill, dim3((np + 255) / 256), dim3(256), 0, st, s->grads.as<float>(), np, 0.0f);
     HIP_TRY(hipGetLastError());
     const int nloss = 256;
-    HIP_TRY(s->tmp.ensure((size_t)batch * nloss * sizeof(double) + 64 * 1024 * 4));
+    HIP_TRY(s->tmp.ensure((size_t)batch * nloss * sizeof(double)));
     double* lparts = s->tmp.as<double>();
-    float* padbuf = reinterpret_cast<float*>(lparts + (size_t)batch * nloss);   // [27*32][16] for 1-output layers
     const double scale = 1.0 / ((double)n * batch);
     for (int k = 0; k < batch; ++k) {
         if (!d_x[k] || !d_t[k]) return fail(IG_ERR_INVALID_ARG, "NULL cube %d", k);
@@ -484,16 +494,7 @@ extern "C" ig_status ig_surrogate_train_step(ig_surrogate* s, const float* const
         for (int l = s->L - 1; l >= 0; --l) {
             float* dW = s->grads.as<float>() + s->w_off[l];
             float* db = s->grads.as<float>() + s->b_off[l];
-            if (s->cout[l] == 32) {
-                HIP_TRY(launch_wgrad(s->cin[l], 32, s->act[l].p, g, s->part, s->partb, dW, db, 1, nx, ny, nz, st));
-            } else {   // 1 output channel: fold into a 16-column buffer, then keep column 0
-                HIP_TRY(launch_wgrad(s->cin[l], 1, s->act[l].p, g, s->part, s->partb, padbuf, padbuf + 27 * 32 * 16, 0,
-                                     nx, ny, nz, st));
-                const int rows = 27 * s->cin[l];
-                hipLaunchKernelGGL(k_unpad, dim3((rows + 255) / 256), dim3(256), 0, st, padbuf, rows, 16, 1, dW, 1);
-                hipLaunchKernelGGL(k_unpad, dim3(1), dim3(256), 0, st, padbuf + 27 * 32 * 16, 1, 16, 1, db, 1);
-                HIP_TRY(hipGetLastError());
-            }
+            HIP_TRY(launch_wgrad(s->cin[l], s->cout[l], s->act[l].p, g, s->part, dW, db, 1, nx, ny, nz, st));
             if (l > 0) {   // gradient of the layer's input, through gelu' of the layer below
                 void* dst = (g == s->dzA.p) ? s->dzB.p : s->dzA.p;
                 HIP_TRY(launch_conv(s->cout[l], s->cin[l], EPI_BACK_GELU, g, s->pk_d[l].as<bf16x8>(), nullptr, dst,
@@ -865,18 +866,8 @@ extern "C" ig_status ig_conv3d_weight_grad(const void* d_a, int32_t c_in, const 
     if (nx < 1 || ny < 1 || nz < 1) return fail(IG_ERR_INVALID_ARG, "bad shape");
     if (nx * ny * nz >= kMaxConvVox) return fail(IG_ERR_INVALID_ARG, "cube too large: voxels x 32 must stay below 2^31");
     hipStream_t st = (hipStream_t)hip_stream;
-    Dev part, partb, pad;
-    if (c_out == 32) {
-        HIP_TRY(launch_wgrad(c_in, 32, d_a, d_dz, part, partb, d_dw, d_db, 0, nx, ny, nz, st));
-    } else {
-        HIP_TRY(pad.ensure((27 * 32 * 16 + 16) * 4));
-        float* pw = pad.as<float>();
-        HIP_TRY(launch_wgrad(c_in, 1, d_a, d_dz, part, partb, pw, pw + 27 * 32 * 16, 0, nx, ny, nz, st));
-        const int rows = 27 * c_in;
-        hipLaunchKernelGGL(k_unpad, dim3((rows + 255) / 256), dim3(256), 0, st, pw, rows, 16, 1, d_dw, 0);
-        hipLaunchKernelGGL(k_unpad, dim3(1), dim3(256), 0, st, pw + 27 * 32 * 16, 1, 16, 1, d_db, 0);
-        HIP_TRY(hipGetLastError());
-    }
+    Dev part;
+    HIP_TRY(launch_wgrad(c_in, c_out, d_a, d_dz, part, d_dw, d_db, 0, nx, ny, nz, st));
     HIP_TRY(hipStreamSynchronize(st));
     return IG_OK;
 }

@@ -34,15 +34,6 @@ typedef unsigned short u16;
 
 enum { EPI_RAW = 0, EPI_GELU = 1, EPI_BACK_GELU = 2, EPI_RESID = 3 };
 
-constexpr int TX = 32;   // output tile: 32 voxels in x (two 16-row MFMA tiles) ...
-constexpr int TY = 4;    // ... by 4 rows in y (one per wavefront), one plane in z
-
-// LDS stride of one voxel's channels: 32 channels padded to 40 (80 bytes), so
-// the 16 lanes of one pass of a 16-byte LDS read (16 consecutive voxels, one
-// 8-channel group) start 20 banks apart and cover all 64 banks once; at 64
-// bytes they would meet on the same 4 banks (4-way conflicts).
-template <int C> constexpr int lds_stride() { return C == 32 ? 40 : C; }
-
 __device__ __forceinline__ float bf2f(u16 h) { return __uint_as_float((unsigned)h << 16); }
 __device__ __forceinline__ u16 f2bf(float f) {   // round to nearest, ties to even (finite inputs)
     unsigned u = __float_as_uint(f);
@@ -530,188 +521,373 @@ k_conv_out1(const u16* __restrict__ in, const bf16x8* __restrict__ wp, const flo
 }
 
 // ---------------------------------------------------------- weight grad
-// Partial dW of one workgroup: a contiguous range of "tile-planes" (32 x 4
-// voxels of one plane; unit u = (z * nty + ty) * ntx + tx), the same fixed
-// split of the units for every call, so the partials and their fold are
-// deterministic.  Few workgroups (a couple per CU), each over many units, keep
-// the partials (and the fold that reads them) small.
-// CIN == 32: rows = input channels, each wavefront owns taps t = w, w+4, ...
-// CIN == 1:  rows = taps (27, padded to 32), one set of accumulators.
-// COUT = 32 (NB = 2) or 1 (NB = 1, only column 0 non-zero).
-// part[wg][27*CIN][COUTP] in FP32; bias partials in part_b[wg][COUTP].
-template <int CIN, int NB>
-__global__ void __launch_bounds__(256)
-k_wgrad(const u16* __restrict__ a, const u16* __restrict__ dz, int cout, float* __restrict__ part,
-        float* __restrict__ part_b, int nx, int ny, int nz, int ntx, int nty, long units) {
-    constexpr int COUTP = 16 * NB;
-    constexpr int LX = TX + 2, LY = TY + 2;
-    constexpr int NT = CIN == 32 ? 7 : 1;           // taps per wavefront (CIN == 32)
-    constexpr int CS = lds_stride<CIN>();
-    __shared__ __attribute__((aligned(16))) u16 at[3 * LY * LX * CS];
-    __shared__ __attribute__((aligned(16))) u16 gt[TY * TX * COUTP];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int i = lane & 15, kg = lane >> 4;
-    const long wg = blockIdx.x;
-    const long u0 = wg * units / gridDim.x, u1 = (wg + 1) * units / gridDim.x;
+// dW[t][c][n] = sum over voxels v of a[v + t][c] dz[v][n]: the matrix cores sum
+// over K = 32 voxels of a row, so both operands are wanted voxel-minor while
+// memory holds them channel-minor.  gfx950's transposing LDS read
+// (ds_read_b64_tr_b16) does that: of each 16 lanes, lane l passes the address
+// of voxel l / 4, channels 4 (l % 4) .., and receives channel l of the four
+// voxels, so two reads make one operand fragment at the full LDS rate.
+//
+// Work: the cube is cut into tiles of 32 x 8 voxels and the sequence (tile,
+// plane) is dealt to the workgroups in equal contiguous runs, the same for
+// every call; a workgroup streams the planes of its runs with its sums in
+// registers throughout, and writes one partial.  The partials are folded in
+// a fixed order, so the gradient is bitwise reproducible.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+constexpr int kWgX = 32, kWgY = 8;                          // tile
+constexpr int kWgThreads = 512;
+constexpr int kWgLX = kWgX + 2, kWgLY = kWgY + 2;           // with the margin
+constexpr int kWgPlA = kWgLX * kWgLY * 32, kWgPlB = kWgX * kWgY * 32;   // u16 of a staged plane
+constexpr size_t kWgLds = (size_t)4 * 27 * 64 * 16;         // the final exchange; the four staged planes fit in it
+static_assert(kWgLds >= (size_t)2 * (kWgPlA + kWgPlB) * 2, "staging fits the exchange buffer");
 
-    // accumulators: CIN == 32 -> [tap slot][channel subtile][nb]; CIN == 1 -> [tap subtile][nb]
-    constexpr int MS = 2;
-    f32x4 acc[NT][MS][NB];
-#pragma unroll
-    for (int q = 0; q < NT; ++q)
-#pragma unroll
-        for (int ms = 0; ms < MS; ++ms)
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) acc[q][ms][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float bsum = 0.0f;   // bias gradient of channel threadIdx.x (< COUTP), this workgroup
-
-    for (long u = u0; u < u1; ++u) {
-        const int x0 = (int)(u % ntx) * TX, y0 = (int)((u / ntx) % nty) * TY, z0 = (int)(u / ((long)ntx * nty));
-        __syncthreads();
-        // stage activations (with margin, zero outside) and the output gradient tile
-        if constexpr (CIN % 8 == 0) {
-            constexpr int CH = CIN / 8;
-            for (int q = threadIdx.x; q < 3 * LY * LX * CH; q += 256) {
-                const int c = q % CH, vox = q / CH;
-                const int xx = vox % LX, yy = (vox / LX) % LY, zz = vox / (LX * LY);
-                const int x = x0 + xx - 1, y = y0 + yy - 1, z = z0 + zz - 1;
-                uint4 v = make_uint4(0, 0, 0, 0);
-                if (x >= 0 && x < nx && y >= 0 && y < ny && z >= 0 && z < nz)
-                    v = *reinterpret_cast<const uint4*>(a + ((long)(z * ny + y) * nx + x) * CIN + 8 * c);
-                *reinterpret_cast<uint4*>(at + vox * CS + 8 * c) = v;
-            }
-        } else {
-            for (int vox = threadIdx.x; vox < 3 * LY * LX; vox += 256) {
-                const int xx = vox % LX, yy = (vox / LX) % LY, zz = vox / (LX * LY);
-                const int x = x0 + xx - 1, y = y0 + yy - 1, z = z0 + zz - 1;
-                at[vox] = (x >= 0 && x < nx && y >= 0 && y < ny && z >= 0 && z < nz)
-                              ? a[(long)(z * ny + y) * nx + x] : (u16)0;
-            }
-        }
-        for (int q = threadIdx.x; q < TY * TX * COUTP; q += 256) {
-            const int n = q % COUTP, vox = q / COUTP;
-            const int xx = vox % TX, yy = vox / TX;
-            const int x = x0 + xx, y = y0 + yy;
-            u16 g = 0;
-            if (x < nx && y < ny && n < cout) g = dz[((long)(z0 * ny + y) * nx + x) * cout + n];
-            gt[q] = g;
-        }
-        __syncthreads();
-        if (threadIdx.x < COUTP) {
-            for (int vox = 0; vox < TY * TX; ++vox) bsum += bf2f(gt[vox * COUTP + threadIdx.x]);
-        }
-        // K-steps: 32 voxels = one row (yy) of the tile
-        for (int yy = 0; yy < TY; ++yy) {
-            // B: gradient of voxels 8*kg .. 8*kg+7 of row yy, output channel 16*nb + i
-            bf16x8 b[NB];
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    b[nb][e] = __builtin_bit_cast(__bf16, gt[(yy * TX + 8 * kg + e) * COUTP + 16 * nb + i]);
-            if constexpr (CIN == 32) {
-#pragma unroll
-                for (int q = 0; q < NT; ++q) {
-                    const int t = w + 4 * q;
-                    if (t < 27) {
-                        const int dz_ = t / 9, dy = (t / 3) % 3, dx = t % 3;
-#pragma unroll
-                        for (int ms = 0; ms < MS; ++ms) {
-                            bf16x8 av;   // A[c = 16*ms + i][k = voxel 8*kg + e]
-#pragma unroll
-                            for (int e = 0; e < 8; ++e) {
-                                const int vox = (dz_ * LY + (yy + dy)) * LX + (8 * kg + e + dx);
-                                av[e] = __builtin_bit_cast(__bf16, at[vox * CS + 16 * ms + i]);
-                            }
-#pragma unroll
-                            for (int nb = 0; nb < NB; ++nb)
-                                acc[q][ms][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, b[nb], acc[q][ms][nb], 0, 0, 0);
-                        }
-                    }
-                }
-            } else {
-                if (w == 0) {
-#pragma unroll
-                    for (int ms = 0; ms < MS; ++ms) {
-                        bf16x8 av;   // A[t = 16*ms + i][k = voxel]
-                        const int t = 16 * ms + i;
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            u16 h = 0;
-                            if (t < 27) {
-                                const int dz_ = t / 9, dy = (t / 3) % 3, dx = t % 3;
-                                h = at[(dz_ * LY + (yy + dy)) * LX + (8 * kg + e + dx)];
-                            }
-                            av[e] = __builtin_bit_cast(__bf16, h);
-                        }
-#pragma unroll
-                        for (int nb = 0; nb < NB; ++nb)
-                            acc[0][ms][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, b[nb], acc[0][ms][nb], 0, 0, 0);
-                    }
-                }
-            }
-        }
-    }
-    // write this workgroup's partials: row r = t*CIN + c (CIN == 32) or t (CIN == 1)
-    float* P = part + wg * (27L * CIN * COUTP);
-    if constexpr (CIN == 32) {
-#pragma unroll
-        for (int q = 0; q < NT; ++q) {
-            const int t = w + 4 * q;
-            if (t >= 27) continue;
-#pragma unroll
-            for (int ms = 0; ms < MS; ++ms)
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int c = 16 * ms + 4 * kg + e, n = 16 * nb + i;
-                        P[(t * 32 + c) * COUTP + n] = acc[q][ms][nb][e];
-                    }
-        }
-    } else {
-        if (w == 0) {
-#pragma unroll
-            for (int ms = 0; ms < MS; ++ms)
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int t = 16 * ms + 4 * kg + e, n = 16 * nb + i;
-                        if (t < 27) P[t * COUTP + n] = acc[0][ms][nb][e];
-                    }
-        }
-    }
-    if (threadIdx.x < COUTP) part_b[wg * COUTP + threadIdx.x] = bsum;
+// the fragment [voxels 8 kg ..][channel l % 16] at p = (voxel 8 kg + (l % 16) / 4,
+// channels 4 (l % 4) ..) of rows of 32 channels
+__device__ __forceinline__ bf16x8 tr_frag(const u16* p) {
+    typedef __attribute__((address_space(3))) s16x4* lp;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(p));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(p + 4 * 32));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-// dW[j] (+)= sum over workgroups of part[wg][j] in a fixed order: wavefront
-// q of the block sums the workgroups [q nwg/4, (q+1) nwg/4) in order for 64
-// consecutive j (eight loads in flight), then the four sums are added in
-// order q = 0..3.
-__global__ void __launch_bounds__(256)
-k_wgrad_fold(const float* __restrict__ part, long nwg, long len, float* __restrict__ dst, int accumulate) {
-    __shared__ float sh[4][64];
+// 32 input and 32 output channels.  Wavefront (ms, nb, h) owns input channels
+// 16 ms .., output channels 16 nb .. and the tile rows 4 h .. 4 h + 3, with the
+// sums of all 27 taps in registers (108).  Per input plane z' it reads each
+// activation fragment (row, dx) once and multiplies it with the gradient rows
+// of planes z' - 1, z', z' + 1 that it meets, which stay in registers while the
+// planes pass (each read from LDS once): 22 fragment reads for 108 products,
+// where a read per operand would take 216.  Bound by the matrix cores: 3456
+// cycles of MFMA per tile plane against 1400 of LDS reads.  The two row halves
+// are added through LDS at the end, half 0 first.  The bias gradient is one
+// more product with a fragment of ones.  96^3 voxels: 263 -> 56 us (870
+// TFLOP/s) against 2-byte gathered LDS reads, one pair of fragments per product.
+__global__ void __launch_bounds__(kWgThreads)
+k_wgrad32(const u16* __restrict__ a, const u16* __restrict__ dz, float* __restrict__ part, int nx, int ny, int nz,
+          int ntx, int nty) {
+    extern __shared__ uint4 wg_smem[];
+    u16* As = reinterpret_cast<u16*>(wg_smem);   // two planes of activations, then two of gradients
+    u16* Bs = As + 2 * kWgPlA;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int ms = w & 1, nb = (w >> 1) & 1, h = w >> 2;
+    const int i = lane & 15, kg = lane >> 4;
+    const int frag = (8 * kg + i / 4) * 32 + 4 * (i & 3);
+    const u16* Ab = As + 4 * h * kWgLX * 32 + frag + 16 * ms;
+    const u16* Bb = Bs + 4 * h * kWgX * 32 + frag + 16 * nb;
+
+    f32x4 acc[27], accb = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 27; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 ones;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
+
+    const long units = (long)ntx * nty * nz;
+    const long u0 = blockIdx.x * units / gridDim.x, u1 = (blockIdx.x + 1) * units / gridDim.x;
+    for (long u = u0; u < u1;) {
+        const int tile = (int)(u / nz), z0 = (int)(u % nz);
+        const int np = (int)min((long)(nz - z0), u1 - u);      // planes of this run in this tile
+        const int x0 = tile % ntx * kWgX, y0 = tile / ntx * kWgY;
+        u += np;
+        // the 16-byte chunks this thread stages: byte offsets from the tile's
+        // first row of a plane (below 2^32: the cube has fewer than 2^26
+        // voxels), clamped into the cube; `ok` bits: the chunk lies in it
+        uint4 sa[3], sb[2];
+        unsigned oa[3], ob[2];
+        int ok = 0;
+        const int yb = max(y0 - 1, 0);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const int q = tid + kWgThreads * k, vox = q >> 2;
+            const int x = x0 + vox % kWgLX - 1, y = y0 + vox / kWgLX - 1;
+            if (x >= 0 && x < nx && y >= 0 && y < ny) ok |= 1 << k;
+            oa[k] = (unsigned)(((long)(min(max(y, 0), ny - 1) - yb) * nx + min(max(x, 0), nx - 1)) * 64 + 16 * (q & 3));
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int q = tid + kWgThreads * k, vox = q >> 2;
+            const int x = x0 + vox % kWgX, y = y0 + vox / kWgX;
+            if (x < nx && y < ny) ok |= 8 << k;
+            ob[k] = (unsigned)(((long)(min(y, ny - 1) - yb) * nx + min(x, nx - 1)) * 64 + 16 * (q & 3));
+        }
+        auto fetch_a = [&](int z) {
+            const char* base = reinterpret_cast<const char*>(a) + ((long)min(max(z, 0), nz - 1) * ny + yb) * nx * 64;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) sa[k] = *reinterpret_cast<const uint4*>(base + oa[k]);
+        };
+        auto fetch_b = [&](int z) {
+            const char* base = reinterpret_cast<const char*>(dz) + ((long)z * ny + yb) * nx * 64;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) sb[k] = *reinterpret_cast<const uint4*>(base + ob[k]);
+        };
+        auto put_a = [&](int slot, int z) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const int q = tid + kWgThreads * k;
+                const bool in = ((ok >> k) & 1) && z >= 0 && z < nz;
+                if (q < kWgLX * kWgLY * 4) reinterpret_cast<uint4*>(As + slot * kWgPlA)[q] = in ? sa[k] : make_uint4(0, 0, 0, 0);
+            }
+        };
+        auto put_b = [&](int slot) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+                reinterpret_cast<uint4*>(Bs + slot * kWgPlB)[tid + kWgThreads * k] = (ok >> (3 + k)) & 1 ? sb[k] : make_uint4(0, 0, 0, 0);
+        };
+        fetch_a(z0 - 1);
+        fetch_b(z0);
+        put_a(0, z0 - 1);
+        put_b(0);
+        __syncthreads();
+        // step s: input plane z0 - 1 + s (LDS slot s mod 2) meets the gradient
+        // planes z0 + s (tap dz = 0; LDS slot s mod 2, read here into registers
+        // B[s mod 3]), z0 + s - 1 (dz = 1) and z0 + s - 2 (dz = 2), those of
+        // them that lie in the run
+        bf16x8 B[3][4];
+        auto step = [&](int s, auto rot) {
+            constexpr int R0 = decltype(rot)::value, R1 = (R0 + 2) % 3, R2 = (R0 + 1) % 3;
+            const bool on0 = s < np, on1 = s >= 1 && s <= np, on2 = s >= 2;
+            if (s <= np) fetch_a(z0 + s);
+            if (s + 1 < np) fetch_b(z0 + s + 1);
+            const u16* A = Ab + (s & 1) * kWgPlA;
+            const u16* Bn = Bb + (s & 1) * kWgPlB;
+            // input rows 4 h - 1 + j, each at three shifts: fragment m = 3 j + dx,
+            // read two ahead of its products
+            bf16x8 f[3];
+            f[0] = tr_frag(A);
+            f[1] = tr_frag(A + 32);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) B[R0][r] = tr_frag(Bn + r * kWgX * 32);   // not used unless on0
+#pragma unroll
+            for (int m = 0; m < 18; ++m) {
+                const int j = m / 3, dx = m % 3;
+                if (m + 2 < 18) f[(m + 2) % 3] = tr_frag(A + ((m + 2) / 3 * kWgLX + (m + 2) % 3) * 32);
+                __builtin_amdgcn_sched_barrier(0);
+                auto taps = [&](int d, const bf16x8 (&b)[4]) {
+#pragma unroll
+                    for (int dy = 0; dy < 3; ++dy)
+                        if (j - dy >= 0 && j - dy < 4) {   // gradient row j - dy
+                            const int t = 9 * d + 3 * dy + dx;
+                            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[m % 3], b[j - dy], acc[t], 0, 0, 0);
+                        }
+                };
+                if (on2) taps(2, B[R2]);
+                if (on1) taps(1, B[R1]);
+                if (on0) taps(0, B[R0]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (ms == 0 && on1)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, B[R1][r], accb, 0, 0, 0);
+            if (s <= np) put_a((s + 1) & 1, z0 + s);
+            if (s + 1 < np) put_b((s + 1) & 1);
+            __syncthreads();
+        };
+        for (int s = 0; s <= np + 1; s += 3) {
+            step(s, std::integral_constant<int, 0>{});
+            if (s + 1 <= np + 1) step(s + 1, std::integral_constant<int, 1>{});
+            if (s + 2 <= np + 1) step(s + 2, std::integral_constant<int, 2>{});
+        }
+    }
+    // add the row halves and write the partial: W[27][32][32], then b[32]
+    float4* red = reinterpret_cast<float4*>(wg_smem) + (w & 3) * 27 * 64 + lane;
+    __shared__ float bred[2][16];
+    if (h == 1) {
+#pragma unroll
+        for (int t = 0; t < 27; ++t) red[t * 64] = __builtin_bit_cast(float4, acc[t]);
+        if (ms == 0 && kg == 0) bred[nb][i] = accb[0];
+    }
+    __syncthreads();
+    if (h == 1) return;
+    float* P = part + blockIdx.x * (27L * 1024 + 32);
+#pragma unroll
+    for (int t = 0; t < 27; ++t) {
+        const f32x4 o = __builtin_bit_cast(f32x4, red[t * 64]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) P[(t * 32 + 16 * ms + 4 * kg + e) * 32 + 16 * nb + i] = acc[t][e] + o[e];
+    }
+    if (ms == 0 && kg == 0) P[27 * 1024 + 16 * nb + i] = accb[0] + bred[nb][i];
+}
+
+// One side with a single channel: H[t][c] = sum over voxels v of p[v][c] q[v + t],
+// p with CP channels (32, or 1) and q with one.  The first layer's gradient is
+// H with p = dz and q = x; the last layer's, sum of a[v + t] dz[v], is H with p =
+// a and q = dz at the mirrored tap 26 - t (`mirror`).  M = the 27 taps, a row of
+// ones as tap 27 (the sums of p: the bias gradient when p = dz) and zeros; N =
+// channels; K = 32 voxels, one tile row per wavefront.  q's planes are staged
+// three times, shifted by dx, so a lane's 8 values are one aligned read.  With
+// mirror the bias gradient is the sum of q, kept per thread as it stages q.
+// Bound by reading p.  96^3 voxels: 15 us (3.8 TB/s), from 143
+// us (first layer) and 185 us (last) with gathered reads and padded products.
+constexpr int kWg1Row = 40;                                  // u16 per staged q row (32, padded to spread the banks)
+constexpr int kWg1Copy = kWgLY * kWg1Row, kWg1Pl = 3 * kWg1Copy;
+template <int CP>
+__global__ void __launch_bounds__(kWgThreads)
+k_wgrad1(const u16* __restrict__ p, const u16* __restrict__ q, int mirror, float* __restrict__ part, int nx, int ny,
+         int nz, int ntx, int nty) {
+    constexpr int NB = CP == 32 ? 2 : 1;
+    __shared__ __attribute__((aligned(16))) u16 Ps[2 * kWgPlB];
+    __shared__ __attribute__((aligned(16))) u16 Qs[4 * kWg1Pl + 16];   // + eight ones, eight zeros
+    __shared__ float qs[kWgThreads / 64];
+    static_assert(sizeof(Ps) >= (size_t)8 * 2 * NB * 64 * 16, "the final exchange fits the staged planes");
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int i = lane & 15, kg = lane >> 4;
+    if (tid < 16) Qs[4 * kWg1Pl + tid] = tid < 8 ? 0x3f80 : 0;
+    if (CP == 1)
+        for (int k = tid; k < 2 * kWgPlB / 8; k += kWgThreads) reinterpret_cast<uint4*>(Ps)[k] = make_uint4(0, 0, 0, 0);
+
+    // this lane's taps t = 16 m + i: plane offset dz (or -1: the constants) and place in the staged plane
+    int tz[2], to[2];
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        const int t = 16 * m + i;
+        tz[m] = t < 27 ? t / 9 : -1;
+        to[m] = t < 27 ? (t % 3) * kWg1Copy + (w + (t / 3) % 3) * kWg1Row + 8 * kg : 4 * kWg1Pl + (t == 27 ? 0 : 8);
+    }
+    const u16* Pb = Ps + (w * kWgX + 8 * kg + i / 4) * 32 + 4 * (i & 3);
+    f32x4 acc[2][NB];
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[m][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float qsum = 0.0f;
+
+    const long units = (long)ntx * nty * nz;
+    const long u0 = blockIdx.x * units / gridDim.x, u1 = (blockIdx.x + 1) * units / gridDim.x;
+    const int qc = tid % kWgLX, qr = tid / kWgLX;            // the q voxel this thread stages
+    const bool qon = tid < kWgLX * kWgLY;
+    const bool qin = qc >= 1 && qc <= kWgX && qr >= 1 && qr <= kWgY;
+    for (long u = u0; u < u1;) {
+        const int tile = (int)(u / nz), z0 = (int)(u % nz);
+        const int np = (int)min((long)(nz - z0), u1 - u);
+        const int x0 = tile % ntx * kWgX, y0 = tile / ntx * kWgY;
+        u += np;
+        const int qx = x0 + qc - 1, qy = y0 + qr - 1;
+        const bool qok = qon && qx >= 0 && qx < nx && qy >= 0 && qy < ny;
+        uint4 sp[2];
+        auto fetch_q = [&](int z) -> u16 { return qok && z >= 0 && z < nz ? q[((long)z * ny + qy) * nx + qx] : (u16)0; };
+        auto put_q = [&](int k, u16 v) {                     // plane z0 - 1 + k
+            if (qon)
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx)
+                    if (qc - dx >= 0 && qc - dx < kWgX) Qs[(k & 3) * kWg1Pl + dx * kWg1Copy + qr * kWg1Row + qc - dx] = v;
+            if (qin && k >= 1 && k <= np) qsum += bf2f(v);
+        };
+        auto fetch_p = [&](int z) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int c = tid + kWgThreads * k, vox = CP == 32 ? c >> 2 : c;
+                const int x = x0 + vox % kWgX, y = y0 + vox / kWgX;
+                sp[k] = make_uint4(0, 0, 0, 0);
+                if (vox < kWgX * kWgY && x < nx && y < ny) {
+                    const long v = ((long)z * ny + y) * nx + x;
+                    if constexpr (CP == 32) sp[k] = *reinterpret_cast<const uint4*>(p + v * 32 + 8 * (c & 3));
+                    else sp[k].x = p[v];
+                }
+            }
+        };
+        auto put_p = [&](int slot) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int c = tid + kWgThreads * k;
+                if constexpr (CP == 32) reinterpret_cast<uint4*>(Ps + slot * kWgPlB)[c] = sp[k];
+                else if (c < kWgX * kWgY) Ps[slot * kWgPlB + c * 32] = (u16)sp[k].x;
+            }
+        };
+        __syncthreads();   // the constants are written; the previous run is done with the planes
+        fetch_p(z0);
+        const u16 q0 = fetch_q(z0 - 1), q1 = fetch_q(z0), q2 = fetch_q(z0 + 1);
+        put_q(0, q0);
+        put_q(1, q1);
+        put_q(2, q2);
+        put_p(0);
+        __syncthreads();
+        for (int s = 0; s < np; ++s) {
+            u16 qn = 0;
+            if (s + 1 < np) {
+                fetch_p(z0 + s + 1);
+                qn = fetch_q(z0 + s + 2);
+            }
+            bf16x8 b[NB];
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) b[nb] = tr_frag(Pb + (s & 1) * kWgPlB + 16 * nb);
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                const int at = tz[m] < 0 ? to[m] : ((s + tz[m]) & 3) * kWg1Pl + to[m];
+                const bf16x8 f = *reinterpret_cast<const bf16x8*>(Qs + at);
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+                    acc[m][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, b[nb], acc[m][nb], 0, 0, 0);
+            }
+            if (s + 1 < np) {
+                put_p((s + 1) & 1);
+                put_q(s + 3, qn);
+            }
+            __syncthreads();
+        }
+    }
+    // add the wavefronts in order
+    __syncthreads();
+    float4* red = reinterpret_cast<float4*>(Ps);
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) red[((w * 2 + m) * NB + nb) * 64 + lane] = __builtin_bit_cast(float4, acc[m][nb]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) qsum += __shfl_xor(qsum, o, 64);
+    if (lane == 0) qs[w] = qsum;
+    __syncthreads();
+    float* P = part + (long)blockIdx.x * (28 * CP);
+    for (int k = tid; k < 2 * NB * 64; k += kWgThreads) {
+        const int m = k / (NB * 64), nb = k / 64 % NB, l = k % 64;
+        f32x4 v = {0.f, 0.f, 0.f, 0.f};
+        for (int ww = 0; ww < kWgThreads / 64; ++ww) v += __builtin_bit_cast(f32x4, red[((ww * 2 + m) * NB + nb) * 64 + l]);
+        const int c = 16 * nb + (l & 15);
+        if (c < CP)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int t = 16 * m + 4 * (l >> 4) + e;
+                if (t < 27) P[(mirror ? 26 - t : t) * CP + c] = v[e];
+                else if (t == 27 && !mirror) P[27 * CP + c] = v[e];
+            }
+    }
+    if (mirror && tid == 0) {
+        float t = 0.0f;
+        for (int ww = 0; ww < kWgThreads / 64; ++ww) t += qs[ww];
+        P[27 * CP] = t;
+    }
+}
+
+// dW[j] (j < lenw) and db[j - lenw] (+)= sum over workgroups of part[wg][j] in a
+// fixed order: wavefront q of the block sums the workgroups [q nwg/16, (q+1)
+// nwg/16) in order for 64 consecutive j (eight loads in flight), then the 16
+// sums are added in order.
+__global__ void __launch_bounds__(1024)
+k_wgrad_fold(const float* __restrict__ part, long nwg, long stride, long lenw, long len, float* __restrict__ dW,
+             float* __restrict__ db, int accumulate) {
+    __shared__ float sh[16][64];
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
     const long j = (long)blockIdx.x * 64 + lane;
-    const long k0 = q * nwg / 4, k1 = (q + 1) * nwg / 4;
+    const long k0 = q * nwg / 16, k1 = (q + 1) * nwg / 16;
     float s = 0.0f;
     if (j < len) {
         long k = k0;
         for (; k + 8 <= k1; k += 8) {
             float v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = part[(k + u) * len + j];
+            for (int u = 0; u < 8; ++u) v[u] = part[(k + u) * stride + j];
 #pragma unroll
             for (int u = 0; u < 8; ++u) s += v[u];
         }
-        for (; k < k1; ++k) s += part[k * len + j];
+        for (; k < k1; ++k) s += part[k * stride + j];
     }
     sh[q][lane] = s;
     __syncthreads();
     if (q == 0 && j < len) {
-        const float t = ((sh[0][lane] + sh[1][lane]) + sh[2][lane]) + sh[3][lane];
-        dst[j] = accumulate ? dst[j] + t : t;
+        float t = sh[0][lane];
+#pragma unroll
+        for (int u = 1; u < 16; ++u) t += sh[u][lane];
+        float* d = j < lenw ? dW + j : db + (j - lenw);
+        *d = accumulate ? *d + t : t;
     }
 }
 

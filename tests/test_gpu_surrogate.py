@@ -129,6 +129,24 @@ def test_conv_weight_grad(dev, cin, cout):
     _within(db.cpu().numpy(), rb, tb, "bias gradient")
 
 
+# tiles of 32 x 8 voxels: partial, whole and one past; single planes; and more
+# (tile, plane) units than workgroups, so that runs cross tiles
+@pytest.mark.parametrize("shape", [(1, 1, 1), (1, 8, 32), (2, 9, 33), (4, 7, 31), (3, 17, 65), (40, 40, 70)])
+@pytest.mark.parametrize("cin,cout", [(32, 32), (1, 32), (32, 1), (1, 1)])
+def test_conv_weight_grad_tiles(dev, cin, cout, shape):
+    import torch
+    from paper_1609_03782_amd import surrogate as sg
+    rng = np.random.default_rng(zlib.crc32(repr((shape, cin, cout)).encode()))
+    a, ta = _bf(rng.standard_normal(shape + (cin,)))
+    dz, tdz = _bf(rng.standard_normal(shape + (cout,)))
+    dW, db = sg.conv3d_weight_grad(ta.to(dev), cin, tdz.to(dev), cout)
+    again = sg.conv3d_weight_grad(ta.to(dev), cin, tdz.to(dev), cout)
+    assert torch.equal(dW, again[0]) and torch.equal(db, again[1])
+    rW, tW, rb, tb = S.weight_grad_ref(a, dz)
+    _within(dW.cpu().numpy(), rW, tW, "weight gradient")
+    _within(db.cpu().numpy(), rb, tb, "bias gradient")
+
+
 def _net(depth=4, seed=3):
     """Weights exact in bf16 and biases exact in FP32, so both sides start
     from the same numbers."""
