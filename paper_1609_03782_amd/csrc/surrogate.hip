@@ -110,19 +110,16 @@ ZsGrid zs_grid(long nx, long ny, long nz, int xw, bool pairs) {
     return g;
 }
 
-// 32-channel input: 8 rows of 32 voxels (2 M-tiles) per workgroup, the largest
-// tile whose four staged planes and the weights fit the 160 KB of LDS
-template <int NB, int EPI>
+// 32-channel input
+template <int NB, int EPI, bool KEEP = false>
 hipError_t zs_launch(const u16* x, const bf16x8* wp, const float* b, void* out, const void* aux, long nx, long ny,
                      long nz, hipStream_t s) {
-    constexpr int MT = 2;
-    static_assert(zs_lds_bytes<MT, 2>() <= 160 * 1024, "z-stream tile exceeds LDS");
-    const ZsGrid g = zs_grid(nx, ny, nz, 16 * MT, true);
-    const size_t lds = zs_lds_bytes<MT, NB>();
-    auto kern = k_conv_zs<NB, EPI, MT>;
-    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    static_assert(kZsLds <= 160 * 1024, "z-stream tile exceeds LDS");
+    const ZsGrid g = zs_grid(nx, ny, nz, kZsX, true);
+    auto kern = k_conv_zs<NB, EPI, KEEP>;
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kZsLds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)g.groups), dim3(64 * kZsRows), lds, s, x, wp, b, out, aux, (int)nx,
+    hipLaunchKernelGGL(kern, dim3((unsigned)g.groups), dim3(64 * kZsRows), kZsLds, s, x, wp, b, out, aux, (int)nx,
                        (int)ny, (int)nz, g.ntx, g.nty, g.zch);
     return hipGetLastError();
 }
@@ -163,17 +160,21 @@ hipError_t launch_conv(int cin, int cout, int epi, const void* in, const bf16x8*
         return out1_launch<EPI_RESID>(x, wp, b, out, aux, nx, ny, nz, s);
     }
 #define Z(F, NBV, EPIV) return F<NBV, EPIV>(x, wp, b, out, aux, nx, ny, nz, s)
-#define PICK(F)                                                                                             \
-    if (NB == 2) {                                                                                          \
-        if (epi == EPI_RAW) Z(F, 2, EPI_RAW); else if (epi == EPI_GELU) Z(F, 2, EPI_GELU);                  \
-        else if (epi == EPI_BACK_GELU) Z(F, 2, EPI_BACK_GELU); else Z(F, 2, EPI_RESID);                     \
-    } else {                                                                                                \
-        if (epi == EPI_RAW) Z(F, 1, EPI_RAW); else if (epi == EPI_GELU) Z(F, 1, EPI_GELU);                  \
-        else if (epi == EPI_BACK_GELU) Z(F, 1, EPI_BACK_GELU); else Z(F, 1, EPI_RESID);                     \
+    if (cin == 32) {   // the GELU forms have 32 outputs, the residual one (above)
+        if (NB == 1) Z(zs_launch, 1, EPI_RAW);
+        if (epi == EPI_RAW) Z(zs_launch, 2, EPI_RAW);
+        if (epi == EPI_GELU && aux) return zs_launch<2, EPI_GELU, true>(x, wp, b, out, aux, nx, ny, nz, s);
+        if (epi == EPI_GELU) Z(zs_launch, 2, EPI_GELU);
+        Z(zs_launch, 2, EPI_BACK_GELU);
     }
-    if (cin == 32) { PICK(zs_launch) }
-    PICK(zs1_launch)
-#undef PICK
+    if (NB == 2) {
+        if (epi == EPI_RAW) Z(zs1_launch, 2, EPI_RAW);
+        if (epi == EPI_GELU) Z(zs1_launch, 2, EPI_GELU);
+        if (epi == EPI_BACK_GELU) Z(zs1_launch, 2, EPI_BACK_GELU);
+        Z(zs1_launch, 2, EPI_RESID);
+    }
+    if (epi == EPI_RAW) Z(zs1_launch, 1, EPI_RAW);
+    Z(zs1_launch, 1, EPI_RESID);
 #undef Z
 }
 

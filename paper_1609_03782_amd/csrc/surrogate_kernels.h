@@ -25,6 +25,7 @@
 #include <stdint.h>
 
 #include <type_traits>
+#include <utility>
 
 namespace igs {
 
@@ -40,6 +41,17 @@ __device__ __forceinline__ u16 f2bf(float f) {   // round to nearest, ties to ev
     if ((u & 0x7f800000u) == 0x7f800000u) return (u16)((u >> 16) | ((u & 0xffffu) ? 0x40u : 0u));
     u += 0x7fffu + ((u >> 16) & 1u);
     return (u16)(u >> 16);
+}
+
+// f(integral_constant<int, 0>) .. f(integral_constant<int, N - 1>): a loop whose
+// index is a constant in the body whatever the body's size
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+    static_for_impl(static_cast<F&&>(f), std::make_integer_sequence<int, N>{});
 }
 
 // ------------------------------------------------ conv, z-streaming, 32 in
@@ -62,18 +74,19 @@ __device__ __forceinline__ float erf_as(float x, float* e2) {
 // gelu(z) = z/2 (1 + erf(z/sqrt2)); gelu'(z) = (1 + erf(z/sqrt2))/2 + z e^{-z^2/2}/sqrt(2 pi)
 // GELU through the complementary function the same formula gives directly,
 // erfc(x) = (a1 t + ... + a5 t^5) e^{-x^2} for x >= 0: with c = erfc(|z|/sqrt2),
-// gelu(z) = max(z, 0) - |z|/2 c on both sides of 0 (12 VALU operations, a
+// gelu(z) = max(z, 0) - |z|/2 c on both sides of 0 (11 VALU operations, a
 // reciprocal and an exp2).
 __device__ __forceinline__ float gelu_fast(float z) {
     const float az = fabsf(z);
     const float t = __builtin_amdgcn_rcpf(__builtin_fmaf(0.3275911f * 0.70710678118654752f, az, 1.0f));
     const float ex = __builtin_amdgcn_exp2f((z * -0.72134752044448170f) * z);   // e^{-z^2/2}
-    float pl = __builtin_fmaf(1.061405429f, t, -1.453152027f);
-    pl = __builtin_fmaf(pl, t, 1.421413741f);
-    pl = __builtin_fmaf(pl, t, -0.284496736f);
-    pl = __builtin_fmaf(pl, t, 0.254829592f);
+    // the coefficients halved: c / 2 with the same roundings, one product fewer
+    float pl = __builtin_fmaf(0.5f * 1.061405429f, t, 0.5f * -1.453152027f);
+    pl = __builtin_fmaf(pl, t, 0.5f * 1.421413741f);
+    pl = __builtin_fmaf(pl, t, 0.5f * -0.284496736f);
+    pl = __builtin_fmaf(pl, t, 0.5f * 0.254829592f);
     const float c = (pl * t) * ex;
-    return __builtin_fmaf(-0.5f * az, c, fmaxf(z, 0.0f));
+    return __builtin_fmaf(-az, c, fmaxf(z, 0.0f));
 }
 __device__ __forceinline__ float gelu_grad_fast(float z) {
     float e;
@@ -89,28 +102,44 @@ __device__ __forceinline__ uint2 pack_bf16x4(float a, float b, float c, float d)
 }
 
 // The convolution of a 32-channel input as a z-stream: a workgroup of 8
-// wavefronts owns an output tile of 16*MT voxels in x by 8 rows in y (one
-// row per wavefront, MT 16-voxel tiles each) and a chunk of planes [z0, z1),
-// computed two planes at a time.  The packed weight fragments of all 27 taps
-// are copied to LDS once; input planes z-1 .. z+2 (tile plus a one-voxel
-// margin, zeros outside the cube) sit in a ring of four LDS slots, and while
-// planes z and z+1 are computed the global loads of planes z+3 and z+4 are in
-// flight in registers.  The LDS bandwidth (128 bytes per clock per CU for
-// 16-byte reads, whatever the address pattern: measured) bounds this kernel,
-// so each weight fragment read from LDS serves both planes: 6 fragment reads
-// per tap feed 8 MFMAs instead of 4 reads feeding 4.  The weights are the
-// MFMA's A operand and the activations its B operand (the same register
-// fragments as the other way round), so each lane ends with four consecutive
-// output channels of one voxel and stores them with one 8-byte write.  Per
-// output the taps are accumulated in the order 0..26, then the bias is added.
-constexpr int kZsRows = 8;
-constexpr int kZsAhead = 2;   // taps whose LDS fragments are in flight ahead of the MFMAs
-constexpr int kZsCS = 32;     // u16 per staged voxel (32 channels, unpadded)
+// wavefronts owns an output tile of 32 voxels in x by 8 rows in y and a chunk of
+// planes [z0, z1), computed two planes at a time.  Wavefront (nb, xs, yg)
+// computes 16 output channels (nb) of 16 voxels (xs) of 4 rows (yg), and holds
+// the weights of its channels, all 27 taps, in registers (108) for the whole
+// chunk, so the LDS only feeds activations: each fragment (input plane, row,
+// x shift) is read once and multiplied with every weight it meets, up to 3 rows
+// by 2 planes: 72 reads of 1 KB for 216 products, where weights in LDS and one
+// row per wavefront took 162.  The LDS bandwidth (128 bytes per clock per CU for
+// 16-byte reads, whatever the address pattern: measured) bounded that form.
+// Input planes (tile plus a one-voxel margin, zeros outside the cube) sit in a
+// ring of six LDS slots: planes z-1 .. z+2 are read while z+3 and z+4 are
+// staged, so one barrier per pair of planes suffices.  The weights are the
+// MFMA's A operand and the activations its B operand, so each lane ends with
+// four consecutive output channels of one voxel and stores them with one
+// 8-byte write.  Per output the taps are accumulated in the order 0..26, then
+// the bias is added.  The pass is one block of code whose issue order is laid
+// out (below), the epilogue's VALU work behind the products.
+// What bounds it now is power: 897 TFLOP/s on 360 x 360 x 150 (a library matrix
+// product reaches 1127 on the same card), the matrix cores 52 % busy at 1.8 GHz;
+// staging straight to LDS took 9 % of the cycles and none of the time (the clock
+// fell with them).  A 32-channel layer of that cube went from 1483 to 1199 us,
+// of 96^3 from 69 to 56 us.
+constexpr int kZsRows = 8;    // tile rows
+constexpr int kZsX = 32;      // tile columns
+constexpr int kZsAhead = 3;   // activation fragments in flight ahead of their products
+constexpr int kZsSlots = 6;   // LDS ring
+constexpr int kZsValu = 3;    // VALU operations issued behind a product
+constexpr int kZsLX = kZsX + 2, kZsLY = kZsRows + 2;
+constexpr int kZsPer = (kZsLX * kZsLY * 4 + 511) / 512;   // 16-byte chunks of a staged plane per thread
+constexpr int kZsPl = kZsPer * 512 * 8;     // u16 of a slot: a plane and what the last threads write past it
+constexpr size_t kZsLds = (size_t)kZsSlots * kZsPl * 2;
 
-template <int MT>
-constexpr int zs_plane_u16() { return (16 * MT + 2) * (kZsRows + 2) * kZsCS; }
-template <int MT, int NB>
-constexpr size_t zs_lds_bytes() { return (size_t)27 * NB * 64 * 16 + (size_t)4 * zs_plane_u16<MT>() * 2; }
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+// A raw buffer over `bytes` from p: accesses at or past its end are dropped
+// (loads give zeros), so a store that must not happen needs no branch around it
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t raw_buffer(const void* p, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
+}
 
 // Epilogue of the z-stream kernels: lane (i + 16 kg) holds D[m = 4 kg + e][n = i]
 // of each (s, nb), output channels 16 nb + 4 kg + e of voxel 16 s + i of row y,
@@ -179,144 +208,198 @@ __device__ __forceinline__ void zs_store(const f32x4 (&acc)[MT][NB], const float
         }
 }
 
-template <int NB, int EPI, int MT>
+// products of fragment m of a pass, and the epilogue values begun before it
+// (32 over 216 products)
+constexpr int zs_products(int m) {
+    const int q = m / 18, j = m / 3 % 6;
+    return (q == 0 || q == 3 ? 1 : 2) * (j == 0 || j == 5 ? 1 : j == 1 || j == 4 ? 2 : 3);
+}
+constexpr int zs_value(int m) {
+    int n = 0;
+    for (int k = 0; k < m; ++k) n += zs_products(k);
+    return n * 32 / 216;
+}
+
+// NB = 1 (up to 16 output channels): the wavefronts nb = 1 compute nothing that
+// is stored.  KEEP: the pre-activations go to aux (EPI_GELU).
+template <int NB, int EPI, bool KEEP>
 __global__ void __launch_bounds__(512)
 k_conv_zs(const u16* __restrict__ in, const bf16x8* __restrict__ wp, const float* __restrict__ bias,
           void* __restrict__ out, const void* __restrict__ aux, int nx, int ny, int nz, int ntx, int nty, int zch) {
-    constexpr int XW = 16 * MT, LX = XW + 2, LY = kZsRows + 2;
-    constexpr int PLU = zs_plane_u16<MT>();
-    constexpr int NT = 64 * kZsRows;                // threads
-    constexpr int NCH = LX * LY * 4;               // 16-byte chunks of one staged plane
-    constexpr int PER = (NCH + NT - 1) / NT;
+    constexpr int NT = 512, PER = kZsPer;
     extern __shared__ uint4 zs_smem[];
-    bf16x8* Bs = reinterpret_cast<bf16x8*>(zs_smem);
-    u16* ring = reinterpret_cast<u16*>(zs_smem + 27 * NB * 64);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    u16* ring = reinterpret_cast<u16*>(zs_smem);
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nb = w & 1, xs = (w >> 1) & 1, yg = w >> 2;
     const int i = lane & 15, kg = lane >> 4;
     const int bt = blockIdx.x;
     const int tx = bt % ntx, ty = (bt / ntx) % nty, tz = bt / (ntx * nty);
-    const int x0 = tx * XW, y0 = ty * kZsRows;
+    const int x0 = tx * kZsX, y0 = ty * kZsRows;
     const int z0 = tz * zch, z1 = min(nz, z0 + zch);
+    const bool act = nb < NB;                      // this wavefront's channels exist
 
-    for (int q = threadIdx.x; q < 27 * NB * 64; q += NT) Bs[q] = wp[q];
+    bf16x8 wf[27];
+#pragma unroll
+    for (int t = 0; t < 27; ++t) wf[t] = wp[(t * NB + (act ? nb : 0)) * 64 + lane];
 
-    uint4 st[2][PER];
-    auto fetch = [&](int z, uint4 (&dst)[PER]) {
+    // the chunks this thread stages: offset from the tile's first row of a
+    // plane in units of 16 bytes (below 2^32: a piece has at most 2^28
+    // voxels), clamped into the cube; mask: all ones if the chunk lies in it
+    unsigned off[PER], mask[PER];
+    const int yb = max(y0 - 1, 0);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int q = tid + NT * k, vox = q >> 2;
+        const int x = x0 + vox % kZsLX - 1, y = y0 + vox / kZsLX - 1;
+        mask[k] = x >= 0 && x < nx && y >= 0 && y < ny ? ~0u : 0u;
+        off[k] = (unsigned)(((long)(min(max(y, 0), ny - 1) - yb) * nx + min(max(x, 0), nx - 1)) * 4 + (q & 3));
+    }
+    uint4 st[PER];
+    auto fetch = [&](int z) {
+        const uint4* base = reinterpret_cast<const uint4*>(in) + ((long)min(max(z, 0), nz - 1) * ny + yb) * nx * 4;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) st[k] = base[off[k]];
+    };
+    auto put = [&](int z, int slot) {
+        const bool zin = z >= 0 && z < nz;
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
-            const int q = threadIdx.x + NT * k;
-            uint4 v = make_uint4(0, 0, 0, 0);
-            const int c = q & 3, vox = q >> 2;
-            const int x = x0 + vox % LX - 1, y = y0 + vox / LX - 1;
-            if (q < NCH && z >= 0 && z < nz && x >= 0 && x < nx && y >= 0 && y < ny)
-                v = *reinterpret_cast<const uint4*>(in + ((long)(z * ny + y) * nx + x) * 32 + 8 * c);
-            dst[k] = v;
+            const unsigned m = zin ? mask[k] : 0u;
+            reinterpret_cast<uint4*>(ring + slot * kZsPl)[tid + NT * k] =
+                make_uint4(st[k].x & m, st[k].y & m, st[k].z & m, st[k].w & m);
         }
     };
-    auto put = [&](int z, const uint4 (&src)[PER]) {   // plane z goes to slot z mod 4
-        u16* slot = ring + ((z + 4) & 3) * PLU;
+    // plane z0 - 1 + k sits in slot k mod 6
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int q = threadIdx.x + NT * k;
-            if (q < NCH) *reinterpret_cast<uint4*>(slot + (q >> 2) * kZsCS + 8 * (q & 3)) = src[k];
+    for (int k = 0; k < 4; ++k) {
+        fetch(z0 - 1 + k);
+        put(z0 - 1 + k, k);
+    }
+    __syncthreads();
+
+    const u16* lb = ring + ((4 * yg) * kZsLX + 16 * xs + i) * 32 + 8 * kg;
+    // this wavefront's part of output row y + r, plane z: a buffer of bytes
+    // `vb` per voxel from voxel x0, empty where nothing is to be stored
+    const int y = y0 + 4 * yg, n0 = 16 * nb + 4 * kg;
+    const int cols = min(nx - x0, kZsX);
+    auto row = [&](const void* p, int z, int r, int vb) {   // no branch: it would split the pass's schedule
+        const int on = -(int)(act & (z >= 0) & (z < z1) & (y + r < ny));
+        return raw_buffer(static_cast<const char*>(p) +
+                              (((long)max(z, 0) * ny + min(y + r, ny - 1)) * nx + x0) * vb, on & (cols * vb));
+    };
+    const int lo = (16 * xs + i) * 64 + 2 * n0;    // this lane's four bf16 channels in such a row
+    f32x4 bv = {0.f, 0.f, 0.f, 0.f};
+    if (EPI != EPI_BACK_GELU && bias && act)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bv[e] = bias[n0 + e];
+    // the results of the previous pair of planes (zp, zp + 1): their epilogue (GELU,
+    // packing, stores) is spread over the next pair's products, a value at a
+    // time and with no branch, so that it runs beside the matrix cores
+    constexpr int NV = 32;
+    f32x4 acc[2][4], prev[2][4];
+    uint2 pre[2][4];
+    int zp = -2;
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            prev[p][r] = f32x4{0.f, 0.f, 0.f, 0.f};
+            pre[p][r] = make_uint2(0, 0);
+        }
+    auto store2 = [&](void* p, int z, int r, uint2 v) {
+        __builtin_amdgcn_raw_buffer_store_b64(u32x2{v.x, v.y}, row(p, z, r, 64), lo, 0, 0);
+    };
+    auto epi = [&](auto vc) {   // value e of row r, plane zp + p
+        constexpr int v = decltype(vc)::value, p = v / 16, r = v / 4 % 4, e = v % 4;
+        f32x4& d = prev[p][r];
+        if constexpr (EPI == EPI_GELU) {
+            if constexpr (e == 0) {
+                d += bv;
+                if constexpr (KEEP) store2(const_cast<void*>(aux), zp + p, r, pack_bf16x4(d[0], d[1], d[2], d[3]));
+            }
+            d[e] = gelu_fast(d[e]);
+            if constexpr (e == 3) store2(out, zp + p, r, pack_bf16x4(d[0], d[1], d[2], d[3]));
+        } else if constexpr (EPI == EPI_BACK_GELU) {
+            const unsigned u = e < 2 ? pre[p][r].x : pre[p][r].y;
+            d[e] *= gelu_grad_fast(__uint_as_float(e & 1 ? u & 0xffff0000u : u << 16));
+            if constexpr (e == 3) store2(out, zp + p, r, pack_bf16x4(d[0], d[1], d[2], d[3]));
+        } else if constexpr (e == 3) {
+            typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+            const f32x4 o = d + bv;
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), row(out, zp + p, r, 64 * NB),
+                                                   (16 * xs + i) * 64 * NB + 4 * n0, 0, 0);
         }
     };
-    fetch(z0 - 1, st[0]);
-    put(z0 - 1, st[0]);
-    fetch(z0, st[0]);
-    put(z0, st[0]);
-    fetch(z0 + 1, st[0]);
-    fetch(z0 + 2, st[1]);
-
-    const int y = y0 + w;
-    // results of the previous pair of planes (zp, zp + 1), stored piecewise
-    // during the next pair's tap loop so the epilogue's VALU work (GELU) runs
-    // beside the MFMAs and LDS reads instead of between two barriers
-    // (EPI_BACK_GELU: the pre-activations they need are loaded before the next
-    // planes' staging loads, so their wait does not include those)
-    constexpr int NPART = 2 * MT * NB;
-    f32x4 prev[2][MT][NB];
-    uint2 pre[2][MT][NB];
-    int zp = -1;
-    bool zp2 = false;   // the previous pair's second plane is an output
-    auto store_part = [&](int j) {
-        const int pp = j / (MT * NB), s = (j / NB) % MT, nb = j % NB;
-        if (zp >= 0 && (pp == 0 || zp2))
-            zs_store_one<NB, EPI>(prev[pp][s][nb], pre[pp][s][nb], s, nb, bias, out, aux, x0, y, zp + pp, nx, ny, i, kg);
-    };
+    int sl = 0;                                    // slot of plane z - 1
     for (int z = z0; z < z1; z += 2) {
-        put(z + 1, st[0]);
-        put(z + 2, st[1]);
-        __syncthreads();
-        if (z + 2 < z1) {
-            fetch(z + 3, st[0]);
-            fetch(z + 4, st[1]);
-        }
-
-        // planes z and z + 1 (the second is computed but not stored when the
-        // chunk ends at z + 1; its inputs are the ring's planes z .. z + 2)
-        f32x4 acc[2][MT][NB];
+        const u16* lq[4];
+        int sw[2];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) lq[q] = lb + (sl + q < kZsSlots ? sl + q : sl + q - kZsSlots) * kZsPl;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) sw[q] = sl + 4 + q < kZsSlots ? sl + 4 + q : sl + 4 + q - kZsSlots;
+        fetch(z + 3);                              // the last pair stages planes no one reads
+        // fragment m: input plane z - 1 + q, row 4 yg - 1 + j of the tile, shift dx
+        bf16x8 f[kZsAhead + 1];
+        auto load = [&](auto mc) {
+            constexpr int m = decltype(mc)::value;
+            f[m % (kZsAhead + 1)] = *reinterpret_cast<const bf16x8*>(lq[m / 18] + ((m / 3 % 6) * kZsLX + m % 3) * 32);
+        };
+        static_for<kZsAhead>(load);
+        // half a pass: 36 fragments, 108 products, 16 values of the epilogue
+        auto half = [&](auto hc) {
+            constexpr int M0 = 36 * decltype(hc)::value;
+            static_for<36>([&](auto mc) {
+                constexpr int m = M0 + decltype(mc)::value, q = m / 18, j = m / 3 % 6, dx = m % 3;
+                if constexpr (m + kZsAhead < 72) load(std::integral_constant<int, m + kZsAhead>{});
+#pragma unroll
+                for (int p = 0; p < 2; ++p)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (q - p >= 0 && q - p < 3 && j - r >= 0 && j - r < 3)
+                            acc[p][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                wf[9 * (q - p) + 3 * (j - r) + dx], f[m % (kZsAhead + 1)],
+                                q == p && j == r && dx == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[p][r], 0, 0, 0);
+                constexpr int v0 = zs_value(m), v1 = zs_value(m + 1);
+                if constexpr (v1 > v0) epi(std::integral_constant<int, v0>{});
+            });
+            // the order to issue it in: each fragment's read kZsAhead fragments
+            // ahead, and behind each product the two or three VALU operations that
+            // fit under its 16 cycles
+            static_for<36>([&](auto mc) {
+                constexpr int m = M0 + decltype(mc)::value;
+                if constexpr (m + kZsAhead < 72) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                static_for<zs_products(m)>([&](auto) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, kZsValu, 0);
+                });
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        __builtin_amdgcn_sched_barrier(0);
+        half(std::integral_constant<int, 0>{});
+        put(z + 3, sw[0]);
+        fetch(z + 4);
+        __builtin_amdgcn_sched_barrier(0);
+        half(std::integral_constant<int, 1>{});
+        zp = z;
 #pragma unroll
         for (int p = 0; p < 2; ++p)
 #pragma unroll
-            for (int s = 0; s < MT; ++s)
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb) acc[p][s][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        // taps in order 0..26, the LDS fragments of tap t + kZsAhead read while
-        // tap t's MFMAs run (the scheduling barriers keep the compiler from
-        // sinking each read down to its use, which left every pair of MFMAs
-        // waiting for the LDS)
-        bf16x8 wr[kZsAhead + 1][NB], ar[kZsAhead + 1][2][MT];
-        auto load = [&](int t, bf16x8 (&wf)[NB], bf16x8 (&av)[2][MT]) {
-            const int dz = t / 9, dy = (t / 3) % 3, dx = t % 3;
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) wf[nb] = Bs[(t * NB + nb) * 64 + lane];
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                const u16* slot = ring + ((z + 3 + p + dz) & 3) * PLU;   // plane z + p - 1 + dz
-#pragma unroll
-                for (int s = 0; s < MT; ++s) {
-                    const int vox = (w + dy) * LX + (16 * s + i + dx);
-                    av[p][s] = *reinterpret_cast<const bf16x8*>(slot + vox * kZsCS + 8 * kg);
-                }
-            }
-        };
-#pragma unroll
-        for (int t = 0; t < kZsAhead; ++t) load(t, wr[t], ar[t]);
-#pragma unroll
-        for (int t = 0; t < 27; ++t) {
-            if (t + kZsAhead < 27) load(t + kZsAhead, wr[(t + kZsAhead) % (kZsAhead + 1)], ar[(t + kZsAhead) % (kZsAhead + 1)]);
-            __builtin_amdgcn_sched_barrier(0);
-            const int r = t % (kZsAhead + 1);
+            for (int r = 0; r < 4; ++r) prev[p][r] = acc[p][r];
+        put(z + 4, sw[1]);
+        if constexpr (EPI == EPI_BACK_GELU)
 #pragma unroll
             for (int p = 0; p < 2; ++p)
 #pragma unroll
-                for (int s = 0; s < MT; ++s)
-#pragma unroll
-                    for (int nb = 0; nb < NB; ++nb)
-                        acc[p][s][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[r][nb], ar[r][p][s], acc[p][s][nb], 0, 0, 0);
-            // one part of the previous pair's epilogue after every third tap
-            if (t % 3 == 1 && t / 3 < NPART) store_part(t / 3);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int j = 9; j < NPART; ++j) store_part(j);
-#pragma unroll
-        for (int p = 0; p < 2; ++p)
-#pragma unroll
-            for (int s = 0; s < MT; ++s)
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb) {
-                    prev[p][s][nb] = acc[p][s][nb];
-                    pre[p][s][nb] = EPI == EPI_BACK_GELU && (p == 0 || z + 1 < z1)
-                                        ? zs_pre<NB>(aux, s, nb, x0, y, z + p, nx, ny, i, kg) : make_uint2(0, 0);
+                for (int r = 0; r < 4; ++r) {
+                    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(row(aux, z + p, r, 64), lo, 0, 0);
+                    pre[p][r] = make_uint2(v.x, v.y);
                 }
-        zp = z;
-        zp2 = z + 1 < z1;
-        __syncthreads();   // every wavefront is done with slots z - 1 and z before they take planes z + 3, z + 4
+        sl = sl + 2 < kZsSlots ? sl + 2 : sl + 2 - kZsSlots;
+        __syncthreads();
     }
-#pragma unroll
-    for (int j = 0; j < NPART; ++j) store_part(j);
+    static_for<NV>(epi);
 }
 
 // The convolution of a 1-channel input as a z-stream (the network's first

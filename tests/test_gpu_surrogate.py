@@ -66,6 +66,33 @@ def test_conv_forward_raw(dev, shape, cin, cout):
     _within(got, ref, tol, "raw conv")
 
 
+# tiles of 32 x 8 voxels and pairs of planes: partial, whole, one past; and
+# channel counts of one and of two 16-channel blocks
+@pytest.mark.parametrize("shape", [(1, 1, 1), (2, 8, 32), (9, 17, 65), (6, 9, 31)])
+@pytest.mark.parametrize("cout", [5, 16, 17, 32])
+def test_conv_forward_tiles(dev, shape, cout):
+    import torch
+    from paper_1609_03782_amd import surrogate as sg
+    rng = np.random.default_rng(zlib.crc32(repr((shape, cout)).encode()))
+    a, ta = _bf(rng.standard_normal(shape + (32,)))
+    W, _ = _bf(rng.standard_normal((27, 32, cout)) * 0.2)
+    b = rng.standard_normal(cout).astype(np.float32)
+    tW, tb = torch.from_numpy(W.astype(np.float32)).to(dev), torch.from_numpy(b).to(dev)
+    out = sg.conv3d_forward(ta.to(dev), 32, tW, tb, cout, epilogue=0)
+    ref, tol = S.conv_ref(a, W, b.astype(np.float64))
+    _within(out.cpu().numpy()[..., :cout].astype(np.float64), ref, tol, "raw conv")
+    if cout == 32:
+        pre = torch.empty(shape + (32,), dtype=torch.bfloat16, device=dev)
+        act, act_tol, zb, zb_tol = S.conv_gelu_ref(a, W, b.astype(np.float64))
+        kept = sg.conv3d_forward(ta.to(dev), 32, tW, tb, 32, epilogue=1, aux=pre)
+        _within(kept.double().cpu().numpy(), act, act_tol, "gelu activation")
+        _within(pre.double().cpu().numpy(), zb, zb_tol, "bf16 pre-activation")
+        assert torch.equal(kept, sg.conv3d_forward(ta.to(dev), 32, tW, tb, 32, epilogue=1))
+        got = sg.conv3d_input_grad(ta.to(dev), 32, tW, 32, aux=pre)
+        r2, t2 = S.input_grad_ref(a, W, pre.double().cpu().numpy())
+        _within(got.double().cpu().numpy(), r2, t2, "input gradient times gelu'")
+
+
 def test_conv_forward_gelu_and_residual(dev):
     import torch
     from paper_1609_03782_amd import surrogate as sg
