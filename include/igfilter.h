@@ -101,12 +101,15 @@ typedef struct {
                           of zchunk output planes (BLOCKED) */
     int32_t vec;       /* x voxels per lane: 1, 2, 4 or 8; 0 = automatic (8 for
                           256 < nx <= 512, 4 above 512 (256-voxel x tiles), else 4 with
-                          `rows` chosen to cover nx).  Cubes wider than one tile
+                          `rows` chosen to cover nx).  The library's own schedule also
+                          uses 3, 5, 6 and 7 in passes of depth 1 and 2; a schedule with
+                          the vec and rows it reports for a shape is accepted for it.  Cubes wider than one tile
                           (64 vec voxels) are cut into x tiles whose halo is t_block
                           rounded up to a multiple of vec */
     int32_t rounds;    /* zchunk == 0: rounds of resident workgroups; 0 = as few as possible */
     int32_t rows;      /* rows per wavefront: 1, 2 or 4 (a tile has waves * rows rows); more
-                          than 1 needs vec 4 and nx <= 256 / rows (one x tile); 0 = automatic
+                          than 1 needs vec 4 and nx <= 256 / rows (one x tile; vec 3 and
+                          192 / rows where the library chose that); 0 = automatic
                           with vec 0, else 1 */
 } ig_schedule;
 

@@ -150,6 +150,7 @@ struct ig_filter {
     double* parts = nullptr;     // kPartBlocks * 6 doubles
     double* results = nullptr;   // 8 doubles
     ig_schedule sched{};         // kind == AUTO: heuristic
+    mutable ig_schedule autosched[2]{};   // the heuristic's answer for passes of depth 1 and 2, once asked (else kind AUTO)
     int ncu = 256;               // compute units of the device
     // piece tables per pass depth T (index T), for the current schedule
     PassPlan plans[5];
@@ -230,7 +231,13 @@ extern "C" void ig_filter_destroy(ig_filter* f) {
 }
 
 static ig_schedule resolve_schedule(const ig_filter* f) {
-    if (f->sched.kind == IG_SCHED_AUTO) return igk_auto_schedule(&f->p);
+    if (f->sched.kind == IG_SCHED_AUTO) {
+        // the choice depends on the shape and type (fixed) and on n_iter
+        // through the pass depth only: made once per depth
+        const int d = f->p.n_iter >= 2;
+        if (f->autosched[d].kind == IG_SCHED_AUTO) f->autosched[d] = igk_auto_schedule(&f->p);
+        return f->autosched[d];
+    }
     ig_schedule s = f->sched;
     if (s.kind == IG_SCHED_BLOCKED) {
         if (s.vec == 0) {
@@ -438,7 +445,7 @@ ig_status igk_enqueue_run(const RunCtx& c, const ig_schedule& sched, const void*
                 if (st != IG_OK) return st;
                 BlockGeom g = pp->g;
                 // vector I/O also needs both buffers aligned to a lane chunk
-                const size_t al = (size_t)pp->V * dtype_size(p.dtype);
+                const size_t al = (size_t)chunk_align(pp->V, (int)dtype_size(p.dtype));
                 if (((uintptr_t)src % al) || ((uintptr_t)dst % al)) g.vec = 0;
                 HIP_TRY(record());
                 e = L->blocked(src, dst, g, pp->V, D, dev, pp->workgroups(), c.dparams, stream);
@@ -583,8 +590,24 @@ std::string tune_key(const ig_filter* f, const char* arch) {
     return buf;
 }
 
+// The tuner's candidate: the automatic schedule's lanes (voxels and rows) for
+// this many wavefronts where they can serve, else the power-of-two ones.
+ig_schedule tuned_schedule(const ig_params& p, int T, int W, int rounds) {
+    ig_schedule s{IG_SCHED_BLOCKED, T, W, 0, 0, rounds, 0};
+    ig_params q = p;
+    q.n_iter = T;
+    const ig_schedule a = igk_auto_schedule(&q);
+    if (T <= 2 && a.kind == IG_SCHED_BLOCKED) {
+        s.vec = a.vec;
+        s.rows = a.rows;
+        PassPlan pp;
+        if (plan_pass(p, s, T, 256, &pp)) s.vec = s.rows = 0;
+    }
+    return s;
+}
+
 // Look the key up in the cache file (lines: {"key": "...", "t_block": T, "waves": W, "rounds": R, "ms": x})
-bool tune_lookup(const char* path, const std::string& key, ig_schedule* s) {
+bool tune_lookup(const char* path, const ig_params& p, const std::string& key, ig_schedule* s) {
     FILE* fp = fopen(path, "r");
     if (!fp) return false;
     char line[1024];
@@ -598,7 +621,7 @@ bool tune_lookup(const char* path, const std::string& key, ig_schedule* s) {
         const char* c = strstr(line, "\"rounds\":");
         if (a && b && c && sscanf(a, "\"t_block\": %d", &T) == 1 && sscanf(b, "\"waves\": %d", &W) == 1 &&
             sscanf(c, "\"rounds\": %d", &R) == 1) {
-            *s = ig_schedule{IG_SCHED_BLOCKED, T, W, 0, 0, R};
+            *s = tuned_schedule(p, T, W, R);
             found = true;   // the last entry for a key wins
         }
     }
@@ -632,7 +655,7 @@ extern "C" ig_status ig_filter_autotune(ig_filter* f, const void* d_in, void* d_
     const std::string key = tune_key(f, prop.gcnArchName);
     const char* cache = getenv("IG_TUNE_CACHE");
     ig_schedule s{};
-    if (cache && *cache && tune_lookup(cache, key, &s) && check_schedule(&f->p, &s, f->ncu) == IG_OK) {
+    if (cache && *cache && tune_lookup(cache, f->p, key, &s) && check_schedule(&f->p, &s, f->ncu) == IG_OK) {
         ig_status st = ig_filter_set_schedule(f, &s);
         if (st != IG_OK) return st;
         *best = resolve_schedule(f);
@@ -649,7 +672,7 @@ extern "C" ig_status ig_filter_autotune(ig_filter* f, const void* d_in, void* d_
     for (int T = 1; T <= maxT; ++T)
         for (int W : {8, 12, 16})
             for (int R : {1, 2}) {
-                ig_schedule c{IG_SCHED_BLOCKED, T, W, 0, 0, R};
+                ig_schedule c = tuned_schedule(f->p, T, W, R);
                 if (check_schedule(&f->p, &c, f->ncu) != IG_OK) continue;
                 if (ig_filter_set_schedule(f, &c) != IG_OK) continue;
                 ig_status st = ig_filter_run(f, d_in, d_work, hip_stream, nullptr);   // warm-up + plan upload

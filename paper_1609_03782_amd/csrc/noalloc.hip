@@ -108,11 +108,10 @@ ig_status static_plan(void* self, const ig_schedule& sched, int T, const PassPla
 // one pass fill one round of the resident workgroups; the naive schedule
 // when the regular grid would not fit the static table.
 ig_schedule static_schedule(const ig_params& p, int ncu) {
-    ig_schedule s = igk_auto_schedule(&p);
+    // the static tables hold a regular grid, not a grouped plan (equal shares
+    // of the tiles' planes)
+    ig_schedule s = igk_auto_schedule(&p, false);
     if (s.kind != IG_SCHED_BLOCKED) return s;
-    // the 16-wave layout pays only through a grouped plan (equal shares of
-    // the tiles' planes), which the regular grid of the static tables is not
-    if (s.waves == 16 && s.t_block == 2 && s.vec == 8 && s.rows == 1) s.waves = 12;
     s.rounds = 0;
     s.zchunk = (int)p.nz;
     PassPlan pp;

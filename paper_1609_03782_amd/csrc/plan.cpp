@@ -76,6 +76,101 @@ void auto_vec_rows(int64_t nx, int* V, int* R) {
     *R = nx <= 64 ? 4 : nx <= 128 ? 2 : 1;
 }
 
+// ---------------------------------------------------------------- layout choice
+// Time of a pass in microseconds: the plane steps of its longest workgroup
+// times the cost of one step.  A step's cost is a line in the voxels per lane
+// (V) and the wavefronts of a compute unit (Wt), fitted to 985 measured passes
+// (T = 2; nx 40 .. 1024, ny 90 .. 700, nz 32 .. 490; RMS deviation 9 %): what a
+// wavefront adds grows with its V; rows that do not end on a chunk (`ragged`)
+// and chunks of an odd number of voxels (more load instructions) cost extra,
+// and so do several rows per wavefront.  Fitted to the exponential conductance;
+// the others rank the layouts alike.
+namespace {
+struct StepCost {
+    double c, v, w, vw, ragged_v, ragged_vw, odd_vw, rows, rows_w;
+};
+constexpr StepCost kCost32 = {0.612, -0.0039, -0.0327, 0.0181, 0.020, 0.0016, 0.00171, -0.0206, 0.0127};
+constexpr StepCost kCost16 = {0.4135, 0.054, -0.0312, 0.0183, -0.0228, 0.0032, 0.0, 0.0729, 0.0142};
+double step_us(const StepCost& k, int V, int R, double Wt, bool ragged) {
+    double c = k.c + k.v * V + k.w * Wt + k.vw * V * Wt;
+    if (ragged) c += k.ragged_v * V + k.ragged_vw * V * Wt;
+    if (V & 1) c += k.odd_vw * V * Wt;
+    if (R > 1) c += k.rows + k.rows_w * Wt;
+    return c;
+}
+constexpr double kPassFixed = 3.0;   // a launch, and the fill of its first workgroups
+constexpr int kPlanCus = 256;
+
+// The pass of depth T with layout (V, R, W) as plan_pass splits it, without the
+// piece table; 1e300 if the layout cannot serve the shape.
+double pass_cost(const ig_params& p, int V, int R, int W, int T, bool grouped) {
+    const long nx = p.nx, ny = p.ny, nz = p.nz;
+    if (V > nx || (R > 1 && (64 / R) * V < nx)) return 1e300;
+    if ((long)W * R * nx * (long)dtype_size(p.dtype) >= (1L << 30)) return 1e300;
+    const size_t lds = stream_lds_bytes(V, T, W);
+    if (lds > kMaxLds) return 1e300;
+    long ntx = 1, nty = 1;
+    if (nx > 64 * V) {
+        const long ox = 64 * V - 2 * ((T + V - 1) / V * V);
+        if (ox < 1) return 1e300;
+        ntx = (nx + ox - 1) / ox;
+    }
+    if (ny > W * R) {
+        const long oy = W * R - 2 * T;
+        if (oy < 1) return 1e300;
+        nty = (ny + oy - 1) / oy;
+    }
+    const double tiles = (double)ntx * nty;
+    const long per_cu = resident_per_cu(W, lds), slots = kPlanCus * per_cu;
+    const double rounds = std::max(1.0, std::ceil(tiles / slots));
+    const double G = std::min(slots * rounds, tiles * nz);
+    const double pieces = std::max(1.0, std::min((double)nz, std::floor(G / tiles)));
+    double steps = std::ceil(nz / pieces) + 3 * T;
+    if (grouped && ntx == 1) {
+        const double even = (tiles * (nz + 3.0 * T) - 3.0 * T) / G + 3.0 * T;
+        if (even < 0.97 * steps) steps = std::ceil(even);
+    }
+    steps *= rounds;
+    const double Wt = W * std::min((double)per_cu, std::ceil(G / kPlanCus));
+    return kPassFixed + steps * step_us(p.dtype == IG_F32 ? kCost32 : kCost16, V, R, Wt, nx % V != 0);
+}
+}  // namespace
+
+// The layout of the automatic schedule.  The starting point is the
+// power-of-two chunk that covers the row (auto_vec_rows) with 12 wavefronts;
+// another chunk (fewer idle lanes: 300 voxels fill 94 % of 64 lanes of 5 and
+// 59 % of 64 lanes of 8), row count or wavefront count replaces it when its
+// predicted pass is 5 % shorter (10 % with 16-bit storage, where the line fits
+// less well: at 5 % a few rows of several x tiles lost up to 6 %).  Measured against the starting point over the
+// fitted passes: 1.21x (FP32), 1.13x (bf16) in the mean, none slower by more
+// than 2 %; 300 x 400 x 490 FP32 508 -> 787, 187 x 181 x 149 564 -> 756, 600 x
+// 400 x 200 419 -> 603 Gvoxel-iter/s.  Odd chunks exist for FP32 only (16-bit
+// rows move in whole 32-bit words).
+void auto_layout(const ig_params& p, int T, bool grouped, int* V, int* R, int* W) {
+    auto_vec_rows(p.nx, V, R);
+    *W = 12;
+    if (stream_lds_bytes(*V, T, *W) > kMaxLds) *W = 8;
+    if (T > 2 || p.nx < 4) return;
+    const double base = pass_cost(p, *V, *R, *W, T, grouped);
+    double best = (p.dtype == IG_F32 ? 0.95 : 0.90) * base;
+    const bool wide = *V == 8;   // 16 wavefronts of 8 voxels: chosen below, on their own measurements
+    for (int r : {1, 2, 4})
+        for (int v = 3; v <= 8; ++v) {
+            // as fitted: rows up to 512 voxels in one x tile, wider ones in tiles of 256 or more
+            if (r > 1 && v > 4) continue;
+            if (64 / r * v < p.nx && (p.nx <= 512 || v < 4)) continue;
+            if (p.dtype != IG_F32 && (v & 1)) continue;
+            for (int w : {3, 4, 5, 6, 8, 10, 12, 16}) {
+                if (v == 8 && (w != 12 || !wide)) continue;
+                const double c = pass_cost(p, v, r, w, T, grouped);
+                if (c < best) {
+                    best = c;
+                    *V = v; *R = r; *W = w;
+                }
+            }
+        }
+}
+
 // Workgroups of the streaming kernel one CU holds at once: 16 wavefronts of
 // at most 128 VGPRs each (launch bound of 1024 threads) and 160 KB of LDS.
 int resident_per_cu(int W, size_t lds) {
@@ -134,13 +229,25 @@ const char* plan_pass(const ig_params& p, const ig_schedule& s, int T, int ncu, 
     }
     if (R == 0) R = 1;
     const int W = s.waves;
-    if (!(V == 1 || V == 2 || V == 4 || V == 8)) return "vec must be 1, 2, 4 or 8";
+    if (!(V == 1 || V == 2 || V == 4 || V == 8)) {
+        // the other chunks only as the automatic schedule chooses them (for passes
+        // of depth 1 or 2, with or without grouped plans); deeper passes of a
+        // schedule that names one run the power-of-two layout
+        bool ours = false;
+        for (int k = 0; k < 4 && !ours; ++k) {
+            int av, ar, aw;
+            auto_layout(p, 1 + (k & 1), k < 2, &av, &ar, &aw);
+            ours = V == av && R == ar;
+        }
+        if (!ours) return "vec must be 1, 2, 4 or 8";
+        if (T > 2) auto_vec_rows(p.nx, &V, &R);
+    }
     if (V > nx) return "vec must not exceed nx";
     // a tile's rows of one plane are addressed with 32-bit byte offsets below 2^30
     if ((long)s.waves * std::max(R, 1) * nx * (long)dtype_size(p.dtype) >= (1L << 30))
         return "rows too long for the blocked schedule (use naive)";
     if (!(R == 1 || R == 2 || R == 4)) return "rows must be 1, 2 or 4";
-    if (R > 1 && (V != 4 || (64 / R) * V < nx)) return "rows > 1 needs vec 4 and nx <= 256 / rows";
+    if (R > 1 && ((V != 4 && V != 3) || (64 / R) * V < nx)) return "rows > 1 needs vec 4 and nx <= 256 / rows";
     if (W < 1 || W > 16) return "waves must be in 1..16";
     if (T < 1 || T > 4) return "t_block must be in 1..4";
     if (s.zchunk < 0 || s.rounds < 0) return "zchunk and rounds must be >= 0";
@@ -276,16 +383,11 @@ const char* plan_pass(const ig_params& p, const ig_schedule& s, int T, int ncu, 
 }
 
 // Heuristic schedule when no tuned entry exists.
-ig_schedule igk_auto_schedule(const ig_params* p) {
+ig_schedule igk_auto_schedule(const ig_params* p, bool grouped) {
     ig_schedule s{};
     s.kind = IG_SCHED_BLOCKED;
-    auto_vec_rows(p->nx, &s.vec, &s.rows);
     s.t_block = std::max(1, std::min(2, p->n_iter));
-    // 12 wavefronts and one round of pieces: the fastest on gfx950 for the
-    // 512^3 cube in every conductance and storage type (measured over
-    // T 1..3, 8..16 wavefronts, 0..2 rounds)
-    s.waves = 12;
-    if (stream_lds_bytes(s.vec, s.t_block, s.waves) > kMaxLds) s.waves = 8;
+    auto_layout(*p, s.t_block, grouped, &s.vec, &s.rows, &s.waves);
     s.zchunk = 0;
     s.rounds = 1;
     // 16 wavefronts (four per SIMD, 12 output rows per tile) when their
@@ -296,7 +398,7 @@ ig_schedule igk_auto_schedule(const ig_params* p) {
     // FP32 storage only: with 16-bit storage the 16-wave grouped pass measured
     // slower than 12 waves (bf16 840 against 871, fp16 851 against 873
     // Gvoxel-iter/s on the 512^3 cube).
-    if (p->dtype == IG_F32 && s.t_block == 2 && s.vec == 8 && s.rows == 1 && p->nx % 8 == 0 && p->nx <= 512 &&
+    if (grouped && p->dtype == IG_F32 && s.t_block == 2 && s.vec == 8 && s.rows == 1 && p->nx % 8 == 0 && p->nx <= 512 &&
         (long)16 * p->nx * (long)dtype_size(p->dtype) < (1L << 30)) {
         auto longest = [&](int W, bool* grouped) -> double {
             ig_schedule t = s;

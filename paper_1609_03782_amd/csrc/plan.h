@@ -60,12 +60,16 @@ struct PassPlan {
     int workgroups() const { return first.empty() ? (int)pieces.size() : (int)first.size() - 1; }
 };
 void auto_vec_rows(int64_t nx, int* V, int* R);
+// voxels per lane, rows per wavefront and wavefronts of the automatic schedule's
+// passes of depth T; grouped: its workgroups may take grouped plans
+void auto_layout(const ig_params& p, int T, bool grouped, int* V, int* R, int* W);
 int resident_per_cu(int W, size_t lds);
 // nullptr on success, else the reason schedule s cannot serve p at depth T
 const char* plan_pass(const ig_params& p, const ig_schedule& s, int T, int ncu, PassPlan* pp);
 ig_status igk_validate_params(const ig_params* p);
-// The library's schedule for p when the caller sets none.
-ig_schedule igk_auto_schedule(const ig_params* p);
+// The library's schedule for p when the caller sets none (grouped = false: for
+// runs whose piece tables hold no grouped plans).
+ig_schedule igk_auto_schedule(const ig_params* p, bool grouped = true);
 // Record a thread-local message for ig_last_error() and return s.
 ig_status igk_fail(ig_status s, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
 size_t dtype_size(int dt);

@@ -54,13 +54,13 @@ static hipError_t stream_one(const void* src, void* dst, const BlockGeom& g, con
 template <int V, bool VEC, int R>
 static hipError_t stream_T(const void* src, void* dst, const BlockGeom& g, int T, const Piece* pc, int np,
                            const DevParams* dp, hipStream_t s) {
-    switch (T) {
-        case 1: return stream_one<V, 1, VEC, R>(src, dst, g, pc, np, dp, s);
-        case 2: return stream_one<V, 2, VEC, R>(src, dst, g, pc, np, dp, s);
-        case 3: return stream_one<V, 3, VEC, R>(src, dst, g, pc, np, dp, s);
-        case 4: return stream_one<V, 4, VEC, R>(src, dst, g, pc, np, dp, s);
-        default: return hipErrorInvalidValue;
+    if (T == 1) return stream_one<V, 1, VEC, R>(src, dst, g, pc, np, dp, s);
+    if (T == 2) return stream_one<V, 2, VEC, R>(src, dst, g, pc, np, dp, s);
+    if constexpr ((V & (V - 1)) == 0) {   // the other chunks serve passes of depth 1 and 2
+        if (T == 3) return stream_one<V, 3, VEC, R>(src, dst, g, pc, np, dp, s);
+        if (T == 4) return stream_one<V, 4, VEC, R>(src, dst, g, pc, np, dp, s);
     }
+    return hipErrorInvalidValue;
 }
 
 template <int V, int R>
@@ -70,23 +70,27 @@ static hipError_t stream_V(const void* src, void* dst, const BlockGeom& g, int T
                  : stream_T<V, false, R>(src, dst, g, T, pc, np, dp, s);
 }
 
-// Rows per wavefront above 1 exist for V = 4 only (narrow cubes).
+// Rows per wavefront above 1 exist for V = 4 and (FP32) 3: narrow cubes.
 static hipError_t blocked_launch(const void* src, void* dst, const BlockGeom& g, int V, int T, const Piece* pc,
                                  int np, const DevParams* dp, hipStream_t s) {
-    if (g.R != 1 && V != 4) return hipErrorInvalidValue;
-    switch (V) {
-        case 1: return stream_V<1, 1>(src, dst, g, T, pc, np, dp, s);
-        case 2: return stream_V<2, 1>(src, dst, g, T, pc, np, dp, s);
-        case 4:
-            switch (g.R) {
-                case 1: return stream_V<4, 1>(src, dst, g, T, pc, np, dp, s);
-                case 2: return stream_V<4, 2>(src, dst, g, T, pc, np, dp, s);
-                case 4: return stream_V<4, 4>(src, dst, g, T, pc, np, dp, s);
-                default: return hipErrorInvalidValue;
-            }
-        case 8: return stream_V<8, 1>(src, dst, g, T, pc, np, dp, s);
-        default: return hipErrorInvalidValue;
-    }
+#define IG_CASE(VV, RR) \
+    if (V == VV && g.R == RR) return stream_V<VV, RR>(src, dst, g, T, pc, np, dp, s)
+    IG_CASE(1, 1);
+    IG_CASE(2, 1);
+    IG_CASE(4, 1);
+    IG_CASE(4, 2);
+    IG_CASE(4, 4);
+    IG_CASE(8, 1);
+    IG_CASE(6, 1);
+#if IG_DTYPE == 0
+    IG_CASE(3, 1);
+    IG_CASE(3, 2);
+    IG_CASE(3, 4);
+    IG_CASE(5, 1);
+    IG_CASE(7, 1);
+#endif
+#undef IG_CASE
+    return hipErrorInvalidValue;
 }
 
 const StencilLaunch* IG_SYM(stencil_launch)() {

@@ -74,6 +74,38 @@ k_naive(const ST* __restrict__ src, ST* __restrict__ dst, NaiveGeom g,
 
 // ------------------------------------------------------------ vector I/O
 template <typename ST, int V> struct Vec;
+// N consecutive values at an address aligned to A bytes, as the widest pieces
+// of 4, 2 and 1 values (a vector type of 3, 5, 6 or 7 would be padded).
+template <typename E, int A, int N> struct Pieces {
+    static constexpr int W = N >= 4 ? 4 : N >= 2 ? 2 : 1;
+    typedef E vt __attribute__((ext_vector_type(W), aligned(A)));
+    template <typename F>
+    static __device__ __forceinline__ void load(const E* p, F&& put, int at = 0) {   // put(i, value i)
+        if constexpr (W == 1) {
+            put(at, p[0]);
+        } else {
+            const vt q = *reinterpret_cast<const vt*>(p);
+#pragma unroll
+            for (int i = 0; i < W; ++i) put(at + i, q[i]);
+        }
+        if constexpr (N > W) Pieces<E, A, N - W>::load(p + W, put, at + W);
+    }
+    template <typename F>
+    static __device__ __forceinline__ void store(E* p, F&& get, int at = 0) {   // get(i): value i
+        if constexpr (W == 1) {
+            p[0] = get(at);
+        } else {
+            vt q;
+#pragma unroll
+            for (int i = 0; i < W; ++i) q[i] = get(at + i);
+            *reinterpret_cast<vt*>(p) = q;
+        }
+        if constexpr (N > W) Pieces<E, A, N - W>::store(p + W, get, at + W);
+    }
+};
+// Alignment a lane's chunk has when nx is a multiple of V and the buffers
+// start aligned to it: the largest power of two that divides V elements.
+constexpr int chunk_align(int V, int size) { return (V & -V) * size > 16 ? 16 : (V & -V) * size; }
 template <int V> struct Vec<float, V> {
     static __device__ __forceinline__ void load(const float* p, float (&o)[V]) {
         if constexpr (V % 4 == 0) {
@@ -82,11 +114,8 @@ template <int V> struct Vec<float, V> {
                 const float4 q = reinterpret_cast<const float4*>(p)[k];
                 o[4 * k] = q.x; o[4 * k + 1] = q.y; o[4 * k + 2] = q.z; o[4 * k + 3] = q.w;
             }
-        } else if constexpr (V == 2) {
-            const float2 q = *reinterpret_cast<const float2*>(p);
-            o[0] = q.x; o[1] = q.y;
         } else {
-            o[0] = p[0];
+            Pieces<float, chunk_align(V, 4), V>::load(p, [&](int i, float v) { o[i] = v; });
         }
     }
     static __device__ __forceinline__ void store(float* p, const float (&v)[V]) {
@@ -94,10 +123,8 @@ template <int V> struct Vec<float, V> {
 #pragma unroll
             for (int k = 0; k < V / 4; ++k)
                 reinterpret_cast<float4*>(p)[k] = make_float4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]);
-        } else if constexpr (V == 2) {
-            *reinterpret_cast<float2*>(p) = make_float2(v[0], v[1]);
         } else {
-            p[0] = v[0];
+            Pieces<float, chunk_align(V, 4), V>::store(p, [&](int i) { return v[i]; });
         }
     }
 };
@@ -155,41 +182,28 @@ template <int V> struct Vec<__half, V> : Vec16<__half, V> {};
 // target allows unaligned ones and splits them otherwise.
 template <typename ST, int V> struct VecU;
 template <int V> struct VecU<float, V> {
-    typedef float vt __attribute__((ext_vector_type(V), aligned(4)));
     static __device__ __forceinline__ void load(const float* p, float (&o)[V]) {
-        const vt q = *reinterpret_cast<const vt*>(p);
-#pragma unroll
-        for (int i = 0; i < V; ++i) o[i] = q[i];
+        Pieces<float, 4, V>::load(p, [&](int i, float v) { o[i] = v; });
     }
     static __device__ __forceinline__ void store(float* p, const float (&v)[V]) {
-        vt q;
-#pragma unroll
-        for (int i = 0; i < V; ++i) q[i] = v[i];
-        *reinterpret_cast<vt*>(p) = q;
+        Pieces<float, 4, V>::store(p, [&](int i) { return v[i]; });
     }
 };
 template <typename ST, int V> struct VecU16 {
-    typedef unsigned short vt __attribute__((ext_vector_type(V), aligned(2)));
     static __device__ __forceinline__ void load(const ST* p, float (&o)[V]) {
-        const vt q = *reinterpret_cast<const vt*>(p);
-#pragma unroll
-        for (int i = 0; i < V; ++i) {
-            const unsigned short u = q[i];
+        Pieces<unsigned short, 2, V>::load(reinterpret_cast<const unsigned short*>(p), [&](int i, unsigned short u) {
             ST h;
             __builtin_memcpy(&h, &u, 2);
             o[i] = Store<ST>::load(h);
-        }
+        });
     }
     static __device__ __forceinline__ void store(ST* p, const float (&v)[V]) {
-        vt q;
-#pragma unroll
-        for (int i = 0; i < V; ++i) {
+        Pieces<unsigned short, 2, V>::store(reinterpret_cast<unsigned short*>(p), [&](int i) {
             const ST h = Store<ST>::store(v[i]);
             unsigned short u;
             __builtin_memcpy(&u, &h, 2);
-            q[i] = u;
-        }
-        *reinterpret_cast<vt*>(p) = q;
+            return u;
+        });
     }
 };
 template <int V> struct VecU<__hip_bfloat16, V> : VecU16<__hip_bfloat16, V> {};
@@ -226,6 +240,7 @@ __device__ __forceinline__ void shift_clamp(const float (&q)[V], int sh, float (
 constexpr int kBufWord3 = 0x00020000;
 constexpr int kBufOffNone = 0x40000000;   // past the end of every buffer made here
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x3 __attribute__((ext_vector_type(3)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 template <typename ST, int V> struct BufRow16 {
@@ -251,6 +266,9 @@ template <typename ST, int V> struct BufRow16 {
             if constexpr (NW == 4) {
                 const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
                 wd[0] = q.x; wd[1] = q.y; wd[2] = q.z; wd[3] = q.w;
+            } else if constexpr (NW == 3) {
+                const u32x3 q = __builtin_amdgcn_raw_buffer_load_b96(r, off, 0, 0);
+                wd[0] = q.x; wd[1] = q.y; wd[2] = q.z;
             } else if constexpr (NW == 2) {
                 const u32x2 q = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
                 wd[0] = q.x; wd[1] = q.y;
@@ -274,6 +292,8 @@ template <typename ST, int V> struct BufRow16 {
             for (int k = 0; k < NW; ++k) wd[k] = bits(v[2 * k]) | (unsigned)bits(v[2 * k + 1]) << 16;
             if constexpr (NW == 4) {
                 __builtin_amdgcn_raw_buffer_store_b128(u32x4{wd[0], wd[1], wd[2], wd[3]}, r, off, 0, 0);
+            } else if constexpr (NW == 3) {
+                __builtin_amdgcn_raw_buffer_store_b96(u32x3{wd[0], wd[1], wd[2]}, r, off, 0, 0);
             } else if constexpr (NW == 2) {
                 __builtin_amdgcn_raw_buffer_store_b64(u32x2{wd[0], wd[1]}, r, off, 0, 0);
             } else {
@@ -296,22 +316,24 @@ __device__ __forceinline__ void store_row_f32(__amdgpu_buffer_rsrc_t r, int full
     unsigned w[V];
 #pragma unroll
     for (int i = 0; i < V; ++i) w[i] = __builtin_bit_cast(unsigned, v[i]);
-    if constexpr (V >= 4) {
 #pragma unroll
-        for (int c = 0; c < V / 4; ++c)
-            __builtin_amdgcn_raw_buffer_store_b128(u32x4_{w[4 * c], w[4 * c + 1], w[4 * c + 2], w[4 * c + 3]}, r,
-                                                   full == kBufOffNone ? kBufOffNone : full + 16 * c, 0, 0);
-    } else if constexpr (V == 2) {
-        __builtin_amdgcn_raw_buffer_store_b64(u32x2_{w[0], w[1]}, r, full, 0, 0);
-    }
+    for (int c = 0; c < V / 4; ++c)
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4_{w[4 * c], w[4 * c + 1], w[4 * c + 2], w[4 * c + 3]}, r,
+                                               full == kBufOffNone ? kBufOffNone : full + 16 * c, 0, 0);
+    constexpr int C2 = V / 4 * 4, C1 = V / 2 * 2;   // where the rest of 2 and of 1 start
+    if constexpr (V & 2)
+        __builtin_amdgcn_raw_buffer_store_b64(u32x2_{w[C2 % V], w[(C2 + 1) % V]}, r,
+                                              full == kBufOffNone ? kBufOffNone : full + 4 * C2, 0, 0);
+    if constexpr (V & 1)
+        __builtin_amdgcn_raw_buffer_store_b32(w[C1 % V], r, full == kBufOffNone ? kBufOffNone : full + 4 * C1, 0, 0);
     if constexpr (V >= 2) {
-        // chunk of 4 at element 0 (V = 8 only: k < 8), of 2 at element k & 4,
+        // chunk of 4 at element 0 (k >= 4 needs V > 4), of 2 at element k & 4,
         // of 1 at element k & 6
-        if constexpr (V == 8)
-            __builtin_amdgcn_raw_buffer_store_b128(u32x4_{w[0], w[1], w[2], w[3]}, r,
+        if constexpr (V > 4)
+            __builtin_amdgcn_raw_buffer_store_b128(u32x4_{w[0], w[1 % V], w[2 % V], w[3 % V]}, r,
                                                    (k & 4) ? tail : kBufOffNone, 0, 0);
-        if constexpr (V >= 4) {
-            const bool hi = (k & 4) != 0;
+        if constexpr (V >= 3) {
+            const bool hi = V > 4 && (k & 4) != 0;
             __builtin_amdgcn_raw_buffer_store_b64(u32x2_{hi ? w[4 % V] : w[0], hi ? w[5 % V] : w[1]}, r,
                                                   (k & 2) ? tail + 4 * (k & 4) : kBufOffNone, 0, 0);
         }
@@ -442,7 +464,7 @@ __device__ __forceinline__ void stream_piece(const ST* __restrict__ src, ST* __r
     // waits for an input plane count exactly the operations issued after it
     // (measured: 760 -> 870 Gvoxel-iter/s for bfloat16 on the 512^3 cube; FP32
     // keeps plain loads and stores, which the halo rows skip, and is 2 % faster so).
-    constexpr bool BUF = VEC && sizeof(ST) == 2;
+    constexpr bool BUF = VEC && sizeof(ST) == 2 && (V % 2 == 0 || V == 1);
     const int yb = max(ry0, 0);
     const int tile_bytes = (min(ry0 + rows, ny) - yb) * nx * (int)sizeof(ST);
     const int st_off = (row_store && xl0 >= ox0 && xl0 + V <= ox1) ? ((y - yb) * nx + xl0) * (int)sizeof(ST)

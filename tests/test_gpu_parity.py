@@ -329,3 +329,51 @@ def test_grouped_workgroups_16bit_bitwise(dev, dtype):
     y = f.run(x)
     torch.cuda.synchronize()
     assert torch.equal(y, y0)
+
+
+# The automatic schedule's chunks of 3, 5, 6 and 7 voxels per lane (one x tile
+# and several, rows that end on a chunk and rows that do not, buffers that
+# start off a chunk's alignment), bitwise against the naive schedule.
+CHUNK_SHAPES = [((24, 20, 187), 3), ((24, 20, 186), 3), ((30, 20, 90), 3), ((30, 20, 91), 3), ((30, 20, 45), 3),
+                ((40, 30, 300), 5), ((40, 31, 293), 5), ((120, 300, 601), 5), ((40, 30, 384), 6), ((40, 30, 381), 6),
+                ((80, 300, 702), 6), ((24, 60, 441), 7), ((30, 24, 431), 7)]
+
+
+@pytest.mark.parametrize("cond", CONDS)
+@pytest.mark.parametrize("shape,vec", CHUNK_SHAPES)
+def test_automatic_chunks_bitwise(dev, cond, shape, vec):
+    import torch
+    import paper_1609_03782_amd as ig
+    assert ig.schedule_auto(shape, cond=cond)["vec"] == vec
+    n = shape[0] * shape[1] * shape[2]
+    big = torch.randn(n + 8, generator=torch.Generator(device=dev).manual_seed(n), device=dev) * 2.0
+    big[n // 2] = 14.0
+    for dtype, tt in (("f32", torch.float32), ("bf16", torch.bfloat16), ("f16", torch.float16)):
+        src = big.to(tt)
+        for n_iter, off in ((1, 0), (5, 0), (4, 1), (4, 2)):
+            x = src[off:off + n].view(shape)
+            f = ig.Filter(shape, K=1.7, tau=0.05, n_iter=n_iter, C=(1.0, 0.8, 1.3), cond=cond, dtype=dtype)
+            dst = torch.full((n + 8,), 7.0, device=dev, dtype=tt)
+            y = f.run(x, dst[off:off + n].view(shape))
+            sched = f.schedule()
+            f.set_schedule(kind="naive")
+            ref = f.run(x)
+            assert torch.equal(y, ref), (dtype, n_iter, off, sched)
+            assert bool((dst[:off] == 7.0).all()) and bool((dst[off + n:] == 7.0).all())
+            f.set_schedule(**sched)          # what the library reports it also takes
+            assert torch.equal(f.run(x), ref)
+            f.close()
+
+
+def test_automatic_chunk_schedule_feeds_deeper_passes(dev):
+    import torch
+    import paper_1609_03782_amd as ig
+    shape = (40, 30, 300)
+    x = torch.randn(shape, generator=torch.Generator(device=dev).manual_seed(3), device=dev)
+    f = ig.Filter(shape, n_iter=7)
+    y, sched = f.run(x), f.schedule()
+    assert sched["vec"] == 5
+    f.set_schedule(**dict(sched, t_block=3))
+    assert torch.equal(f.run(x), y)
+    with pytest.raises(ig.IgError):
+        f.set_schedule(**dict(sched, vec=7))
