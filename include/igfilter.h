@@ -287,7 +287,9 @@ int32_t ig_batch_cache_size(void);
 
 /* Schedule of later ig_filter_batch plans: steps per pass t_block (1..4; 0 =
  * library default), wavefronts per workgroup (1..16, > 2 t_block) and planes
- * per z-chunk of a piece (1..4096; default 32).  All items of a batch must
+ * per z-chunk of a piece of the persistent launch (1..4096; default 32; the
+ * launches per pass round deal equal shares of planes to their workgroups
+ * whatever it is).  All items of a batch must
  * share one conductance, and those not run LDS-resident need nx <= 256. */
 ig_status ig_batch_set_schedule(int32_t t_block, int32_t waves, int32_t zchunk);
 
@@ -307,7 +309,7 @@ ig_status ig_batch_set_resident(int32_t max_voxels);
 ig_status ig_batch_get_resident(int32_t* max_voxels);
 
 /* Batch autotuner: runs the batch with t_block 1..4, waves 8, 12 and 16,
- * z-chunks of 16, 32 and 64 planes, both launch modes, and, when some cube is
+ * both launch modes (the persistent one with z-chunks of 16, 32 and 64 planes), and, when some cube is
  * small enough, with the resident limit at 32768 and at 0; keeps the fastest
  * (sets it as by ig_batch_set_schedule, ig_batch_set_launch and
  * ig_batch_set_resident, and keeps only that plan cached) and returns the

@@ -30,6 +30,7 @@ def _units():
              ("smooth", "smooth.hip", []), ("wavelet", "wavelet.hip", []),
              ("noalloc", "noalloc.hip", [])]
     for c in range(3):
+        units.append((f"batch_c{c}", "batch_inst.hip", [f"-DIG_COND={c}"]))
         for d in range(3):
             units.append((f"stencil_c{c}_d{d}", "stencil_inst.hip", [f"-DIG_COND={c}", f"-DIG_DTYPE={d}"]))
     extra = os.path.join(CSRC, "surrogate.hip")

@@ -353,7 +353,8 @@ extern "C" ig_status ig_filter_get_schedule(const ig_filter* f, ig_schedule* s) 
 // Plan (once) and upload the piece table of the pass of depth T.
 static ig_status get_plan(ig_filter* f, const ig_schedule& sched, int T, const PassPlan** out, const Piece** dev) {
     if (!f->planned[T]) {
-        const char* why = plan_pass(f->p, sched, T, f->ncu, &f->plans[T]);
+        // a caller's schedule was checked when it was set
+        const char* why = plan_pass(f->p, sched, T, f->ncu, &f->plans[T], true);
         if (why) return fail(IG_ERR_INVALID_ARG, "schedule cannot serve this shape: %s", why);
         // the piece table, then (grouped plans) each workgroup's first piece
         const PassPlan& pl = f->plans[T];

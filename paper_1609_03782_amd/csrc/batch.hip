@@ -3,9 +3,10 @@
 // ig_filter_batch in include/igfilter.h.
 //
 // Work items are (cube, pass, piece).  Round r of the graph is one launch of
-// k_batch_round over the pieces of pass r of every cube that has one, largest
-// cubes first; the kernel boundary between rounds orders the passes, so no
-// workgroup ever waits on another.  Cubes small enough to live in one compute
+// k_batch_round over pass r of every cube that has one, largest cubes first,
+// dealt to the workgroups in equal shares of (cube, tile, plane) steps; the
+// kernel boundary between rounds orders the passes, so no workgroup ever waits
+// on another.  Cubes small enough to live in one compute
 // unit's LDS (at most kResidentMax voxels, when enabled) skip the passes: one
 // workgroup of k_batch_resident loads the cube, runs all n steps in LDS and
 // writes the result.  The graph holds the counter reset (which also stamps
@@ -25,38 +26,11 @@
 #include <string>
 #include <vector>
 
-#include "internal.h"
+#include "batch_kernels.h"
 
 using namespace igk;
 
 namespace igk {
-
-struct BatchCube {
-    const float* in;
-    float* out;
-    float* scratch;
-    BlockGeom g;
-    int V;
-    int npieces;       // pieces per pass
-    int piece_off;     // first piece in the shared table
-    int npass;         // passes
-    int stage;         // 1: input copied to scratch first (in place, odd passes); 2: no passes, copy in -> out
-    int niter;         // iterations (the resident kernel runs them all)
-    long n;
-};
-
-struct BatchItem {
-    int cube, pass, piece, depth;
-};
-
-constexpr int kCtrNext = 0;    // persistent launch: next item to take
-constexpr int kCtrAbort = 1;   // persistent launch: set when a dependency wait ran out of time
-constexpr int kCtrFin = 2;     // + cube: pieces done (rounds: of the last pass; persistent: of every pass)
-// A dependency wait of the persistent launch gives up after 2 s of the
-// 100 MHz constant clock (the whole 96-cube batch takes ~12 ms): every cube
-// is then marked failed and every workgroup leaves, so a mistake ends in an
-// error, never in a wait without end.
-constexpr unsigned long long kWaitTicks = 200000000ULL;
 
 // ------------------------------------------------------------ rms pre-pass
 struct SumChunk {
@@ -174,294 +148,11 @@ k_batch_nan(const BatchCube* __restrict__ cubes, const SumChunk* __restrict__ ch
     for (long i = threadIdx.x; i < ch.len; i += 256) out[ch.off + i] = q;
 }
 
-// Batch cubes have nx <= 256, so the automatic layout is 4 voxels per lane
-// with 1, 2 or 4 rows per wavefront, or 1 or 2 voxels per lane when nx < 4.
-template <int COND, int T, int D>
-__device__ __forceinline__ void run_piece_v(const BatchCube& cb, const float* src, float* dst, const Piece pc,
-                                            const DevParams& P, float* lds) {
-    const bool vec = cb.g.vec;
-    if (cb.V == 1) {
-        stream_piece<COND, float, 1, D, true, 1>(src, dst, cb.g, pc, P, lds);
-        return;
-    }
-    if (cb.V == 2) {
-        vec ? stream_piece<COND, float, 2, D, true, 1>(src, dst, cb.g, pc, P, lds)
-            : stream_piece<COND, float, 2, D, false, 1>(src, dst, cb.g, pc, P, lds);
-        return;
-    }
-    switch (cb.g.R) {
-        case 4: vec ? stream_piece<COND, float, 4, D, true, 4>(src, dst, cb.g, pc, P, lds)
-                    : stream_piece<COND, float, 4, D, false, 4>(src, dst, cb.g, pc, P, lds); break;
-        case 2: vec ? stream_piece<COND, float, 4, D, true, 2>(src, dst, cb.g, pc, P, lds)
-                    : stream_piece<COND, float, 4, D, false, 2>(src, dst, cb.g, pc, P, lds); break;
-        default: vec ? stream_piece<COND, float, 4, D, true, 1>(src, dst, cb.g, pc, P, lds)
-                     : stream_piece<COND, float, 4, D, false, 1>(src, dst, cb.g, pc, P, lds); break;
-    }
-}
-
-// One round: workgroup b runs piece items[b] (one pass of one piece of one cube).
-template <int COND, int T>
-__global__ void __launch_bounds__(1024)
-k_batch_round(const BatchCube* __restrict__ cubes, const BatchItem* __restrict__ items,
-              const Piece* __restrict__ pieces, const DevParams* __restrict__ prm, int* __restrict__ ctr,
-              unsigned long long* __restrict__ stamps) {
-    extern __shared__ float lds[];
-    const int tid = threadIdx.y * 64 + threadIdx.x;
-    const BatchItem item = items[blockIdx.x];
-    const BatchCube& cb = cubes[item.cube];
-    const DevParams P = prm[item.cube];
-    if (P.abort) return;
-    // pass k (1-based) writes out if (npass - k) is even, else scratch
-    const int k = item.pass + 1;
-    const float* src = item.pass == 0 ? (cb.stage ? cb.scratch : cb.in)
-                                      : (((cb.npass - (k - 1)) % 2 == 0) ? cb.out : cb.scratch);
-    float* dst = ((cb.npass - k) % 2 == 0) ? cb.out : cb.scratch;
-    const Piece pc = pieces[cb.piece_off + item.piece];
-    if constexpr (T >= 1) if (item.depth == 1) run_piece_v<COND, T, 1>(cb, src, dst, pc, P, lds);
-    if constexpr (T >= 2) if (item.depth == 2) run_piece_v<COND, T, 2>(cb, src, dst, pc, P, lds);
-    if constexpr (T >= 3) if (item.depth == 3) run_piece_v<COND, T, 3>(cb, src, dst, pc, P, lds);
-    if constexpr (T >= 4) if (item.depth == 4) run_piece_v<COND, T, 4>(cb, src, dst, pc, P, lds);
-    if (item.pass == cb.npass - 1) {   // completion stamp of the cube
-        __syncthreads();
-        if (tid == 0) {
-            const int prev = atomicAdd(&ctr[kCtrFin + item.cube], 1);
-            if (prev + 1 == cb.npieces) stamps[1 + item.cube] = wall_clock64();
-        }
-    }
-}
-
-// The whole item list in one launch: each workgroup takes the next item from
-// a counter, waits until every piece of the previous pass of its cube is
-// done, runs the piece and counts it done.  Items are listed pass-major (all
-// cubes' pass r before any cube's pass r + 1), so an item waits only on items
-// taken earlier by running workgroups, which wait only on still earlier ones:
-// every wait ends.  Cross-XCD visibility (each XCD has its own L2): the
-// waiting wavefront polls with relaxed device-scope loads (no cache
-// invalidation per poll), then takes one acquire fence (invalidate) before
-// the workgroup reads the previous pass; after a piece, every wavefront
-// drains its stores, the workgroup synchronises, and wavefront 0 takes one
-// release fence (L2 write-back) before counting the piece.  Pieces of a cube
-// whose input was non-finite run nothing but are still counted.
-//
-// All control flow around the barriers is wave-uniform: wavefront 0 as a
-// whole takes, waits for and publishes items, every value it branches on is
-// made uniform with readfirstlane, and each counter update is one atomic whose
-// other lanes add 0.  (With a single-lane `if` around the dequeue, the
-// compiler let the other lanes of the loop pass the start barrier without the
-// dequeue, so they kept rerunning the previous item.)
-template <int COND, int T>
-__global__ void __launch_bounds__(1024)
-k_batch_persist(const BatchCube* __restrict__ cubes, const BatchItem* __restrict__ items, int nitems,
-                const Piece* __restrict__ pieces, DevParams* __restrict__ prm, int ncubes, int* __restrict__ ctr,
-                unsigned long long* __restrict__ stamps) {
-    extern __shared__ float lds[];
-    __shared__ int s_item, s_go;
-    const int lane = threadIdx.x;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.y);
-    const unsigned long long t_end = wall_clock64() + kWaitTicks;
-    const int one = lane == 0 ? 1 : 0;
-    for (;;) {
-        if (w == 0) {
-            const int it = __builtin_amdgcn_readfirstlane(atomicAdd(&ctr[kCtrNext], one));
-            int go = it < nitems ? 1 : 0;
-            if (go && __builtin_amdgcn_readfirstlane(
-                          __hip_atomic_load(&ctr[kCtrAbort], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
-                go = 0;
-            if (go) {
-                const int cube = __builtin_amdgcn_readfirstlane(items[it].cube);
-                const int need = __builtin_amdgcn_readfirstlane(items[it].pass * cubes[cube].npieces);
-                if (need > 0) {
-                    for (;;) {
-                        const int fin = __builtin_amdgcn_readfirstlane(
-                            __hip_atomic_load(&ctr[kCtrFin + cube], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-                        if (fin >= need) break;
-                        if (__builtin_amdgcn_readfirstlane(
-                                __hip_atomic_load(&ctr[kCtrAbort], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
-                            go = 0;
-                            break;
-                        }
-                        if (wall_clock64() > t_end) {
-                            __hip_atomic_store(&ctr[kCtrAbort], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            for (int c = lane; c < ncubes; c += 64)
-                                __hip_atomic_store(&prm[c].abort, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            go = 0;
-                            break;
-                        }
-                        __builtin_amdgcn_s_sleep(8);
-                    }
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-                    __builtin_amdgcn_s_waitcnt(0);
-                }
-            }
-            s_item = it;   // every lane writes the same values
-            s_go = go;
-        }
-        __syncthreads();
-        const int go = __builtin_amdgcn_readfirstlane(s_go);
-        if (!go) break;
-        const int it = __builtin_amdgcn_readfirstlane(s_item);
-        const BatchItem item = items[it];
-        const BatchCube& cb = cubes[item.cube];
-        const DevParams P = prm[item.cube];
-        if (!P.abort) {
-            const int k = item.pass + 1;
-            const float* src = item.pass == 0 ? (cb.stage ? cb.scratch : cb.in)
-                                              : (((cb.npass - (k - 1)) % 2 == 0) ? cb.out : cb.scratch);
-            float* dst = ((cb.npass - k) % 2 == 0) ? cb.out : cb.scratch;
-            const Piece pc = pieces[cb.piece_off + item.piece];
-            if constexpr (T >= 1) if (item.depth == 1) run_piece_v<COND, T, 1>(cb, src, dst, pc, P, lds);
-            if constexpr (T >= 2) if (item.depth == 2) run_piece_v<COND, T, 2>(cb, src, dst, pc, P, lds);
-            if constexpr (T >= 3) if (item.depth == 3) run_piece_v<COND, T, 3>(cb, src, dst, pc, P, lds);
-            if constexpr (T >= 4) if (item.depth == 4) run_piece_v<COND, T, 4>(cb, src, dst, pc, P, lds);
-        }
-        __builtin_amdgcn_s_waitcnt(0);   // this wavefront's stores have reached its L2
-        __syncthreads();
-        if (w == 0) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-            __builtin_amdgcn_s_waitcnt(0);
-            const int prev = __builtin_amdgcn_readfirstlane(
-                __hip_atomic_fetch_add(&ctr[kCtrFin + item.cube], one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-            if (prev + 1 == cb.npass * cb.npieces) stamps[1 + item.cube] = wall_clock64();
-        }
-    }
-}
-
-// LDS-resident cubes.  One workgroup holds the whole cube in LDS; with nth
-// threads (64 to kResThreads, sized to the cube so that small cubes share a
-// compute unit), voxel v = tid + nth k belongs to thread tid.  Each
-// step, every thread evaluates its voxels from LDS into registers with the
-// per-voxel formula of every other schedule (the edge terms and combine()
-// in the same order), the workgroup synchronises, the new values go back to
-// LDS, and it synchronises again.  A neighbour outside the cube is read as
-// the voxel itself, so its difference is +0 and its edge term +0, bitwise
-// what the closed coefficient gives.  HBM is read once and written once.
-constexpr int kResThreads = 1024;
-constexpr int kResPerThread = 32;
-
-template <int COND>
-__global__ void __launch_bounds__(kResThreads)
-k_batch_resident(const BatchCube* __restrict__ cubes, const int* __restrict__ res, const DevParams* __restrict__ prm,
-                 unsigned long long* __restrict__ stamps) {
-    extern __shared__ float lds[];
-    const int c = res[blockIdx.x];
-    const BatchCube& cb = cubes[c];
-    const DevParams P = prm[c];
-    if (P.abort) return;
-    const int nx = cb.g.nx, ny = cb.g.ny, nz = cb.g.nz;
-    const int plane = nx * ny, N = plane * nz;
-    const int tid = threadIdx.x, nth = blockDim.x;
-    for (int v = tid; v < N; v += nth) lds[v] = cb.in[v];
-    // which of the six neighbours of each of this thread's voxels exist: six
-    // bits per voxel, four voxels per register
-    // (coordinates stepped from voxel to voxel: v grows by nth)
-    unsigned fm[kResPerThread / 4];
-#pragma unroll
-    for (int j = 0; j < kResPerThread / 4; ++j) fm[j] = 0u;
-    {
-        const int dx = nth % nx, dy = (nth / nx) % ny, dz = nth / plane;
-        int x = tid % nx, y = (tid / nx) % ny, z = tid / plane;
-#pragma unroll
-        for (int k = 0; k < kResPerThread; ++k) {
-            const unsigned b = (x > 0 ? 1u : 0u) | (x + 1 < nx ? 2u : 0u) | (y > 0 ? 4u : 0u) |
-                               (y + 1 < ny ? 8u : 0u) | (z > 0 ? 16u : 0u) | (z + 1 < nz ? 32u : 0u);
-            fm[k / 4] |= b << (8 * (k % 4));
-            x += dx;
-            if (x >= nx) { x -= nx; ++y; }
-            y += dy;
-            if (y >= ny) { y -= ny; ++z; }
-            z += dz;
-        }
-    }
-    __syncthreads();
-    for (int s = 0; s < cb.niter; ++s) {
-        // recompute the neighbour addresses every step rather than keep 6 per
-        // voxel live across the loop (they would not fit in registers)
-        int t0 = tid;
-        asm volatile("" : "+v"(t0));
-        unsigned fs[kResPerThread / 4];
-#pragma unroll
-        for (int j = 0; j < kResPerThread / 4; ++j) {
-            fs[j] = fm[j];
-            asm volatile("" : "+v"(fs[j]));
-        }
-        float nv[kResPerThread];
-#pragma unroll
-        for (int k = 0; k < kResPerThread; ++k) {
-            const int v = t0 + nth * k;
-            if (v < N) {
-                const unsigned m = fs[k / 4] >> (8 * (k % 4));
-                const float I = lds[v];
-                const float xm = lds[(m & 1u) ? v - 1 : v], xp = lds[(m & 2u) ? v + 1 : v];
-                const float ym = lds[(m & 4u) ? v - nx : v], yp = lds[(m & 8u) ? v + nx : v];
-                const float zm = lds[(m & 16u) ? v - plane : v], zp = lds[(m & 32u) ? v + plane : v];
-                const float exm = edge_term<COND>(I - xm, P.coef[0], P.kap);
-                const float exp_ = edge_term<COND>(xp - I, P.coef[0], P.kap);
-                const float eym = edge_term<COND>(I - ym, P.coef[1], P.kap);
-                const float eyp = edge_term<COND>(yp - I, P.coef[1], P.kap);
-                const float ezm = edge_term<COND>(I - zm, P.coef[2], P.kap);
-                const float ezp = edge_term<COND>(zp - I, P.coef[2], P.kap);
-                nv[k] = combine<COND>(I, exm, exp_, eym, eyp, ezm, ezp, P.kap, P.tau);
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < kResPerThread; ++k) {
-            const int v = t0 + nth * k;
-            if (v < N) lds[v] = nv[k];
-        }
-        __syncthreads();
-    }
-    for (int v = tid; v < N; v += nth) cb.out[v] = lds[v];
-    __syncthreads();
-    if (tid == 0) stamps[1 + c] = wall_clock64();
-}
-
-using ResidentKernel = void (*)(const BatchCube*, const int*, const DevParams*, unsigned long long*);
-static ResidentKernel resident_kernel(int cond) {
-    switch (cond) {
-        case COND_INTENSITY: return k_batch_resident<COND_INTENSITY>;
-        case COND_PM_EXP: return k_batch_resident<COND_PM_EXP>;
-        default: return k_batch_resident<COND_PM_RATIONAL>;
-    }
-}
-
-using BatchKernel = void (*)(const BatchCube*, const BatchItem*, const Piece*, const DevParams*, int*,
-                             unsigned long long*);
-
-template <int COND>
-static BatchKernel batch_kernel_T(int T) {
-    switch (T) {
-        case 1: return k_batch_round<COND, 1>;
-        case 2: return k_batch_round<COND, 2>;
-        case 3: return k_batch_round<COND, 3>;
-        default: return k_batch_round<COND, 4>;
-    }
-}
-static BatchKernel batch_kernel(int cond, int T) {
-    switch (cond) {
-        case COND_INTENSITY: return batch_kernel_T<COND_INTENSITY>(T);
-        case COND_PM_EXP: return batch_kernel_T<COND_PM_EXP>(T);
-        default: return batch_kernel_T<COND_PM_RATIONAL>(T);
-    }
-}
-
-using PersistKernel = void (*)(const BatchCube*, const BatchItem*, int, const Piece*, DevParams*, int, int*,
-                               unsigned long long*);
-template <int COND>
-static PersistKernel persist_kernel_T(int T) {
-    switch (T) {
-        case 1: return k_batch_persist<COND, 1>;
-        case 2: return k_batch_persist<COND, 2>;
-        case 3: return k_batch_persist<COND, 3>;
-        default: return k_batch_persist<COND, 4>;
-    }
-}
-static PersistKernel persist_kernel(int cond, int T) {
-    switch (cond) {
-        case COND_INTENSITY: return persist_kernel_T<COND_INTENSITY>(T);
-        case COND_PM_EXP: return persist_kernel_T<COND_PM_EXP>(T);
-        default: return persist_kernel_T<COND_PM_RATIONAL>(T);
-    }
+const BatchKernels* batch_kernels_c0();
+const BatchKernels* batch_kernels_c1();
+const BatchKernels* batch_kernels_c2();
+const BatchKernels* batch_kernels(int cond) {
+    return cond == COND_INTENSITY ? batch_kernels_c0() : cond == COND_PM_EXP ? batch_kernels_c1() : batch_kernels_c2();
 }
 
 }  // namespace igk
@@ -516,7 +207,8 @@ struct BatchPlan {
     std::vector<size_t> res_lds;  // per class: LDS bytes of its largest cube
     std::vector<int> resident;    // per cube: wavefronts of its resident workgroup (0: not resident)
     std::vector<int> niter;
-    std::vector<int> round_off;   // items of round r: [round_off[r], round_off[r+1])
+    std::vector<int> round_off;   // round r: workgroups [round_off[r], round_off[r+1]), first items at d_first[round_off[r] + r]
+    DevBuf<int> d_first;
     int nitems = 0, nchunks = 0;
     size_t lds = 0;
     hipStream_t cap = nullptr;
@@ -603,6 +295,65 @@ ig_status rebind(BatchPlan* bp, const ig_batch_item* items, int count, hipStream
     return IG_OK;
 }
 
+// The rounds: round r lays the tiles of pass r of every cube (largest cubes
+// first) end to end as a sequence of plane steps and deals it to the workgroups
+// in contiguous shares of equal cost, so that no round waits for a longest
+// piece (fixed chunks of 32 planes left the 96-cube batch's first rounds six
+// turns of the GPU for 5.7 turns' work, and paid the pipeline's fill on every
+// chunk; 96 cubes of 32 .. 256 voxels a side: 9.11 -> 6.96 ms, the rows of 3
+// voxels per lane included).  A share's items are its
+// parts of the tiles it meets; each refills the pipeline (3 depths), which
+// counts at the start of a tile.  A plane step's weight is the line of
+// step_weight (idle rows of a tile that is taller than its cube cost little).
+void deal_rounds(std::vector<BatchCube>& cubes, const std::vector<std::vector<int>>& depths,
+                 const std::vector<int>& order, int maxpass, long slots, int W, std::vector<BatchItem>* its,
+                 std::vector<Piece>* pieces, std::vector<int>* first, std::vector<int>* round_off) {
+    struct Tile { int cube, tx, ty; double w, start; };   // start: its cost position
+    for (int k = 0; k < maxpass; ++k) {
+        std::vector<Tile> tiles;
+        double tot = 0.0;
+        long planes = 0;
+        for (int c : order) {
+            if (k >= cubes[c].npass) continue;
+            const BlockGeom& g = cubes[c].g;
+            const int busy = std::min(W, (std::min(g.ny, W * g.R) + g.R - 1) / g.R);
+            const double w = step_weight(cubes[c].V, g.R, busy, g.vec == 0);
+            for (int t = 0; t < g.ntx * g.nty; ++t) {
+                tiles.push_back(Tile{c, t % g.ntx, t / g.ntx, w, tot});
+                tot += w * (g.nz + 3 * depths[c][k]);
+                planes += g.nz;
+            }
+            if (k + 1 == cubes[c].npass) cubes[c].nlast = 0;   // counted below
+        }
+        const long G = std::max(1L, std::min(slots, planes));
+        size_t t = 0;
+        int z = 0;                                   // next plane of tile t
+        for (long b = 0; b < G; ++b) {
+            first->push_back((int)its->size());
+            const double end = b + 1 == G ? 1e300 : tot * (double)(b + 1) / (double)G;
+            while (t < tiles.size()) {
+                const Tile& tl = tiles[t];
+                BatchCube& cb = cubes[tl.cube];
+                const int fill = 3 * depths[tl.cube][k];
+                // planes of this tile that start before the share's end
+                const double upto = (end - tl.start) / tl.w - fill;
+                const int z1 = upto >= cb.g.nz ? cb.g.nz : std::max(z, (int)upto);
+                if (z1 > z) {
+                    its->push_back(BatchItem{tl.cube, k, (int)pieces->size() - cb.piece_off, depths[tl.cube][k]});
+                    pieces->push_back(Piece{tl.tx, tl.ty, z, z1});
+                    if (k + 1 == cb.npass) ++cb.nlast;
+                }
+                z = z1;
+                if (z < cb.g.nz) break;              // the share ends inside this tile
+                ++t;
+                z = 0;
+            }
+        }
+        first->push_back((int)its->size());
+        round_off->push_back(round_off->back() + (int)G);
+    }
+}
+
 ig_status build_plan(const ig_batch_item* items, int count, int device, BatchPlan* bp) {
     bp->device = device;
     bp->count = count;
@@ -683,16 +434,23 @@ ig_status build_plan(const ig_batch_item* items, int count, int device, BatchPla
         s.t_block = T;
         s.waves = W;
         s.zchunk = g_batch_Z;
-        s.vec = 0;
+        // 3 voxels per lane cover rows of up to 48, 96 and 192 voxels with 4, 2
+        // and 1 rows per wavefront: fewer idle lanes than 4 do
+        int V, R;
+        auto_vec_rows(p.nx, &V, &R);
+        if (T <= 2 && V == 4 && (64 / R) * 3 >= p.nx) V = 3;
+        s.vec = V;
+        s.rows = R;
         PassPlan pp;
-        const char* why = plan_pass(p, s, T, ncu, &pp);
+        const char* why = plan_pass(p, s, T, ncu, &pp, true);
         if (why) return fail(IG_ERR_INVALID_ARG, "batch item %d: %s", c, why);
         if (pp.g.grouped) return fail(IG_ERR_DEVICE, "batch item %d: unexpected grouped plan", c);
-        if (pp.V != 4 && pp.V != 2 && pp.V != 1)
+        if (pp.V > 4)
             return fail(IG_ERR_UNSUPPORTED, "batch item %d: layout with %d voxels per lane", c, pp.V);
         lds = std::max(lds, stream_lds_bytes(pp.V, T, W));
         cb.g = pp.g;
-        if (((uintptr_t)cb.in % (pp.V * 4)) || ((uintptr_t)cb.out % (pp.V * 4))) cb.g.vec = 0;
+        const uintptr_t al = (uintptr_t)chunk_align(pp.V, 4);
+        if (((uintptr_t)cb.in % al) || ((uintptr_t)cb.out % al)) cb.g.vec = 0;
         cb.V = pp.V;
         cb.npieces = (int)pp.pieces.size();
         cb.piece_off = (int)pieces.size();
@@ -728,12 +486,17 @@ ig_status build_plan(const ig_batch_item* items, int count, int device, BatchPla
     int maxpass = 0;
     for (int c = 0; c < count; ++c) maxpass = std::max(maxpass, cubes[c].npass);
     std::vector<BatchItem> its;
+    std::vector<int> first;
     bp->round_off.assign(1, 0);
-    for (int k = 0; k < maxpass; ++k) {
-        for (int c : order)
-            if (k < cubes[c].npass)
-                for (int j = 0; j < cubes[c].npieces; ++j) its.push_back(BatchItem{c, k, j, depths[c][k]});
-        bp->round_off.push_back((int)its.size());
+    for (int c = 0; c < count; ++c) cubes[c].nlast = cubes[c].npieces;
+    if (bp->persist) {
+        for (int k = 0; k < maxpass; ++k)
+            for (int c : order)
+                if (k < cubes[c].npass)
+                    for (int j = 0; j < cubes[c].npieces; ++j) its.push_back(BatchItem{c, k, j, depths[c][k]});
+    } else {
+        deal_rounds(cubes, depths, order, maxpass, (long)ncu * resident_per_cu(W, lds), W, &its, &pieces, &first,
+                    &bp->round_off);
     }
     bp->nitems = (int)its.size();
     bp->nchunks = (int)chunks.size();
@@ -743,6 +506,7 @@ ig_status build_plan(const ig_batch_item* items, int count, int device, BatchPla
     HIP_TRY(bp->d_cubes.alloc(count));
     HIP_TRY(bp->d_items.alloc(its.size()));
     HIP_TRY(bp->d_pieces.alloc(pieces.size()));
+    HIP_TRY(bp->d_first.alloc(first.size()));
     HIP_TRY(bp->d_chunks.alloc(chunks.size()));
     HIP_TRY(bp->d_chunk_first.alloc(count + 1));
     HIP_TRY(bp->d_part.alloc(3 * chunks.size()));
@@ -766,13 +530,16 @@ ig_status build_plan(const ig_batch_item* items, int count, int device, BatchPla
         HIP_TRY(hipMemcpy(bp->d_items.p, its.data(), its.size() * sizeof(BatchItem), hipMemcpyHostToDevice));
     if (!pieces.empty())
         HIP_TRY(hipMemcpy(bp->d_pieces.p, pieces.data(), pieces.size() * sizeof(Piece), hipMemcpyHostToDevice));
+    if (!first.empty())
+        HIP_TRY(hipMemcpy(bp->d_first.p, first.data(), first.size() * sizeof(int), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(bp->d_chunks.p, chunks.data(), chunks.size() * sizeof(SumChunk), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(bp->d_chunk_first.p, chunk_first.data(), (count + 1) * sizeof(int), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(bp->d_pin.p, pin.data(), count * sizeof(ParamIn), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(bp->d_nvox.p, nvox.data(), count * sizeof(long), hipMemcpyHostToDevice));
 
-    BatchKernel kern = batch_kernel(bp->cond, T);
-    PersistKernel pkern = persist_kernel(bp->cond, T);
+    const BatchKernels* kernels = batch_kernels(bp->cond);
+    BatchKernel kern = kernels->round[T - 1];
+    PersistKernel pkern = kernels->persist[T - 1];
     if (lds > 65536) {
         HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         HIP_TRY(hipFuncSetAttribute((const void*)pkern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
@@ -781,7 +548,7 @@ ig_status build_plan(const ig_batch_item* items, int count, int device, BatchPla
     // than there are items; the kernel's own 8 bytes of LDS counted), so
     // every workgroup that takes an item is running
     bp->grid = (int)std::min<long>(bp->nitems, (long)ncu * resident_per_cu(W, lds + 16));
-    ResidentKernel rkern = resident_kernel(bp->cond);
+    ResidentKernel rkern = kernels->resident;
     const size_t res_lds_max = *std::max_element(bp->res_lds.begin(), bp->res_lds.end());
     if (res_lds_max > 65536)
         HIP_TRY(hipFuncSetAttribute((const void*)rkern, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -826,8 +593,8 @@ ig_status build_plan(const ig_batch_item* items, int count, int device, BatchPla
         for (size_t r = 0; r + 1 < bp->round_off.size(); ++r) {
             const int n = bp->round_off[r + 1] - bp->round_off[r];
             if (n <= 0) continue;
-            hipLaunchKernelGGL(kern, dim3(n), dim3(64, W), lds, s, bp->d_cubes.p, bp->d_items.p + bp->round_off[r],
-                               bp->d_pieces.p, bp->d_params.p, bp->d_ctr.p, bp->d_stamps.p);
+            hipLaunchKernelGGL(kern, dim3(n), dim3(64, W), lds, s, bp->d_cubes.p, bp->d_items.p,
+                               bp->d_first.p + bp->round_off[r] + r, bp->d_pieces.p, bp->d_params.p, bp->d_ctr.p, bp->d_stamps.p);
             chk(hipGetLastError());
         }
     }
@@ -1025,6 +792,7 @@ extern "C" ig_status ig_batch_autotune(const ig_batch_item* items, int32_t count
                 for (int W : {8, 12, 16})
                     for (int Z : {16, 32, 64}) {
                         if (W <= 2 * T) continue;
+                        if (P == 0 && Z != 32) continue;   // the rounds deal shares, not chunks
                         if (ig_batch_set_schedule(T, W, Z) != IG_OK || ig_batch_set_resident(R) != IG_OK ||
                             ig_batch_set_launch(P) != IG_OK)
                             continue;

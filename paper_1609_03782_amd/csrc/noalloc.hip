@@ -87,7 +87,7 @@ ig_status static_plan(void* self, const ig_schedule& sched, int T, const PassPla
     Piece* d = sp.dev_base + (size_t)(T - 1) * kStaticMaxPieces;
     if (!sp.planned[T]) {
         PassPlan& pp = sp.plans[T];
-        const char* why = plan_pass(*sp.p, sched, T, sp.ncu, &pp);
+        const char* why = plan_pass(*sp.p, sched, T, sp.ncu, &pp, true);
         if (why) return fail(IG_ERR_INVALID_ARG, "schedule cannot serve this shape: %s", why);
         const int count = (int)pp.pieces.size();
         if (count > kStaticMaxPieces) return fail(IG_ERR_UNSUPPORTED, "%d pieces exceed the static table", count);
@@ -115,7 +115,7 @@ ig_schedule static_schedule(const ig_params& p, int ncu) {
     s.rounds = 0;
     s.zchunk = (int)p.nz;
     PassPlan pp;
-    if (plan_pass(p, s, s.t_block, ncu, &pp)) {
+    if (plan_pass(p, s, s.t_block, ncu, &pp, true)) {
         ig_schedule n{};
         n.kind = IG_SCHED_NAIVE;
         return n;

@@ -136,6 +136,8 @@ double pass_cost(const ig_params& p, int V, int R, int W, int T, bool grouped) {
 }
 }  // namespace
 
+double step_weight(int V, int R, int waves, bool ragged) { return step_us(kCost32, V, R, waves, ragged); }
+
 // The layout of the automatic schedule.  The starting point is the
 // power-of-two chunk that covers the row (auto_vec_rows) with 12 wavefronts;
 // another chunk (fewer idle lanes: 300 voxels fill 94 % of 64 lanes of 5 and
@@ -218,7 +220,7 @@ static void group_split(const BlockGeom& g, long ntiles, long G, int T, PassPlan
 
 // Plan the pass of depth T for schedule s; returns nullptr or the reason it
 // cannot serve the shape.
-const char* plan_pass(const ig_params& p, const ig_schedule& s, int T, int ncu, PassPlan* pp) {
+const char* plan_pass(const ig_params& p, const ig_schedule& s, int T, int ncu, PassPlan* pp, bool any_chunk) {
     const int nx = (int)p.nx, ny = (int)p.ny, nz = (int)p.nz;
     int V = s.vec, R = s.rows;
     if (V == 0) {
@@ -233,7 +235,7 @@ const char* plan_pass(const ig_params& p, const ig_schedule& s, int T, int ncu, 
         // the other chunks only as the automatic schedule chooses them (for passes
         // of depth 1 or 2, with or without grouped plans); deeper passes of a
         // schedule that names one run the power-of-two layout
-        bool ours = false;
+        bool ours = any_chunk;
         for (int k = 0; k < 4 && !ours; ++k) {
             int av, ar, aw;
             auto_layout(p, 1 + (k & 1), k < 2, &av, &ar, &aw);

@@ -65,7 +65,10 @@ void auto_vec_rows(int64_t nx, int* V, int* R);
 void auto_layout(const ig_params& p, int T, bool grouped, int* V, int* R, int* W);
 int resident_per_cu(int W, size_t lds);
 // nullptr on success, else the reason schedule s cannot serve p at depth T
-const char* plan_pass(const ig_params& p, const ig_schedule& s, int T, int ncu, PassPlan* pp);
+// (any_chunk: the library's own choice of vec, not the caller's)
+const char* plan_pass(const ig_params& p, const ig_schedule& s, int T, int ncu, PassPlan* pp, bool any_chunk = false);
+// relative cost of a plane step of FP32 tiles with this layout (see plan.cpp)
+double step_weight(int V, int R, int waves, bool ragged);
 ig_status igk_validate_params(const ig_params* p);
 // The library's schedule for p when the caller sets none (grouped = false: for
 // runs whose piece tables hold no grouped plans).

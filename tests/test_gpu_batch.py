@@ -346,3 +346,41 @@ def test_persistent_launch_nonfinite_item(dev):
         ig.batch_set_launch(False)
         ig.batch_set_resident(32768)
         ig.batch_cache_clear()
+
+
+@pytest.mark.parametrize("t_block,waves", [(0, 16), (1, 12), (2, 8), (3, 16)])
+@pytest.mark.parametrize("cond", ["pm_exp", "pm_rational", "intensity"])
+def test_rounds_deal_equal_shares_bitwise(dev, cond, t_block, waves):
+    """Rounds whose workgroups take parts of several cubes and tiles: widths of
+    3 and 4 voxels per lane with 1, 2 and 4 rows per wavefront, whole and ragged
+    rows, buffers off 16-byte alignment, a cube taller and one shorter than a
+    tile; bitwise the naive single-cube run, every cube stamped."""
+    import torch
+    import paper_1609_03782_amd as ig
+    shapes = [(40, 50, 33), (17, 9, 48), (23, 70, 64), (30, 33, 90), (11, 64, 96), (9, 130, 101), (5, 200, 150),
+              (61, 20, 192), (8, 40, 255), (70, 2, 187)]
+    g = torch.Generator(device=dev).manual_seed(5)
+    items, n_iters = [], []
+    for k, s in enumerate(shapes):
+        n, off = s[0] * s[1] * s[2], k % 3
+        x = (torch.randn(n + 4, generator=g, device=dev) * 2.0)[off:off + n].view(s)
+        out = torch.empty(n + 4, device=dev)[off:off + n].view(s)
+        n_iters.append(1 + k % 6)
+        items.append((x, out, dict(K=1.6 + 0.1 * k, tau=0.05, n_iter=n_iters[-1], C=(1.0, 0.8, 1.2), cond=cond,
+                                   rms=1.0 if k % 2 else None)))
+    try:
+        ig.batch_set_resident(0)
+        ig.batch_set_schedule(t_block, waves, 32)
+        res = ig.batch(items, want_latency=True)
+        for _ in range(2):
+            ig.batch(items)
+        for (x, out, kw), lat in zip(items, res["latency_ms"]):
+            f = ig.Filter(tuple(x.shape), **kw)
+            f.set_schedule("naive")
+            assert torch.equal(out, f.run(x)), (tuple(x.shape), kw)
+            assert lat > 0.0
+            f.close()
+    finally:
+        ig.batch_set_resident(32768)
+        ig.batch_set_schedule(0, 16, 32)
+        ig.batch_cache_clear()
