@@ -14,10 +14,14 @@
 //    (a contiguous range of ROI rows per workgroup, four loads in flight per
 //    thread); a fixed shuffle tree and the wavefronts in order make one
 //    partial per workgroup.  Bound by HBM.
-//  * more thresholds: lane j of every wavefront owns mask j.  A wavefront
-//    takes 64-voxel chunks in a fixed order, parks each chunk's three values
-//    as FP64 in its LDS slice, and every lane walks the 64 voxels in order
-//    (a uniform-address LDS read is a broadcast).  One partial per wavefront.
+//  * more thresholds: binned.  With the thresholds sorted, a voxel's filtered
+//    value falls into one bin (the number of thresholds at or below it) and
+//    mask j's sums are the sums of the bins from its rank up, so a voxel costs
+//    one binary search and one addition per sum instead of one per threshold.
+//    The bins live in LDS as FP64, one column per pair of lanes of a
+//    wavefront, the pair's lanes adding one after the other, so no two lanes
+//    ever meet on an address and the order of every sum is fixed.  One partial
+//    per workgroup.
 //
 // k_quality_fold folds each slot over the partials (block b folds slot b:
 // strided per-thread sums, then a fixed tree); k_quality_derive turns the 192
@@ -133,46 +137,165 @@ k_quality_vox(const float* __restrict__ orig, const float* __restrict__ filt, co
     }
 }
 
+// The M_f thresholds in ascending order as FP32 (the smallest value not below
+// the FP64 threshold: the same test), NaN past the last; rank[j]: place of the
+// caller's threshold j.
+struct QSorted {
+    float thr[64];
+    unsigned char rank[64];
+    int n;
+    int pad;
+};
+constexpr int kQCols = 32;      // bin columns of a wavefront
+constexpr int kQU = 16;         // voxels per lane and step, the next step's loads in flight
+constexpr int kQChunk = 256 * kQU;
+
+size_t bins_lds(int n, bool model) {
+    return (size_t)kQWaves * n * kQCols * (model ? 20 : 12);
+}
+
+// STEPS: binary search steps (2^STEPS > n).  FLAT: the ROI is contiguous.  What
+// bounds it: the search and the LDS additions, about 150 cycles of issue per 64
+// voxels with one wavefront per SIMD (the bins fill the LDS).  46 thresholds,
+// a model, 512^3: 425 us (3.8 TB/s), from 4085 us when every voxel was compared
+// with every threshold; the whole call, two noise scans included, 4241 -> 712.
+template <int STEPS, bool MODEL, bool FLAT>
 __global__ void __launch_bounds__(256)
-k_quality_lanes(const float* __restrict__ orig, const float* __restrict__ filt, const float* __restrict__ model,
-                QGeom g, double* __restrict__ part) {
-    __shared__ double vals[kQWaves][64][3];
-    const int lane = threadIdx.x & 63;
-    const int wid = threadIdx.x >> 6;
-    const long nw = (long)gridDim.x * kQWaves;
-    const long gw = (long)blockIdx.x * kQWaves + wid;
-    const double thr = g.thr[lane];
-    const bool mo = lane == 63;
-    double a1 = 0.0, a2 = 0.0, c = 0.0;
-    for (long ch = gw; ch * 64 < g.nroi; ch += nw) {
-        const long r = ch * 64 + lane;
-        double vo = 0.0, vf = 0.0, vm = 0.0;
-        if (r < g.nroi) {
-            const long x = r % g.rx, t = r / g.rx;
-            const long y = t % g.ry, z = t / g.ry;
-            const long idx = (g.x0 + x) + g.nx * ((g.y0 + y) + g.ny * (g.z0 + z));
-            vo = (double)orig[idx];
-            vf = (double)filt[idx];
-            if (g.has_model) vm = (double)model[idx];
-        }
-        vals[wid][lane][0] = vo;
-        vals[wid][lane][1] = vf;
-        vals[wid][lane][2] = vm;
-        __builtin_amdgcn_wave_barrier();
-        const int nv = (int)min(64L, g.nroi - ch * 64);
-        for (int k = 0; k < nv; ++k) {
-            const double so = vals[wid][k][0], sf = vals[wid][k][1], sm = vals[wid][k][2];
-            const bool pass = mo ? (so >= thr) : (sf >= thr);
-            a1 += pass ? so : 0.0;
-            a2 += (pass || mo) ? sm : 0.0;
-            c += pass ? 1.0 : 0.0;
-        }
-        __builtin_amdgcn_wave_barrier();
+k_quality_bins(const float* __restrict__ orig, const float* __restrict__ filt, const float* __restrict__ model,
+               QGeom g, QSorted q, double* __restrict__ part) {
+    extern __shared__ double qb[];
+    __shared__ float T[64];
+    __shared__ double tot[3][64];
+    __shared__ double red[kQWaves][3];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int n = q.n, cells = n * kQCols;
+    if (tid < 64) T[tid] = q.thr[tid];
+    double* so = qb + w * cells;                               // bin b (1..n), column c at [(b - 1) kQCols + c]
+    double* sm = qb + (kQWaves + w) * cells;
+    unsigned* sc = reinterpret_cast<unsigned*>(qb + (MODEL ? 2 : 1) * kQWaves * cells) + w * cells;
+    for (int k = lane; k < cells; k += 64) {
+        so[k] = 0.0;
+        if (MODEL) sm[k] = 0.0;
+        sc[k] = 0;
     }
-    double* out = part + gw * kQSlots;
-    out[3 * lane] = a1;
-    out[3 * lane + 1] = a2;
-    out[3 * lane + 2] = c;
+    __syncthreads();
+    const int col = lane & (kQCols - 1);
+    const bool second = lane >= kQCols;
+    const double thr_o = g.thr[63];
+    double a_oo = 0.0, a_m = 0.0, a_n = 0.0;
+    typedef __attribute__((address_space(3))) double* ldp;
+
+    const long chunks = (g.nroi + kQChunk - 1) / kQChunk;
+    const bool big = g.rx >= (1L << 31) || g.ry >= (1L << 31);
+    const long flat0 = g.x0 + g.nx * (g.y0 + g.ny * g.z0);     // FLAT: first voxel of the ROI
+    auto load = [&](long ch, float (&fo)[kQU], float (&ff)[kQU], float (&fm)[kQU]) {
+        const long e0 = min(ch, chunks - 1) * kQChunk;
+        const int last = (int)min((long)kQChunk, g.nroi - e0) - 1;
+        long rz = 0, ry = 0, rx = 0;                           // of element e0 (the same for the whole workgroup)
+        if constexpr (!FLAT) {
+            const long row = e0 / g.rx;
+            rx = e0 - row * g.rx;
+            rz = row / g.ry;
+            ry = row - rz * g.ry;
+        }
+#pragma unroll
+        for (int u = 0; u < kQU; ++u) {
+            const int k = min(u * 256 + tid, last);
+            long idx;
+            if constexpr (FLAT) {
+                idx = flat0 + e0 + k;
+            } else if (big) {
+                const long x = rx + k, dr = x / g.rx, y = ry + dr, dz = y / g.ry;
+                idx = (g.x0 + (x - dr * g.rx)) + g.nx * ((g.y0 + (y - dz * g.ry)) + g.ny * (g.z0 + rz + dz));
+            } else {   // 32-bit divisions: at most one row and kQChunk voxels past the chunk's start
+                const unsigned x = (unsigned)rx + k, dr = x / (unsigned)g.rx;
+                const unsigned y = (unsigned)ry + dr, dz = y / (unsigned)g.ry;
+                idx = (g.x0 + (x - dr * (unsigned)g.rx)) +
+                      g.nx * ((g.y0 + (y - dz * (unsigned)g.ry)) + g.ny * (g.z0 + rz + dz));
+            }
+            fo[u] = orig[idx];
+            ff[u] = filt[idx];
+            if constexpr (MODEL) fm[u] = model[idx];
+        }
+    };
+    auto take = [&](long ch, const float (&fo)[kQU], const float (&ff)[kQU], const float (&fm)[kQU]) {
+        const int count = (int)max(0L, min((long)kQChunk, g.nroi - ch * kQChunk));
+        int bin[kQU];
+#pragma unroll
+        for (int u = 0; u < kQU; ++u) {
+            int b = 0;
+#pragma unroll
+            for (int st = 1 << (STEPS - 1); st > 0; st >>= 1) b += ff[u] >= T[b + st - 1] ? st : 0;
+            bin[u] = b;
+        }
+#pragma unroll
+        for (int u = 0; u < kQU; ++u) {
+            const bool in = u * 256 + tid < count;
+            const double o = fo[u];
+            const bool po = in && o >= thr_o;
+            a_oo += po ? o : 0.0;
+            a_n += po ? 1.0 : 0.0;
+            double m = 0.0;
+            if constexpr (MODEL) {
+                m = fm[u];
+                a_m += in ? m : 0.0;
+            }
+            const bool on = in && bin[u] > 0;
+            const int at = (bin[u] - 1) * kQCols + col;
+            if (on && !second) {
+                __builtin_amdgcn_ds_atomic_fadd_f64((ldp)(so + at), o);
+                if constexpr (MODEL) __builtin_amdgcn_ds_atomic_fadd_f64((ldp)(sm + at), m);
+                __hip_atomic_fetch_add(sc + at, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+            if (on && second) {
+                __builtin_amdgcn_ds_atomic_fadd_f64((ldp)(so + at), o);
+                if constexpr (MODEL) __builtin_amdgcn_ds_atomic_fadd_f64((ldp)(sm + at), m);
+                __hip_atomic_fetch_add(sc + at, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+        }
+    };
+    float fo[2][kQU], ff[2][kQU], fm[2][kQU];
+    load(blockIdx.x, fo[0], ff[0], fm[0]);
+    for (long ch = blockIdx.x; ch < chunks; ch += 2L * gridDim.x) {
+        load(ch + gridDim.x, fo[1], ff[1], fm[1]);             // past the last chunk: the last again, not taken
+        take(ch, fo[0], ff[0], fm[0]);
+        load(ch + 2L * gridDim.x, fo[0], ff[0], fm[0]);
+        take(ch + gridDim.x, fo[1], ff[1], fm[1]);
+    }
+    const double r0 = wsum(a_oo), r1 = wsum(a_m), r2 = wsum(a_n);
+    if (lane == 0) {
+        red[w][0] = r0;
+        red[w][1] = r1;
+        red[w][2] = r2;
+    }
+    __syncthreads();
+    // bin totals: a wavefront per bin, its 4 x 32 columns in a fixed tree
+    for (int b = w; b < n; b += kQWaves) {
+        double t[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < kQWaves / 2; ++k) {
+            const int ww = 2 * k + (second ? 1 : 0), at = b * kQCols + col;
+            t[0] += qb[ww * cells + at];
+            if constexpr (MODEL) t[1] += qb[(kQWaves + ww) * cells + at];
+            t[2] += (double)(reinterpret_cast<unsigned*>(qb + (MODEL ? 2 : 1) * kQWaves * cells)[ww * cells + at]);
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const double v = wsum(t[c]);
+            if (lane == 0) tot[c][b] = v;
+        }
+    }
+    __syncthreads();
+    double* out = part + (long)blockIdx.x * kQSlots;
+    for (int sl = tid; sl < kQSlots; sl += 256) {
+        const int j = sl / 3, c = sl % 3;
+        double v = 0.0;
+        if (j < n)
+            for (int b = q.rank[j]; b < n; ++b) v += tot[c][b];
+        else if (j == 63)
+            for (int ww = 0; ww < kQWaves; ++ww) v += red[ww][c];
+        out[sl] = v;
+    }
 }
 
 // Block b folds slot b over `count` partials: thread t sums partials t,
@@ -345,11 +468,36 @@ extern "C" ig_status ig_quality(const ig_quality_params* q, const float* d_orig,
         hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, s, d_orig, d_filt, d_model, g, qs.part);
         count = blocks;
     } else {
-        const long chunks = (g.nroi + 63) / 64;
-        const int blocks = (int)std::min<long>(kQMaxBlocks, (chunks + kQWaves - 1) / kQWaves);
-        hipLaunchKernelGGL(k_quality_lanes, dim3(blocks), dim3(64 * kQWaves), 0, s, d_orig, d_filt, d_model, g,
-                           qs.part);
-        count = (long)blocks * kQWaves;
+        QSorted qsrt{};
+        int order[64];
+        for (int j = 0; j < q->n_thr; ++j) order[j] = j;
+        std::stable_sort(order, order + q->n_thr, [&](int a, int b) { return g.thr[a] < g.thr[b]; });
+        for (int r = 0; r < 64; ++r) {
+            qsrt.thr[r] = NAN;
+            if (r >= q->n_thr) continue;
+            const float f = (float)g.thr[order[r]];
+            qsrt.thr[r] = (double)f < g.thr[order[r]] ? std::nextafterf(f, INFINITY) : f;
+            qsrt.rank[order[r]] = (unsigned char)r;
+        }
+        qsrt.n = q->n_thr;
+        const bool flat = g.rx == nx && (g.ry == ny || r[5] - r[4] == 1), mod = g.has_model != 0;
+        using Kern = void (*)(const float*, const float*, const float*, QGeom, QSorted, double*);
+        const Kern kerns[3][2][2] = {
+            {{k_quality_bins<4, false, false>, k_quality_bins<4, false, true>},
+             {k_quality_bins<4, true, false>, k_quality_bins<4, true, true>}},
+            {{k_quality_bins<5, false, false>, k_quality_bins<5, false, true>},
+             {k_quality_bins<5, true, false>, k_quality_bins<5, true, true>}},
+            {{k_quality_bins<6, false, false>, k_quality_bins<6, false, true>},
+             {k_quality_bins<6, true, false>, k_quality_bins<6, true, true>}}};
+        const Kern k = kerns[q->n_thr < 16 ? 0 : q->n_thr < 32 ? 1 : 2][mod][flat];
+        const size_t lds = bins_lds(q->n_thr, mod);
+        if (lds > 65536)
+            HIP_TRY(hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        // one round of workgroups: what the compute units hold with these bins
+        const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(4, (kMaxLds - 2048) / lds));
+        const int blocks = (int)std::min<long>(256L * per_cu, (g.nroi + kQChunk - 1) / kQChunk);
+        hipLaunchKernelGGL(k, dim3(blocks), dim3(256), lds, s, d_orig, d_filt, d_model, g, qsrt, qs.part);
+        count = blocks;
     }
     HIP_TRY(hipGetLastError());
     hipLaunchKernelGGL(k_quality_fold, dim3(kQSlots), dim3(256), 0, s, qs.part, count, qs.sums);

@@ -151,3 +151,44 @@ def test_voxel_parallel_and_lane_paths_agree(dev):
     _check(a, ref, orig, model, roi)
     for x, y in zip(a["S_of"] + a["S_mf"], b["S_of"][:8] + b["S_mf"][:8]):
         assert x == pytest.approx(y, rel=1e-12, abs=1e-9)
+
+
+# the binned sums (more than 8 thresholds): each search depth at its ends,
+# thresholds in any order with ties among them and with voxels, ROIs of whole
+# planes (contiguous), of rows, of one voxel, and of more than one chunk per
+# workgroup
+@pytest.mark.parametrize("k", [9, 15, 16, 31, 32, 63])
+@pytest.mark.parametrize("roi", [None, (0, 70, 0, 45, 3, 27), (0, 70, 7, 8, 5, 6), (1, 68, 2, 44, 1, 29), (5, 6, 7, 8, 9, 10)])
+def test_binned_thresholds(dev, k, roi):
+    import paper_1609_03782_amd as ig
+    shape = (30, 45, 70)
+    rng = np.random.default_rng(k)
+    orig = np.rint(rng.standard_normal(shape) * 4).astype(np.float32) / 2
+    filt = np.rint(rng.standard_normal(shape) * 4).astype(np.float32) / 2
+    model = igsynth.random_cube(shape, seed=k)
+    thr = np.round(rng.uniform(-1.0, 3.0, k) * 2) / 2
+    thr[0] = thr[-1]
+    for m in (None, model):
+        kw = dict(thr_o=1.0, rms_o=1.0, rms_f=1.0)
+        got = ig.quality(_t(orig, dev), _t(filt, dev), _t(m, dev) if m is not None else None, roi=roi,
+                         thr_f=tuple(thr), **kw)
+        again = ig.quality(_t(orig, dev), _t(filt, dev), _t(m, dev) if m is not None else None, roi=roi,
+                           thr_f=tuple(thr), **kw)
+        assert repr(got) == repr(again)
+        ref = Q.quality(orig, filt, m, roi=roi, thr_f=tuple(thr), **kw)
+        _check(got, ref, orig, m, roi)
+
+
+def test_binned_nonfinite_and_large(dev):
+    """NaN and infinities of the filtered cube fall where the comparison puts
+    them, and a cube of many chunks per workgroup adds up."""
+    import paper_1609_03782_amd as ig
+    shape = (64, 200, 300)
+    orig = igsynth.random_cube(shape, seed=1)
+    filt = igsynth.random_cube(shape, seed=2)
+    filt[3, 4, 5], filt[6, 7, 8], filt[9, 10, 11] = np.nan, np.inf, -np.inf
+    thr = tuple(np.linspace(-2.0, 4.0, 40))
+    got = ig.quality(_t(orig, dev), _t(filt, dev), thr_f=thr, rms_o=1.0, rms_f=1.0)
+    with np.errstate(invalid="ignore"):
+        ref = Q.quality(orig, filt, None, thr_f=thr, rms_o=1.0, rms_f=1.0)
+    _check(got, ref, orig, None, None)
