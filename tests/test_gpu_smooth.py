@@ -155,3 +155,20 @@ def test_long_rows_take_the_three_pass_route(dev):
                 ig.smooth_set_path(0)
             b = ig.smooth(x, "gauss", (2.0, 1.0, 1.0))
             assert torch.equal(a, b)
+
+
+# the rotated kernel's column form: every z half-width it is compiled for and
+# the first it is not, with two rows per thread (small x and y widths) and one,
+# on cubes of whole tiles (64 x 8 x 8), one past them and less than one
+@pytest.mark.parametrize("fz", [0.6, 1.3, 2.0, 2.8, 3.6, 4.4, 5.2, 6.0, 7.0])
+@pytest.mark.parametrize("fxy", [1.5, 4.0])
+def test_rotated_column_form(dev, fz, fxy):
+    import torch
+    import paper_1609_03782_amd as ig
+    theta = (0.0, 0.0, 30.0)
+    for shape in ((16, 16, 128), (25, 17, 129), (7, 3, 40)):
+        cube = igsynth.random_cube(shape, seed=int(10 * fz))
+        y = ig.smooth(torch.from_numpy(cube).to(dev), "gauss", (fxy, 1.2 * fxy, fz), theta)
+        ref = Sm.smooth(cube, _kernel("gauss", (fxy, 1.2 * fxy, fz), theta))
+        err = np.abs(y.cpu().numpy() - ref).max()
+        assert err <= _tol(cube, "gauss", theta), (shape, err)
