@@ -392,9 +392,9 @@ ig_status igk_enqueue_run(const RunCtx& c, const ig_schedule& sched, const void*
     in.cond = p.cond;
     in.abort_on_nonfinite = 1;
     in.rms = p.rms;
+    bool nan_done = !scan;   // a failed run's NaN: written by the scan itself for small cubes
     if (scan) {
-        HIP_TRY(launch_sum_partial(p.dtype, d_in, n, c.parts, kPartBlocks, stream));
-        HIP_TRY(launch_params_final(c.parts, kPartBlocks, n, in, c.dparams, stream));
+        HIP_TRY(launch_scan(p.dtype, d_in, n, in, c.parts, kPartBlocks, c.dparams, d_out, &nan_done, stream));
     } else {
         HIP_TRY(launch_params_final(nullptr, 0, n, in, c.dparams, stream));
     }
@@ -458,7 +458,7 @@ ig_status igk_enqueue_run(const RunCtx& c, const ig_schedule& sched, const void*
     }
     // a non-finite input voxel (found by the scan) turns the whole output into
     // NaN, so a caller that asked for no statistics still sees the failure
-    if (scan) HIP_TRY(launch_nan_if_abort(p.dtype, d_out, n, c.dparams, stream));
+    if (!nan_done) HIP_TRY(launch_nan_if_abort(p.dtype, d_out, n, c.dparams, stream));
     if (passes_out) *passes_out = P;
     return IG_OK;
 }

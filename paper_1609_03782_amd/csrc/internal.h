@@ -28,6 +28,10 @@ struct NaiveGeom;
 hipError_t launch_sum_partial(int dtype, const void* x, long n, double* part, int nblk, hipStream_t s);
 hipError_t launch_params_final(const double* part, int nparts, long n, const ParamIn& in, DevParams* out,
                                hipStream_t s);
+// The scan of a run's input x and the constants it gives, through up to nblk
+// partials; nan_done: a failed run's NaN has been written to y.
+hipError_t launch_scan(int dtype, const void* x, long n, const ParamIn& in, double* part, int nblk, DevParams* out,
+                       void* y, bool* nan_done, hipStream_t s);
 hipError_t launch_compare(int dtype, const void* x, const double* ref, long n, double tol, double* part,
                           int nblk, double* out, hipStream_t s);
 hipError_t launch_copy(int dtype, const void* a, void* b, long n, const DevParams* dp, hipStream_t s);

@@ -377,3 +377,35 @@ def test_automatic_chunk_schedule_feeds_deeper_passes(dev):
     assert torch.equal(f.run(x), y)
     with pytest.raises(ig.IgError):
         f.set_schedule(**dict(sched, vec=7))
+
+
+@pytest.mark.parametrize("n_iter", [0, 1, 4])
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (3, 7, 11), (64, 4, 64), (1, 129, 128), (128, 64, 128),
+                                   (128, 64, 129)])
+def test_scan_launch_forms(dev, shape, dtype, n_iter):
+    """The scan in one workgroup (up to 2^14 voxels, (64, 4, 64)), in two
+    launches (up to 2^20, (128, 64, 128)) and in three: rho and the sum against FP64 (terms of one sign or
+    squares, so 1e-13 covers the order), from buffers on and off 16 bytes, and
+    the NaN of a failed run in place and out of place."""
+    import torch
+    import paper_1609_03782_amd as ig
+    n = int(np.prod(shape))
+    v = torch.from_numpy(np.abs(igsynth.random_cube(shape, seed=n)) + 0.5).to(
+        {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[dtype])
+    f = ig.Filter(shape, n_iter=n_iter, dtype=dtype)
+    for off in (0, 1):
+        x = torch.empty(n + off, dtype=v.dtype, device=dev)[off:].view(shape)
+        x.copy_(v)
+        _, st = f.run(x, stats=True)
+        d = v.double().numpy()
+        assert st.rms_used == pytest.approx(float(np.sqrt((d * d).mean())), rel=1e-13)
+        assert st.sum_in == pytest.approx(float(d.sum()), rel=1e-13)
+        x.view(-1)[n // 2] = float("nan")
+        out = torch.zeros_like(x)
+        f.run(x, out=out)
+        torch.cuda.synchronize()
+        assert bool(torch.isnan(out).all()) and int(torch.isnan(x).sum()) == 1
+        f.run(x, out=x)
+        torch.cuda.synchronize()
+        assert bool(torch.isnan(x).all())
