@@ -386,8 +386,8 @@ constexpr bool y_row_shared() {
 }
 
 // One piece of one pass: the whole per-workgroup algorithm above.  `lds`
-// must hold stream_lds_bytes(V, T, W) bytes.  Called by k_stream (one cube)
-// and by the batch round kernel.
+// must hold stream_lds_bytes(V, T, W) bytes; `lane` is threadIdx.x.  Called by
+// k_stream (one cube) and by the batch round kernel.
 // Calls f(std::integral_constant<int, 2^k - 1>) for the k in 0..K with
 // vmask == 2^k - 1 (k = 0 when no larger one matches).
 template <int K, typename F>
@@ -402,11 +402,11 @@ __device__ __forceinline__ void level_mask_dispatch(int vmask, F&& f) {
 
 template <int COND, typename ST, int V, int T, bool VEC, int R>
 __device__ __forceinline__ void stream_piece(const ST* __restrict__ src, ST* __restrict__ dst, const BlockGeom& g,
-                                             const Piece pc, const DevParams& P, float* __restrict__ lds) {
+                                             const Piece pc, const DevParams& P, float* __restrict__ lds,
+                                             const int lane = threadIdx.x) {
     constexpr int RX = 64 * V;
     constexpr int LR = 64 / R;                    // lanes per row
     constexpr bool RS = y_row_shared<COND>();
-    const int lane = threadIdx.x;
     const int sr = R == 1 ? 0 : lane / LR;        // this lane's row within the wavefront
     const int lr = R == 1 ? lane : lane % LR;     // this lane's place in its row
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.y);
@@ -748,6 +748,11 @@ k_stream(const ST* __restrict__ src, ST* __restrict__ dst, BlockGeom g, const Pi
 // workgroup-uniform addresses, so the loop is uniform).  A kernel of its own:
 // the loop around the streaming body raises register pressure (the per-lane
 // geometry stays live across pieces), which the one-piece kernel should not pay.
+// With 16-bit storage the lane number is made anew for each piece, so that its
+// geometry is computed there and not kept: with it kept, rows of 6 voxels per
+// lane waited in the loop (300 x 400 x 490 bf16 677 -> 764, 384 x 400 x 300 804
+// -> 905 Gvoxel-iter/s; 8 per lane spilled, and gain 0 to 1 %).  FP32 keeps it:
+// up to 1.5 % faster so.
 template <int COND, typename ST, int V, int T, bool VEC, int R>
 __global__ void __launch_bounds__(1024)
 k_stream_grouped(const ST* __restrict__ src, ST* __restrict__ dst, BlockGeom g, const Piece* __restrict__ pieces,
@@ -759,7 +764,9 @@ k_stream_grouped(const ST* __restrict__ src, ST* __restrict__ dst, BlockGeom g, 
     const int k0 = first[blockIdx.x], k1 = first[blockIdx.x + 1];
     for (int k = k0; k < k1; ++k) {
         if (k > k0) __syncthreads();   // the previous piece is done with the LDS
-        stream_piece<COND, ST, V, T, VEC, R>(src, dst, g, pieces[k], P, lds);
+        int lane = threadIdx.x;
+        if constexpr (sizeof(ST) == 2) asm volatile("" : "+v"(lane));
+        stream_piece<COND, ST, V, T, VEC, R>(src, dst, g, pieces[k], P, lds, lane);
     }
 }
 
