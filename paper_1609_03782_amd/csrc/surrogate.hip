@@ -83,13 +83,12 @@ WgradPlan wgrad_plan(int cin, int cout, long nx, long ny, long nz) {
 // Grid of the z-streaming kernels (tiles of xw voxels by kZsRows rows, one
 // workgroup per (tile, z chunk)): the z chunk that minimises the slowest
 // compute unit's share (in planes, counting the two margin planes and the
-// set-up as about two more, and for a kernel that computes planes in pairs an
-// odd chunk's last plane as a whole pair) with one workgroup per CU.
+// set-up as about two more) with one workgroup per CU.
 struct ZsGrid {
     int ntx, nty, zch;
     long groups;
 };
-ZsGrid zs_grid(long nx, long ny, long nz, int xw, bool pairs) {
+ZsGrid zs_grid(long nx, long ny, long nz, int xw) {
     ZsGrid g;
     g.ntx = (int)((nx + xw - 1) / xw);
     g.nty = (int)((ny + kZsRows - 1) / kZsRows);
@@ -101,7 +100,7 @@ ZsGrid zs_grid(long nx, long ny, long nz, int xw, bool pairs) {
     for (long nzc = 1; nzc <= nz; ++nzc) {
         const long zc = (nz + nzc - 1) / nzc;
         const long groups = tiles * ((nz + zc - 1) / zc);
-        const long cost = ((groups + ncu - 1) / ncu) * (zc + (pairs ? (zc & 1) : 0) + 4);
+        const long cost = ((groups + ncu - 1) / ncu) * (zc + 4);
         if (best_cost < 0 || cost < best_cost) { best_cost = cost; zch = zc; }
         if (zc == 1) break;
     }
@@ -115,7 +114,7 @@ template <int NB, int EPI, bool KEEP = false>
 hipError_t zs_launch(const u16* x, const bf16x8* wp, const float* b, void* out, const void* aux, long nx, long ny,
                      long nz, hipStream_t s) {
     static_assert(kZsLds <= 160 * 1024, "z-stream tile exceeds LDS");
-    const ZsGrid g = zs_grid(nx, ny, nz, kZsX, true);
+    const ZsGrid g = zs_grid(nx, ny, nz, kZsX);
     auto kern = k_conv_zs<NB, EPI, KEEP>;
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kZsLds);
     if (e != hipSuccess) return e;
@@ -129,7 +128,7 @@ template <int NB, int EPI>
 hipError_t zs1_launch(const u16* x, const bf16x8* wp, const float* b, void* out, const void* aux, long nx, long ny,
                       long nz, hipStream_t s) {
     constexpr int MT = 2;
-    const ZsGrid g = zs_grid(nx, ny, nz, 16 * MT, false);
+    const ZsGrid g = zs_grid(nx, ny, nz, 16 * MT);
     hipLaunchKernelGGL((k_conv1_zs<NB, EPI, MT>), dim3((unsigned)g.groups), dim3(64 * kZsRows), 0, s, x, wp, b, out,
                        aux, (int)nx, (int)ny, (int)nz, g.ntx, g.nty, g.zch);
     return hipGetLastError();
@@ -140,7 +139,7 @@ template <int EPI>
 hipError_t out1_launch(const u16* x, const bf16x8* wp, const float* b, void* out, const void* aux, long nx, long ny,
                        long nz, hipStream_t s) {
     static_assert(kO1Lds <= 160 * 1024, "tap partials exceed LDS");
-    const ZsGrid g = zs_grid(nx, ny, nz, kO1X, false);
+    const ZsGrid g = zs_grid(nx, ny, nz, kO1X);
     auto kern = k_conv_out1<EPI>;
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kO1Lds);
     if (e != hipSuccess) return e;

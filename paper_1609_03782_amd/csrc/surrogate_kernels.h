@@ -103,31 +103,36 @@ __device__ __forceinline__ uint2 pack_bf16x4(float a, float b, float c, float d)
 
 // The convolution of a 32-channel input as a z-stream: a workgroup of 8
 // wavefronts owns an output tile of 32 voxels in x by 8 rows in y and a chunk of
-// planes [z0, z1), computed two planes at a time.  Wavefront (nb, xs, yg)
+// planes [z0, z1).  Wavefront (nb, xs, yg)
 // computes 16 output channels (nb) of 16 voxels (xs) of 4 rows (yg), and holds
 // the weights of its channels, all 27 taps, in registers (108) for the whole
-// chunk, so the LDS only feeds activations: each fragment (input plane, row,
-// x shift) is read once and multiplied with every weight it meets, up to 3 rows
-// by 2 planes: 72 reads of 1 KB for 216 products, where weights in LDS and one
-// row per wavefront took 162.  The LDS bandwidth (128 bytes per clock per CU for
-// 16-byte reads, whatever the address pattern: measured) bounded that form.
+// chunk, so the LDS only feeds activations.  A step takes one input plane and
+// adds it to the sums of the three output planes it reaches: each fragment
+// (row, x shift) is read once and multiplied with every weight it meets, up to 3
+// rows by 3 planes: 18 reads of 1 KB for 108 products, where weights in LDS and
+// one row per wavefront took 81, and two output planes at a time from four input
+// planes 36.  The three sums of a row move on by name: a plane's first product
+// takes the sum of the plane before as its addend.  The first two and the last
+// two steps of a chunk leave out the tap planes that reach no output of it.
 // Input planes (tile plus a one-voxel margin, zeros outside the cube) sit in a
-// ring of six LDS slots: planes z-1 .. z+2 are read while z+3 and z+4 are
-// staged, so one barrier per pair of planes suffices.  The weights are the
-// MFMA's A operand and the activations its B operand, so each lane ends with
-// four consecutive output channels of one voxel and stores them with one
-// 8-byte write.  Per output the taps are accumulated in the order 0..26, then
-// the bias is added.  The pass is one block of code whose issue order is laid
-// out (below), the epilogue's VALU work behind the products.
-// What bounds it now is power: 897 TFLOP/s on 360 x 360 x 150 (a library matrix
-// product reaches 1127 on the same card), the matrix cores 52 % busy at 1.8 GHz;
-// staging straight to LDS took 9 % of the cycles and none of the time (the clock
-// fell with them).  A 32-channel layer of that cube went from 1483 to 1199 us,
-// of 96^3 from 69 to 56 us.
+// ring of three LDS slots: plane z is read (and z + 1 at the end, so no step
+// starts by waiting for LDS) while z + 2 is staged, one barrier per plane.  The
+// weights are the MFMA's A operand and the activations its B operand, so each
+// lane ends with four consecutive output channels of one voxel and stores them
+// with one 8-byte write.  Per output the taps are accumulated in the order
+// 0..26, then the bias is added.  The step is one block of code whose issue order
+// is laid out (below), the epilogue's VALU work behind the products.
+// What bounds it now is power: 960 TFLOP/s of products executed on 360 x 360 x
+// 150 (a library matrix product reaches 1127 on the same card), the matrix cores
+// 53 % busy at 1.74 GHz; staging straight to LDS took 9 % of the cycles and none
+// of the time (the clock fell with them).  A prediction on that cube (six such
+// layers) went from 9.0 ms with weights in LDS to 7.7 with weights in registers
+// and 7.4 with every fragment read once; a training step on four 96^3 cubes from
+// 4.96 to 4.82 ms by the last.
 constexpr int kZsRows = 8;    // tile rows
 constexpr int kZsX = 32;      // tile columns
-constexpr int kZsAhead = 3;   // activation fragments in flight ahead of their products
-constexpr int kZsSlots = 6;   // LDS ring
+constexpr int kZsAhead = 2;   // activation fragments in flight ahead of their products (across steps)
+constexpr int kZsSlots = 3;   // LDS ring
 constexpr int kZsValu = 3;    // VALU operations issued behind a product
 constexpr int kZsLX = kZsX + 2, kZsLY = kZsRows + 2;
 constexpr int kZsPer = (kZsLX * kZsLY * 4 + 511) / 512;   // 16-byte chunks of a staged plane per thread
@@ -208,16 +213,16 @@ __device__ __forceinline__ void zs_store(const f32x4 (&acc)[MT][NB], const float
         }
 }
 
-// products of fragment m of a pass, and the epilogue values begun before it
-// (32 over 216 products)
+// products per tap plane of fragment m of a step, and the epilogue values begun
+// before it (16 over a step)
 constexpr int zs_products(int m) {
-    const int q = m / 18, j = m / 3 % 6;
-    return (q == 0 || q == 3 ? 1 : 2) * (j == 0 || j == 5 ? 1 : j == 1 || j == 4 ? 2 : 3);
+    const int j = m / 3;
+    return j == 0 || j == 5 ? 1 : j == 1 || j == 4 ? 2 : 3;
 }
 constexpr int zs_value(int m) {
     int n = 0;
     for (int k = 0; k < m; ++k) n += zs_products(k);
-    return n * 32 / 216;
+    return n * 16 / 36;
 }
 
 // NB = 1 (up to 16 output channels): the wavefronts nb = 1 compute nothing that
@@ -269,12 +274,13 @@ k_conv_zs(const u16* __restrict__ in, const bf16x8* __restrict__ wp, const float
                 make_uint4(st[k].x & m, st[k].y & m, st[k].z & m, st[k].w & m);
         }
     };
-    // plane z0 - 1 + k sits in slot k mod 6
+    // plane z0 - 1 + k sits in slot k mod 3
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < 2; ++k) {
         fetch(z0 - 1 + k);
         put(z0 - 1 + k, k);
     }
+    fetch(z0 + 1);
     __syncthreads();
 
     const u16* lb = ring + ((4 * yg) * kZsLX + 16 * xs + i) * 32 + 8 * kg;
@@ -283,7 +289,7 @@ k_conv_zs(const u16* __restrict__ in, const bf16x8* __restrict__ wp, const float
     const int y = y0 + 4 * yg, n0 = 16 * nb + 4 * kg;
     const int cols = min(nx - x0, kZsX);
     auto row = [&](const void* p, int z, int r, int vb) {   // no branch: it would split the pass's schedule
-        const int on = -(int)(act & (z >= 0) & (z < z1) & (y + r < ny));
+        const int on = -(int)(act & (z >= z0) & (z < z1) & (y + r < ny));
         return raw_buffer(static_cast<const char*>(p) +
                               (((long)max(z, 0) * ny + min(y + r, ny - 1)) * nx + x0) * vb, on & (cols * vb));
     };
@@ -292,84 +298,88 @@ k_conv_zs(const u16* __restrict__ in, const bf16x8* __restrict__ wp, const float
     if (EPI != EPI_BACK_GELU && bias && act)
 #pragma unroll
         for (int e = 0; e < 4; ++e) bv[e] = bias[n0 + e];
-    // the results of the previous pair of planes (zp, zp + 1): their epilogue (GELU,
-    // packing, stores) is spread over the next pair's products, a value at a
-    // time and with no branch, so that it runs beside the matrix cores
-    constexpr int NV = 32;
-    f32x4 acc[2][4], prev[2][4];
-    uint2 pre[2][4];
-    int zp = -2;
+    // a0, a1, a2: the sums that the current input plane reaches with the taps of
+    // plane 0, 1 and 2.  prev: the finished output plane zp; its epilogue (GELU,
+    // packing, stores) is spread over the next step's products, a value at a time
+    // and with no branch, so that it runs beside the matrix cores
+    constexpr int NV = 16;
+    f32x4 a0[4], a1[4], a2[4], prev[4];
+    uint2 pre[4];
+    int zp = z0 - 1;
 #pragma unroll
-    for (int p = 0; p < 2; ++p)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            prev[p][r] = f32x4{0.f, 0.f, 0.f, 0.f};
-            pre[p][r] = make_uint2(0, 0);
-        }
+    for (int r = 0; r < 4; ++r) {
+        prev[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+        pre[r] = make_uint2(0, 0);
+    }
     auto store2 = [&](void* p, int z, int r, uint2 v) {
         __builtin_amdgcn_raw_buffer_store_b64(u32x2{v.x, v.y}, row(p, z, r, 64), lo, 0, 0);
     };
-    auto epi = [&](auto vc) {   // value e of row r, plane zp + p
-        constexpr int v = decltype(vc)::value, p = v / 16, r = v / 4 % 4, e = v % 4;
-        f32x4& d = prev[p][r];
+    auto epi = [&](auto vc) {   // value e of row r
+        constexpr int v = decltype(vc)::value, r = v / 4, e = v % 4;
+        f32x4& d = prev[r];
         if constexpr (EPI == EPI_GELU) {
             if constexpr (e == 0) {
                 d += bv;
-                if constexpr (KEEP) store2(const_cast<void*>(aux), zp + p, r, pack_bf16x4(d[0], d[1], d[2], d[3]));
+                if constexpr (KEEP) store2(const_cast<void*>(aux), zp, r, pack_bf16x4(d[0], d[1], d[2], d[3]));
             }
             d[e] = gelu_fast(d[e]);
-            if constexpr (e == 3) store2(out, zp + p, r, pack_bf16x4(d[0], d[1], d[2], d[3]));
+            if constexpr (e == 3) store2(out, zp, r, pack_bf16x4(d[0], d[1], d[2], d[3]));
         } else if constexpr (EPI == EPI_BACK_GELU) {
-            const unsigned u = e < 2 ? pre[p][r].x : pre[p][r].y;
+            const unsigned u = e < 2 ? pre[r].x : pre[r].y;
             d[e] *= gelu_grad_fast(__uint_as_float(e & 1 ? u & 0xffff0000u : u << 16));
-            if constexpr (e == 3) store2(out, zp + p, r, pack_bf16x4(d[0], d[1], d[2], d[3]));
+            if constexpr (e == 3) store2(out, zp, r, pack_bf16x4(d[0], d[1], d[2], d[3]));
         } else if constexpr (e == 3) {
             typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
             const f32x4 o = d + bv;
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), row(out, zp + p, r, 64 * NB),
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), row(out, zp, r, 64 * NB),
                                                    (16 * xs + i) * 64 * NB + 4 * n0, 0, 0);
         }
     };
-    int sl = 0;                                    // slot of plane z - 1
-    for (int z = z0; z < z1; z += 2) {
-        const u16* lq[4];
-        int sw[2];
+    // fragment m: row 4 yg - 1 + j (j = m / 3) of the tile, shift dx = m % 3
+    constexpr int FR = kZsAhead + 1;
+    static_assert(18 % FR == 0, "the ring of fragments repeats with the steps");
+    bf16x8 f[FR];
+    int sl = 0;                                    // slot of the current plane
+    const u16 *lq = lb, *lq1 = lb + kZsPl;         // the current plane and the next
+    auto load = [&](auto mc) {                     // (18 and up: of the next plane, staged two steps ahead)
+        constexpr int m = decltype(mc)::value, n = m % 18;
+        f[m % FR] = *reinterpret_cast<const bf16x8*>((m < 18 ? lq : lq1) + ((n / 3) * kZsLX + n % 3) * 32);
+    };
+    static_for<kZsAhead>(load);
+    // input plane z with the tap planes LO .. HI
+    auto step = [&](auto loc, auto hic, int z) {
+        constexpr int LO = decltype(loc)::value, HI = decltype(hic)::value;
+        const int sw = sl == 0 ? 2 : sl - 1;       // slot of plane z + 2
+        auto part = [&](auto hc) {
+            constexpr int M0 = 9 * decltype(hc)::value;
+            static_for<9>([&](auto mc) {
+                constexpr int m = M0 + decltype(mc)::value, j = m / 3, dx = m % 3;
+                load(std::integral_constant<int, m + kZsAhead>{});
+                // tap plane 2 first: a sum moves on by being the next plane's
+                // first addend, before its place is taken
 #pragma unroll
-        for (int q = 0; q < 4; ++q) lq[q] = lb + (sl + q < kZsSlots ? sl + q : sl + q - kZsSlots) * kZsPl;
-#pragma unroll
-        for (int q = 0; q < 2; ++q) sw[q] = sl + 4 + q < kZsSlots ? sl + 4 + q : sl + 4 + q - kZsSlots;
-        fetch(z + 3);                              // the last pair stages planes no one reads
-        // fragment m: input plane z - 1 + q, row 4 yg - 1 + j of the tile, shift dx
-        bf16x8 f[kZsAhead + 1];
-        auto load = [&](auto mc) {
-            constexpr int m = decltype(mc)::value;
-            f[m % (kZsAhead + 1)] = *reinterpret_cast<const bf16x8*>(lq[m / 18] + ((m / 3 % 6) * kZsLX + m % 3) * 32);
-        };
-        static_for<kZsAhead>(load);
-        // half a pass: 36 fragments, 108 products, 16 values of the epilogue
-        auto half = [&](auto hc) {
-            constexpr int M0 = 36 * decltype(hc)::value;
-            static_for<36>([&](auto mc) {
-                constexpr int m = M0 + decltype(mc)::value, q = m / 18, j = m / 3 % 6, dx = m % 3;
-                if constexpr (m + kZsAhead < 72) load(std::integral_constant<int, m + kZsAhead>{});
-#pragma unroll
-                for (int p = 0; p < 2; ++p)
+                for (int d = HI; d >= LO; --d)
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
-                        if (q - p >= 0 && q - p < 3 && j - r >= 0 && j - r < 3)
-                            acc[p][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                wf[9 * (q - p) + 3 * (j - r) + dx], f[m % (kZsAhead + 1)],
-                                q == p && j == r && dx == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[p][r], 0, 0, 0);
-                constexpr int v0 = zs_value(m), v1 = zs_value(m + 1);
-                if constexpr (v1 > v0) epi(std::integral_constant<int, v0>{});
+                        if (j - r >= 0 && j - r < 3) {
+                            const bool first = j == r && dx == 0;
+                            f32x4* o = d == 0 ? a0 : d == 1 ? a1 : a2;
+                            const f32x4 c = !first ? o[r] : d == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : d == 1 ? a0[r] : a1[r];
+                            o[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[9 * d + 3 * (j - r) + dx], f[m % FR], c,
+                                                                           0, 0, 0);
+                        }
+                if constexpr (HI == 2) {
+                    constexpr int v0 = zs_value(m), v1 = zs_value(m + 1);
+                    static_for<v1 - v0>([&](auto k) { epi(std::integral_constant<int, v0 + decltype(k)::value>{}); });
+                }
             });
             // the order to issue it in: each fragment's read kZsAhead fragments
             // ahead, and behind each product the two or three VALU operations that
             // fit under its 16 cycles
-            static_for<36>([&](auto mc) {
+            static_for<9>([&](auto mc) {
                 constexpr int m = M0 + decltype(mc)::value;
-                if constexpr (m + kZsAhead < 72) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                static_for<zs_products(m)>([&](auto) {
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                static_for<zs_products(m) * (HI - LO + 1)>([&](auto) {
                     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                     __builtin_amdgcn_sched_group_barrier(0x002, kZsValu, 0);
                 });
@@ -377,28 +387,37 @@ k_conv_zs(const u16* __restrict__ in, const bf16x8* __restrict__ wp, const float
             __builtin_amdgcn_sched_barrier(0);
         };
         __builtin_amdgcn_sched_barrier(0);
-        half(std::integral_constant<int, 0>{});
-        put(z + 3, sw[0]);
-        fetch(z + 4);
-        __builtin_amdgcn_sched_barrier(0);
-        half(std::integral_constant<int, 1>{});
-        zp = z;
+        part(std::integral_constant<int, 0>{});
+        if constexpr (LO == 0) {                   // the last two steps stage nothing
+            put(z + 2, sw);
+            fetch(z + 3);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        part(std::integral_constant<int, 1>{});
+        if constexpr (HI == 2) {
+            zp = z - 1;
 #pragma unroll
-        for (int p = 0; p < 2; ++p)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) prev[p][r] = acc[p][r];
-        put(z + 4, sw[1]);
-        if constexpr (EPI == EPI_BACK_GELU)
-#pragma unroll
-            for (int p = 0; p < 2; ++p)
+            for (int r = 0; r < 4; ++r) prev[r] = a2[r];
+            if constexpr (EPI == EPI_BACK_GELU)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(row(aux, z + p, r, 64), lo, 0, 0);
-                    pre[p][r] = make_uint2(v.x, v.y);
+                    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(row(aux, zp, r, 64), lo, 0, 0);
+                    pre[r] = make_uint2(v.x, v.y);
                 }
-        sl = sl + 2 < kZsSlots ? sl + 2 : sl + 2 - kZsSlots;
+        }
+        sl = sl == 2 ? 0 : sl + 1;
+        lq = lq1;
+        lq1 = lb + (sl == 2 ? 0 : sl + 1) * kZsPl;
         __syncthreads();
-    }
+    };
+    constexpr std::integral_constant<int, 0> D0{};
+    constexpr std::integral_constant<int, 1> D1{};
+    constexpr std::integral_constant<int, 2> D2{};
+    step(D0, D0, z0 - 1);
+    step(D0, D1, z0);
+    for (int z = z0 + 1; z < z1 - 1; ++z) step(D0, D2, z);
+    if (z1 - 1 > z0) step(D1, D2, z1 - 1);
+    step(D2, D2, z1);
     static_for<NV>(epi);
 }
 

@@ -93,6 +93,13 @@ def test_conv_forward_tiles(dev, shape, cout):
         _within(got.double().cpu().numpy(), r2, t2, "input gradient times gelu'")
 
 
+# enough tiles that the z chunks hold 2, 3 and (last) 3 and 2 planes: the first
+# and last steps of a chunk take some of the tap planes only
+@pytest.mark.parametrize("shape", [(2, 136, 320), (3, 136, 320), (5, 80, 320)])
+def test_conv_forward_chunks(dev, shape):
+    test_conv_forward_tiles(dev, shape, 32)
+
+
 def test_conv_forward_gelu_and_residual(dev):
     import torch
     from paper_1609_03782_amd import surrogate as sg
