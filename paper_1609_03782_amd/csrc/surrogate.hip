@@ -42,20 +42,23 @@ namespace {
 // Workgroups of the weight-gradient kernels (at most): one per compute unit of
 // the 32-channel kernel (108 KB of LDS each), two of the 1-channel one.  Fixed,
 // so a gradient does not depend on the device it was computed on.
+constexpr long kTrainBytes = 8L << 30;   // activations of a group of training cubes
 constexpr long kWgradGroups32 = 256, kWgradGroups1 = 512;
 
 struct Dev {
     void* p = nullptr;
     size_t bytes = 0;
     ~Dev() { igk_free(p); }
+    void release() {
+        if (!p) return;
+        (void)hipDeviceSynchronize();   // queued kernels may still use the buffer
+        igk_free(p);
+        p = nullptr;
+        bytes = 0;
+    }
     hipError_t ensure(size_t b) {
         if (b <= bytes && p) return hipSuccess;
-        if (p) {   // queued kernels may still use the old buffer
-            (void)hipDeviceSynchronize();
-            igk_free(p);
-            p = nullptr;
-            bytes = 0;
-        }
+        release();
         hipError_t e = igk_malloc(&p, std::max<size_t>(b, 256));
         if (e == hipSuccess) bytes = std::max<size_t>(b, 256);
         return e;
@@ -68,67 +71,83 @@ struct WgradPlan {
     int ntx, nty;
     long groups, stride, lenw, len;
 };
-WgradPlan wgrad_plan(int cin, int cout, long nx, long ny, long nz) {
+WgradPlan wgrad_plan(int cin, int cout, long nx, long ny, long nz, long cubes) {
     WgradPlan w;
     w.ntx = (int)((nx + kWgX - 1) / kWgX);
     w.nty = (int)((ny + kWgY - 1) / kWgY);
     const bool both = cin == 32 && cout == 32;
-    w.groups = std::min(both ? kWgradGroups32 : kWgradGroups1, (long)w.ntx * w.nty * nz);
+    w.groups = std::min(both ? kWgradGroups32 : kWgradGroups1, (long)w.ntx * w.nty * nz * cubes);
     w.lenw = 27L * cin * cout;
     w.len = w.lenw + cout;
     w.stride = both ? w.len : 28L * std::max(cin, cout);
     return w;
 }
 
-// Grid of the z-streaming kernels (tiles of xw voxels by kZsRows rows, one
-// workgroup per (tile, z chunk)): the z chunk that minimises the slowest
-// compute unit's share (in planes, counting the two margin planes and the
-// set-up as about two more) with one workgroup per CU.
+// Grid of the z-streaming kernels (tiles of xw voxels by kZsRows rows of `cubes`
+// cubes, one workgroup per (tile, z chunk)): the z chunk that minimises the
+// slowest compute unit's share (in planes, counting the two margin planes and the
+// set-up as about two more) with per_cu workgroups on a CU at once.
 struct ZsGrid {
     int ntx, nty, zch;
-    long groups;
+    long groups, cost;
 };
-ZsGrid zs_grid(long nx, long ny, long nz, int xw) {
+ZsGrid zs_grid(long nx, long ny, long nz, int xw, long cubes, int per_cu, int* ncu_out = nullptr) {
     ZsGrid g;
     g.ntx = (int)((nx + xw - 1) / xw);
     g.nty = (int)((ny + kZsRows - 1) / kZsRows);
-    const long tiles = (long)g.ntx * g.nty;
+    const long tiles = (long)g.ntx * g.nty * cubes;
     int ncu = 256;
     int dev = 0;
     if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+    if (ncu_out) *ncu_out = ncu;
+    const long slots = (long)ncu * per_cu;
     long best_cost = -1, zch = nz;
     for (long nzc = 1; nzc <= nz; ++nzc) {
         const long zc = (nz + nzc - 1) / nzc;
         const long groups = tiles * ((nz + zc - 1) / zc);
-        const long cost = ((groups + ncu - 1) / ncu) * (zc + 4);
+        const long cost = ((groups + slots - 1) / slots) * (zc + 4);
         if (best_cost < 0 || cost < best_cost) { best_cost = cost; zch = zc; }
         if (zc == 1) break;
     }
     g.zch = (int)zch;
     g.groups = tiles * ((nz + zch - 1) / zch);
+    g.cost = best_cost;
     return g;
 }
 
 // 32-channel input
 template <int NB, int EPI, bool KEEP = false>
 hipError_t zs_launch(const u16* x, const bf16x8* wp, const float* b, void* out, const void* aux, long nx, long ny,
-                     long nz, hipStream_t s) {
+                     long nz, long cubes, hipStream_t s) {
     static_assert(kZsLds <= 160 * 1024, "z-stream tile exceeds LDS");
-    const ZsGrid g = zs_grid(nx, ny, nz, kZsX);
+    int ncu;
+    ZsGrid g = zs_grid(nx, ny, nz, kZsX, cubes, 1, &ncu);
+    // Equal shares of the planes of all tiles, one per CU, where they predict a
+    // shorter longest share than whole rounds of chunks do: 360 x 360 x 150, six
+    // layers, 7404 -> 7089 us (2700 chunks of 30 planes made 11 rounds of 34 where
+    // 325 planes are the share).
+    const long tiles = (long)g.ntx * g.nty * cubes, share = (tiles * nz + ncu - 1) / ncu;
+    if (tiles * nz > ncu && share + 4 * (share / nz + 2) < g.cost) {
+        g.groups = ncu;
+        g.zch = 0;
+    }
     auto kern = k_conv_zs<NB, EPI, KEEP>;
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kZsLds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)g.groups), dim3(64 * kZsRows), kZsLds, s, x, wp, b, out, aux, (int)nx,
-                       (int)ny, (int)nz, g.ntx, g.nty, g.zch);
+                       (int)ny, (int)nz, ZsSplit{g.ntx, g.nty, g.zch, (int)cubes});
     return hipGetLastError();
 }
 
-// 1-channel input (first layer; input gradient of a 1-channel output)
+// 1-channel input (first layer; input gradient of a 1-channel output).  Small
+// tiles and few registers: several workgroups share a CU, and small cubes are cut
+// fine enough for that (96^3: first layer 43 -> 30 us a cube, last 30 -> 24).
+constexpr int kZs1PerCu = 4, kO1PerCu = 2;
 template <int NB, int EPI>
 hipError_t zs1_launch(const u16* x, const bf16x8* wp, const float* b, void* out, const void* aux, long nx, long ny,
-                      long nz, hipStream_t s) {
+                      long nz, long cubes, hipStream_t s) {
     constexpr int MT = 2;
-    const ZsGrid g = zs_grid(nx, ny, nz, 16 * MT);
+    const ZsGrid g = zs_grid(nx, ny, nz, 16 * MT, cubes, kZs1PerCu);
     hipLaunchKernelGGL((k_conv1_zs<NB, EPI, MT>), dim3((unsigned)g.groups), dim3(64 * kZsRows), 0, s, x, wp, b, out,
                        aux, (int)nx, (int)ny, (int)nz, g.ntx, g.nty, g.zch);
     return hipGetLastError();
@@ -139,7 +158,7 @@ template <int EPI>
 hipError_t out1_launch(const u16* x, const bf16x8* wp, const float* b, void* out, const void* aux, long nx, long ny,
                        long nz, hipStream_t s) {
     static_assert(kO1Lds <= 160 * 1024, "tap partials exceed LDS");
-    const ZsGrid g = zs_grid(nx, ny, nz, kO1X);
+    const ZsGrid g = zs_grid(nx, ny, nz, kO1X, 1, kO1PerCu);
     auto kern = k_conv_out1<EPI>;
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kO1Lds);
     if (e != hipSuccess) return e;
@@ -149,20 +168,21 @@ hipError_t out1_launch(const u16* x, const bf16x8* wp, const float* b, void* out
     return hipGetLastError();
 }
 
-// forward conv launch (packed weights); cin is 1 or 32
+// forward conv launch (packed weights) over `cubes` cubes laid one after another
+// (one cube for the one-output forms); cin is 1 or 32
 hipError_t launch_conv(int cin, int cout, int epi, const void* in, const bf16x8* wp, const float* b, void* out,
-                       const void* aux, long nx, long ny, long nz, hipStream_t s) {
+                       const void* aux, long nx, long ny, long nz, long cubes, hipStream_t s) {
     const int NB = cout > 16 ? 2 : 1;
     const u16* x = static_cast<const u16*>(in);
     if (cin == 32 && cout == 1 && (epi == EPI_RAW || epi == EPI_RESID)) {
         if (epi == EPI_RAW) return out1_launch<EPI_RAW>(x, wp, b, out, aux, nx, ny, nz, s);
         return out1_launch<EPI_RESID>(x, wp, b, out, aux, nx, ny, nz, s);
     }
-#define Z(F, NBV, EPIV) return F<NBV, EPIV>(x, wp, b, out, aux, nx, ny, nz, s)
+#define Z(F, NBV, EPIV) return F<NBV, EPIV>(x, wp, b, out, aux, nx, ny, nz, cubes, s)
     if (cin == 32) {   // the GELU forms have 32 outputs, the residual one (above)
         if (NB == 1) Z(zs_launch, 1, EPI_RAW);
         if (epi == EPI_RAW) Z(zs_launch, 2, EPI_RAW);
-        if (epi == EPI_GELU && aux) return zs_launch<2, EPI_GELU, true>(x, wp, b, out, aux, nx, ny, nz, s);
+        if (epi == EPI_GELU && aux) return zs_launch<2, EPI_GELU, true>(x, wp, b, out, aux, nx, ny, nz, cubes, s);
         if (epi == EPI_GELU) Z(zs_launch, 2, EPI_GELU);
         Z(zs_launch, 2, EPI_BACK_GELU);
     }
@@ -192,8 +212,8 @@ size_t packed_count(int cin, int cout, int mode) {
 // outputs: per-workgroup partials, then a fixed-order fold into dW [27][cin][cout]
 // and db [cout]
 hipError_t launch_wgrad(int cin, int cout, const void* a, const void* dz, Dev& part, float* dW, float* db,
-                        int accumulate, long nx, long ny, long nz, hipStream_t s) {
-    const WgradPlan w = wgrad_plan(cin, cout, nx, ny, nz);
+                        int accumulate, long nx, long ny, long nz, long cubes, hipStream_t s) {
+    const WgradPlan w = wgrad_plan(cin, cout, nx, ny, nz, cubes);
     hipError_t e = part.ensure((size_t)w.groups * w.stride * sizeof(float));
     if (e != hipSuccess) return e;
     const u16* A = static_cast<const u16*>(a);
@@ -203,13 +223,13 @@ hipError_t launch_wgrad(int cin, int cout, const void* a, const void* dz, Dev& p
     if (cin == 32 && cout == 32) {
         e = hipFuncSetAttribute((const void*)k_wgrad32, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kWgLds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_wgrad32, g, b, kWgLds, s, A, D, part.as<float>(), x, y, z, w.ntx, w.nty);
+        hipLaunchKernelGGL(k_wgrad32, g, b, kWgLds, s, A, D, part.as<float>(), x, y, z, w.ntx, w.nty, (int)cubes);
     } else if (cin == 32) {
-        hipLaunchKernelGGL(k_wgrad1<32>, g, b, 0, s, A, D, 1, part.as<float>(), x, y, z, w.ntx, w.nty);
+        hipLaunchKernelGGL(k_wgrad1<32>, g, b, 0, s, A, D, 1, part.as<float>(), x, y, z, w.ntx, w.nty, (int)cubes);
     } else if (cout == 32) {
-        hipLaunchKernelGGL(k_wgrad1<32>, g, b, 0, s, D, A, 0, part.as<float>(), x, y, z, w.ntx, w.nty);
+        hipLaunchKernelGGL(k_wgrad1<32>, g, b, 0, s, D, A, 0, part.as<float>(), x, y, z, w.ntx, w.nty, (int)cubes);
     } else {
-        hipLaunchKernelGGL(k_wgrad1<1>, g, b, 0, s, D, A, 0, part.as<float>(), x, y, z, w.ntx, w.nty);
+        hipLaunchKernelGGL(k_wgrad1<1>, g, b, 0, s, D, A, 0, part.as<float>(), x, y, z, w.ntx, w.nty, (int)cubes);
     }
     e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -285,16 +305,21 @@ struct ig_surrogate {
 namespace {
 
 ig_status repack(ig_surrogate* s, hipStream_t st) {
+    PackAll a{};
+    a.layers = s->L;
     for (int l = 0; l < s->L; ++l) {
-        const float* W = s->params.as<float>() + s->w_off[l];
-        HIP_TRY(launch_pack(W, s->cin[l], s->cout[l], 0, s->pk_f[l].as<bf16x8>(), st));
-        HIP_TRY(launch_pack(W, s->cin[l], s->cout[l], 1, s->pk_d[l].as<bf16x8>(), st));
+        a.out[2 * l] = s->pk_f[l].as<bf16x8>();
+        a.out[2 * l + 1] = s->pk_d[l].as<bf16x8>();
     }
+    const unsigned blocks = (unsigned)((packed_count(32, 32, 0) + 255) / 256);   // of the largest form
+    hipLaunchKernelGGL(k_pack_all, dim3(blocks, 2 * s->L), dim3(256), 0, st, s->params.as<float>(), a);
+    HIP_TRY(hipGetLastError());
     return IG_OK;
 }
 
 ig_status ensure_acts(ig_surrogate* s, long n) {
     if (n <= s->cap) return IG_OK;
+    s->cap = 0;   // until every buffer has grown
     s->act.resize(s->L);
     s->pre.resize(s->L);
     HIP_TRY(s->act[0].ensure(n * 2));
@@ -308,6 +333,13 @@ ig_status ensure_acts(ig_surrogate* s, long n) {
     HIP_TRY(s->dzB.ensure(n * 32 * 2));
     s->cap = n;
     return IG_OK;
+}
+
+void release_acts(ig_surrogate* s) {
+    s->cap = 0;
+    for (Dev& d : s->act) d.release();
+    for (Dev& d : s->pre) d.release();
+    for (Dev* d : {&s->y, &s->dy, &s->dzA, &s->dzB}) d->release();
 }
 
 ig_status to_bf16(const float* x, void* a, long n, hipStream_t st);
@@ -336,28 +368,28 @@ ig_status forward_infer(ig_surrogate* s, const float* x, float* y, long nx, long
         if (l < s->L - 1) {
             void* o = s->iact[l & 1].p;
             HIP_TRY(launch_conv(s->cin[l], s->cout[l], EPI_GELU, in, s->pk_f[l].as<bf16x8>(), b, o, nullptr, nx, ny, nz,
-                                st));
+                                1, st));
             in = o;
         } else {
-            HIP_TRY(launch_conv(s->cin[l], s->cout[l], EPI_RESID, in, s->pk_f[l].as<bf16x8>(), b, y, x, nx, ny, nz, st));
+            HIP_TRY(launch_conv(s->cin[l], s->cout[l], EPI_RESID, in, s->pk_f[l].as<bf16x8>(), b, y, x, nx, ny, nz, 1, st));
         }
     }
     return IG_OK;
 }
 
-// forward pass on one cube already converted to act[0]; writes y (FP32)
-ig_status forward(ig_surrogate* s, const float* x, float* y, long nx, long ny, long nz, bool keep_pre, hipStream_t st) {
+// forward pass on `cubes` cubes already converted to act[0], one after another;
+// writes y (FP32) likewise and keeps the pre-activations
+ig_status forward(ig_surrogate* s, const float* const* x, float* y, long nx, long ny, long nz, long cubes,
+                  hipStream_t st) {
     const float* P = s->params.as<float>();
-    for (int l = 0; l < s->L; ++l) {
-        const float* b = P + s->b_off[l];
-        if (l < s->L - 1) {
-            HIP_TRY(launch_conv(s->cin[l], s->cout[l], EPI_GELU, s->act[l].p, s->pk_f[l].as<bf16x8>(), b,
-                                s->act[l + 1].p, keep_pre ? s->pre[l + 1].p : nullptr, nx, ny, nz, st));
-        } else {
-            HIP_TRY(launch_conv(s->cin[l], s->cout[l], EPI_RESID, s->act[l].p, s->pk_f[l].as<bf16x8>(), b, y, x,
-                                nx, ny, nz, st));
-        }
-    }
+    const long n = nx * ny * nz;
+    for (int l = 0; l + 1 < s->L; ++l)
+        HIP_TRY(launch_conv(s->cin[l], s->cout[l], EPI_GELU, s->act[l].p, s->pk_f[l].as<bf16x8>(), P + s->b_off[l],
+                            s->act[l + 1].p, s->pre[l + 1].p, nx, ny, nz, cubes, st));
+    const int l = s->L - 1;
+    for (long k = 0; k < cubes; ++k)
+        HIP_TRY(launch_conv(s->cin[l], s->cout[l], EPI_RESID, s->act[l].as<u16>() + k * n * 32,
+                            s->pk_f[l].as<bf16x8>(), P + s->b_off[l], y + k * n, x[k], nx, ny, nz, 1, st));
     return IG_OK;
 }
 
@@ -467,10 +499,25 @@ extern "C" ig_status ig_surrogate_train_step(ig_surrogate* s, const float* const
         if (cb == IG_OK) cb = igk_check_buffer(d_t[k], (size_t)n * 4, s->device, "d_t[k]");
         if (cb != IG_OK) return cb;
     }
-    ig_status rc = ensure_acts(s, n);
+    // The cubes go through the layers in groups, a launch per layer and group: one
+    // cube of 96^3 gives each compute unit 14 planes, too few for the kernels'
+    // set-up, and every launch of a weight gradient writes and folds a partial per
+    // workgroup.  Four 96^3 cubes: 4822 -> 4148 us with the shares above (weight
+    // gradient of a layer 4 x 59 -> 213 us, its folds 4 x 6.3 -> 6.5).
+    // A group's activations stay below kTrainBytes (more than one cube only); a
+    // group that cannot be allocated is halved.
+    const long per_cube = n * (128L * s->L + 8);
+    int group = (int)std::max<long>(1, std::min<long>(batch, kTrainBytes / per_cube));
+    ig_status rc = ensure_acts(s, n * group);
+    while (rc != IG_OK && group > 1) {
+        (void)hipGetLastError();
+        release_acts(s);
+        group /= 2;
+        rc = ensure_acts(s, n * group);
+    }
     if (rc != IG_OK) return rc;
     for (int l = 0; l < s->L; ++l) {   // weight-gradient partials for the largest layer, sized before any launch
-        const WgradPlan w = wgrad_plan(s->cin[l], s->cout[l], nx, ny, nz);
+        const WgradPlan w = wgrad_plan(s->cin[l], s->cout[l], nx, ny, nz, group);
         HIP_TRY(s->part.ensure((size_t)w.groups * w.stride * sizeof(float)));
     }
     const long np = (long)s->nparam;
@@ -480,25 +527,28 @@ extern "C" ig_status ig_surrogate_train_step(ig_surrogate* s, const float* const
     HIP_TRY(s->tmp.ensure((size_t)batch * nloss * sizeof(double)));
     double* lparts = s->tmp.as<double>();
     const double scale = 1.0 / ((double)n * batch);
-    for (int k = 0; k < batch; ++k) {
-        if (!d_x[k] || !d_t[k]) return fail(IG_ERR_INVALID_ARG, "NULL cube %d", k);
-        rc = to_bf16(d_x[k], s->act[0].p, n, st);
+    for (int k0 = 0; k0 < batch; k0 += group) {
+        const int cubes = std::min(group, batch - k0);
+        for (int k = 0; k < cubes; ++k) {
+            rc = to_bf16(d_x[k0 + k], s->act[0].as<u16>() + k * n, n, st);
+            if (rc != IG_OK) return rc;
+        }
+        rc = forward(s, d_x + k0, s->y.as<float>(), nx, ny, nz, cubes, st);
         if (rc != IG_OK) return rc;
-        rc = forward(s, d_x[k], s->y.as<float>(), nx, ny, nz, true, st);
-        if (rc != IG_OK) return rc;
-        hipLaunchKernelGGL(k_mse, dim3(nloss), dim3(256), 0, st, s->y.as<float>(), d_t[k], n, scale,
-                           s->dy.as<u16>(), lparts + (size_t)k * nloss);
+        for (int k = 0; k < cubes; ++k)
+            hipLaunchKernelGGL(k_mse, dim3(nloss), dim3(256), 0, st, s->y.as<float>() + k * n, d_t[k0 + k], n, scale,
+                               s->dy.as<u16>() + k * n, lparts + (size_t)(k0 + k) * nloss);
         HIP_TRY(hipGetLastError());
         // backward: dz of layer l lives in `g` (1 channel for the last layer)
         const void* g = s->dy.p;
         for (int l = s->L - 1; l >= 0; --l) {
             float* dW = s->grads.as<float>() + s->w_off[l];
             float* db = s->grads.as<float>() + s->b_off[l];
-            HIP_TRY(launch_wgrad(s->cin[l], s->cout[l], s->act[l].p, g, s->part, dW, db, 1, nx, ny, nz, st));
+            HIP_TRY(launch_wgrad(s->cin[l], s->cout[l], s->act[l].p, g, s->part, dW, db, 1, nx, ny, nz, cubes, st));
             if (l > 0) {   // gradient of the layer's input, through gelu' of the layer below
                 void* dst = (g == s->dzA.p) ? s->dzB.p : s->dzA.p;
                 HIP_TRY(launch_conv(s->cout[l], s->cin[l], EPI_BACK_GELU, g, s->pk_d[l].as<bf16x8>(), nullptr, dst,
-                                    s->pre[l].p, nx, ny, nz, st));
+                                    s->pre[l].p, nx, ny, nz, cubes, st));
                 g = dst;
             }
         }
@@ -513,7 +563,7 @@ extern "C" ig_status ig_surrogate_train_step(ig_surrogate* s, const float* const
         double* norm = reinterpret_cast<double*>(s->clipbuf.as<char>() + 8);
         double* cparts = reinterpret_cast<double*>(s->clipbuf.as<char>() + 64);
         hipLaunchKernelGGL(k_sumsq, dim3(1024), dim3(256), 0, st, s->grads.as<float>(), np, cparts);
-        hipLaunchKernelGGL(k_clip_factor, dim3(1), dim3(64), 0, st, cparts, 1024, s->clip, factor, norm);
+        hipLaunchKernelGGL(k_clip_factor, dim3(1), dim3(256), 0, st, cparts, 1024, s->clip, factor, norm);
         hipLaunchKernelGGL(k_adam, dim3((np + 255) / 256), dim3(256), 0, st, s->params.as<float>(),
                            s->grads.as<float>(), s->m.as<float>(), s->v.as<float>(), np, s->p.lr, b1, b2, s->p.eps, bc1,
                            bc2, (const float*)factor);
@@ -836,7 +886,7 @@ extern "C" ig_status ig_conv3d_forward(const void* d_in, int32_t c_in, const flo
     hipLaunchKernelGGL(k_fill, dim3(1), dim3(256), 0, st, bias.as<float>(), 32, 0.0f);
     if (d_b) HIP_TRY(hipMemcpyAsync(bias.p, d_b, c_out * 4, hipMemcpyDeviceToDevice, st));
     HIP_TRY(launch_pack(d_w, c_in, c_out, 0, pk.as<bf16x8>(), st));
-    HIP_TRY(launch_conv(c_in, c_out, epilogue, d_in, pk.as<bf16x8>(), bias.as<float>(), d_out, d_aux, nx, ny, nz, st));
+    HIP_TRY(launch_conv(c_in, c_out, epilogue, d_in, pk.as<bf16x8>(), bias.as<float>(), d_out, d_aux, nx, ny, nz, 1, st));
     HIP_TRY(hipStreamSynchronize(st));
     return IG_OK;
 }
@@ -854,7 +904,7 @@ extern "C" ig_status ig_conv3d_input_grad(const void* d_dz, int32_t c_out, const
     HIP_TRY(pk.ensure(packed_count(c_in, c_out, 1) * 16));
     HIP_TRY(launch_pack(d_w, c_in, c_out, 1, pk.as<bf16x8>(), st));
     HIP_TRY(launch_conv(c_out, c_in, d_aux ? EPI_BACK_GELU : EPI_RAW, d_dz, pk.as<bf16x8>(), nullptr, d_out, d_aux, nx,
-                        ny, nz, st));
+                        ny, nz, 1, st));
     HIP_TRY(hipStreamSynchronize(st));
     return IG_OK;
 }
@@ -867,7 +917,7 @@ extern "C" ig_status ig_conv3d_weight_grad(const void* d_a, int32_t c_in, const 
     if (nx * ny * nz >= kMaxConvVox) return fail(IG_ERR_INVALID_ARG, "cube too large: voxels x 32 must stay below 2^31");
     hipStream_t st = (hipStream_t)hip_stream;
     Dev part;
-    HIP_TRY(launch_wgrad(c_in, c_out, d_a, d_dz, part, d_dw, d_db, 0, nx, ny, nz, st));
+    HIP_TRY(launch_wgrad(c_in, c_out, d_a, d_dz, part, d_dw, d_db, 0, nx, ny, nz, 1, st));
     HIP_TRY(hipStreamSynchronize(st));
     return IG_OK;
 }

@@ -58,19 +58,7 @@ __device__ __forceinline__ void static_for(F&& f) {
 // Error function by Abramowitz & Stegun, Handbook of Mathematical Functions,
 // formula 7.1.26: erf(x) = 1 - (a1 t + ... + a5 t^5) e^{-x^2}, t = 1/(1 + p x)
 // for x >= 0, |error| <= 1.5e-7 (far below the bf16 rounding of every value
-// it feeds).  e2 returns e^{-x^2}, which GELU' reuses.
-__device__ __forceinline__ float erf_as(float x, float* e2) {
-    const float ax = fabsf(x);
-    const float t = __builtin_amdgcn_rcpf(__builtin_fmaf(0.3275911f, ax, 1.0f));
-    const float ex = __builtin_amdgcn_exp2f(-(ax * ax) * 1.4426950408889634f);
-    float pl = __builtin_fmaf(1.061405429f, t, -1.453152027f);
-    pl = __builtin_fmaf(pl, t, 1.421413741f);
-    pl = __builtin_fmaf(pl, t, -0.284496736f);
-    pl = __builtin_fmaf(pl, t, 0.254829592f);
-    const float y = 1.0f - (pl * t) * ex;
-    *e2 = ex;
-    return x < 0.0f ? -y : y;
-}
+// it feeds).
 // gelu(z) = z/2 (1 + erf(z/sqrt2)); gelu'(z) = (1 + erf(z/sqrt2))/2 + z e^{-z^2/2}/sqrt(2 pi)
 // GELU through the complementary function the same formula gives directly,
 // erfc(x) = (a1 t + ... + a5 t^5) e^{-x^2} for x >= 0: with c = erfc(|z|/sqrt2),
@@ -88,10 +76,19 @@ __device__ __forceinline__ float gelu_fast(float z) {
     const float c = (pl * t) * ex;
     return __builtin_fmaf(-az, c, fmaxf(z, 0.0f));
 }
+// With h = erfc(|x|)/2, x = z/sqrt2: (1 + erf(x))/2 = 1/2 + sign(z) (1/2 - h), the
+// coefficients halved as above (every rounding is that of the formula as written).
 __device__ __forceinline__ float gelu_grad_fast(float z) {
-    float e;
-    const float er = erf_as(z * 0.70710678118654752f, &e);
-    return 0.5f * (1.0f + er) + z * (0.39894228040143268f * e);
+    const float x = z * 0.70710678118654752f;
+    const float t = __builtin_amdgcn_rcpf(__builtin_fmaf(0.3275911f, fabsf(x), 1.0f));
+    const float ex = __builtin_amdgcn_exp2f((x * x) * -1.4426950408889634f);   // e^{-z^2/2}
+    float pl = __builtin_fmaf(0.5f * 1.061405429f, t, 0.5f * -1.453152027f);
+    pl = __builtin_fmaf(pl, t, 0.5f * 1.421413741f);
+    pl = __builtin_fmaf(pl, t, 0.5f * -0.284496736f);
+    pl = __builtin_fmaf(pl, t, 0.5f * 0.254829592f);
+    const float u = 0.5f - (pl * t) * ex;
+    const float su = __uint_as_float(__float_as_uint(u) ^ (__float_as_uint(z) & 0x80000000u));
+    return (0.5f + su) + z * (0.39894228040143268f * ex);
 }
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 // four FP32 values to four bf16 (round to nearest, ties to even; the gfx950
@@ -213,6 +210,36 @@ __device__ __forceinline__ void zs_store(const f32x4 (&acc)[MT][NB], const float
         }
 }
 
+// How the tile planes (tiles of 32 x 8 voxels) of `cubes` cubes of one shape, laid
+// one after another, are dealt to the workgroups: chunks of zch planes of one
+// tile, or (zch = 0) equal contiguous shares of the sequence cube, tile, plane,
+// which a workgroup takes as runs of planes of one tile.
+struct ZsSplit {
+    int ntx, nty, zch, cubes;
+    __device__ __forceinline__ void share(int nz, int* u0, int* u1) const {
+        const int tiles = ntx * nty;
+        if (zch > 0) {
+            const int nzc = (nz + zch - 1) / zch, t = blockIdx.x % tiles, q = blockIdx.x / tiles;
+            const int z0 = q % nzc * zch;
+            *u0 = (q / nzc * tiles + t) * nz + z0;
+            *u1 = *u0 + min(zch, nz - z0);
+        } else {
+            const long total = (long)tiles * cubes * nz;
+            *u0 = (int)(total * blockIdx.x / gridDim.x);
+            *u1 = (int)(total * (blockIdx.x + 1) / gridDim.x);
+        }
+    }
+    // the run that starts at u of a share that ends at u1; returns the cube
+    __device__ __forceinline__ int run(int nz, int u, int u1, int* x0, int* y0, int* z0, int* z1) const {
+        const int tiles = ntx * nty, t = u / nz, tile = t % tiles;
+        *x0 = tile % ntx * kZsX;
+        *y0 = tile / ntx * kZsRows;
+        *z0 = u - t * nz;
+        *z1 = min(nz, *z0 + (u1 - u));
+        return t / tiles;
+    }
+};
+
 // products per tap plane of fragment m of a step, and the epilogue values begun
 // before it (16 over a step)
 constexpr int zs_products(int m) {
@@ -229,196 +256,204 @@ constexpr int zs_value(int m) {
 // is stored.  KEEP: the pre-activations go to aux (EPI_GELU).
 template <int NB, int EPI, bool KEEP>
 __global__ void __launch_bounds__(512)
-k_conv_zs(const u16* __restrict__ in, const bf16x8* __restrict__ wp, const float* __restrict__ bias,
-          void* __restrict__ out, const void* __restrict__ aux, int nx, int ny, int nz, int ntx, int nty, int zch) {
+k_conv_zs(const u16* __restrict__ in0, const bf16x8* __restrict__ wp, const float* __restrict__ bias,
+          void* __restrict__ out0, const void* __restrict__ aux0, int nx, int ny, int nz, ZsSplit sp) {
     constexpr int NT = 512, PER = kZsPer;
     extern __shared__ uint4 zs_smem[];
     u16* ring = reinterpret_cast<u16*>(zs_smem);
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nb = w & 1, xs = (w >> 1) & 1, yg = w >> 2;
     const int i = lane & 15, kg = lane >> 4;
-    const int bt = blockIdx.x;
-    const int tx = bt % ntx, ty = (bt / ntx) % nty, tz = bt / (ntx * nty);
-    const int x0 = tx * kZsX, y0 = ty * kZsRows;
-    const int z0 = tz * zch, z1 = min(nz, z0 + zch);
+    const int n0 = 16 * nb + 4 * kg;
     const bool act = nb < NB;                      // this wavefront's channels exist
 
     bf16x8 wf[27];
 #pragma unroll
     for (int t = 0; t < 27; ++t) wf[t] = wp[(t * NB + (act ? nb : 0)) * 64 + lane];
-
-    // the chunks this thread stages: offset from the tile's first row of a
-    // plane in units of 16 bytes (below 2^32: a piece has at most 2^28
-    // voxels), clamped into the cube; mask: all ones if the chunk lies in it
-    unsigned off[PER], mask[PER];
-    const int yb = max(y0 - 1, 0);
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int q = tid + NT * k, vox = q >> 2;
-        const int x = x0 + vox % kZsLX - 1, y = y0 + vox / kZsLX - 1;
-        mask[k] = x >= 0 && x < nx && y >= 0 && y < ny ? ~0u : 0u;
-        off[k] = (unsigned)(((long)(min(max(y, 0), ny - 1) - yb) * nx + min(max(x, 0), nx - 1)) * 4 + (q & 3));
-    }
-    uint4 st[PER];
-    auto fetch = [&](int z) {
-        const uint4* base = reinterpret_cast<const uint4*>(in) + ((long)min(max(z, 0), nz - 1) * ny + yb) * nx * 4;
-#pragma unroll
-        for (int k = 0; k < PER; ++k) st[k] = base[off[k]];
-    };
-    auto put = [&](int z, int slot) {
-        const bool zin = z >= 0 && z < nz;
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const unsigned m = zin ? mask[k] : 0u;
-            reinterpret_cast<uint4*>(ring + slot * kZsPl)[tid + NT * k] =
-                make_uint4(st[k].x & m, st[k].y & m, st[k].z & m, st[k].w & m);
-        }
-    };
-    // plane z0 - 1 + k sits in slot k mod 3
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        fetch(z0 - 1 + k);
-        put(z0 - 1 + k, k);
-    }
-    fetch(z0 + 1);
-    __syncthreads();
-
-    const u16* lb = ring + ((4 * yg) * kZsLX + 16 * xs + i) * 32 + 8 * kg;
-    // this wavefront's part of output row y + r, plane z: a buffer of bytes
-    // `vb` per voxel from voxel x0, empty where nothing is to be stored
-    const int y = y0 + 4 * yg, n0 = 16 * nb + 4 * kg;
-    const int cols = min(nx - x0, kZsX);
-    auto row = [&](const void* p, int z, int r, int vb) {   // no branch: it would split the pass's schedule
-        const int on = -(int)(act & (z >= z0) & (z < z1) & (y + r < ny));
-        return raw_buffer(static_cast<const char*>(p) +
-                              (((long)max(z, 0) * ny + min(y + r, ny - 1)) * nx + x0) * vb, on & (cols * vb));
-    };
-    const int lo = (16 * xs + i) * 64 + 2 * n0;    // this lane's four bf16 channels in such a row
     f32x4 bv = {0.f, 0.f, 0.f, 0.f};
     if (EPI != EPI_BACK_GELU && bias && act)
 #pragma unroll
         for (int e = 0; e < 4; ++e) bv[e] = bias[n0 + e];
-    // a0, a1, a2: the sums that the current input plane reaches with the taps of
-    // plane 0, 1 and 2.  prev: the finished output plane zp; its epilogue (GELU,
-    // packing, stores) is spread over the next step's products, a value at a time
-    // and with no branch, so that it runs beside the matrix cores
-    constexpr int NV = 16;
-    f32x4 a0[4], a1[4], a2[4], prev[4];
-    uint2 pre[4];
-    int zp = z0 - 1;
+
+    // runs of planes of one tile of one cube
+    int u0, u1;
+    sp.share(nz, &u0, &u1);
+    for (int u = u0; u < u1;) {
+        int x0, y0, z0, z1;
+        const long cube = sp.run(nz, u, u1, &x0, &y0, &z0, &z1) * ((long)nx * ny * nz);
+        u += z1 - z0;
+        const u16* in = in0 + cube * 32;
+        const void* aux = static_cast<const char*>(aux0) + cube * 64;   // (bf16, with 32 channels)
+        void* out = static_cast<char*>(out0) + cube * (EPI == EPI_RAW ? 64 * NB : 64);
+
+        // the chunks this thread stages: offset from the tile's first row of a
+        // plane in units of 16 bytes (below 2^32: a piece has at most 2^28
+        // voxels), clamped into the cube; mask: all ones if the chunk lies in it
+        unsigned off[PER], mask[PER];
+        const int yb = max(y0 - 1, 0);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        prev[r] = f32x4{0.f, 0.f, 0.f, 0.f};
-        pre[r] = make_uint2(0, 0);
-    }
-    auto store2 = [&](void* p, int z, int r, uint2 v) {
-        __builtin_amdgcn_raw_buffer_store_b64(u32x2{v.x, v.y}, row(p, z, r, 64), lo, 0, 0);
-    };
-    auto epi = [&](auto vc) {   // value e of row r
-        constexpr int v = decltype(vc)::value, r = v / 4, e = v % 4;
-        f32x4& d = prev[r];
-        if constexpr (EPI == EPI_GELU) {
-            if constexpr (e == 0) {
-                d += bv;
-                if constexpr (KEEP) store2(const_cast<void*>(aux), zp, r, pack_bf16x4(d[0], d[1], d[2], d[3]));
-            }
-            d[e] = gelu_fast(d[e]);
-            if constexpr (e == 3) store2(out, zp, r, pack_bf16x4(d[0], d[1], d[2], d[3]));
-        } else if constexpr (EPI == EPI_BACK_GELU) {
-            const unsigned u = e < 2 ? pre[r].x : pre[r].y;
-            d[e] *= gelu_grad_fast(__uint_as_float(e & 1 ? u & 0xffff0000u : u << 16));
-            if constexpr (e == 3) store2(out, zp, r, pack_bf16x4(d[0], d[1], d[2], d[3]));
-        } else if constexpr (e == 3) {
-            typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-            const f32x4 o = d + bv;
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), row(out, zp, r, 64 * NB),
-                                                   (16 * xs + i) * 64 * NB + 4 * n0, 0, 0);
+        for (int k = 0; k < PER; ++k) {
+            const int q = tid + NT * k, vox = q >> 2;
+            const int x = x0 + vox % kZsLX - 1, y = y0 + vox / kZsLX - 1;
+            mask[k] = x >= 0 && x < nx && y >= 0 && y < ny ? ~0u : 0u;
+            off[k] = (unsigned)(((long)(min(max(y, 0), ny - 1) - yb) * nx + min(max(x, 0), nx - 1)) * 4 + (q & 3));
         }
-    };
-    // fragment m: row 4 yg - 1 + j (j = m / 3) of the tile, shift dx = m % 3
-    constexpr int FR = kZsAhead + 1;
-    static_assert(18 % FR == 0, "the ring of fragments repeats with the steps");
-    bf16x8 f[FR];
-    int sl = 0;                                    // slot of the current plane
-    const u16 *lq = lb, *lq1 = lb + kZsPl;         // the current plane and the next
-    auto load = [&](auto mc) {                     // (18 and up: of the next plane, staged two steps ahead)
-        constexpr int m = decltype(mc)::value, n = m % 18;
-        f[m % FR] = *reinterpret_cast<const bf16x8*>((m < 18 ? lq : lq1) + ((n / 3) * kZsLX + n % 3) * 32);
-    };
-    static_for<kZsAhead>(load);
-    // input plane z with the tap planes LO .. HI
-    auto step = [&](auto loc, auto hic, int z) {
-        constexpr int LO = decltype(loc)::value, HI = decltype(hic)::value;
-        const int sw = sl == 0 ? 2 : sl - 1;       // slot of plane z + 2
-        auto part = [&](auto hc) {
-            constexpr int M0 = 9 * decltype(hc)::value;
-            static_for<9>([&](auto mc) {
-                constexpr int m = M0 + decltype(mc)::value, j = m / 3, dx = m % 3;
-                load(std::integral_constant<int, m + kZsAhead>{});
-                // tap plane 2 first: a sum moves on by being the next plane's
-                // first addend, before its place is taken
+        uint4 st[PER];
+        auto fetch = [&](int z) {
+            const uint4* base = reinterpret_cast<const uint4*>(in) + ((long)min(max(z, 0), nz - 1) * ny + yb) * nx * 4;
 #pragma unroll
-                for (int d = HI; d >= LO; --d)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (j - r >= 0 && j - r < 3) {
-                            const bool first = j == r && dx == 0;
-                            f32x4* o = d == 0 ? a0 : d == 1 ? a1 : a2;
-                            const f32x4 c = !first ? o[r] : d == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : d == 1 ? a0[r] : a1[r];
-                            o[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[9 * d + 3 * (j - r) + dx], f[m % FR], c,
-                                                                           0, 0, 0);
-                        }
-                if constexpr (HI == 2) {
-                    constexpr int v0 = zs_value(m), v1 = zs_value(m + 1);
-                    static_for<v1 - v0>([&](auto k) { epi(std::integral_constant<int, v0 + decltype(k)::value>{}); });
-                }
-            });
-            // the order to issue it in: each fragment's read kZsAhead fragments
-            // ahead, and behind each product the two or three VALU operations that
-            // fit under its 16 cycles
-            static_for<9>([&](auto mc) {
-                constexpr int m = M0 + decltype(mc)::value;
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                static_for<zs_products(m) * (HI - LO + 1)>([&](auto) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, kZsValu, 0);
-                });
-            });
-            __builtin_amdgcn_sched_barrier(0);
+            for (int k = 0; k < PER; ++k) st[k] = base[off[k]];
         };
-        __builtin_amdgcn_sched_barrier(0);
-        part(std::integral_constant<int, 0>{});
-        if constexpr (LO == 0) {                   // the last two steps stage nothing
-            put(z + 2, sw);
-            fetch(z + 3);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        part(std::integral_constant<int, 1>{});
-        if constexpr (HI == 2) {
-            zp = z - 1;
+        auto put = [&](int z, int slot) {
+            const bool zin = z >= 0 && z < nz;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) prev[r] = a2[r];
-            if constexpr (EPI == EPI_BACK_GELU)
+            for (int k = 0; k < PER; ++k) {
+                const unsigned m = zin ? mask[k] : 0u;
+                reinterpret_cast<uint4*>(ring + slot * kZsPl)[tid + NT * k] =
+                    make_uint4(st[k].x & m, st[k].y & m, st[k].z & m, st[k].w & m);
+            }
+        };
+        // plane z0 - 1 + k sits in slot k mod 3
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(row(aux, zp, r, 64), lo, 0, 0);
-                    pre[r] = make_uint2(v.x, v.y);
-                }
+        for (int k = 0; k < 2; ++k) {
+            fetch(z0 - 1 + k);
+            put(z0 - 1 + k, k);
         }
-        sl = sl == 2 ? 0 : sl + 1;
-        lq = lq1;
-        lq1 = lb + (sl == 2 ? 0 : sl + 1) * kZsPl;
+        fetch(z0 + 1);
         __syncthreads();
-    };
-    constexpr std::integral_constant<int, 0> D0{};
-    constexpr std::integral_constant<int, 1> D1{};
-    constexpr std::integral_constant<int, 2> D2{};
-    step(D0, D0, z0 - 1);
-    step(D0, D1, z0);
-    for (int z = z0 + 1; z < z1 - 1; ++z) step(D0, D2, z);
-    if (z1 - 1 > z0) step(D1, D2, z1 - 1);
-    step(D2, D2, z1);
-    static_for<NV>(epi);
+
+        const u16* lb = ring + ((4 * yg) * kZsLX + 16 * xs + i) * 32 + 8 * kg;
+        // this wavefront's part of output row y + r, plane z: a buffer of bytes
+        // `vb` per voxel from voxel x0, empty where nothing is to be stored
+        const int y = y0 + 4 * yg;
+        const int cols = min(nx - x0, kZsX);
+        auto row = [&](const void* p, int z, int r, int vb) {   // no branch: it would split the pass's schedule
+            const int on = -(int)(act & (z >= z0) & (z < z1) & (y + r < ny));
+            return raw_buffer(static_cast<const char*>(p) +
+                                  (((long)max(z, 0) * ny + min(y + r, ny - 1)) * nx + x0) * vb, on & (cols * vb));
+        };
+        const int lo = (16 * xs + i) * 64 + 2 * n0;    // this lane's four bf16 channels in such a row
+        // a0, a1, a2: the sums that the current input plane reaches with the taps of
+        // plane 0, 1 and 2.  prev: the finished output plane zp; its epilogue (GELU,
+        // packing, stores) is spread over the next step's products, a value at a time
+        // and with no branch, so that it runs beside the matrix cores
+        constexpr int NV = 16;
+        f32x4 a0[4], a1[4], a2[4], prev[4];
+        uint2 pre[4];
+        int zp = z0 - 1;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            prev[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+            pre[r] = make_uint2(0, 0);
+        }
+        auto store2 = [&](void* p, int z, int r, uint2 v) {
+            __builtin_amdgcn_raw_buffer_store_b64(u32x2{v.x, v.y}, row(p, z, r, 64), lo, 0, 0);
+        };
+        auto epi = [&](auto vc) {   // value e of row r
+            constexpr int v = decltype(vc)::value, r = v / 4, e = v % 4;
+            f32x4& d = prev[r];
+            if constexpr (EPI == EPI_GELU) {
+                if constexpr (e == 0) {
+                    d += bv;
+                    if constexpr (KEEP) store2(const_cast<void*>(aux), zp, r, pack_bf16x4(d[0], d[1], d[2], d[3]));
+                }
+                d[e] = gelu_fast(d[e]);
+                if constexpr (e == 3) store2(out, zp, r, pack_bf16x4(d[0], d[1], d[2], d[3]));
+            } else if constexpr (EPI == EPI_BACK_GELU) {
+                const unsigned u = e < 2 ? pre[r].x : pre[r].y;
+                d[e] *= gelu_grad_fast(__uint_as_float(e & 1 ? u & 0xffff0000u : u << 16));
+                if constexpr (e == 3) store2(out, zp, r, pack_bf16x4(d[0], d[1], d[2], d[3]));
+            } else if constexpr (e == 3) {
+                typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+                const f32x4 o = d + bv;
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), row(out, zp, r, 64 * NB),
+                                                       (16 * xs + i) * 64 * NB + 4 * n0, 0, 0);
+            }
+        };
+        // fragment m: row 4 yg - 1 + j (j = m / 3) of the tile, shift dx = m % 3
+        constexpr int FR = kZsAhead + 1;
+        static_assert(18 % FR == 0, "the ring of fragments repeats with the steps");
+        bf16x8 f[FR];
+        int sl = 0;                                    // slot of the current plane
+        const u16 *lq = lb, *lq1 = lb + kZsPl;         // the current plane and the next
+        auto load = [&](auto mc) {                     // (18 and up: of the next plane, staged two steps ahead)
+            constexpr int m = decltype(mc)::value, n = m % 18;
+            f[m % FR] = *reinterpret_cast<const bf16x8*>((m < 18 ? lq : lq1) + ((n / 3) * kZsLX + n % 3) * 32);
+        };
+        static_for<kZsAhead>(load);
+        // input plane z with the tap planes LO .. HI
+        auto step = [&](auto loc, auto hic, int z) {
+            constexpr int LO = decltype(loc)::value, HI = decltype(hic)::value;
+            const int sw = sl == 0 ? 2 : sl - 1;       // slot of plane z + 2
+            auto part = [&](auto hc) {
+                constexpr int M0 = 9 * decltype(hc)::value;
+                static_for<9>([&](auto mc) {
+                    constexpr int m = M0 + decltype(mc)::value, j = m / 3, dx = m % 3;
+                    load(std::integral_constant<int, m + kZsAhead>{});
+                    // tap plane 2 first: a sum moves on by being the next plane's
+                    // first addend, before its place is taken
+#pragma unroll
+                    for (int d = HI; d >= LO; --d)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            if (j - r >= 0 && j - r < 3) {
+                                const bool first = j == r && dx == 0;
+                                f32x4* o = d == 0 ? a0 : d == 1 ? a1 : a2;
+                                const f32x4 c = !first ? o[r] : d == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : d == 1 ? a0[r] : a1[r];
+                                o[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[9 * d + 3 * (j - r) + dx], f[m % FR], c,
+                                                                               0, 0, 0);
+                            }
+                    if constexpr (HI == 2) {
+                        constexpr int v0 = zs_value(m), v1 = zs_value(m + 1);
+                        static_for<v1 - v0>([&](auto k) { epi(std::integral_constant<int, v0 + decltype(k)::value>{}); });
+                    }
+                });
+                // the order to issue it in: each fragment's read kZsAhead fragments
+                // ahead, and behind each product the two or three VALU operations that
+                // fit under its 16 cycles
+                static_for<9>([&](auto mc) {
+                    constexpr int m = M0 + decltype(mc)::value;
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                    static_for<zs_products(m) * (HI - LO + 1)>([&](auto) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x002, kZsValu, 0);
+                    });
+                });
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            __builtin_amdgcn_sched_barrier(0);
+            part(std::integral_constant<int, 0>{});
+            if constexpr (LO == 0) {                   // the last two steps stage nothing
+                put(z + 2, sw);
+                fetch(z + 3);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            part(std::integral_constant<int, 1>{});
+            if constexpr (HI == 2) {
+                zp = z - 1;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) prev[r] = a2[r];
+                if constexpr (EPI == EPI_BACK_GELU)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(row(aux, zp, r, 64), lo, 0, 0);
+                        pre[r] = make_uint2(v.x, v.y);
+                    }
+            }
+            sl = sl == 2 ? 0 : sl + 1;
+            lq = lq1;
+            lq1 = lb + (sl == 2 ? 0 : sl + 1) * kZsPl;
+            __syncthreads();
+        };
+        constexpr std::integral_constant<int, 0> D0{};
+        constexpr std::integral_constant<int, 1> D1{};
+        constexpr std::integral_constant<int, 2> D2{};
+        step(D0, D0, z0 - 1);
+        step(D0, D1, z0);
+        for (int z = z0 + 1; z < z1 - 1; ++z) step(D0, D2, z);
+        if (z1 - 1 > z0) step(D1, D2, z1 - 1);
+        step(D2, D2, z1);
+        static_for<NV>(epi);    }
 }
 
 // The convolution of a 1-channel input as a z-stream (the network's first
@@ -433,13 +468,19 @@ template <int NB, int EPI, int MT>
 __global__ void __launch_bounds__(512)
 k_conv1_zs(const u16* __restrict__ in, const bf16x8* __restrict__ wp, const float* __restrict__ bias,
            void* __restrict__ out, const void* __restrict__ aux, int nx, int ny, int nz, int ntx, int nty, int zch) {
+    // z chunks of one cube after another
+    const int nzc = (nz + zch - 1) / zch;
+    const long cube = (int)(blockIdx.x / (ntx * nty)) / nzc * ((long)nx * ny * nz);
+    in += cube;
+    if (aux) aux = static_cast<const char*>(aux) + cube * (EPI == EPI_RESID ? 4 : 32 * NB);
+    out = static_cast<char*>(out) + cube * (EPI == EPI_RAW ? 64 * NB : EPI == EPI_RESID ? 4 : 32 * NB);
     constexpr int XW = 16 * MT, LX = XW + 2, LY = kZsRows + 2, NPL = LX * LY;
     static_assert(NPL <= 64 * kZsRows, "one staged voxel per thread");
     __shared__ u16 ring[3 * NPL + 16 * MT];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int i = lane & 15, kg = lane >> 4;
     const int bt = blockIdx.x;
-    const int tx = bt % ntx, ty = (bt / ntx) % nty, tz = bt / (ntx * nty);
+    const int tx = bt % ntx, ty = (bt / ntx) % nty, tz = bt / (ntx * nty) % nzc;
     const int x0 = tx * XW, y0 = ty * kZsRows;
     const int z0 = tz * zch, z1 = min(nz, z0 + zch);
 
@@ -665,8 +706,8 @@ __device__ __forceinline__ bf16x8 tr_frag(const u16* p) {
 // more product with a fragment of ones.  96^3 voxels: 263 -> 56 us (870
 // TFLOP/s) against 2-byte gathered LDS reads, one pair of fragments per product.
 __global__ void __launch_bounds__(kWgThreads)
-k_wgrad32(const u16* __restrict__ a, const u16* __restrict__ dz, float* __restrict__ part, int nx, int ny, int nz,
-          int ntx, int nty) {
+k_wgrad32(const u16* __restrict__ a0, const u16* __restrict__ dz0, float* __restrict__ part, int nx, int ny, int nz,
+          int ntx, int nty, int cubes) {
     extern __shared__ uint4 wg_smem[];
     u16* As = reinterpret_cast<u16*>(wg_smem);   // two planes of activations, then two of gradients
     u16* Bs = As + 2 * kWgPlA;
@@ -684,10 +725,13 @@ k_wgrad32(const u16* __restrict__ a, const u16* __restrict__ dz, float* __restri
 #pragma unroll
     for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
 
-    const long units = (long)ntx * nty * nz;
+    const int tiles = ntx * nty;
+    const long units = (long)tiles * nz * cubes;   // planes of tiles of one cube after another
     const long u0 = blockIdx.x * units / gridDim.x, u1 = (blockIdx.x + 1) * units / gridDim.x;
     for (long u = u0; u < u1;) {
-        const int tile = (int)(u / nz), z0 = (int)(u % nz);
+        const int ct = (int)(u / nz), z0 = (int)(u % nz), tile = ct % tiles;
+        const long cube = ct / tiles * ((long)nx * ny * nz);
+        const u16 *a = a0 + cube * 32, *dz = dz0 + cube * 32;
         const int np = (int)min((long)(nz - z0), u1 - u);      // planes of this run in this tile
         const int x0 = tile % ntx * kWgX, y0 = tile / ntx * kWgY;
         u += np;
@@ -824,8 +868,8 @@ constexpr int kWg1Row = 40;                                  // u16 per staged q
 constexpr int kWg1Copy = kWgLY * kWg1Row, kWg1Pl = 3 * kWg1Copy;
 template <int CP>
 __global__ void __launch_bounds__(kWgThreads)
-k_wgrad1(const u16* __restrict__ p, const u16* __restrict__ q, int mirror, float* __restrict__ part, int nx, int ny,
-         int nz, int ntx, int nty) {
+k_wgrad1(const u16* __restrict__ p0, const u16* __restrict__ q0, int mirror, float* __restrict__ part, int nx, int ny,
+         int nz, int ntx, int nty, int cubes) {
     constexpr int NB = CP == 32 ? 2 : 1;
     __shared__ __attribute__((aligned(16))) u16 Ps[2 * kWgPlB];
     __shared__ __attribute__((aligned(16))) u16 Qs[4 * kWg1Pl + 16];   // + eight ones, eight zeros
@@ -853,13 +897,16 @@ k_wgrad1(const u16* __restrict__ p, const u16* __restrict__ q, int mirror, float
         for (int nb = 0; nb < NB; ++nb) acc[m][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
     float qsum = 0.0f;
 
-    const long units = (long)ntx * nty * nz;
+    const int tiles = ntx * nty;
+    const long units = (long)tiles * nz * cubes;   // planes of tiles of one cube after another
     const long u0 = blockIdx.x * units / gridDim.x, u1 = (blockIdx.x + 1) * units / gridDim.x;
     const int qc = tid % kWgLX, qr = tid / kWgLX;            // the q voxel this thread stages
     const bool qon = tid < kWgLX * kWgLY;
     const bool qin = qc >= 1 && qc <= kWgX && qr >= 1 && qr <= kWgY;
     for (long u = u0; u < u1;) {
-        const int tile = (int)(u / nz), z0 = (int)(u % nz);
+        const int ct = (int)(u / nz), z0 = (int)(u % nz), tile = ct % tiles;
+        const long cube = ct / tiles * ((long)nx * ny * nz);
+        const u16 *p = p0 + cube * CP, *q = q0 + cube;
         const int np = (int)min((long)(nz - z0), u1 - u);
         const int x0 = tile % ntx * kWgX, y0 = tile / ntx * kWgY;
         u += np;
@@ -897,10 +944,10 @@ k_wgrad1(const u16* __restrict__ p, const u16* __restrict__ q, int mirror, float
         };
         __syncthreads();   // the constants are written; the previous run is done with the planes
         fetch_p(z0);
-        const u16 q0 = fetch_q(z0 - 1), q1 = fetch_q(z0), q2 = fetch_q(z0 + 1);
-        put_q(0, q0);
-        put_q(1, q1);
-        put_q(2, q2);
+        const u16 qa = fetch_q(z0 - 1), qb = fetch_q(z0), qc1 = fetch_q(z0 + 1);
+        put_q(0, qa);
+        put_q(1, qb);
+        put_q(2, qc1);
         put_p(0);
         __syncthreads();
         for (int s = 0; s < np; ++s) {
@@ -1022,7 +1069,7 @@ k_mse(const float* __restrict__ y, const float* __restrict__ t, long n, double s
 
 // ---------------------------------------------------------- optimiser
 // Gradient clipping by global norm: FP64 sum of squares of the gradient per
-// workgroup, then one workgroup folds the partials in order and writes the
+// workgroup, then one workgroup folds the partials in a fixed order and writes the
 // factor min(1, max_norm / ||g||) (1 when max_norm <= 0).
 __global__ void __launch_bounds__(256)
 k_sumsq(const float* __restrict__ g, long n, double* __restrict__ part) {
@@ -1040,12 +1087,20 @@ k_sumsq(const float* __restrict__ g, long n, double* __restrict__ part) {
     }
     if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
 }
-__global__ void k_clip_factor(const double* __restrict__ part, int nparts, float max_norm, float* __restrict__ factor,
-                              double* __restrict__ norm_out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+__global__ void __launch_bounds__(256)
+k_clip_factor(const double* __restrict__ part, int nparts, float max_norm, float* __restrict__ factor,
+              double* __restrict__ norm_out) {
+    __shared__ double sh[256];
     double s = 0.0;
-    for (int k = 0; k < nparts; ++k) s += part[k];
-    const double nrm = sqrt(s);
+    for (int k = threadIdx.x; k < nparts; k += 256) s += part[k];
+    sh[threadIdx.x] = s;
+    __syncthreads();
+    for (int o = 128; o > 0; o >>= 1) {
+        if (threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
+        __syncthreads();
+    }
+    if (threadIdx.x != 0) return;
+    const double nrm = sqrt(sh[0]);
     *norm_out = nrm;
     *factor = (max_norm > 0.0f && nrm > (double)max_norm) ? (float)((double)max_norm / nrm) : 1.0f;
 }
@@ -1068,12 +1123,12 @@ __global__ void k_adam(float* __restrict__ p, const float* __restrict__ g, float
 //   mode 0 (forward):  B_t[k = c][n = o]               = W[t][c][o]
 //   mode 1 (input gradient): B_t[k = o][n = c]         = W[26 - t][c][o]
 // For a 1-channel K (cin == 1 in mode 0, cout == 1 in mode 1) the taps are K.
-__global__ void k_pack(const float* __restrict__ W, int cin, int cout, int mode, bf16x8* __restrict__ out) {
+__device__ __forceinline__ void pack_one(const float* __restrict__ W, int cin, int cout, int mode, int q,
+                                         bf16x8* __restrict__ out) {
     const int kin = mode == 0 ? cin : cout, nout = mode == 0 ? cout : cin;
     const int NB = (nout + 15) / 16;
     const int ntap_blocks = kin == 1 ? 1 : 27;
     const int total = ntap_blocks * NB * 64;
-    const int q = blockIdx.x * 256 + threadIdx.x;
     if (q >= total) return;
     const int lane = q % 64, nb = (q / 64) % NB, tb = q / (64 * NB);
     const int n = 16 * nb + (lane & 15);
@@ -1095,6 +1150,22 @@ __global__ void k_pack(const float* __restrict__ W, int cin, int cout, int mode,
         r[e] = __builtin_bit_cast(__bf16, f2bf(val));
     }
     out[q] = r;
+}
+__global__ void k_pack(const float* __restrict__ W, int cin, int cout, int mode, bf16x8* __restrict__ out) {
+    pack_one(W, cin, cout, mode, blockIdx.x * 256 + threadIdx.x, out);
+}
+// Every layer of a network in both forms in one launch (blockIdx.y = 2 layer + mode).
+constexpr int kMaxLayers = 64;
+struct PackAll {
+    int layers;
+    bf16x8* out[2 * kMaxLayers];
+};
+__global__ void k_pack_all(const float* __restrict__ params, PackAll a) {
+    const int l = blockIdx.y >> 1, mode = blockIdx.y & 1;
+    const int cin = l == 0 ? 1 : 32, cout = l + 1 == a.layers ? 1 : 32;
+    // parameters: layer by layer, W[27][cin][cout] then b[cout]
+    const long off = l == 0 ? 0 : 27L * 32 + 32 + (l - 1) * (27L * 1024 + 32);
+    pack_one(params + off, cin, cout, mode, blockIdx.x * 256 + threadIdx.x, a.out[blockIdx.y]);
 }
 
 }  // namespace igs

@@ -335,6 +335,31 @@ def test_training_gradient_matches_oracle(dev):
         assert np.array_equal(gW[l], cW[l]) and np.array_equal(gb[l], cb[l]), l
 
 
+# one group of cubes; two (the activations of 16 cubes of 96^3 exceed a group's
+# limit); tiles in equal shares that begin inside a cube, and in chunks
+@pytest.mark.parametrize("shape,batch", [((96, 96, 96), 16), ((37, 20, 70), 4), ((3, 5, 6), 2), ((40, 64, 100), 8)])
+def test_training_batch_is_the_sum_of_its_cubes(dev, shape, batch):
+    """The loss and gradients of a batch against the FP64 mean of its cubes', each a
+    batch of its own.  A power-of-two batch scales every rounded value exactly,
+    so only the order of the FP32 sums differs: chains of up to a few thousand
+    terms, 1e-5 of the gradient's norm."""
+    import torch
+    from paper_1609_03782_amd import surrogate as sg
+    depth = 8
+    Ws, bs = _net(depth, seed=9)
+    net = sg.Surrogate(depth=depth, seed=2, lr=1e-12)
+    net.set_weights(sg.join_params([W.astype(np.float32) for W in Ws], [b.astype(np.float32) for b in bs]))
+    gen = torch.Generator(device=dev).manual_seed(3)
+    xs = [torch.randn(shape, generator=gen, device=dev) for _ in range(batch)]
+    ts = [x + 0.5 * torch.randn(shape, generator=gen, device=dev) for x in xs]
+    loss = net.train_step(xs, ts)
+    g = net.get_grads().astype(np.float64)
+    one = [(net.train_step([x], [t]), net.get_grads().astype(np.float64)) for x, t in zip(xs, ts)]
+    assert loss == pytest.approx(sum(v for v, _ in one) / batch, rel=1e-10)
+    ref = sum(v for _, v in one) / batch
+    assert np.linalg.norm(g - ref) <= 1e-5 * np.linalg.norm(ref)
+
+
 def test_training_lowers_the_loss(dev):
     import torch
     import paper_1609_03782_amd as ig
