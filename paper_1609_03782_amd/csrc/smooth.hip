@@ -614,18 +614,26 @@ k_dense(const float* __restrict__ src, float* __restrict__ dst, DenseGeom g) {
 }
 
 // Dense pass for a z half-width RZ known at compile time (1..8): a thread
-// computes YO (1 or 2) rows by 8 planes of outputs.  The loops run over (dy, dx)
-// outside and dz inside, so each input column of 8 + 2 RZ values is read from
-// LDS once into registers and serves the (2 RZ + 1) x 8 products of every
-// output row that meets it; the weights of a (dy, dx) column come from one LDS
-// read, a weight per lane, and go to scalar registers (v_readlane), so no
-// product waits for a weight.  Bound by the FMAs: 144 VALU operations of 164 per
-// (dy, dx) step at RZ = 4, YO = 2.  Two rows per thread halve the column reads
-// and the halo a tile stages.  At a face the divisor is the sum of the in-cube
-// weights, first over (dy, dx) per dz, then over dz.  567 taps, 360 x 350 x 290:
-// 1875 -> 1276 us (sigma rotated, FP32; loops over taps with the weight read from
-// LDS per product before).
+// computes YO (1 or 2) rows by 8 planes of outputs.  The loops run over dx, dy
+// and dz from the outside, so each input column of 8 + 2 RZ values is read from
+// LDS once into registers, a row ahead, and serves the (2 RZ + 1) x 8 products of
+// every output row that meets it; the weights of a (dy, dx) column come from one
+// LDS read, a weight per lane, and go to scalar registers (v_readlane), once for
+// both rows, so no product waits for a weight.  Bound by the FMAs: 144 VALU
+// operations of 162 per (dy, dx) step at RZ = 4, YO = 2.  Two rows per thread
+// halve the column reads and the halo a tile stages.  At a face the divisor is
+// the sum of the in-cube weights, of whole columns where only x or y is cut.  567
+// taps, 360 x 350 x 290: 1875 us (loops over taps with the weight read from LDS
+// per product) -> 1276 (columns) -> 1243 (no bank conflicts) -> 1186 (a row
+// ahead, weights shared by the rows).
 constexpr int dense_column(int rz) { return (8 + 2 * rz + 3) / 4 * 4; }   // floats of a staged column
+// the column's 16-byte chunk i, from its place: columns of 16 floats take their
+// chunks in another order with each fourth column x, else 16 lanes' chunks i
+// would fall into a quarter of the LDS banks
+template <int RZ>
+__device__ __forceinline__ int dense_chunk(int x, int i) {
+    return dense_column(RZ) == 16 ? (4 * i) ^ (x & 12) : 4 * i;
+}
 template <int RZ, int YO>
 __global__ void __launch_bounds__(256)
 k_dense_t(const float* __restrict__ src, float* __restrict__ dst, DenseGeom g) {
@@ -637,7 +645,8 @@ k_dense_t(const float* __restrict__ src, float* __restrict__ dst, DenseGeom g) {
     const int TXh = 64 + 2 * rx, TYh = TY + 2 * ry;
     const int cols = TXh * TYh;
     float* T = reinterpret_cast<float*>(sm4);   // [y][x][z]: a column's NC values together, ZS apart
-    float* W = T + cols * ZS;                   // [dy][dx][dz]
+    float* W = T + cols * ZS;                   // [dx][dy][dz], then 64 floats that a read of 64 may reach
+    float* S = W + nw + 64;                     // [dx][dy]: the sums over dz
     __shared__ float total_sh;
     const int tx = threadIdx.x, ty = threadIdx.y, tid = ty * 64 + tx;
     const long x0 = (long)blockIdx.x * 64, y0 = (long)blockIdx.y * TY, z0 = (long)blockIdx.z * TZ;
@@ -649,7 +658,7 @@ k_dense_t(const float* __restrict__ src, float* __restrict__ dst, DenseGeom g) {
         const double R10 = sz * cy, R11 = sz * sy * sx + cz * cx, R12 = sz * sy * cx - cz * sx;
         const double R20 = -sy, R21 = cy * sx, R22 = cy * cx;
         for (int t = tid; t < nw; t += 256) {
-            const int iz = t % KZ, ix = (t / KZ) % kx, iy = t / (KZ * kx);
+            const int iz = t % KZ, iy = (t / KZ) % ky, ix = t / (KZ * ky);
             const double dx = ix - rx, dy = iy - ry, dz = iz - RZ;
             const double u0 = R00 * dx + R10 * dy + R20 * dz;
             const double u1 = R01 * dx + R11 * dy + R21 * dz;
@@ -662,7 +671,8 @@ k_dense_t(const float* __restrict__ src, float* __restrict__ dst, DenseGeom g) {
     // input tile with halo (zeros outside the cube), a column along z at a time:
     // NC loads in flight, then 16-byte LDS writes
     for (int q = tid; q < cols; q += 256) {
-        const long x = x0 - rx + q % TXh, y = y0 - ry + q / TXh;
+        const int qx = q % TXh;
+        const long x = x0 - rx + qx, y = y0 - ry + q / TXh;
         const bool in = x >= 0 && x < g.nx && y >= 0 && y < g.ny;
         const float* p = src + (in ? x + g.nx * y : 0);
         float v[ZS];
@@ -676,17 +686,25 @@ k_dense_t(const float* __restrict__ src, float* __restrict__ dst, DenseGeom g) {
         }
 #pragma unroll
         for (int i = 0; i < ZS / 4; ++i)
-            *reinterpret_cast<float4*>(T + q * ZS + 4 * i) = make_float4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
+            *reinterpret_cast<float4*>(T + q * ZS + dense_chunk<RZ>(qx, i)) = make_float4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
     }
     __syncthreads();
-    if (tid < 64) {   // total weight, fixed order (strided partials over [dz][dy][dx], then a tree)
+    // the total weight, in a fixed order (strided partials, then a tree), and, for
+    // tiles at a face, the sums over dz
+    if (tid < 64) {
         float s = 0.0f;
-        for (int t = tid; t < nw; t += 64) s += W[(t % (kx * ky)) * KZ + t / (kx * ky)];
+        for (int t = tid; t < kx * ky; t += 64) {
+            float sz = 0.0f;
+            for (int k = 0; k < KZ; ++k) sz += W[t * KZ + k];
+            S[t] = sz;
+            s += sz;
+        }
         for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
         if (tid == 0) total_sh = s;
     }
-    const bool edge = x0 - rx < 0 || x0 + 63 + rx >= g.nx || y0 - ry < 0 || y0 + TY - 1 + ry >= g.ny ||
-                      z0 - RZ < 0 || z0 + TZ - 1 + RZ >= g.nz;
+    const bool edge_xy = x0 - rx < 0 || x0 + 63 + rx >= g.nx || y0 - ry < 0 || y0 + TY - 1 + ry >= g.ny;
+    const bool edge_z = z0 - RZ < 0 || z0 + TZ - 1 + RZ >= g.nz;
+    if (edge_xy) __syncthreads();   // S is read below (the same for the whole workgroup)
     float acc[YO][TZ], sw[YO][KZ];
 #pragma unroll
     for (int o = 0; o < YO; ++o) {
@@ -695,46 +713,85 @@ k_dense_t(const float* __restrict__ src, float* __restrict__ dst, DenseGeom g) {
 #pragma unroll
         for (int k = 0; k < KZ; ++k) sw[o][k] = 0.0f;
     }
-    // input row dyp of the thread's first output row: output row o meets it at dy = dyp - o
+    // Input row dyp of the thread's first output row: output row o meets it at dy =
+    // dyp - o, so the second row's weights are the first's of the row before.
+    // Columns are read one row ahead of their products.  EDGE 1 (a face in x or y):
+    // sw[o][0] sums the in-cube weights of whole columns; EDGE 2 (in z): per dz.
     auto sweep = [&](auto edge_c) {
-        for (int dyp = -ry; dyp <= ry + YO - 1; ++dyp) {
-            const long yy = y0 + YO * ty + dyp;
-            const bool in_y = yy >= 0 && yy < g.ny;
-            const float* row = T + ((YO * ty + ry + dyp) * TXh + tx + rx) * ZS;
-            auto line = [&](auto m) {                      // m: bit o set if output row o meets this input row
-                for (int dx = -rx; dx <= rx; ++dx) {
-                    float c[ZS], wl[YO];
+        constexpr int EDGE = decltype(edge_c)::value;
+        for (int dx = -rx; dx <= rx; ++dx) {
+            const int xq = tx + rx + dx;
+            const float* col[ZS / 4];
 #pragma unroll
-                    for (int o = 0; o < YO; ++o)
-                        wl[o] = (decltype(m)::value >> o) & 1
-                                    ? W[min(((dyp - o + ry) * kx + dx + rx) * KZ + (tid & 63), nw - 1)] : 0.0f;
+            for (int i = 0; i < ZS / 4; ++i) col[i] = T + (YO * ty * TXh + xq) * ZS + dense_chunk<RZ>(xq, i);
+            const float* wp = W + (dx + rx) * ky * KZ + (tid & 63);
+            const float* sp = S + (dx + rx) * ky;
+            const bool in_x = x0 + tx + dx >= 0 && x0 + tx + dx < g.nx;
+            float ca[ZS], cb[ZS], wn, wa[KZ], wb[KZ], sa = 0.0f, sb = 0.0f;
+            int yy = (int)(y0 + YO * ty) - ry;
+            auto fetch = [&](float (&c)[ZS]) {               // the next row of the column
 #pragma unroll
-                    for (int i = 0; i < ZS / 4; ++i) {
-                        const float4 f = *reinterpret_cast<const float4*>(row + dx * ZS + 4 * i);
-                        c[4 * i] = f.x; c[4 * i + 1] = f.y; c[4 * i + 2] = f.z; c[4 * i + 3] = f.w;
-                    }
-                    const long xx = x0 + tx + dx;
-                    const float in = in_y && xx >= 0 && xx < g.nx ? 1.0f : 0.0f;
-#pragma unroll
-                    for (int o = 0; o < YO; ++o)
-                        if ((decltype(m)::value >> o) & 1)
-#pragma unroll
-                            for (int k = 0; k < KZ; ++k) {
-                                const float wv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wl[o]), k));
-#pragma unroll
-                                for (int j = 0; j < TZ; ++j) acc[o][j] = __builtin_fmaf(wv, c[j + k], acc[o][j]);
-                                if constexpr (decltype(edge_c)::value) sw[o][k] = __builtin_fmaf(wv, in, sw[o][k]);
-                            }
+                for (int i = 0; i < ZS / 4; ++i) {
+                    const float4 f = *reinterpret_cast<const float4*>(col[i]);
+                    c[4 * i] = f.x; c[4 * i + 1] = f.y; c[4 * i + 2] = f.z; c[4 * i + 3] = f.w;
+                    col[i] += TXh * ZS;
                 }
             };
-            if constexpr (YO == 1) line(std::integral_constant<int, 1>{});
-            else if (dyp == -ry) line(std::integral_constant<int, 1>{});
-            else if (dyp == ry + 1) line(std::integral_constant<int, 2>{});
-            else line(std::integral_constant<int, 3>{});
+            // bit o of M: output row o meets this input row; NEXT: there is another
+            auto row = [&](auto mc, auto nextc, const float (&c)[ZS], float (&cn)[ZS]) {
+                constexpr int M = decltype(mc)::value;
+                if constexpr (M & 1) {
+#pragma unroll
+                    for (int k = 0; k < KZ; ++k) wa[k] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wn), k));
+                    wp += KZ;
+                    wn = *wp;                                // (past the last row: the 64 floats)
+                    if constexpr (EDGE == 1) sa = *sp++;
+                }
+                if constexpr (decltype(nextc)::value) fetch(cn);
+                const bool in = in_x && yy >= 0 && yy < (int)g.ny;
+                ++yy;
+#pragma unroll
+                for (int o = 0; o < YO; ++o)
+                    if ((M >> o) & 1) {
+#pragma unroll
+                        for (int k = 0; k < KZ; ++k) {
+                            const float wv = o == 0 ? wa[k] : wb[k];
+#pragma unroll
+                            for (int j = 0; j < TZ; ++j) acc[o][j] = __builtin_fmaf(wv, c[j + k], acc[o][j]);
+                            if constexpr (EDGE == 2) sw[o][k] += in ? wv : 0.0f;
+                        }
+                        if constexpr (EDGE == 1) sw[o][0] += in ? (o == 0 ? sa : sb) : 0.0f;
+                    }
+#pragma unroll
+                for (int k = 0; k < KZ; ++k) wb[k] = wa[k];
+                sb = sa;
+            };
+            constexpr std::integral_constant<int, 1> first{};
+            constexpr std::integral_constant<int, YO == 2 ? 3 : 1> both{};
+            constexpr std::integral_constant<int, 2> last{};
+            constexpr std::true_type more{};
+            constexpr std::false_type none{};
+            wn = *wp;
+            fetch(ca);
+            if constexpr (YO == 2) {
+                row(first, more, ca, cb);
+                for (int p = 0; p < ry; ++p) {
+                    row(both, more, cb, ca);
+                    row(both, more, ca, cb);
+                }
+                row(last, none, cb, ca);
+            } else {
+                for (int p = 0; p < ry; ++p) {
+                    row(both, more, ca, cb);
+                    row(both, more, cb, ca);
+                }
+                row(both, none, ca, cb);
+            }
         }
     };
-    if (edge) sweep(std::true_type{});
-    else sweep(std::false_type{});
+    if (edge_z) sweep(std::integral_constant<int, 2>{});
+    else if (edge_xy) sweep(std::integral_constant<int, 1>{});
+    else sweep(std::integral_constant<int, 0>{});
     __syncthreads();
     const float total = total_sh;
     const long x = x0 + tx;
@@ -746,8 +803,8 @@ k_dense_t(const float* __restrict__ src, float* __restrict__ dst, DenseGeom g) {
 #pragma unroll
         for (int j = 0; j < TZ; ++j) {
             const long z = z0 + j;
-            float d = total;
-            if (edge) {
+            float d = edge_xy ? sw[o][0] : total;
+            if (edge_z) {
                 d = 0.0f;
 #pragma unroll
                 for (int k = 0; k < KZ; ++k) d += z + k - RZ >= 0 && z + k - RZ < g.nz ? sw[o][k] : 0.0f;
@@ -903,7 +960,7 @@ hipError_t launch_dense(const SmoothPlan& p, int tz, const float* in, float* out
         // the column kernel where its tile fits, with two rows per thread while
         // two workgroups' tiles share a compute unit
         auto need = [&](int r) {
-            return ((size_t)(2 * g.rx + 1) * (2 * g.ry + 1) * (2 * g.rz + 1) +
+            return ((size_t)(2 * g.rx + 1) * (2 * g.ry + 1) * (2 * g.rz + 2) + 64 +
                     (size_t)(64 + 2 * g.rx) * (r + 2 * g.ry) * dense_column(g.rz)) * sizeof(float);
         };
         if (2 * (need(8) + 256) <= kMaxLds && g.ny > 4) {
