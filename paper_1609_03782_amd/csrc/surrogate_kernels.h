@@ -596,8 +596,10 @@ k_conv_out1(const u16* __restrict__ in, const bf16x8* __restrict__ wp, const flo
         vin[k] = g < kO1Groups && q < kO1Vox && qx >= 0 && qx < nx && qy >= 0 && qy < ny;
         voff[k] = vin[k] ? ((long)qy * nx + qx) * 32 + 8 * kg : 0;
     }
-    uint4 b[GPW];
-    auto fetch = [&](int u) {
+    // a plane's fragments are loaded two steps ahead, the residual's input one (a
+    // step is shorter than a load under way: 360 x 360 x 150 421 -> 322 us, 3.9 TB/s)
+    uint4 b0[GPW], b1[GPW];
+    auto fetch = [&](int u, uint4 (&b)[GPW]) {
 #pragma unroll
         for (int k = 0; k < GPW; ++k)
             b[k] = (vin[k] && u >= 0 && u < nz) ? *reinterpret_cast<const uint4*>(in + u * plane * 32 + voff[k])
@@ -611,8 +613,8 @@ k_conv_out1(const u16* __restrict__ in, const bf16x8* __restrict__ wp, const flo
     const bool store = owner && x < nx && y < ny;
     float a_prev = 0.f, a_cur = 0.f;   // sums of outputs z = u - 1 and z = u
 
-    fetch(z0 - 1);
-    for (int u = z0 - 1; u <= z1; ++u) {
+    float ax = 0.f;
+    auto step = [&](int u, uint4 (&b)[GPW]) {
         float* P = o1_smem + (u & 1) * 27 * kO1Stride;
 #pragma unroll
         for (int k = 0; k < GPW; ++k) {
@@ -630,9 +632,11 @@ k_conv_out1(const u16* __restrict__ in, const bf16x8* __restrict__ wp, const flo
                 }
             }
         }
-        if (u < z1) fetch(u + 1);
+        if (u + 1 < z1) fetch(u + 2, b);
         __syncthreads();
         if (owner) {
+            const float res = ax;
+            if (EPI == EPI_RESID && store && u < z1) ax = aux[(long)max(u, 0) * plane + (long)y * nx + x];
             const float* c = P + oy * LX + ox;
             float a_next = c[0];
 #pragma unroll
@@ -645,7 +649,7 @@ k_conv_out1(const u16* __restrict__ in, const bf16x8* __restrict__ wp, const flo
             if (store && zo >= z0) {
                 const long v = (long)zo * plane + (long)y * nx + x;
                 if constexpr (EPI == EPI_RESID) {
-                    out[v] = aux[v] + (a_prev + bias[0]);
+                    out[v] = res + (a_prev + bias[0]);
                 } else {
                     float4 r0, r1, r2, r3;
                     r0.x = a_prev + (bias ? bias[0] : 0.0f);
@@ -660,6 +664,12 @@ k_conv_out1(const u16* __restrict__ in, const bf16x8* __restrict__ wp, const flo
             a_prev = a_cur;
             a_cur = a_next;
         }
+    };
+    fetch(z0 - 1, b0);
+    fetch(z0, b1);
+    for (int u = z0 - 1; u <= z1; u += 2) {
+        step(u, b0);
+        if (u + 1 <= z1) step(u + 1, b1);
     }
 }
 
