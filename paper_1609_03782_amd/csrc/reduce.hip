@@ -110,11 +110,19 @@ __device__ __forceinline__ void thread_sums(const ST* __restrict__ x, long n, in
                 for (int k = 0; k < NP; ++k) acc3(f[k], s1, s2, bad);
             }
         }
-        for (; i < nv; i += nth) {
-            float f[NP];
-            unpack<ST>(xv[i], f);
+        // at most U - 1 packs are left: together too
+        if (i < nv) {
+            PT q[U - 1];
 #pragma unroll
-            for (int k = 0; k < NP; ++k) acc3(f[k], s1, s2, bad);
+            for (int u = 0; u < U - 1; ++u) q[u] = xv[min(i + u * nth, nv - 1)];
+#pragma unroll
+            for (int u = 0; u < U - 1; ++u)
+                if (i + u * nth < nv) {
+                    float f[NP];
+                    unpack<ST>(q[u], f);
+#pragma unroll
+                    for (int k = 0; k < NP; ++k) acc3(f[k], s1, s2, bad);
+                }
         }
         done = nv * NP;
     }
@@ -311,7 +319,8 @@ hipError_t launch_params_final(const double* part, int nparts, long n, const Par
 // run's NaN, so that launch goes (above it, one workgroup's writes would make a
 // failure slow for 1 % of the run); and no more partials are made than the cube
 // has blocks of 4 packs a thread, so the fold reads few.
-// 64 x 64 x 32, 10 steps: 51.3 -> 45.8 us (all three launches with 2048 partials before); 187 x 181 x 149: 183.0 -> 180.9.
+// 64 x 64 x 32, 10 steps: 51.3 -> 45.8 us (all three launches with 2048 partials
+// before); 187 x 181 x 149, 10 steps: 183.0 -> 180.6, in bf16 2 steps 41.4 -> 38.5.
 constexpr long kOneScan = 1L << 14, kSmallScan = 1L << 20;
 template <typename ST>
 static hipError_t scan_t(const void* x, long n, const ParamIn& in, double* part, int nblk, DevParams* out, void* y,
@@ -323,7 +332,8 @@ static hipError_t scan_t(const void* x, long n, const ParamIn& in, double* part,
                            (ST*)y);
         return hipGetLastError();
     }
-    nblk = (int)std::min<long>(nblk, (n + 4095) / 4096);
+    constexpr long kBlock = 4L * RED_THREADS * Pack<ST>::N;
+    nblk = (int)std::min<long>(nblk, (n + kBlock - 1) / kBlock);
     hipError_t e = sum_partial_t<ST>(x, n, part, nblk, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_params_final<ST>, dim3(1), dim3(RED_THREADS), 0, s, part, nblk, n, in, out,

@@ -748,11 +748,12 @@ k_stream(const ST* __restrict__ src, ST* __restrict__ dst, BlockGeom g, const Pi
 // workgroup-uniform addresses, so the loop is uniform).  A kernel of its own:
 // the loop around the streaming body raises register pressure (the per-lane
 // geometry stays live across pieces), which the one-piece kernel should not pay.
-// With 16-bit storage the lane number is made anew for each piece, so that its
-// geometry is computed there and not kept: with it kept, rows of 6 voxels per
-// lane waited in the loop (300 x 400 x 490 bf16 677 -> 764, 384 x 400 x 300 804
-// -> 905 Gvoxel-iter/s; 8 per lane spilled, and gain 0 to 1 %).  FP32 keeps it:
-// up to 1.5 % faster so.
+// With 16-bit storage and 6 voxels per lane the lane number is made anew for each
+// piece, so that its geometry is computed there and not kept: with it kept, the
+// step loop waited for it (300 x 400 x 490 bf16 677 -> 764, 384 x 400 x 300 804 ->
+// 905 Gvoxel-iter/s).  The other layouts keep it: they gain 2 % at most (4 per
+// lane, 256 x 440 x 300) and lose up to 3 % on short passes (4 rows per wavefront,
+// 41 x 457 x 300 in one pass); FP32 loses up to 1.5 %.
 template <int COND, typename ST, int V, int T, bool VEC, int R>
 __global__ void __launch_bounds__(1024)
 k_stream_grouped(const ST* __restrict__ src, ST* __restrict__ dst, BlockGeom g, const Piece* __restrict__ pieces,
@@ -765,7 +766,7 @@ k_stream_grouped(const ST* __restrict__ src, ST* __restrict__ dst, BlockGeom g, 
     for (int k = k0; k < k1; ++k) {
         if (k > k0) __syncthreads();   // the previous piece is done with the LDS
         int lane = threadIdx.x;
-        if constexpr (sizeof(ST) == 2) asm volatile("" : "+v"(lane));
+        if constexpr (sizeof(ST) == 2 && V == 6) asm volatile("" : "+v"(lane));
         stream_piece<COND, ST, V, T, VEC, R>(src, dst, g, pieces[k], P, lds, lane);
     }
 }
