@@ -89,7 +89,10 @@ ig_status ig_surrogate_last_grad_norm(const ig_surrogate* s, double* norm);
 
 /* One Adam step on the mean squared error over `batch` cubes of one shape:
  * d_x[k], d_t[k] are device FP32 cubes (input, target).  loss (nullable)
- * receives the mean squared error before the step (the call then waits). */
+ * receives the mean squared error before the step (the call then waits).  The
+ * cubes go through the layers in groups; the handle keeps the activations of
+ * one (128 depth + 8 bytes per voxel, as many cubes as fit 8 GiB and at least
+ * one; fewer where they cannot be allocated). */
 ig_status ig_surrogate_train_step(ig_surrogate* s, const float* const* d_x, const float* const* d_t, int32_t batch,
                                   int64_t nx, int64_t ny, int64_t nz, void* hip_stream, double* loss);
 

@@ -453,7 +453,8 @@ k_conv_zs(const u16* __restrict__ in0, const bf16x8* __restrict__ wp, const floa
         for (int z = z0 + 1; z < z1 - 1; ++z) step(D0, D2, z);
         if (z1 - 1 > z0) step(D1, D2, z1 - 1);
         step(D2, D2, z1);
-        static_for<NV>(epi);    }
+        static_for<NV>(epi);
+    }
 }
 
 // The convolution of a 1-channel input as a z-stream (the network's first
