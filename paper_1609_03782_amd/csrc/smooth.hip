@@ -959,15 +959,36 @@ hipError_t launch_dense(const SmoothPlan& p, int tz, const float* in, float* out
     if (tz == 8 && g.rz >= 1 && g.rz <= 8) {
         // the column kernel where its tile fits, with two rows per thread while
         // two workgroups' tiles share a compute unit
+        const long kx = 2 * g.rx + 1, ky = 2 * g.ry + 1, kz = 2 * g.rz + 1;
         auto need = [&](int r) {
-            return ((size_t)(2 * g.rx + 1) * (2 * g.ry + 1) * (2 * g.rz + 2) + 64 +
+            return ((size_t)kx * ky * (kz + 1) + 64 +
                     (size_t)(64 + 2 * g.rx) * (r + 2 * g.ry) * dense_column(g.rz)) * sizeof(float);
         };
-        if (2 * (need(8) + 256) <= kMaxLds && g.ny > 4) {
+        // Two rows take fewer operations a row, but half as many workgroups and a
+        // larger tile.  Where those workgroups leave the last turn of the GPU nearly
+        // empty, one row is faster: the turns times a workgroup's vector operations
+        // (products, what goes with a column, staging at 250 a column, weights)
+        // predict that (216 random cubes and angles: 1.04x in the mean, none slower
+        // beyond noise).  And where twice as many of the one-row tiles fit a compute
+        // unit (4, the registers' limit, against 2): half-widths 3, 2, 3 on 400 x 300 x
+        // 200 459 -> 423 us, on 840 x 274 x 102 445 -> 429; 4, 2, 4 606 -> 583; with 3
+        // against 2 (3, 3, 3 on 634 x 98 x 314) two rows are faster, 431 against 445.
+        int dev = 0, ncu = 256;
+        if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+        auto cost = [&](int yo) {
+            const long r = 4 * yo, wgs = ((g.nx + 63) / 64) * ((g.ny + r - 1) / r) * ((g.nz + 7) / 8);
+            const long work = kx * (yo * ky * 8 * kz + (ky + yo - 1) * (kz + 9)) +
+                              250 * (((64 + 2 * g.rx) * (r + 2 * g.ry) + 255) / 256) + 200 * ((kx * ky * kz + 255) / 256) + 300;
+            return (double)((wgs + ncu - 1) / ncu) * work;
+        };
+        const bool two = 2 * (need(8) + 256) <= kMaxLds && g.ny > 4;
+        const bool one = need(4) + 256 <= kMaxLds;
+        auto resident = [&](int r) { return std::min<size_t>(4, kMaxLds / (need(r) + 256)); };
+        if (two && !(one && (cost(1) < 0.95 * cost(2) || resident(4) >= 2 * resident(8)))) {
             rows = 8;
             k = dense_t_kernel<2>(g.rz);
             lds = need(8);
-        } else if (need(4) + 256 <= kMaxLds) {
+        } else if (one) {
             k = dense_t_kernel<1>(g.rz);
             lds = need(4);
         }
