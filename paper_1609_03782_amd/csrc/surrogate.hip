@@ -39,11 +39,13 @@ extern "C" int64_t ig_debug_set_infer_piece_limit(int64_t voxels) {
 
 namespace {
 
-// Workgroups of the weight-gradient kernels (at most): one per compute unit of
-// the 32-channel kernel (108 KB of LDS each), two of the 1-channel one.  Fixed,
-// so a gradient does not depend on the device it was computed on.
+// Runs that a cube's units are cut into for its weight gradients (at most).  They
+// set the order of the sums, so the number is fixed.
+constexpr long kWgradGroups = 512;
+// Partials of a launch: half of what the last-level cache holds, so that the fold
+// finds them there (four 96^3 cubes at once 221 + 47 us a layer, two by two 2 x 106 + 2 x 20)
+constexpr long kWgradPartBytes = 128L << 20;
 constexpr long kTrainBytes = 8L << 30;   // activations of a group of training cubes
-constexpr long kWgradGroups32 = 256, kWgradGroups1 = 512;
 
 struct Dev {
     void* p = nullptr;
@@ -66,20 +68,20 @@ struct Dev {
     template <typename T> T* as() const { return static_cast<T*>(p); }
 };
 
-// Weight-gradient partials: workgroups and floats of one (weights, then biases).
+// Weight-gradient partials: runs of a cube and floats of one (weights, then biases).
 struct WgradPlan {
     int ntx, nty;
-    long groups, stride, lenw, len;
+    long groups, lenw, len;
+    long bytes() const { return groups * len * (long)sizeof(float); }            // of a cube
+    long cubes() const { return std::max(1L, kWgradPartBytes / bytes()); }       // of a launch
 };
-WgradPlan wgrad_plan(int cin, int cout, long nx, long ny, long nz, long cubes) {
+WgradPlan wgrad_plan(int cin, int cout, long nx, long ny, long nz) {
     WgradPlan w;
     w.ntx = (int)((nx + kWgX - 1) / kWgX);
     w.nty = (int)((ny + kWgY - 1) / kWgY);
-    const bool both = cin == 32 && cout == 32;
-    w.groups = std::min(both ? kWgradGroups32 : kWgradGroups1, (long)w.ntx * w.nty * nz * cubes);
+    w.groups = std::min(kWgradGroups, (long)w.ntx * w.nty * nz);
     w.lenw = 27L * cin * cout;
     w.len = w.lenw + cout;
-    w.stride = both ? w.len : 28L * std::max(cin, cout);
     return w;
 }
 
@@ -91,14 +93,17 @@ struct ZsGrid {
     int ntx, nty, zch;
     long groups, cost;
 };
+int compute_units() {
+    int ncu = 256, dev = 0;
+    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+    return ncu;
+}
 ZsGrid zs_grid(long nx, long ny, long nz, int xw, long cubes, int per_cu, int* ncu_out = nullptr) {
     ZsGrid g;
     g.ntx = (int)((nx + xw - 1) / xw);
     g.nty = (int)((ny + kZsRows - 1) / kZsRows);
     const long tiles = (long)g.ntx * g.nty * cubes;
-    int ncu = 256;
-    int dev = 0;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+    const int ncu = compute_units();
     if (ncu_out) *ncu_out = ncu;
     const long slots = (long)ncu * per_cu;
     long best_cost = -1, zch = nz;
@@ -209,33 +214,38 @@ size_t packed_count(int cin, int cout, int mode) {
 }
 
 // weight gradient of a conv with cin (1 or 32) inputs and cout (1 or 32)
-// outputs: per-workgroup partials, then a fixed-order fold into dW [27][cin][cout]
-// and db [cout]
+// outputs over `cubes` cubes laid one after another: a partial per run, then a
+// fixed-order fold into dW [27][cin][cout] and db [cout], as many cubes at a time as
+// keep their partials below kWgradPartBytes (and at least one)
 hipError_t launch_wgrad(int cin, int cout, const void* a, const void* dz, Dev& part, float* dW, float* db,
                         int accumulate, long nx, long ny, long nz, long cubes, hipStream_t s) {
-    const WgradPlan w = wgrad_plan(cin, cout, nx, ny, nz, cubes);
-    hipError_t e = part.ensure((size_t)w.groups * w.stride * sizeof(float));
+    const WgradPlan w = wgrad_plan(cin, cout, nx, ny, nz);
+    const long most = std::min(cubes, w.cubes());
+    hipError_t e = part.ensure((size_t)w.bytes() * most);
     if (e != hipSuccess) return e;
-    const u16* A = static_cast<const u16*>(a);
-    const u16* D = static_cast<const u16*>(dz);
-    const dim3 g((unsigned)w.groups), b(kWgThreads);
-    const int x = (int)nx, y = (int)ny, z = (int)nz;
-    if (cin == 32 && cout == 32) {
-        e = hipFuncSetAttribute((const void*)k_wgrad32, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kWgLds);
+    auto kern = cin == 32 ? (cout == 32 ? k_wgrad32<2> : k_wgrad32<1>) : (cout == 32 ? k_wgrad1<2> : k_wgrad1<1>);
+    const int nb = cout == 32 ? 2 : 1;
+    const size_t lds = cin == 32 ? wg_lds(nb) : 0;
+    if (lds > 65536) {
+        e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_wgrad32, g, b, kWgLds, s, A, D, part.as<float>(), x, y, z, w.ntx, w.nty, (int)cubes);
-    } else if (cin == 32) {
-        hipLaunchKernelGGL(k_wgrad1<32>, g, b, 0, s, A, D, 1, part.as<float>(), x, y, z, w.ntx, w.nty, (int)cubes);
-    } else if (cout == 32) {
-        hipLaunchKernelGGL(k_wgrad1<32>, g, b, 0, s, D, A, 0, part.as<float>(), x, y, z, w.ntx, w.nty, (int)cubes);
-    } else {
-        hipLaunchKernelGGL(k_wgrad1<1>, g, b, 0, s, D, A, 0, part.as<float>(), x, y, z, w.ntx, w.nty, (int)cubes);
     }
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_wgrad_fold, dim3((unsigned)((w.len + 63) / 64)), dim3(1024), 0, s, part.as<float>(), w.groups,
-                       w.stride, w.lenw, w.len, dW, db, accumulate);
-    return hipGetLastError();
+    const long n = nx * ny * nz;
+    for (long c = 0; c < cubes; c += most) {
+        // k_wgrad32: a workgroup per compute unit takes its share of the runs in turn
+        const long m = std::min(most, cubes - c), runs = w.groups * m;
+        const long blocks = cin == 32 ? std::min<long>(runs, compute_units()) : runs;
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(cin == 32 ? wg_threads(nb) : kWg1Threads), lds, s,
+                           static_cast<const u16*>(a) + c * n * cin, static_cast<const u16*>(dz) + c * n * cout,
+                           part.as<float>(), (int)nx, (int)ny, (int)nz, w.ntx, w.nty, (int)w.groups, (int)runs);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_wgrad_fold, dim3((unsigned)((w.len + 63) / 64)), dim3(1024), 0, s, part.as<float>(),
+                           w.groups, (int)m, w.lenw, w.len, dW, db, accumulate || c > 0);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 __global__ void k_fill(float* __restrict__ p, long n, float v) {
@@ -339,7 +349,7 @@ void release_acts(ig_surrogate* s) {
     s->cap = 0;
     for (Dev& d : s->act) d.release();
     for (Dev& d : s->pre) d.release();
-    for (Dev* d : {&s->y, &s->dy, &s->dzA, &s->dzB}) d->release();
+    for (Dev* d : {&s->y, &s->dy, &s->dzA, &s->dzB, &s->part}) d->release();
 }
 
 ig_status to_bf16(const float* x, void* a, long n, hipStream_t st);
@@ -501,24 +511,23 @@ extern "C" ig_status ig_surrogate_train_step(ig_surrogate* s, const float* const
     }
     // The cubes go through the layers in groups, a launch per layer and group: one
     // cube of 96^3 gives each compute unit 14 planes, too few for the kernels'
-    // set-up, and every launch of a weight gradient writes and folds a partial per
-    // workgroup.  Four 96^3 cubes: 4822 -> 4148 us with the shares above (weight
-    // gradient of a layer 4 x 59 -> 213 us, its folds 4 x 6.3 -> 6.5).
-    // A group's activations stay below kTrainBytes (more than one cube only); a
-    // group that cannot be allocated is halved.
+    // set-up.  What a group keeps stays below kTrainBytes (more than one cube only);
+    // a group that cannot be allocated is halved.  No sum depends on the group.
+    const WgradPlan wide = wgrad_plan(32, 32, nx, ny, nz);   // the largest layer's partials
     const long per_cube = n * (128L * s->L + 8);
     int group = (int)std::max<long>(1, std::min<long>(batch, kTrainBytes / per_cube));
-    ig_status rc = ensure_acts(s, n * group);
-    while (rc != IG_OK && group > 1) {
+    ig_status rc;
+    for (;; group /= 2) {
+        rc = ensure_acts(s, n * group);
+        if (rc == IG_OK) {
+            const hipError_t e = s->part.ensure((size_t)wide.bytes() * std::min<long>(group, wide.cubes()));
+            if (e == hipSuccess) break;
+            rc = fail(e == hipErrorOutOfMemory ? IG_ERR_OUT_OF_MEMORY : IG_ERR_DEVICE, "weight-gradient partials: %s",
+                      hipGetErrorString(e));
+        }
+        if (group == 1) return rc;
         (void)hipGetLastError();
         release_acts(s);
-        group /= 2;
-        rc = ensure_acts(s, n * group);
-    }
-    if (rc != IG_OK) return rc;
-    for (int l = 0; l < s->L; ++l) {   // weight-gradient partials for the largest layer, sized before any launch
-        const WgradPlan w = wgrad_plan(s->cin[l], s->cout[l], nx, ny, nz, group);
-        HIP_TRY(s->part.ensure((size_t)w.groups * w.stride * sizeof(float)));
     }
     const long np = (long)s->nparam;
     hipLaunchKernelGGL(k_fill, dim3((np + 255) / 256), dim3(256), 0, st, s->grads.as<float>(), np, 0.0f);

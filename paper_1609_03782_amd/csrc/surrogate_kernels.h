@@ -732,373 +732,441 @@ k_conv_out1(const u16* __restrict__ in, const bf16x8* __restrict__ wp, const flo
 // of voxel l / 4, channels 4 (l % 4) .., and receives channel l of the four
 // voxels, so two reads make one operand fragment at the full LDS rate.
 //
-// Work: the cube is cut into tiles of 32 x 8 voxels and the sequence (tile,
-// plane) is dealt to the workgroups in equal contiguous runs, the same for
-// every call; a workgroup streams the planes of its runs with its sums in
-// registers throughout, and writes one partial.  The partials are folded in
-// a fixed order, so the gradient is bitwise reproducible.
+// The order of the FP32 sums is fixed by the cube's shape alone: a cube's units
+// (32 x 4 voxels of one plane, u = (z nty + ty) ntx + tx) are cut into `groups`
+// contiguous runs, the same for every call; a run's sums go through its units
+// and their four rows in order, one product of 32 voxels per row, and its bias
+// sums voxel by voxel; the runs of a cube are folded in quarters and the cubes of
+// a batch added one after another (k_wgrad_fold).  So a gradient depends neither
+// on how many cubes share a launch nor on the device's memory, and weights
+// trained with it stay the same to the last bit from one version to the next.
 typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
-constexpr int kWgX = 32, kWgY = 8;                          // tile
-constexpr int kWgThreads = 512;
+constexpr int kWgX = 32, kWgY = 4;                          // a unit
+constexpr int kWgAhead = 2;                                 // activation fragments in flight ahead of their products
 constexpr int kWgLX = kWgX + 2, kWgLY = kWgY + 2;           // with the margin
 constexpr int kWgPlA = kWgLX * kWgLY * 32, kWgPlB = kWgX * kWgY * 32;   // u16 of a staged plane
-constexpr size_t kWgLds = (size_t)4 * 27 * 64 * 16;         // the final exchange; the four staged planes fit in it
-static_assert(kWgLds >= (size_t)2 * (kWgPlA + kWgPlB) * 2, "staging fits the exchange buffer");
 
-// the fragment [voxels 8 kg ..][channel l % 16] at p = (voxel 8 kg + (l % 16) / 4,
-// channels 4 (l % 4) ..) of rows of 32 channels
-__device__ __forceinline__ bf16x8 tr_frag(const u16* p) {
-    typedef __attribute__((address_space(3))) s16x4* lp;
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(p));
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(p + 4 * 32));
-    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+// the fragment [voxels 8 kg ..][channel l % 16]: lo = (voxel 8 kg + (l % 16) / 4,
+// channels 4 (l % 4) ..) of rows of 32 channels, hi the same four voxels on
+__device__ __forceinline__ bf16x8 tr_frag(const u16* lo, const u16* hi) {
+    const s16x4 l = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(lo));
+    const s16x4 h = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(hi));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(l, h, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+// A staged voxel x of a row keeps its two halves of 16 channels in turn where bit 3
+// of x is set, so that the 32 lanes of one LDS pass, which read 16 channels of
+// voxels x and x + 8, meet no bank twice.
+__device__ __forceinline__ int wg_half(int x, int half) { return x * 32 + ((half ^ (x >> 3)) & 1) * 16; }
+
+// The gradient of a unit: NB = 2, 32 channels a voxel; NB = 1, one channel, a voxel per
+// dword.  This lane's place in a row's fragment of channels 16 nb .., and that of row r
+// at S = the gradient + the place
+template <int NB>
+__device__ __forceinline__ int wg_grad_lane(int lane, int nb) {
+    const int i = lane & 15, kg = lane >> 4;
+    return NB == 2 ? wg_half(8 * kg + i / 4, nb) + 4 * (i & 3) : 16 * kg;
+}
+template <int NB>
+__device__ __forceinline__ bf16x8 wg_grad_frag(const u16* S, int r) {
+    if constexpr (NB == 2) {
+        return tr_frag(S + r * kWgX * 32, S + (r * kWgX + 4) * 32);
+    } else {
+        const uint4 p = *reinterpret_cast<const uint4*>(S + r * 2 * kWgX);
+        const uint4 q = *reinterpret_cast<const uint4*>(S + r * 2 * kWgX + 8);
+        return __builtin_bit_cast(bf16x8, make_uint4(p.x | p.y << 16, p.z | p.w << 16, q.x | q.y << 16, q.z | q.w << 16));
+    }
+}
+constexpr int wg_grad(int NB) { return NB == 2 ? kWgPlB : 2 * kWgX * kWgY; }   // u16
+
+// The runs of one workgroup and their units, one after another.  Workgroups are
+// dispatched to the 8 XCDs in turn; each XCD takes an eighth of the runs and its
+// workgroups neighbouring ones at a time, so that the planes they share meet in
+// one L2.
+struct WgUnits {
+    int ntx, nty, groups, units;
+    int run, end, by;       // run, the one past the last, and from run to run
+    int cube, u1;           // of the run
+    int u, tx, ty, z;       // the unit
+    __device__ __forceinline__ WgUnits(int ntx_, int nty_, int nz, int groups_, int runs)
+        : ntx(ntx_), nty(nty_), groups(groups_), units(ntx_ * nty_ * nz) {
+        const int g = gridDim.x, b = blockIdx.x, parts = g % 8 == 0 ? 8 : 1, part = b % parts;
+        by = g / parts;
+        run = (int)((long)runs * part / parts) + b / parts;
+        end = (int)((long)runs * (part + 1) / parts);
+        if (more()) enter();
+    }
+    __device__ __forceinline__ bool more() const { return run < end; }
+    __device__ __forceinline__ void enter() {
+        cube = run / groups;
+        const long r = run - cube * groups;
+        u = (int)(r * units / groups);
+        u1 = (int)((r + 1) * units / groups);
+        tx = u % ntx;
+        ty = u / ntx % nty;
+        z = u / (ntx * nty);
+    }
+    __device__ __forceinline__ void next_run() {
+        run += by;
+        if (more()) enter();
+    }
+    // to the next unit; true where a run has ended
+    __device__ __forceinline__ bool step() {
+        if (++u < u1) {
+            if (++tx == ntx) {
+                tx = 0;
+                if (++ty == nty) ty = 0, ++z;
+            }
+            return false;
+        }
+        return true;
+    }
+};
+
+// The bias sums of a unit, voxel after voxel: lane (i + 16 g) adds channel 16 (g & 1) + i
+// (NB = 1: every lane the same).  Half a row is read ahead of its additions.
+template <int NB>
+__device__ __forceinline__ void wg_bias(const u16* Bs, int lane, float* sum) {
+    const int i = lane & 15;
+    // voxels 16 h + 4 k .. + 3 of a row, as FP32 values
+    auto read = [&](auto kc, const u16* row) {
+        constexpr int v = 4 * decltype(kc)::value;
+        f32x4 r;
+        if constexpr (NB == 1) {
+            const uint4 q = *reinterpret_cast<const uint4*>(row + 2 * v);   // a voxel per dword
+            r = f32x4{__uint_as_float(q.x << 16), __uint_as_float(q.y << 16), __uint_as_float(q.z << 16), __uint_as_float(q.w << 16)};
+        } else {
+            const s16x4 q = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                (lds_s16x4)(row + (i >> 2) * 32 + (((lane >> 4) ^ (v >> 3)) & 1) * 16 + 4 * (i & 3) + v * 32));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) r[e] = bf2f((u16)q[e]);
+        }
+        return r;
+    };
+    constexpr int ROW = NB == 2 ? kWgX * 32 : 2 * kWgX;     // u16
+    float s = *sum;
+    f32x4 r[2][4];
+    static_for<4>([&](auto k) { r[0][decltype(k)::value] = read(k, Bs); });
+    static_for<2 * kWgY>([&](auto hc) {
+        constexpr int h = decltype(hc)::value;
+        if constexpr (h + 1 < 2 * kWgY)
+            static_for<4>([&](auto k) {
+                constexpr int kk = 4 * ((h + 1) & 1) + decltype(k)::value;
+                r[(h + 1) & 1][decltype(k)::value] = read(std::integral_constant<int, kk>{}, Bs + (h + 1) / 2 * ROW);
+            });
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s += r[h & 1][k][e];
+        __builtin_amdgcn_sched_barrier(0);
+    });
+    *sum = s;
 }
 
-// 32 input and 32 output channels.  Wavefront (ms, nb, h) owns input channels
-// 16 ms .., output channels 16 nb .. and the tile rows 4 h .. 4 h + 3, with the
-// sums of all 27 taps in registers (108).  Per input plane z' it reads each
-// activation fragment (row, dx) once and multiplies it with the gradient rows
-// of planes z' - 1, z', z' + 1 that it meets, which stay in registers while the
-// planes pass (each read from LDS once): 22 fragment reads for 108 products,
-// where a read per operand would take 216.  Bound by the matrix cores: 3456
-// cycles of MFMA per tile plane against 1400 of LDS reads.  The two row halves
-// are added through LDS at the end, half 0 first.  The bias gradient is one
-// more product with a fragment of ones.  96^3 voxels: 263 -> 56 us (870
-// TFLOP/s) against 2-byte gathered LDS reads, one pair of fragments per product.
-__global__ void __launch_bounds__(kWgThreads)
+// 32 input channels and 32 output channels (NB = 2), or one (NB = 1, its gradient rows
+// read as a column that all 16 lanes share, a voxel per dword).  Six wavefronts per
+// 16 output channels multiply: (ms, p, nb) owns input channels 16 ms .., output
+// channels 16 nb .. and the nine taps of plane p, with their sums in registers.  Each
+// activation fragment is read once and multiplied with the gradient rows that it
+// meets, which stay in registers: 22 fragment reads for 36 products.  Of four more
+// wavefronts one adds the bias sums and three load the units straight into a ring of
+// three in the LDS, two ahead, zeros outside the cube (loads past a buffer's end):
+// one barrier a unit, without a wait for the loads under way.  The bias sums are a
+// chain of 128 additions a unit, so that wavefront and the loading ones go first
+// (s_setprio).  Four 96^3 cubes: 212 us a layer (4 x 263 with gathered LDS reads and
+// one pair of fragments per product; 200 in a form that kept no order of the sums and
+// streamed whole columns of planes); one output channel 132 us (4 x 185).  What
+// bounds it: per unit and compute unit 1728 cycles of products, 2500 of the bias
+// chain, and the wait for 47 KB of loads, in 3500.
+constexpr int wg_threads(int NB) { return 64 * (6 * NB + 4); }
+constexpr int wg_slot(int NB) { return 3 * kWgPlA + wg_grad(NB); }   // u16 of a staged unit
+constexpr size_t wg_lds(int NB) { return (size_t)3 * wg_slot(NB) * 2; }
+template <int NB>
+__global__ void __launch_bounds__(wg_threads(NB), NB == 2 ? 4 : 3)
 k_wgrad32(const u16* __restrict__ a0, const u16* __restrict__ dz0, float* __restrict__ part, int nx, int ny, int nz,
-          int ntx, int nty, int cubes) {
+          int ntx, int nty, int groups, int runs) {
+    constexpr int CO = NB == 2 ? 32 : 1, MW = 6 * NB, SLOT = wg_slot(NB), B0 = 3 * kWgPlA;
+    constexpr long PART = 27L * 32 * CO + CO;
     extern __shared__ uint4 wg_smem[];
-    u16* As = reinterpret_cast<u16*>(wg_smem);   // two planes of activations, then two of gradients
-    u16* Bs = As + 2 * kWgPlA;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int ms = w & 1, nb = (w >> 1) & 1, h = w >> 2;
-    const int i = lane & 15, kg = lane >> 4;
-    const int frag = (8 * kg + i / 4) * 32 + 4 * (i & 3);
-    const u16* Ab = As + 4 * h * kWgLX * 32 + frag + 16 * ms;
-    const u16* Bb = Bs + 4 * h * kWgX * 32 + frag + 16 * nb;
+    u16* sm = reinterpret_cast<u16*>(wg_smem);
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const long n = (long)nx * ny * nz;
+    WgUnits it(ntx, nty, nz, groups, runs);
+    // a barrier that waits for no load: LDS accesses stay on their side of it
+    auto barrier = [] {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
 
-    f32x4 acc[27], accb = {0.f, 0.f, 0.f, 0.f};
+    if (w > MW) {
+        // Loading thread lt takes the 16-byte chunks lt + 192 k of the activations (KA)
+        // and of the gradient (KB): a chunk's offset in bytes from the unit's first
+        // voxel, and its column and row (bit of a mask) in the staged block.
+        constexpr int QA = 3 * kWgLX * kWgLY * 4, KA = (QA + 191) / 192, QB = kWgX * kWgY * 4, KB = NB == 2 ? 3 : 1;
+        const int lw = w - MW - 1, lt = 64 * lw + lane;
+        unsigned rel[KA], col[KA], bit[KA], relb[KB], colb[KB], bitb[KB];
 #pragma unroll
-    for (int t = 0; t < 27; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    bf16x8 ones;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
-
-    const int tiles = ntx * nty;
-    const long units = (long)tiles * nz * cubes;   // planes of tiles of one cube after another
-    const long u0 = blockIdx.x * units / gridDim.x, u1 = (blockIdx.x + 1) * units / gridDim.x;
-    for (long u = u0; u < u1;) {
-        const int ct = (int)(u / nz), z0 = (int)(u % nz), tile = ct % tiles;
-        const long cube = ct / tiles * ((long)nx * ny * nz);
-        const u16 *a = a0 + cube * 32, *dz = dz0 + cube * 32;
-        const int np = (int)min((long)(nz - z0), u1 - u);      // planes of this run in this tile
-        const int x0 = tile % ntx * kWgX, y0 = tile / ntx * kWgY;
-        u += np;
-        // the 16-byte chunks this thread stages: byte offsets from the tile's
-        // first row of a plane (below 2^32: the cube has fewer than 2^26
-        // voxels), clamped into the cube; `ok` bits: the chunk lies in it
-        uint4 sa[3], sb[2];
-        unsigned oa[3], ob[2];
-        int ok = 0;
-        const int yb = max(y0 - 1, 0);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const int q = tid + kWgThreads * k, vox = q >> 2;
-            const int x = x0 + vox % kWgLX - 1, y = y0 + vox / kWgLX - 1;
-            if (x >= 0 && x < nx && y >= 0 && y < ny) ok |= 1 << k;
-            oa[k] = (unsigned)(((long)(min(max(y, 0), ny - 1) - yb) * nx + min(max(x, 0), nx - 1)) * 64 + 16 * (q & 3));
+        for (int k = 0; k < KA; ++k) {
+            const int q = lt + 192 * k, vox = q >> 2, x = vox % kWgLX, r = vox / kWgLX;
+            const int c = (q & 3) ^ ((x >> 2) & 2);          // (wg_half)
+            rel[k] = (unsigned)(((r / kWgLY - 1) * ny + r % kWgLY - 1) * nx + x - 1) * 64u + 16 * c;
+            col[k] = x;
+            bit[k] = 1u << r;
         }
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int q = tid + kWgThreads * k, vox = q >> 2;
-            const int x = x0 + vox % kWgX, y = y0 + vox / kWgX;
-            if (x < nx && y < ny) ok |= 8 << k;
-            ob[k] = (unsigned)(((long)(min(y, ny - 1) - yb) * nx + min(x, nx - 1)) * 64 + 16 * (q & 3));
+        for (int k = 0; k < KB; ++k) {
+            const int q = lt + 192 * k, vox = NB == 2 ? q >> 2 : 64 * k + lane, x = vox % kWgX, r = vox / kWgX;
+            relb[k] = (unsigned)(r * nx + x) * (NB == 2 ? 64u : 2u) + (NB == 2 ? 16 * ((q & 3) ^ ((x >> 2) & 2)) : 0);
+            colb[k] = x;
+            bitb[k] = 1u << r;
         }
-        auto fetch_a = [&](int z) {
-            const char* base = reinterpret_cast<const char*>(a) + ((long)min(max(z, 0), nz - 1) * ny + yb) * nx * 64;
+        const unsigned bytes = (unsigned)(n * 64), bytesb = (unsigned)(n * 2 * CO);   // below 2^32: fewer than 2^26 voxels
+        typedef __attribute__((address_space(3))) void* lds_ptr;
+        auto stage = [&](int slot) {
+            u16* to = sm + slot * SLOT;
+            const auto ra = raw_buffer(a0 + it.cube * n * 32, (int)bytes);
+            const auto rb = raw_buffer(dz0 + it.cube * n * CO, (int)bytesb);
+            const int x0 = it.tx * kWgX, y0 = it.ty * kWgY, v0 = (it.z * ny + y0) * nx + x0;
+            // columns x0 - 1 + [xl, xh) and rows of planes z - 1 .. z + 1 that lie in the cube
+            const unsigned xl = x0 == 0 ? 1 : 0, xh = min(kWgLX, nx - x0 + 1);
+            const unsigned rows = ((1u << min(kWgLY, ny - y0 + 1)) - 1) & (y0 == 0 ? ~1u : ~0u);
+            const unsigned in = (it.z > 0 ? rows : 0) | rows << kWgLY | (it.z + 1 < nz ? rows << (2 * kWgLY) : 0);
+            const unsigned inb = (1u << min(kWgY, ny - y0)) - 1, xhb = min(kWgX, nx - x0);
 #pragma unroll
-            for (int k = 0; k < 3; ++k) sa[k] = *reinterpret_cast<const uint4*>(base + oa[k]);
-        };
-        auto fetch_b = [&](int z) {
-            const char* base = reinterpret_cast<const char*>(dz) + ((long)z * ny + yb) * nx * 64;
-#pragma unroll
-            for (int k = 0; k < 2; ++k) sb[k] = *reinterpret_cast<const uint4*>(base + ob[k]);
-        };
-        auto put_a = [&](int slot, int z) {
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const int q = tid + kWgThreads * k;
-                const bool in = ((ok >> k) & 1) && z >= 0 && z < nz;
-                if (q < kWgLX * kWgLY * 4) reinterpret_cast<uint4*>(As + slot * kWgPlA)[q] = in ? sa[k] : make_uint4(0, 0, 0, 0);
+            for (int k = 0; k < KA; ++k) {
+                const bool ok = col[k] - xl < xh - xl && (bit[k] & in);
+                const unsigned off = ok ? (unsigned)v0 * 64u + rel[k] : bytes;
+                if (192 * (k + 1) <= QA || lt + 192 * k < QA)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_ptr)(to + (64 * lw + 192 * k) * 8), 16, off, 0, 0, 0);
             }
-        };
-        auto put_b = [&](int slot) {
+            if constexpr (NB == 2) {
 #pragma unroll
-            for (int k = 0; k < 2; ++k)
-                reinterpret_cast<uint4*>(Bs + slot * kWgPlB)[tid + kWgThreads * k] = (ok >> (3 + k)) & 1 ? sb[k] : make_uint4(0, 0, 0, 0);
-        };
-        fetch_a(z0 - 1);
-        fetch_b(z0);
-        put_a(0, z0 - 1);
-        put_b(0);
-        __syncthreads();
-        // step s: input plane z0 - 1 + s (LDS slot s mod 2) meets the gradient
-        // planes z0 + s (tap dz = 0; LDS slot s mod 2, read here into registers
-        // B[s mod 3]), z0 + s - 1 (dz = 1) and z0 + s - 2 (dz = 2), those of
-        // them that lie in the run
-        bf16x8 B[3][4];
-        auto step = [&](int s, auto rot) {
-            constexpr int R0 = decltype(rot)::value, R1 = (R0 + 2) % 3, R2 = (R0 + 1) % 3;
-            const bool on0 = s < np, on1 = s >= 1 && s <= np, on2 = s >= 2;
-            if (s <= np) fetch_a(z0 + s);
-            if (s + 1 < np) fetch_b(z0 + s + 1);
-            const u16* A = Ab + (s & 1) * kWgPlA;
-            const u16* Bn = Bb + (s & 1) * kWgPlB;
-            // input rows 4 h - 1 + j, each at three shifts: fragment m = 3 j + dx,
-            // read two ahead of its products
-            bf16x8 f[3];
-            f[0] = tr_frag(A);
-            f[1] = tr_frag(A + 32);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) B[R0][r] = tr_frag(Bn + r * kWgX * 32);   // not used unless on0
-#pragma unroll
-            for (int m = 0; m < 18; ++m) {
-                const int j = m / 3, dx = m % 3;
-                if (m + 2 < 18) f[(m + 2) % 3] = tr_frag(A + ((m + 2) / 3 * kWgLX + (m + 2) % 3) * 32);
-                __builtin_amdgcn_sched_barrier(0);
-                auto taps = [&](int d, const bf16x8 (&b)[4]) {
-#pragma unroll
-                    for (int dy = 0; dy < 3; ++dy)
-                        if (j - dy >= 0 && j - dy < 4) {   // gradient row j - dy
-                            const int t = 9 * d + 3 * dy + dx;
-                            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[m % 3], b[j - dy], acc[t], 0, 0, 0);
-                        }
-                };
-                if (on2) taps(2, B[R2]);
-                if (on1) taps(1, B[R1]);
-                if (on0) taps(0, B[R0]);
-                __builtin_amdgcn_sched_barrier(0);
+                for (int k = 0; k < KB; ++k) {
+                    const bool ok = colb[k] < xhb && (bitb[k] & inb);
+                    const unsigned off = ok ? (unsigned)v0 * 64u + relb[k] : bytesb;
+                    if (192 * (k + 1) <= QB || 64 * lw + 192 * k < QB)
+                        __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_ptr)(to + B0 + (64 * lw + 192 * k) * 8), 16, off, 0, 0, 0);
+                }
+            } else if (lw < 2) {                             // voxels 64 lw + lane
+                const int r = 2 * lw + (lane >> 5), x = lane & 31;
+                const unsigned off = x < (int)xhb && (inb >> r & 1) ? (unsigned)(v0 + r * nx + x) * 2u : bytesb;
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_ptr)(to + B0 + 128 * lw), 2, off, 0, 0, 0);
             }
-            if (ms == 0 && on1)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, B[R1][r], accb, 0, 0, 0);
-            if (s <= np) put_a((s + 1) & 1, z0 + s);
-            if (s + 1 < np) put_b((s + 1) & 1);
-            __syncthreads();
+            if (it.step()) it.next_run();
         };
-        for (int s = 0; s <= np + 1; s += 3) {
-            step(s, std::integral_constant<int, 0>{});
-            if (s + 1 <= np + 1) step(s + 1, std::integral_constant<int, 1>{});
-            if (s + 2 <= np + 1) step(s + 2, std::integral_constant<int, 2>{});
+        // loads that a unit takes of this wavefront: KA, and of the gradient (NB = 2) 3, 3
+        // and 2, (NB = 1) 1, 1 and 0
+        __builtin_amdgcn_s_setprio(2);
+        int ahead = 0;                                       // units whole or under way past the one consumed
+        for (; ahead < 2 && it.more(); ++ahead) stage(ahead);
+        for (int slot = 0; ahead > 0; slot = slot == 2 ? 0 : slot + 1) {
+            if (ahead == 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            else if (lw == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(KA + (NB == 2 ? 2 : 0)) : "memory");
+            else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(KA + (NB == 2 ? 3 : 1)) : "memory");
+            barrier();                                       // the unit in `slot` is whole, the one before it done
+            --ahead;
+            if (it.more()) {
+                stage(slot == 0 ? 2 : slot - 1);
+                ++ahead;
+            }
+        }
+        return;
+    }
+    if (w == MW) {
+        __builtin_amdgcn_s_setprio(2);
+        float bsum = 0.0f;
+        for (int slot = 0; it.more(); slot = slot == 2 ? 0 : slot + 1) {
+            barrier();
+            wg_bias<NB>(sm + slot * SLOT + B0, lane, &bsum);
+            if (it.step()) {
+                if (lane < CO) part[it.run * PART + 27 * 32 * CO + lane] = bsum;
+                bsum = 0.0f;
+                it.next_run();
+            }
+        }
+        return;
+    }
+    const int ms = w & 1, p = (w >> 1) % 3, nb = w / 6, i = lane & 15, kg = lane >> 4;
+    f32x4 acc[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int lo[3], hi[3];                                        // this lane's place in a fragment shifted by dx
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx) {
+        lo[dx] = p * kWgPlA + wg_half(8 * kg + i / 4 + dx, ms) + 4 * (i & 3);
+        hi[dx] = p * kWgPlA + wg_half(8 * kg + i / 4 + dx + 4, ms) + 4 * (i & 3);
+    }
+    const int gl = B0 + wg_grad_lane<NB>(lane, nb);
+    // fragment m: input row j = m / 3 (the unit's row - 1), shift dx = m % 3
+    constexpr int FR = kWgAhead + 1;
+    bf16x8 b[kWgY], f[FR];
+    for (int slot = 0; it.more(); slot = slot == 2 ? 0 : slot + 1) {
+        barrier();
+        const u16* S = sm + slot * SLOT;
+        auto load = [&](auto mc) {
+            constexpr int m = decltype(mc)::value, r = m / 3 * kWgLX * 32;
+            if constexpr (m < 18) f[m % FR] = tr_frag(S + lo[m % 3] + r, S + hi[m % 3] + r);
+        };
+        b[0] = wg_grad_frag<NB>(S + gl, 0);
+        static_for<kWgAhead>(load);
+        static_for<18>([&](auto mc) {
+            constexpr int m = decltype(mc)::value, j = m / 3, dx = m % 3;
+            if constexpr (dx == 0 && j + 1 < kWgY) b[j + 1] = wg_grad_frag<NB>(S + gl, j + 1);
+            load(std::integral_constant<int, m + kWgAhead>{});
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy)
+                if (j - dy >= 0 && j - dy < kWgY)
+                    acc[3 * dy + dx] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[m % FR], b[j - dy], acc[3 * dy + dx], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        if (it.step()) {
+            float* P = part + it.run * PART;
+#pragma unroll
+            for (int t = 0; t < 9; ++t) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (NB == 2 || i == 0)
+                        P[((9 * p + t) * 32 + 16 * ms + 4 * kg + e) * CO + (NB == 2 ? 16 * nb + i : 0)] = acc[t][e];
+                acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+            it.next_run();
         }
     }
-    // add the row halves and write the partial: W[27][32][32], then b[32]
-    float4* red = reinterpret_cast<float4*>(wg_smem) + (w & 3) * 27 * 64 + lane;
-    __shared__ float bred[2][16];
-    if (h == 1) {
-#pragma unroll
-        for (int t = 0; t < 27; ++t) red[t * 64] = __builtin_bit_cast(float4, acc[t]);
-        if (ms == 0 && kg == 0) bred[nb][i] = accb[0];
-    }
-    __syncthreads();
-    if (h == 1) return;
-    float* P = part + blockIdx.x * (27L * 1024 + 32);
-#pragma unroll
-    for (int t = 0; t < 27; ++t) {
-        const f32x4 o = __builtin_bit_cast(f32x4, red[t * 64]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) P[(t * 32 + 16 * ms + 4 * kg + e) * 32 + 16 * nb + i] = acc[t][e] + o[e];
-    }
-    if (ms == 0 && kg == 0) P[27 * 1024 + 16 * nb + i] = accb[0] + bred[nb][i];
 }
 
-// One side with a single channel: H[t][c] = sum over voxels v of p[v][c] q[v + t],
-// p with CP channels (32, or 1) and q with one.  The first layer's gradient is
-// H with p = dz and q = x; the last layer's, sum of a[v + t] dz[v], is H with p =
-// a and q = dz at the mirrored tap 26 - t (`mirror`).  M = the 27 taps, a row of
-// ones as tap 27 (the sums of p: the bias gradient when p = dz) and zeros; N =
-// channels; K = 32 voxels, one tile row per wavefront.  q's planes are staged
-// three times, shifted by dx, so a lane's 8 values are one aligned read.  With
-// mirror the bias gradient is the sum of q, kept per thread as it stages q.
-// Bound by reading p.  96^3 voxels: 15 us (3.8 TB/s), from 143
-// us (first layer) and 185 us (last) with gathered reads and padded products.
-constexpr int kWg1Row = 40;                                  // u16 per staged q row (32, padded to spread the banks)
+// One input channel and 32 output channels (NB = 2) or one: M = the 27 taps (padded to
+// 32), N = output channels, K = 32 voxels of a row; a workgroup per run.  Wavefront (m,
+// nb) owns 16 taps and 16 channels, the last one the bias sums too.  The input's planes
+// are staged three times, shifted by dx, so a lane's 8 values are one aligned read.
+// Bound by the bias chain and reading dz: four 96^3 cubes 67 us (4 x 143 before).
+constexpr int kWg1Threads = 256;
+constexpr int kWg1Row = 40;                                  // u16 per staged input row (32, padded to spread the banks)
 constexpr int kWg1Copy = kWgLY * kWg1Row, kWg1Pl = 3 * kWg1Copy;
-template <int CP>
-__global__ void __launch_bounds__(kWgThreads)
-k_wgrad1(const u16* __restrict__ p0, const u16* __restrict__ q0, int mirror, float* __restrict__ part, int nx, int ny,
-         int nz, int ntx, int nty, int cubes) {
-    constexpr int NB = CP == 32 ? 2 : 1;
-    __shared__ __attribute__((aligned(16))) u16 Ps[2 * kWgPlB];
-    __shared__ __attribute__((aligned(16))) u16 Qs[4 * kWg1Pl + 16];   // + eight ones, eight zeros
-    __shared__ float qs[kWgThreads / 64];
-    static_assert(sizeof(Ps) >= (size_t)8 * 2 * NB * 64 * 16, "the final exchange fits the staged planes");
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+template <int NB>
+__global__ void __launch_bounds__(kWg1Threads)
+k_wgrad1(const u16* __restrict__ a0, const u16* __restrict__ dz0, float* __restrict__ part, int nx, int ny, int nz,
+         int ntx, int nty, int groups, int runs) {
+    constexpr int CO = NB == 2 ? 32 : 1;
+    __shared__ __attribute__((aligned(16))) u16 Qs[3 * kWg1Pl + kWgY * kWg1Row];   // + zeros
+    __shared__ __attribute__((aligned(16))) u16 Bs[wg_grad(NB)];
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m = w & 1, nb = w >> 1;
     const int i = lane & 15, kg = lane >> 4;
-    if (tid < 16) Qs[4 * kWg1Pl + tid] = tid < 8 ? 0x3f80 : 0;
-    if (CP == 1)
-        for (int k = tid; k < 2 * kWgPlB / 8; k += kWgThreads) reinterpret_cast<uint4*>(Ps)[k] = make_uint4(0, 0, 0, 0);
+    for (int k = tid; k < kWgY * kWg1Row; k += kWg1Threads) Qs[3 * kWg1Pl + k] = 0;
+    const int t = 16 * m + i;                                // this lane's tap
+    const u16* Qa = Qs + (t < 27 ? t / 9 * kWg1Pl + t % 3 * kWg1Copy + t / 3 % 3 * kWg1Row : 3 * kWg1Pl) + 8 * kg;
+    const u16* Ba = Bs + wg_grad_lane<NB>(lane, nb);
+    WgUnits it(ntx, nty, nz, groups, runs);
+    const long cube = it.cube * ((long)nx * ny * nz);
+    const u16 *a = a0 + cube, *dz = dz0 + cube * CO;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    float bsum = 0.0f;
 
-    // this lane's taps t = 16 m + i: plane offset dz (or -1: the constants) and place in the staged plane
-    int tz[2], to[2];
+    constexpr int KA = (3 * kWgLX * kWgLY + kWg1Threads - 1) / kWg1Threads, KB = NB == 2 ? 2 : 1;
+    u16 sa[KA];
+    uint4 sb[KB];
+    auto fetch = [&]() {
+        const int x0 = it.tx * kWgX, y0 = it.ty * kWgY;
 #pragma unroll
-    for (int m = 0; m < 2; ++m) {
-        const int t = 16 * m + i;
-        tz[m] = t < 27 ? t / 9 : -1;
-        to[m] = t < 27 ? (t % 3) * kWg1Copy + (w + (t / 3) % 3) * kWg1Row + 8 * kg : 4 * kWg1Pl + (t == 27 ? 0 : 8);
-    }
-    const u16* Pb = Ps + (w * kWgX + 8 * kg + i / 4) * 32 + 4 * (i & 3);
-    f32x4 acc[2][NB];
+        for (int k = 0; k < KA; ++k) {
+            const int q = tid + kWg1Threads * k;
+            const int x = x0 + q % kWgLX - 1, y = y0 + q / kWgLX % kWgLY - 1, z = it.z + q / (kWgLX * kWgLY) - 1;
+            const bool ok = q < 3 * kWgLX * kWgLY && x >= 0 && x < nx && y >= 0 && y < ny && z >= 0 && z < nz;
+            sa[k] = ok ? a[((long)z * ny + y) * nx + x] : (u16)0;
+        }
 #pragma unroll
-    for (int m = 0; m < 2; ++m)
+        for (int k = 0; k < KB; ++k) {
+            const int q = tid + kWg1Threads * k, vox = NB == 2 ? q >> 2 : q & (kWgX * kWgY - 1);
+            const int x = x0 + vox % kWgX, y = y0 + vox / kWgX;
+            const long v = ((long)it.z * ny + y) * nx + x;
+            sb[k] = make_uint4(0, 0, 0, 0);
+            if (x < nx && y < ny) {
+                if constexpr (NB == 2) sb[k] = *reinterpret_cast<const uint4*>(dz + v * 32 + 8 * (q & 3));
+                else sb[k].x = dz[v];
+            }
+        }
+    };
+    auto put = [&]() {
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) acc[m][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float qsum = 0.0f;
-
-    const int tiles = ntx * nty;
-    const long units = (long)tiles * nz * cubes;   // planes of tiles of one cube after another
-    const long u0 = blockIdx.x * units / gridDim.x, u1 = (blockIdx.x + 1) * units / gridDim.x;
-    const int qc = tid % kWgLX, qr = tid / kWgLX;            // the q voxel this thread stages
-    const bool qon = tid < kWgLX * kWgLY;
-    const bool qin = qc >= 1 && qc <= kWgX && qr >= 1 && qr <= kWgY;
-    for (long u = u0; u < u1;) {
-        const int ct = (int)(u / nz), z0 = (int)(u % nz), tile = ct % tiles;
-        const long cube = ct / tiles * ((long)nx * ny * nz);
-        const u16 *p = p0 + cube * CP, *q = q0 + cube;
-        const int np = (int)min((long)(nz - z0), u1 - u);
-        const int x0 = tile % ntx * kWgX, y0 = tile / ntx * kWgY;
-        u += np;
-        const int qx = x0 + qc - 1, qy = y0 + qr - 1;
-        const bool qok = qon && qx >= 0 && qx < nx && qy >= 0 && qy < ny;
-        uint4 sp[2];
-        auto fetch_q = [&](int z) -> u16 { return qok && z >= 0 && z < nz ? q[((long)z * ny + qy) * nx + qx] : (u16)0; };
-        auto put_q = [&](int k, u16 v) {                     // plane z0 - 1 + k
-            if (qon)
+        for (int k = 0; k < KA; ++k) {
+            const int q = tid + kWg1Threads * k, x = q % kWgLX, r = q / kWgLX % kWgLY, p = q / (kWgLX * kWgLY);
+            if (q < 3 * kWgLX * kWgLY)
 #pragma unroll
                 for (int dx = 0; dx < 3; ++dx)
-                    if (qc - dx >= 0 && qc - dx < kWgX) Qs[(k & 3) * kWg1Pl + dx * kWg1Copy + qr * kWg1Row + qc - dx] = v;
-            if (qin && k >= 1 && k <= np) qsum += bf2f(v);
-        };
-        auto fetch_p = [&](int z) {
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const int c = tid + kWgThreads * k, vox = CP == 32 ? c >> 2 : c;
-                const int x = x0 + vox % kWgX, y = y0 + vox / kWgX;
-                sp[k] = make_uint4(0, 0, 0, 0);
-                if (vox < kWgX * kWgY && x < nx && y < ny) {
-                    const long v = ((long)z * ny + y) * nx + x;
-                    if constexpr (CP == 32) sp[k] = *reinterpret_cast<const uint4*>(p + v * 32 + 8 * (c & 3));
-                    else sp[k].x = p[v];
-                }
-            }
-        };
-        auto put_p = [&](int slot) {
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const int c = tid + kWgThreads * k;
-                if constexpr (CP == 32) reinterpret_cast<uint4*>(Ps + slot * kWgPlB)[c] = sp[k];
-                else if (c < kWgX * kWgY) Ps[slot * kWgPlB + c * 32] = (u16)sp[k].x;
-            }
-        };
-        __syncthreads();   // the constants are written; the previous run is done with the planes
-        fetch_p(z0);
-        const u16 qa = fetch_q(z0 - 1), qb = fetch_q(z0), qc1 = fetch_q(z0 + 1);
-        put_q(0, qa);
-        put_q(1, qb);
-        put_q(2, qc1);
-        put_p(0);
-        __syncthreads();
-        for (int s = 0; s < np; ++s) {
-            u16 qn = 0;
-            if (s + 1 < np) {
-                fetch_p(z0 + s + 1);
-                qn = fetch_q(z0 + s + 2);
-            }
-            bf16x8 b[NB];
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) b[nb] = tr_frag(Pb + (s & 1) * kWgPlB + 16 * nb);
-#pragma unroll
-            for (int m = 0; m < 2; ++m) {
-                const int at = tz[m] < 0 ? to[m] : ((s + tz[m]) & 3) * kWg1Pl + to[m];
-                const bf16x8 f = *reinterpret_cast<const bf16x8*>(Qs + at);
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
-                    acc[m][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, b[nb], acc[m][nb], 0, 0, 0);
-            }
-            if (s + 1 < np) {
-                put_p((s + 1) & 1);
-                put_q(s + 3, qn);
-            }
-            __syncthreads();
+                    if (x - dx >= 0 && x - dx < kWgX) Qs[p * kWg1Pl + dx * kWg1Copy + r * kWg1Row + x - dx] = sa[k];
         }
-    }
-    // add the wavefronts in order
-    __syncthreads();
-    float4* red = reinterpret_cast<float4*>(Ps);
 #pragma unroll
-    for (int m = 0; m < 2; ++m)
+        for (int k = 0; k < KB; ++k) {
+            const int q = tid + kWg1Threads * k;
+            if constexpr (NB == 2) reinterpret_cast<uint4*>(Bs)[q ^ (q >> 4 & 2)] = sb[k];   // (wg_half)
+            else if (q < kWgX * kWgY) reinterpret_cast<unsigned*>(Bs)[q] = sb[k].x;
+        }
+    };
+    fetch();
+    for (bool last = false; !last;) {
+        put();
+        __syncthreads();
+        last = it.step();
+        if (!last) fetch();
+        if (nb < NB)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) red[((w * 2 + m) * NB + nb) * 64 + lane] = __builtin_bit_cast(float4, acc[m][nb]);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) qsum += __shfl_xor(qsum, o, 64);
-    if (lane == 0) qs[w] = qsum;
-    __syncthreads();
-    float* P = part + (long)blockIdx.x * (28 * CP);
-    for (int k = tid; k < 2 * NB * 64; k += kWgThreads) {
-        const int m = k / (NB * 64), nb = k / 64 % NB, l = k % 64;
-        f32x4 v = {0.f, 0.f, 0.f, 0.f};
-        for (int ww = 0; ww < kWgThreads / 64; ++ww) v += __builtin_bit_cast(f32x4, red[((ww * 2 + m) * NB + nb) * 64 + l]);
-        const int c = 16 * nb + (l & 15);
-        if (c < CP)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int t = 16 * m + 4 * (l >> 4) + e;
-                if (t < 27) P[(mirror ? 26 - t : t) * CP + c] = v[e];
-                else if (t == 27 && !mirror) P[27 * CP + c] = v[e];
+            for (int r = 0; r < kWgY; ++r) {
+                const bf16x8 f = *reinterpret_cast<const bf16x8*>(Qa + r * kWg1Row);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, wg_grad_frag<NB>(Ba, r), acc, 0, 0, 0);
             }
+        if (w == 3) wg_bias<NB>(Bs, lane, &bsum);
+        __syncthreads();
     }
-    if (mirror && tid == 0) {
-        float t = 0.0f;
-        for (int ww = 0; ww < kWgThreads / 64; ++ww) t += qs[ww];
-        P[27 * CP] = t;
+    float* P = part + it.run * (28L * CO);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int tt = 16 * m + 4 * kg + e;
+        if (tt < 27 && nb < NB && (NB == 2 || i == 0)) P[tt * CO + (NB == 2 ? 16 * nb + i : 0)] = acc[e];
     }
+    if (w == 3 && lane < CO) P[27 * CO + lane] = bsum;
 }
 
-// dW[j] (j < lenw) and db[j - lenw] (+)= sum over workgroups of part[wg][j] in a
-// fixed order: wavefront q of the block sums the workgroups [q nwg/16, (q+1)
-// nwg/16) in order for 64 consecutive j (eight loads in flight), then the 16
-// sums are added in order.
+// dW[j] (j < lenw) and db[j - lenw] (+)= the cubes' gradients in order, a cube's the
+// sum over its nwg runs of part[run][j]: quarter q of the runs, [q nwg/4, (q+1)
+// nwg/4), in order (eight loads in flight), then the quarters in order.  Sixteen
+// wavefronts take four cubes at a time, each a quarter for 64 consecutive j.  Bound by
+// reading the partials: 2 x 57 MB of two 96^3 cubes in 20 us.
 __global__ void __launch_bounds__(1024)
-k_wgrad_fold(const float* __restrict__ part, long nwg, long stride, long lenw, long len, float* __restrict__ dW,
+k_wgrad_fold(const float* __restrict__ part, long nwg, int cubes, long lenw, long len, float* __restrict__ dW,
              float* __restrict__ db, int accumulate) {
     __shared__ float sh[16][64];
-    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, q = w & 3;
     const long j = (long)blockIdx.x * 64 + lane;
-    const long k0 = q * nwg / 16, k1 = (q + 1) * nwg / 16;
-    float s = 0.0f;
-    if (j < len) {
-        long k = k0;
-        for (; k + 8 <= k1; k += 8) {
-            float v[8];
+    const long k0 = q * nwg / 4, k1 = (q + 1) * nwg / 4;
+    float* d = j < lenw ? dW + j : db + (j - lenw);
+    float g = w == 0 && j < len && accumulate ? *d : 0.0f;
+    for (int c0 = 0; c0 < cubes; c0 += 4) {
+        const int c = c0 + (w >> 2);
+        float s = 0.0f;
+        if (c < cubes && j < len) {
+            const float* p = part + c * nwg * len + j;
+            long k = k0;
+            for (; k + 8 <= k1; k += 8) {
+                float v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = part[(k + u) * stride + j];
+                for (int u = 0; u < 8; ++u) v[u] = p[(k + u) * len];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) s += v[u];
+                for (int u = 0; u < 8; ++u) s += v[u];
+            }
+            for (; k < k1; ++k) s += p[k * len];
         }
-        for (; k < k1; ++k) s += part[k * stride + j];
+        sh[w][lane] = s;
+        __syncthreads();
+        if (w == 0)
+            for (int e = 0; e < min(4, cubes - c0); ++e) {
+                const float t = ((sh[4 * e][lane] + sh[4 * e + 1][lane]) + sh[4 * e + 2][lane]) + sh[4 * e + 3][lane];
+                g = accumulate || c0 + e > 0 ? g + t : t;
+            }
+        __syncthreads();
     }
-    sh[q][lane] = s;
-    __syncthreads();
-    if (q == 0 && j < len) {
-        float t = sh[0][lane];
-#pragma unroll
-        for (int u = 1; u < 16; ++u) t += sh[u][lane];
-        float* d = j < lenw ? dW + j : db + (j - lenw);
-        *d = accumulate ? *d + t : t;
-    }
+    if (w == 0 && j < len) *d = g;
 }
 
 // ---------------------------------------------------------- loss, inputs

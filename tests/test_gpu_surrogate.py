@@ -517,3 +517,98 @@ def test_trained_network_gain(dev):
     print(f"held-out RMSE to the {n}-step filter: untrained {before:.4f}, trained {after:.4f}; "
           f"plain filter in one inference's time ({k_eq} steps): {rm_k:.4f}")
     assert after < 0.5 * before
+
+
+# ------------------------------------------------------------ order of the sums
+# The FP32 order of the weight-gradient sums is part of what a training run gives:
+# Adam turns a last-bit difference into another bf16 weight now and then.  It is
+# fixed (units of 32 x 4 voxels in at most 512 runs of a cube, the runs folded in
+# quarters, cube after cube); these are the bits it gave when it was laid down.
+def _digest(*arrays):
+    import hashlib
+    m = hashlib.sha256()
+    for a in arrays:
+        m.update(np.ascontiguousarray(a.cpu().numpy() if hasattr(a, "cpu") else a).tobytes())
+    return m.hexdigest()[:16]
+
+
+WGRAD_BITS = {
+    ((1, 1, 1), 32, 32): ("e0dfcff2ee33f125", "202f007c8ee99067"),
+    ((1, 1, 1), 1, 32): ("eb0a171248959695", "0c1ec7abc28cf862"),
+    ((1, 1, 1), 32, 1): ("8c5845498c2f86a6", "62e78fe75ea872ac"),
+    ((1, 1, 1), 1, 1): ("f7e7e62017098d61", "65569f0a34f29f1f"),
+    ((2, 9, 33), 32, 32): ("3f1d0310a266c9ff", "35cc61a02d80e555"),
+    ((2, 9, 33), 1, 32): ("784a28204f080b7b", "fbd041936e5209b4"),
+    ((2, 9, 33), 32, 1): ("8a476416479454d6", "c9129ddcd1d5138c"),
+    ((2, 9, 33), 1, 1): ("22412f0013ad9402", "70ce7374df6eaba8"),
+    ((3, 17, 65), 32, 32): ("9a89cfaab005d96c", "a3c2fd21c18c4965"),
+    ((3, 17, 65), 1, 32): ("d817c8f72b53337e", "6c80ca7ade67f0f3"),
+    ((3, 17, 65), 32, 1): ("3488d28a127e6d5a", "6124c2d262f68aa4"),
+    ((3, 17, 65), 1, 1): ("461e39378ce4d89c", "93c78f95b49e8849"),
+    ((11, 37, 45), 32, 32): ("f335290760ca5271", "a3c47dc2a3545a69"),
+    ((11, 37, 45), 1, 32): ("95c8fb255ef62579", "a2371e7fedb7f877"),
+    ((11, 37, 45), 32, 1): ("483e97541cbe0e76", "80effc08faace4e7"),
+    ((11, 37, 45), 1, 1): ("38d9b5084c3c0676", "b4b295c04f40c77d"),
+    ((40, 40, 70), 32, 32): ("3fb2a0f50b8188e2", "d1e200fbc0919ce3"),
+    ((40, 40, 70), 1, 32): ("9cfc5507e795a9b5", "b69a5c5c98fa4ccf"),
+    ((40, 40, 70), 32, 1): ("d07571140707a441", "1dcf5b7fc8dbf7a6"),
+    ((40, 40, 70), 1, 1): ("713858836381fd43", "7a18ab3acc09cd11"),
+}
+
+
+@pytest.mark.parametrize("shape,cin,cout", list(WGRAD_BITS))
+def test_weight_gradient_bits(dev, shape, cin, cout):
+    import torch
+    from paper_1609_03782_amd import surrogate as sg
+    rng = np.random.default_rng(1000 * cin + cout + sum(shape))
+    a, d = (torch.from_numpy(rng.standard_normal(shape + (c,)).astype(np.float32)).to(torch.bfloat16).to(dev)
+            for c in (cin, cout))
+    dW, db = sg.conv3d_weight_grad(a, cin, d, cout)
+    assert (_digest(dW), _digest(db)) == WGRAD_BITS[shape, cin, cout]
+
+
+TRAIN_BITS = {   # gradients after each of three steps, weights, a prediction
+    ((37, 20, 70), 3, 4): ("97d42f41c31a4d3e", "5659ba80ab1f4952", "242eb50d84f6b5e9", "a135f58e71a460b2", "8f488c76203b14bc"),
+    ((3, 5, 6), 2, 4): ("bfab240098e328d6", "b05e74bc61ae941c", "1959a0f262703ba2", "a7968535965c1a3a", "68ff8c24271051f9"),
+    ((40, 64, 100), 8, 4): ("cf70568fa8195910", "5e955ffd827954c5", "c22ede52ecafdb0b", "92ba32b63108bc65", "7f4584444ed451a4"),
+    ((96, 96, 96), 4, 8): ("2ba3f7c74c2f5b3a", "5305c4a9a77c6f58", "f7a2f50e5c17a51a", "11d736ebdfd8b55c", "87f9d32f68641440"),
+}
+
+
+@pytest.mark.parametrize("shape,batch,depth", list(TRAIN_BITS))
+def test_training_bits(dev, shape, batch, depth):
+    import torch
+    from paper_1609_03782_amd import surrogate as sg
+    rng = np.random.default_rng(sum(shape) + batch)
+    net = sg.Surrogate(depth=depth, seed=2, lr=3e-4)
+    w = net.get_weights()
+    net.set_weights((w + 0.02 * rng.standard_normal(w.size)).astype(np.float32))
+    xs = [torch.from_numpy(rng.standard_normal(shape, dtype=np.float32)).to(dev) for _ in range(batch)]
+    ts = [x + 0.5 * torch.from_numpy(rng.standard_normal(shape, dtype=np.float32)).to(dev) for x in xs]
+    got = []
+    for _ in range(3):
+        net.train_step(xs, ts)
+        got.append(_digest(net.get_grads()))
+    assert tuple(got) + (_digest(net.get_weights()), _digest(net.infer(xs[0]))) == TRAIN_BITS[shape, batch, depth]
+
+
+@pytest.mark.parametrize("shape,batch", [((37, 20, 70), 4), ((5, 4, 9), 16), ((48, 64, 64), 8)])
+def test_training_gradient_adds_cube_after_cube(dev, shape, batch):
+    """A batch's gradient is the FP32 sum of its cubes' gradients in their order, bit
+    for bit (a power-of-two batch scales every value exactly), however many cubes
+    share a launch."""
+    import torch
+    from paper_1609_03782_amd import surrogate as sg
+    Ws, bs = _net(4, seed=9)
+    net = sg.Surrogate(depth=4, seed=2, lr=1e-12)
+    net.set_weights(sg.join_params([W.astype(np.float32) for W in Ws], [b.astype(np.float32) for b in bs]))
+    gen = torch.Generator(device=dev).manual_seed(3)
+    xs = [torch.randn(shape, generator=gen, device=dev) for _ in range(batch)]
+    ts = [x + 0.5 * torch.randn(shape, generator=gen, device=dev) for x in xs]
+    net.train_step(xs, ts)
+    g = net.get_grads()
+    want = np.zeros_like(g)
+    for x, t in zip(xs, ts):
+        net.train_step([x], [t])
+        want += net.get_grads() / np.float32(batch)
+    assert np.array_equal(g, want)
