@@ -92,7 +92,10 @@ ig_status ig_surrogate_last_grad_norm(const ig_surrogate* s, double* norm);
  * receives the mean squared error before the step (the call then waits).  The
  * cubes go through the layers in groups; the handle keeps the activations of
  * one (128 depth + 8 bytes per voxel, as many cubes as fit 8 GiB and at least
- * one; fewer where they cannot be allocated). */
+ * one; where they cannot be allocated fewer, for this shape from then on until
+ * another has been trained) and up to 128 MiB of partial gradients.  The order
+ * of every sum is fixed by the cubes' shape and their order in the batch: the
+ * gradient does not depend on the groups. */
 ig_status ig_surrogate_train_step(ig_surrogate* s, const float* const* d_x, const float* const* d_t, int32_t batch,
                                   int64_t nx, int64_t ny, int64_t nz, void* hip_stream, double* loss);
 

@@ -305,6 +305,8 @@ struct ig_surrogate {
     Dev clipbuf;                        // [0]: factor (float), [8..]: norm (double), [64..]: partials
     // activations, sized for the largest cube seen
     long cap = 0;
+    int fit = 0;                        // cubes of shape fit_n a training step has memory for, where more failed
+    int64_t fit_n[3] = {0, 0, 0};
     std::vector<Dev> act, pre;          // act[0] 1 channel, act[1..L-1] 32; pre[1..L-1]
     Dev y, dy, dzA, dzB, part, parts, sub_x, sub_y, tmp;
     // inference: the bf16 input and two 32-channel buffers used in turn
@@ -512,16 +514,27 @@ extern "C" ig_status ig_surrogate_train_step(ig_surrogate* s, const float* const
     // The cubes go through the layers in groups, a launch per layer and group: one
     // cube of 96^3 gives each compute unit 14 planes, too few for the kernels'
     // set-up.  What a group keeps stays below kTrainBytes (more than one cube only);
-    // a group that cannot be allocated is halved.  No sum depends on the group.
+    // a group that cannot be allocated is halved, and what fitted is kept for this
+    // shape, so that the next step does not try again.  No sum depends on the group.
     const WgradPlan wide = wgrad_plan(32, 32, nx, ny, nz);   // the largest layer's partials
     const long per_cube = n * (128L * s->L + 8);
     int group = (int)std::max<long>(1, std::min<long>(batch, kTrainBytes / per_cube));
+    const bool known = s->fit_n[0] == nx && s->fit_n[1] == ny && s->fit_n[2] == nz;
+    if (known) group = std::min(group, s->fit);
     ig_status rc;
-    for (;; group /= 2) {
+    for (bool halved = false;; group /= 2, halved = true) {
         rc = ensure_acts(s, n * group);
         if (rc == IG_OK) {
             const hipError_t e = s->part.ensure((size_t)wide.bytes() * std::min<long>(group, wide.cubes()));
-            if (e == hipSuccess) break;
+            if (e == hipSuccess) {
+                if (halved) {
+                    s->fit = group;
+                    s->fit_n[0] = nx; s->fit_n[1] = ny; s->fit_n[2] = nz;
+                } else if (!known) {
+                    s->fit_n[0] = 0;
+                }
+                break;
+            }
             rc = fail(e == hipErrorOutOfMemory ? IG_ERR_OUT_OF_MEMORY : IG_ERR_DEVICE, "weight-gradient partials: %s",
                       hipGetErrorString(e));
         }

@@ -612,3 +612,29 @@ def test_training_gradient_adds_cube_after_cube(dev, shape, batch):
         net.train_step([x], [t])
         want += net.get_grads() / np.float32(batch)
     assert np.array_equal(g, want)
+
+
+def test_training_group_that_fits_is_remembered(dev):
+    """An allocation that fails halves the group of cubes of a training step: the
+    same bits, and the steps that follow on this shape allocate nothing."""
+    import torch
+    import paper_1609_03782_amd as ig
+    from paper_1609_03782_amd import surrogate as sg
+    shape, batch = (17, 20, 37), 8
+    gen = torch.Generator(device=dev).manual_seed(4)
+    xs = [torch.randn(shape, generator=gen, device=dev) for _ in range(batch)]
+    ts = [x + 0.5 * torch.randn(shape, generator=gen, device=dev) for x in xs]
+    nets = [sg.Surrogate(depth=4, seed=2, lr=3e-4) for _ in range(2)]
+    L = ig.lib()
+    try:
+        for step in range(3):
+            nets[0].train_step(xs, ts)
+            if step < 2:      # two halvings, then a failure that must find no allocation to hit
+                L.ig_debug_fail_alloc(2 if step == 0 else 1)
+            nets[1].train_step(xs, ts)
+            assert np.array_equal(nets[0].get_grads(), nets[1].get_grads())
+            if step == 1:
+                with pytest.raises(ig.IgError):   # still pending: the step made no allocation
+                    ig.Filter((4, 4, 4))
+    finally:
+        L.ig_debug_fail_alloc(0)
