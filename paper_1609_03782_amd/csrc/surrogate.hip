@@ -358,6 +358,7 @@ ig_status to_bf16(const float* x, void* a, long n, hipStream_t st);
 
 ig_status ensure_infer(ig_surrogate* s, long n) {
     if (n <= s->icap) return IG_OK;
+    s->icap = 0;   // until every buffer has grown
     HIP_TRY(s->iact0.ensure(n * 2));
     HIP_TRY(s->iact[0].ensure(n * 32 * 2));
     HIP_TRY(s->iact[1].ensure(n * 32 * 2));

@@ -638,3 +638,23 @@ def test_training_group_that_fits_is_remembered(dev):
                     ig.Filter((4, 4, 4))
     finally:
         L.ig_debug_fail_alloc(0)
+
+
+def test_inference_after_a_failed_allocation(dev):
+    """A prediction that could not get its buffers leaves a handle that predicts: the
+    buffer that failed is not taken for one of the size of before."""
+    import torch
+    import paper_1609_03782_amd as ig
+    from paper_1609_03782_amd import surrogate as sg
+    net = sg.Surrogate(depth=4, seed=3)
+    gen = torch.Generator(device=dev).manual_seed(5)
+    small, big = (torch.randn(s, generator=gen, device=dev) for s in ((6, 9, 33), (12, 17, 65)))
+    ref = net.infer(small)
+    for nth in (1, 2, 3):
+        try:
+            ig.lib().ig_debug_fail_alloc(nth)
+            with pytest.raises(ig.IgError):
+                net.infer(big if nth == 1 else big.repeat(nth, 1, 1))
+        finally:
+            ig.lib().ig_debug_fail_alloc(0)
+        assert torch.equal(net.infer(small), ref)
