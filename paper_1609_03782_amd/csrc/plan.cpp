@@ -83,8 +83,9 @@ void auto_vec_rows(int64_t nx, int* V, int* R) {
 // (T = 2; nx 40 .. 1024, ny 90 .. 700, nz 32 .. 490; RMS deviation 9 %): what a
 // wavefront adds grows with its V; rows that do not end on a chunk (`ragged`)
 // and chunks of an odd number of voxels (more load instructions) cost extra,
-// and so do several rows per wavefront.  Fitted to the exponential conductance;
-// the others rank the layouts alike.
+// and so do several rows per wavefront.  Fitted to the exponential conductance; the
+// others gain as much in the mean (rational 1.20, intensity 1.17, exponential 1.18
+// over passes of depth 2 of 950 random shapes).
 namespace {
 struct StepCost {
     double c, v, w, vw, ragged_v, ragged_vw, odd_vw, rows, rows_w;
@@ -142,19 +143,25 @@ double step_weight(int V, int R, int waves, bool ragged) { return step_us(kCost3
 // power-of-two chunk that covers the row (auto_vec_rows) with 12 wavefronts;
 // another chunk (fewer idle lanes: 300 voxels fill 94 % of 64 lanes of 5 and
 // 59 % of 64 lanes of 8), row count or wavefront count replaces it when its
-// predicted pass is 5 % shorter (10 % with 16-bit storage, where the line fits
-// less well: at 5 % a few rows of several x tiles lost up to 6 %).  Measured against the starting point over the
-// fitted passes: 1.21x (FP32), 1.13x (bf16) in the mean, none slower by more
-// than 2 %; 300 x 400 x 490 FP32 508 -> 787, 187 x 181 x 149 564 -> 756, 600 x
-// 400 x 200 419 -> 603 Gvoxel-iter/s.  Odd chunks exist for FP32 only (16-bit
-// rows move in whole 32-bit words).
+// predicted pass is shorter by kGain, or by kGainUnsure where the line fits less
+// well: with several x tiles, and where the starting point's one y tile holds all
+// rows (its idle wavefronts cost less than the line says).  At a gain of 5 % (10 %
+// with 16-bit storage) for all, 90 of 4500 random shapes whose layout changed (all
+// conductances and types, 1 to 10 steps) were slower by more than 3 %, up to 17 %
+// (6 x 360 x 650: 16 wavefronts); at these gains 13, most of them single passes of 10
+// us, and the mean gain is 1.137 instead of 1.152.  Over the fitted passes: 1.21x
+// (FP32), 1.13x (bf16) in the mean; 300 x 400 x 490 FP32 508 -> 787, 187 x 181 x 149
+// 564 -> 756, 600 x 400 x 200 419 -> 603 Gvoxel-iter/s.  Odd chunks exist for FP32
+// only (16-bit rows move in whole 32-bit words).
+constexpr double kGain = 1.10, kGainUnsure = 1.25;
 void auto_layout(const ig_params& p, int T, bool grouped, int* V, int* R, int* W) {
     auto_vec_rows(p.nx, V, R);
     *W = 12;
     if (stream_lds_bytes(*V, T, *W) > kMaxLds) *W = 8;
     if (T > 2 || p.nx < 4) return;
     const double base = pass_cost(p, *V, *R, *W, T, grouped);
-    double best = (p.dtype == IG_F32 ? 0.95 : 0.90) * base;
+    double best = base;
+    const bool one_y = p.ny <= (int64_t)*W * *R;
     const bool wide = *V == 8;   // 16 wavefronts of 8 voxels: chosen below, on their own measurements
     for (int r : {1, 2, 4})
         for (int v = 3; v <= 8; ++v) {
@@ -165,7 +172,8 @@ void auto_layout(const ig_params& p, int T, bool grouped, int* V, int* R, int* W
             for (int w : {3, 4, 5, 6, 8, 10, 12, 16}) {
                 if (v == 8 && (w != 12 || !wide)) continue;
                 const double c = pass_cost(p, v, r, w, T, grouped);
-                if (c < best) {
+                const double gain = one_y || 64 / r * v < p.nx ? kGainUnsure : kGain;
+                if (c * gain < base && c < best) {
                     best = c;
                     *V = v; *R = r; *W = w;
                 }

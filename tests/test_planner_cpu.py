@@ -227,3 +227,26 @@ def test_auto_schedule_takes_16_waves_for_fp32_only():
         assert s["waves"] == 12 and s["t_block"] == 2, (dt, s)
     # one step: no temporal blocking, no grouped 16-wave plan
     assert ig.schedule_auto((512, 512, 512), n_iter=1)["t_block"] == 1
+
+
+# passes that measured 3 to 17 % slower with the layout that the cost line predicted
+# to be a little shorter: several x tiles, one y tile, small predicted gains
+@pytest.mark.parametrize("shape,kw", [
+    ((6, 360, 650), dict(cond="pm_exp")), ((8, 265, 934), dict(cond="pm_exp")), ((7, 251, 557), dict(cond="pm_rational")),
+    ((345, 21, 40), dict(cond="intensity")), ((427, 13, 197), dict(cond="intensity")), ((66, 8, 801), dict(cond="pm_exp")),
+    ((130, 15, 1099), dict(cond="intensity")), ((57, 280, 235), dict(cond="pm_rational")),
+    ((19, 226, 560), dict(cond="pm_exp", dtype="f16")), ((464, 10, 110), dict(cond="pm_exp", dtype="bf16"))])
+def test_automatic_layout_keeps_its_starting_point(shape, kw):
+    nx = shape[2]
+    vec, rows = (4, 1) if nx > 512 else (8, 1) if nx > 256 else (4, 4 if nx <= 64 else 2 if nx <= 128 else 1)
+    s = ig.schedule_auto(shape, **kw)
+    assert (s["vec"], s["rows"], s["waves"]) == (vec, rows, 12)
+
+
+@pytest.mark.parametrize("shape,kw,layout", [
+    ((32, 64, 64), {}, (4, 4)), ((149, 181, 187), dict(cond="intensity"), (3, 1)), ((490, 400, 300), dict(dtype="bf16"), (6, 1)),
+    ((61, 700, 1000), dict(cond="pm_rational"), (5, 1)), ((512, 512, 512), {}, (8, 1))])
+def test_automatic_layout_where_it_pays(shape, kw, layout):
+    s = ig.schedule_auto(shape, **kw)
+    assert (s["vec"], s["rows"]) == layout
+    assert s["waves"] == {4: 3, 3: 16, 6: 16, 5: 16, 8: 16}[layout[0]]
