@@ -14,6 +14,8 @@
 
 #include <stdint.h>
 
+#include "igfilter.h"
+
 #ifdef __cplusplus
 extern "C" {
 #endif
@@ -37,6 +39,11 @@ void ig_debug_release_caches(void);
  * Returns the previous limit.  Host only; process-wide: lets tests exercise
  * the tiled path on small cubes. */
 int64_t ig_debug_set_infer_piece_limit(int64_t voxels);
+
+/* The schedules ig_filter_autotune times for p on ncu compute units, the
+ * automatic one first; writes at most cap of them to out and returns how many
+ * there are (-1: bad arguments).  Host only. */
+int32_t ig_debug_tune_candidates(const ig_params* p, int32_t ncu, ig_schedule* out, int32_t cap);
 
 #ifdef __cplusplus
 }

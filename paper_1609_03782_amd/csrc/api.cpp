@@ -591,8 +591,8 @@ std::string tune_key(const ig_filter* f, const char* arch) {
     return buf;
 }
 
-// The tuner's candidate: the automatic schedule's lanes (voxels and rows) for
-// this many wavefronts where they can serve, else the power-of-two ones.
+// The automatic schedule's lanes (voxels and rows) for this depth and many
+// wavefronts where they can serve, else the power-of-two ones.
 ig_schedule tuned_schedule(const ig_params& p, int T, int W, int rounds) {
     ig_schedule s{IG_SCHED_BLOCKED, T, W, 0, 0, rounds, 0};
     ig_params q = p;
@@ -605,6 +605,31 @@ ig_schedule tuned_schedule(const ig_params& p, int T, int W, int rounds) {
         if (plan_pass(p, s, T, 256, &pp)) s.vec = s.rows = 0;
     }
     return s;
+}
+
+// The schedules that the tuner times, those that can serve: the automatic one, and
+// for every depth, 8, 12 and 16 wavefronts and one or two rounds the power-of-two
+// lanes and those of the automatic schedule.
+std::vector<ig_schedule> tune_candidates(const ig_params& p, int ncu) {
+    std::vector<ig_schedule> all;
+    auto add = [&](ig_schedule s) {
+        if (s.vec == 0) auto_vec_rows(p.nx, &s.vec, &s.rows);
+        for (const ig_schedule& t : all)
+            if (std::memcmp(&s, &t, sizeof s) == 0) return;
+        PassPlan pp;
+        for (int T = 1; T <= s.t_block; ++T)
+            if (plan_pass(p, s, T, ncu, &pp)) return;
+        all.push_back(s);
+    };
+    const ig_schedule a = igk_auto_schedule(&p);
+    if (a.kind == IG_SCHED_BLOCKED) add(a);
+    for (int T = 1; T <= std::max(1, std::min(4, p.n_iter)); ++T)
+        for (int W : {8, 12, 16})
+            for (int R : {1, 2}) {
+                add(ig_schedule{IG_SCHED_BLOCKED, T, W, 0, 0, R, 0});
+                add(tuned_schedule(p, T, W, R));
+            }
+    return all;
 }
 
 // Look the key up in the cache file (lines: {"key": "...", "t_block": T, "waves": W, "rounds": R, "ms": x})
@@ -639,6 +664,13 @@ void tune_store(const char* path, const std::string& key, const ig_schedule& s, 
 }
 }  // namespace
 
+extern "C" int32_t ig_debug_tune_candidates(const ig_params* p, int32_t ncu, ig_schedule* out, int32_t cap) {
+    if (igk_validate_params(p) != IG_OK || ncu < 1) return -1;
+    const std::vector<ig_schedule> all = tune_candidates(*p, ncu);
+    for (size_t k = 0; out && k < all.size() && k < (size_t)cap; ++k) out[k] = all[k];
+    return (int32_t)all.size();
+}
+
 extern "C" ig_status ig_filter_autotune(ig_filter* f, const void* d_in, void* d_work, void* hip_stream,
                                         ig_schedule* best, double* best_ms) {
     if (!f || !d_in || !d_work || !best) return fail(IG_ERR_INVALID_ARG, "NULL argument");
@@ -669,22 +701,17 @@ extern "C" ig_status ig_filter_autotune(ig_filter* f, const void* d_in, void* d_
     HIP_TRY(hipEventCreate(&e1));
     double best_t = 1e300;
     ig_schedule best_s{};
-    const int maxT = std::max(1, std::min(4, f->p.n_iter));
-    for (int T = 1; T <= maxT; ++T)
-        for (int W : {8, 12, 16})
-            for (int R : {1, 2}) {
-                ig_schedule c = tuned_schedule(f->p, T, W, R);
-                if (check_schedule(&f->p, &c, f->ncu) != IG_OK) continue;
-                if (ig_filter_set_schedule(f, &c) != IG_OK) continue;
-                ig_status st = ig_filter_run(f, d_in, d_work, hip_stream, nullptr);   // warm-up + plan upload
-                if (st != IG_OK) { (void)hipEventDestroy(e0); (void)hipEventDestroy(e1); return st; }
-                float ms = 0.0f;
-                if (hipEventRecord(e0, stream) != hipSuccess) continue;
-                for (int k = 0; k < 2; ++k) (void)ig_filter_run(f, d_in, d_work, hip_stream, nullptr);
-                if (hipEventRecord(e1, stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess) continue;
-                if (hipEventElapsedTime(&ms, e0, e1) != hipSuccess) continue;
-                if (ms / 2 < best_t) { best_t = ms / 2; best_s = c; }
-            }
+    for (const ig_schedule& c : tune_candidates(f->p, f->ncu)) {
+        if (ig_filter_set_schedule(f, &c) != IG_OK) continue;
+        ig_status st = ig_filter_run(f, d_in, d_work, hip_stream, nullptr);   // warm-up + plan upload
+        if (st != IG_OK) { (void)hipEventDestroy(e0); (void)hipEventDestroy(e1); return st; }
+        float ms = 0.0f;
+        if (hipEventRecord(e0, stream) != hipSuccess) continue;
+        for (int k = 0; k < 2; ++k) (void)ig_filter_run(f, d_in, d_work, hip_stream, nullptr);
+        if (hipEventRecord(e1, stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess) continue;
+        if (hipEventElapsedTime(&ms, e0, e1) != hipSuccess) continue;
+        if (ms / 2 < best_t) { best_t = ms / 2; best_s = c; }
+    }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (best_t >= 1e300) return fail(IG_ERR_UNSUPPORTED, "no blocked schedule serves this shape");

@@ -250,3 +250,22 @@ def test_automatic_layout_where_it_pays(shape, kw, layout):
     s = ig.schedule_auto(shape, **kw)
     assert (s["vec"], s["rows"]) == layout
     assert s["waves"] == {4: 3, 3: 16, 6: 16, 5: 16, 8: 16}[layout[0]]
+
+
+@pytest.mark.parametrize("shape", [(32, 64, 64), (149, 181, 187), (61, 700, 1000), (30, 20, 90), (5, 3, 300), (24, 60, 441),
+                                   (1, 1, 1), (512, 512, 512)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n_iter", [1, 7])
+def test_tuner_times_the_automatic_schedule_and_the_power_of_two_lanes(shape, dtype, n_iter):
+    import ctypes
+    p = ig.make_params(shape, dtype=dtype, n_iter=n_iter)
+    buf = (ig.IgSchedule * 64)()
+    n = ig.lib().ig_debug_tune_candidates(ctypes.byref(p), 256, buf, 64)
+    got = [ig._sched_dict(s) for s in buf[:n]]
+    auto = ig.schedule_auto(shape, dtype=dtype, n_iter=n_iter)
+    assert 0 < n <= 37 and got[0] == auto and all(got.count(s) == 1 for s in got)
+    for s in got:
+        assert ig.schedule_check(shape, s, dtype=dtype, n_iter=n_iter) is None, s
+    nx = shape[2]
+    vec = 4 if nx > 512 else 8 if nx > 256 else 4 if nx >= 4 else 1
+    assert {8, 12, 16} <= {s["waves"] for s in got if s["vec"] == vec and s["t_block"] == 1}
