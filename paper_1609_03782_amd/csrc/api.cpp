@@ -632,8 +632,10 @@ std::vector<ig_schedule> tune_candidates(const ig_params& p, int ncu) {
     return all;
 }
 
-// Look the key up in the cache file (lines: {"key": "...", "t_block": T, "waves": W, "rounds": R, "ms": x})
-bool tune_lookup(const char* path, const ig_params& p, const std::string& key, ig_schedule* s) {
+// Look the key up in the cache file (lines: {"key": "...", "t_block": T, "waves": W,
+// "rounds": R, "vec": V, "rows": K, "ms": x}; lines without vec and rows were measured
+// with the power-of-two lanes)
+bool tune_lookup(const char* path, const std::string& key, ig_schedule* s) {
     FILE* fp = fopen(path, "r");
     if (!fp) return false;
     char line[1024];
@@ -647,7 +649,11 @@ bool tune_lookup(const char* path, const ig_params& p, const std::string& key, i
         const char* c = strstr(line, "\"rounds\":");
         if (a && b && c && sscanf(a, "\"t_block\": %d", &T) == 1 && sscanf(b, "\"waves\": %d", &W) == 1 &&
             sscanf(c, "\"rounds\": %d", &R) == 1) {
-            *s = tuned_schedule(p, T, W, R);
+            int V = 0, K = 0;
+            const char* d = strstr(line, "\"vec\":");
+            const char* e = strstr(line, "\"rows\":");
+            if (!(d && e && sscanf(d, "\"vec\": %d", &V) == 1 && sscanf(e, "\"rows\": %d", &K) == 1)) V = K = 0;
+            *s = ig_schedule{IG_SCHED_BLOCKED, T, W, 0, V, R, K};
             found = true;   // the last entry for a key wins
         }
     }
@@ -658,8 +664,8 @@ bool tune_lookup(const char* path, const ig_params& p, const std::string& key, i
 void tune_store(const char* path, const std::string& key, const ig_schedule& s, double ms) {
     FILE* fp = fopen(path, "a");
     if (!fp) return;
-    fprintf(fp, "{\"key\": \"%s\", \"t_block\": %d, \"waves\": %d, \"rounds\": %d, \"ms\": %.6f}\n", key.c_str(),
-            s.t_block, s.waves, s.rounds, ms);
+    fprintf(fp, "{\"key\": \"%s\", \"t_block\": %d, \"waves\": %d, \"rounds\": %d, \"vec\": %d, \"rows\": %d, \"ms\": %.6f}\n",
+            key.c_str(), s.t_block, s.waves, s.rounds, s.vec, s.rows, ms);
     fclose(fp);
 }
 }  // namespace
@@ -688,7 +694,7 @@ extern "C" ig_status ig_filter_autotune(ig_filter* f, const void* d_in, void* d_
     const std::string key = tune_key(f, prop.gcnArchName);
     const char* cache = getenv("IG_TUNE_CACHE");
     ig_schedule s{};
-    if (cache && *cache && tune_lookup(cache, f->p, key, &s) && check_schedule(&f->p, &s, f->ncu) == IG_OK) {
+    if (cache && *cache && tune_lookup(cache, key, &s) && check_schedule(&f->p, &s, f->ncu) == IG_OK) {
         ig_status st = ig_filter_set_schedule(f, &s);
         if (st != IG_OK) return st;
         *best = resolve_schedule(f);

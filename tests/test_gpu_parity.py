@@ -409,3 +409,40 @@ def test_scan_launch_forms(dev, shape, dtype, n_iter):
         f.run(x, out=x)
         torch.cuda.synchronize()
         assert bool(torch.isnan(x).all())
+
+
+def test_tuning_file_keeps_the_lanes(dev, tmp_path, monkeypatch):
+    """A tuning file's line holds the lanes that were measured; one without them (as
+    written before they were kept) means the power-of-two lanes it was measured
+    with, and one whose lanes cannot serve is not used."""
+    import json
+    import torch
+    import paper_1609_03782_amd as ig
+    shape = (30, 20, 90)
+    assert ig.schedule_auto(shape)["vec"] == 3
+    x = torch.randn(shape, generator=torch.Generator(device=dev).manual_seed(2), device=dev)
+    path = tmp_path / "tune.jsonl"
+    monkeypatch.setenv("IG_TUNE_CACHE", str(path))
+
+    def tuned():
+        f = ig.Filter(shape, n_iter=6)
+        best, ms = f.autotune(x)
+        y = f.run(x)
+        torch.cuda.synchronize()
+        f.close()
+        return best, ms, y
+
+    best, ms, ref = tuned()
+    line = json.loads(path.read_text().splitlines()[-1])
+    assert ms > 0 and all(line[k] == best[k] for k in ("t_block", "waves", "rounds", "vec", "rows"))
+    again, ms, y = tuned()
+    assert ms < 0 and again == best and torch.equal(y, ref)
+    for lanes, want in (({}, (4, 2)), ({"vec": 3, "rows": 2}, (3, 2)), ({"vec": 7, "rows": 1}, None)):
+        new = dict(key=line["key"], t_block=2, waves=8, rounds=1, **lanes, ms=1.0)
+        path.write_text(json.dumps(new) + "\n")
+        got, ms, y = tuned()
+        assert torch.equal(y, ref)
+        if want is None:
+            assert ms > 0
+        else:
+            assert ms < 0 and (got["vec"], got["rows"], got["waves"]) == want + (8,)
