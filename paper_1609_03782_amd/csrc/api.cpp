@@ -235,7 +235,7 @@ static ig_schedule resolve_schedule(const ig_filter* f) {
         // the choice depends on the shape and type (fixed) and on n_iter
         // through the pass depth only: made once per depth
         const int d = f->p.n_iter >= 2;
-        if (f->autosched[d].kind == IG_SCHED_AUTO) f->autosched[d] = igk_auto_schedule(&f->p);
+        if (f->autosched[d].kind == IG_SCHED_AUTO) f->autosched[d] = igk_auto_schedule(&f->p, true, f->ncu);
         return f->autosched[d];
     }
     ig_schedule s = f->sched;
@@ -272,7 +272,7 @@ extern "C" ig_status ig_schedule_check(const ig_params* p, const ig_schedule* s)
     ig_status st = igk_validate_params(p);
     if (st != IG_OK) return st;
     if (!s) return fail(IG_ERR_INVALID_ARG, "schedule is NULL");
-    return check_schedule(p, s, 256);
+    return check_schedule(p, s, kFullCus);
 }
 
 extern "C" ig_status ig_schedule_plan(const ig_params* p, const ig_schedule* s, int32_t t_block, int32_t ncu,
@@ -593,16 +593,16 @@ std::string tune_key(const ig_filter* f, const char* arch) {
 
 // The automatic schedule's lanes (voxels and rows) for this depth and many
 // wavefronts where they can serve, else the power-of-two ones.
-ig_schedule tuned_schedule(const ig_params& p, int T, int W, int rounds) {
+ig_schedule tuned_schedule(const ig_params& p, int ncu, int T, int W, int rounds) {
     ig_schedule s{IG_SCHED_BLOCKED, T, W, 0, 0, rounds, 0};
     ig_params q = p;
     q.n_iter = T;
-    const ig_schedule a = igk_auto_schedule(&q);
+    const ig_schedule a = igk_auto_schedule(&q, true, ncu);
     if (T <= 2 && a.kind == IG_SCHED_BLOCKED) {
         s.vec = a.vec;
         s.rows = a.rows;
         PassPlan pp;
-        if (plan_pass(p, s, T, 256, &pp)) s.vec = s.rows = 0;
+        if (plan_pass(p, s, T, ncu, &pp)) s.vec = s.rows = 0;
     }
     return s;
 }
@@ -621,13 +621,13 @@ std::vector<ig_schedule> tune_candidates(const ig_params& p, int ncu) {
             if (plan_pass(p, s, T, ncu, &pp)) return;
         all.push_back(s);
     };
-    const ig_schedule a = igk_auto_schedule(&p);
+    const ig_schedule a = igk_auto_schedule(&p, true, ncu);
     if (a.kind == IG_SCHED_BLOCKED) add(a);
     for (int T = 1; T <= std::max(1, std::min(4, p.n_iter)); ++T)
         for (int W : {8, 12, 16})
             for (int R : {1, 2}) {
                 add(ig_schedule{IG_SCHED_BLOCKED, T, W, 0, 0, R, 0});
-                add(tuned_schedule(p, T, W, R));
+                add(tuned_schedule(p, ncu, T, W, R));
             }
     return all;
 }

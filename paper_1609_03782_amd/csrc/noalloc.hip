@@ -110,7 +110,7 @@ ig_status static_plan(void* self, const ig_schedule& sched, int T, const PassPla
 ig_schedule static_schedule(const ig_params& p, int ncu) {
     // the static tables hold a regular grid, not a grouped plan (equal shares
     // of the tiles' planes)
-    ig_schedule s = igk_auto_schedule(&p, false);
+    ig_schedule s = igk_auto_schedule(&p, false, ncu);
     if (s.kind != IG_SCHED_BLOCKED) return s;
     s.rounds = 0;
     s.zchunk = (int)p.nz;

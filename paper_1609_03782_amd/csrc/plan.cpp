@@ -100,11 +100,10 @@ double step_us(const StepCost& k, int V, int R, double Wt, bool ragged) {
     return c;
 }
 constexpr double kPassFixed = 3.0;   // a launch, and the fill of its first workgroups
-constexpr int kPlanCus = 256;
 
 // The pass of depth T with layout (V, R, W) as plan_pass splits it, without the
 // piece table; 1e300 if the layout cannot serve the shape.
-double pass_cost(const ig_params& p, int V, int R, int W, int T, bool grouped) {
+double pass_cost(const ig_params& p, int V, int R, int W, int T, int ncu, bool grouped) {
     const long nx = p.nx, ny = p.ny, nz = p.nz;
     if (V > nx || (R > 1 && (64 / R) * V < nx)) return 1e300;
     if ((long)W * R * nx * (long)dtype_size(p.dtype) >= (1L << 30)) return 1e300;
@@ -122,7 +121,7 @@ double pass_cost(const ig_params& p, int V, int R, int W, int T, bool grouped) {
         nty = (ny + oy - 1) / oy;
     }
     const double tiles = (double)ntx * nty;
-    const long per_cu = resident_per_cu(W, lds), slots = kPlanCus * per_cu;
+    const long per_cu = resident_per_cu(W, lds), slots = (long)ncu * per_cu;
     const double rounds = std::max(1.0, std::ceil(tiles / slots));
     const double G = std::min(slots * rounds, tiles * nz);
     const double pieces = std::max(1.0, std::min((double)nz, std::floor(G / tiles)));
@@ -132,7 +131,7 @@ double pass_cost(const ig_params& p, int V, int R, int W, int T, bool grouped) {
         if (even < 0.97 * steps) steps = std::ceil(even);
     }
     steps *= rounds;
-    const double Wt = W * std::min((double)per_cu, std::ceil(G / kPlanCus));
+    const double Wt = W * std::min((double)per_cu, std::ceil(G / ncu));
     return kPassFixed + steps * step_us(p.dtype == IG_F32 ? kCost32 : kCost16, V, R, Wt, nx % V != 0);
 }
 }  // namespace
@@ -154,12 +153,12 @@ double step_weight(int V, int R, int waves, bool ragged) { return step_us(kCost3
 // 564 -> 756, 600 x 400 x 200 419 -> 603 Gvoxel-iter/s.  Odd chunks exist for FP32
 // only (16-bit rows move in whole 32-bit words).
 constexpr double kGain = 1.10, kGainUnsure = 1.25;
-void auto_layout(const ig_params& p, int T, bool grouped, int* V, int* R, int* W) {
+void auto_layout(const ig_params& p, int T, int ncu, bool grouped, int* V, int* R, int* W) {
     auto_vec_rows(p.nx, V, R);
     *W = 12;
     if (stream_lds_bytes(*V, T, *W) > kMaxLds) *W = 8;
     if (T > 2 || p.nx < 4) return;
-    const double base = pass_cost(p, *V, *R, *W, T, grouped);
+    const double base = pass_cost(p, *V, *R, *W, T, ncu, grouped);
     double best = base;
     const bool one_y = p.ny <= (int64_t)*W * *R;
     const bool wide = *V == 8;   // 16 wavefronts of 8 voxels: chosen below, on their own measurements
@@ -171,7 +170,7 @@ void auto_layout(const ig_params& p, int T, bool grouped, int* V, int* R, int* W
             if (p.dtype != IG_F32 && (v & 1)) continue;
             for (int w : {3, 4, 5, 6, 8, 10, 12, 16}) {
                 if (v == 8 && (w != 12 || !wide)) continue;
-                const double c = pass_cost(p, v, r, w, T, grouped);
+                const double c = pass_cost(p, v, r, w, T, ncu, grouped);
                 const double gain = one_y || 64 / r * v < p.nx ? kGainUnsure : kGain;
                 if (c * gain < base && c < best) {
                     best = c;
@@ -241,12 +240,13 @@ const char* plan_pass(const ig_params& p, const ig_schedule& s, int T, int ncu, 
     const int W = s.waves;
     if (!(V == 1 || V == 2 || V == 4 || V == 8)) {
         // the other chunks only as the automatic schedule chooses them (for passes
-        // of depth 1 or 2, with or without grouped plans); deeper passes of a
-        // schedule that names one run the power-of-two layout
+        // of depth 1 or 2, with or without grouped plans, on this many compute units
+        // or a whole GPU's); deeper passes of a schedule that names one run the
+        // power-of-two layout
         bool ours = any_chunk;
-        for (int k = 0; k < 4 && !ours; ++k) {
+        for (int k = 0; k < 8 && !ours; ++k) {
             int av, ar, aw;
-            auto_layout(p, 1 + (k & 1), k < 2, &av, &ar, &aw);
+            auto_layout(p, 1 + (k & 1), k < 4 ? ncu : kFullCus, k & 2, &av, &ar, &aw);
             ours = V == av && R == ar;
         }
         if (!ours) return "vec must be 1, 2, 4 or 8";
@@ -393,11 +393,11 @@ const char* plan_pass(const ig_params& p, const ig_schedule& s, int T, int ncu, 
 }
 
 // Heuristic schedule when no tuned entry exists.
-ig_schedule igk_auto_schedule(const ig_params* p, bool grouped) {
+ig_schedule igk_auto_schedule(const ig_params* p, bool grouped, int ncu) {
     ig_schedule s{};
     s.kind = IG_SCHED_BLOCKED;
     s.t_block = std::max(1, std::min(2, p->n_iter));
-    auto_layout(*p, s.t_block, grouped, &s.vec, &s.rows, &s.waves);
+    auto_layout(*p, s.t_block, ncu, grouped, &s.vec, &s.rows, &s.waves);
     s.zchunk = 0;
     s.rounds = 1;
     // 16 wavefronts (four per SIMD, 12 output rows per tile) when their
@@ -414,7 +414,7 @@ ig_schedule igk_auto_schedule(const ig_params* p, bool grouped) {
             ig_schedule t = s;
             t.waves = W;
             PassPlan pp;
-            if (plan_pass(*p, t, 2, 256, &pp)) return 1e300;
+            if (plan_pass(*p, t, 2, ncu, &pp)) return 1e300;
             *grouped = !pp.first.empty();
             double m = 0.0;
             for (int b = 0; b < pp.workgroups(); ++b) {

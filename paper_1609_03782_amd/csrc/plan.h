@@ -61,8 +61,9 @@ struct PassPlan {
 };
 void auto_vec_rows(int64_t nx, int* V, int* R);
 // voxels per lane, rows per wavefront and wavefronts of the automatic schedule's
-// passes of depth T; grouped: its workgroups may take grouped plans
-void auto_layout(const ig_params& p, int T, bool grouped, int* V, int* R, int* W);
+// passes of depth T on ncu compute units; grouped: its workgroups may take grouped plans
+void auto_layout(const ig_params& p, int T, int ncu, bool grouped, int* V, int* R, int* W);
+constexpr int kFullCus = 256;   // compute units of a whole MI355X: what host-only queries plan for
 int resident_per_cu(int W, size_t lds);
 // nullptr on success, else the reason schedule s cannot serve p at depth T
 // (any_chunk: the library's own choice of vec, not the caller's)
@@ -72,7 +73,7 @@ double step_weight(int V, int R, int waves, bool ragged);
 ig_status igk_validate_params(const ig_params* p);
 // The library's schedule for p when the caller sets none (grouped = false: for
 // runs whose piece tables hold no grouped plans).
-ig_schedule igk_auto_schedule(const ig_params* p, bool grouped = true);
+ig_schedule igk_auto_schedule(const ig_params* p, bool grouped = true, int ncu = kFullCus);
 // Record a thread-local message for ig_last_error() and return s.
 ig_status igk_fail(ig_status s, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
 size_t dtype_size(int dt);

@@ -269,3 +269,22 @@ def test_tuner_times_the_automatic_schedule_and_the_power_of_two_lanes(shape, dt
     nx = shape[2]
     vec = 4 if nx > 512 else 8 if nx > 256 else 4 if nx >= 4 else 1
     assert {8, 12, 16} <= {s["waves"] for s in got if s["vec"] == vec and s["t_block"] == 1}
+
+
+def test_automatic_layout_follows_the_compute_units():
+    """A partition of the GPU has fewer compute units: the automatic layout is the one
+    for them, and serves on them."""
+    import ctypes
+    differ = 0
+    for shape in ((32, 64, 64), (149, 181, 187), (24, 20, 187), (40, 30, 300), (80, 300, 702), (128, 64, 128)):
+        p = ig.make_params(shape, n_iter=6)
+        first = {}
+        for ncu in (32, 256):
+            buf = (ig.IgSchedule * 64)()
+            assert ig.lib().ig_debug_tune_candidates(ctypes.byref(p), ncu, buf, 64) > 0
+            first[ncu] = ig._sched_dict(buf[0])
+            g = ig.schedule_plan(shape, first[ncu], t_block=2, ncu=ncu, n_iter=6)
+            assert g is not None
+        differ += first[32] != first[256]
+        assert first[256] == ig.schedule_auto(shape, n_iter=6)
+    assert differ >= 3
