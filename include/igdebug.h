@@ -45,6 +45,10 @@ int64_t ig_debug_set_infer_piece_limit(int64_t voxels);
  * there are (-1: bad arguments).  Host only. */
 int32_t ig_debug_tune_candidates(const ig_params* p, int32_t ncu, ig_schedule* out, int32_t cap);
 
+/* Voxels per lane, rows per wavefront and wavefronts (layout[3]) that the
+ * handle's passes of this depth run with; zeros before the first.  Host only. */
+ig_status ig_debug_filter_layout(const ig_filter* f, int32_t depth, int32_t* layout);
+
 #ifdef __cplusplus
 }
 #endif

@@ -213,7 +213,7 @@ extern "C" ig_status ig_filter_set_params(ig_filter* f, const ig_params* p) {
     if (st != IG_OK) return st;
     if (p->nx != f->p.nx || p->ny != f->p.ny || p->nz != f->p.nz || p->dtype != f->p.dtype)
         return fail(IG_ERR_INVALID_ARG, "set_params keeps the shape and storage type of the handle");
-    // the piece tables depend on the shape, the schedule and the pass depth only
+    // the piece tables depend on the shape, a caller's schedule and the pass depth only
     f->p = *p;
     return IG_OK;
 }
@@ -230,14 +230,20 @@ extern "C" void ig_filter_destroy(ig_filter* f) {
     delete f;
 }
 
-static ig_schedule resolve_schedule(const ig_filter* f) {
-    if (f->sched.kind == IG_SCHED_AUTO) {
-        // the choice depends on the shape and type (fixed) and on n_iter
-        // through the pass depth only: made once per depth
-        const int d = f->p.n_iter >= 2;
-        if (f->autosched[d].kind == IG_SCHED_AUTO) f->autosched[d] = igk_auto_schedule(&f->p, true, f->ncu);
-        return f->autosched[d];
+// The automatic schedule of a pass of depth T (1, or 2): the choice depends on the
+// shape and type (fixed) and on the depth, and is made once for each.
+static const ig_schedule& auto_schedule(const ig_filter* f, int T) {
+    ig_schedule& s = f->autosched[T >= 2];
+    if (s.kind == IG_SCHED_AUTO) {
+        ig_params p = f->p;
+        p.n_iter = T;
+        s = igk_auto_schedule(&p, true, f->ncu);
     }
+    return s;
+}
+
+static ig_schedule resolve_schedule(const ig_filter* f) {
+    if (f->sched.kind == IG_SCHED_AUTO) return auto_schedule(f, f->p.n_iter >= 2 ? 2 : 1);
     ig_schedule s = f->sched;
     if (s.kind == IG_SCHED_BLOCKED) {
         if (s.vec == 0) {
@@ -353,8 +359,11 @@ extern "C" ig_status ig_filter_get_schedule(const ig_filter* f, ig_schedule* s) 
 // Plan (once) and upload the piece table of the pass of depth T.
 static ig_status get_plan(ig_filter* f, const ig_schedule& sched, int T, const PassPlan** out, const Piece** dev) {
     if (!f->planned[T]) {
-        // a caller's schedule was checked when it was set
-        const char* why = plan_pass(f->p, sched, T, f->ncu, &f->plans[T], true);
+        // An automatic pass of depth 1 takes the layout for that depth also where it is
+        // the remainder of deeper ones, so that a handle's plans do not depend on the
+        // step counts it has seen.  A caller's schedule was checked when it was set.
+        const bool by_depth = f->sched.kind == IG_SCHED_AUTO && auto_schedule(f, T).kind == IG_SCHED_BLOCKED;
+        const char* why = plan_pass(f->p, by_depth ? auto_schedule(f, T) : sched, T, f->ncu, &f->plans[T], true);
         if (why) return fail(IG_ERR_INVALID_ARG, "schedule cannot serve this shape: %s", why);
         // the piece table, then (grouped plans) each workgroup's first piece
         const PassPlan& pl = f->plans[T];
@@ -378,6 +387,15 @@ static ig_status handle_plan(void* self, const ig_schedule& sched, int T, const 
 }
 
 static hipError_t hook_record(void* self, hipStream_t s) { return static_cast<TimingHook*>(self)->record(); }
+
+extern "C" ig_status ig_debug_filter_layout(const ig_filter* f, int32_t depth, int32_t* layout) {
+    if (!f || !layout || depth < 1 || depth > 4) return fail(IG_ERR_INVALID_ARG, "bad argument");
+    const PassPlan& p = f->plans[depth];
+    layout[0] = f->planned[depth] ? p.V : 0;
+    layout[1] = f->planned[depth] ? p.g.R : 0;
+    layout[2] = f->planned[depth] ? p.g.W : 0;
+    return IG_OK;
+}
 
 // Enqueue the whole filter: parameters (+ scan), then the passes, then (when
 // the scan ran) the kernel that turns the output into NaN if the input held a

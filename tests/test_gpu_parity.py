@@ -446,3 +446,34 @@ def test_tuning_file_keeps_the_lanes(dev, tmp_path, monkeypatch):
             assert ms > 0
         else:
             assert ms < 0 and (got["vec"], got["rows"], got["waves"]) == want + (8,)
+
+
+@pytest.mark.parametrize("order", [(5, 1, 5), (1, 5, 1), (4, 1, 7)])
+def test_layout_does_not_depend_on_the_step_counts_before(dev, order):
+    """A handle whose step count changes runs the layout that it reports, and that a
+    new handle of this step count runs."""
+    import ctypes
+    import torch
+    import paper_1609_03782_amd as ig
+    shape = (30, 20, 45)
+    x = torch.randn(shape, generator=torch.Generator(device=dev).manual_seed(7), device=dev)
+
+    def layout(f, depth):
+        v = (ctypes.c_int32 * 3)()
+        assert ig.lib().ig_debug_filter_layout(f._h, depth, v) == 0
+        return tuple(v)
+
+    assert ig.schedule_auto(shape, n_iter=1) != ig.schedule_auto(shape, n_iter=5)
+    f = ig.Filter(shape, n_iter=order[0], rms=1.0)
+    for n in order:
+        p = ig.make_params(shape, n_iter=n, rms=1.0)
+        assert ig.lib().ig_filter_set_params(f._h, ctypes.byref(p)) == 0
+        y = f.run(x)
+        new = ig.Filter(shape, n_iter=n, rms=1.0)
+        assert torch.equal(y, new.run(x))
+        s, depth = f.schedule(), min(n, 2)
+        assert s == new.schedule() and layout(f, depth) == (s["vec"], s["rows"], s["waves"])
+        for d in range(1, depth + 1):
+            assert layout(new, d) in (layout(f, d), (0, 0, 0))
+        new.close()
+    f.close()
