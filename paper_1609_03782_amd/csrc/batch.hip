@@ -183,7 +183,7 @@ struct DevBuf {
 };
 struct BatchPlan {
     int device = 0;
-    int cond = 0, T = 1, W = 16, Z = 32;
+    int cond = 0, T = 1, W = 16;
     int persist = 0;              // 1: one persistent launch instead of one launch per round
     int grid = 0;                 // persistent launch: workgroups
     int count = 0;
@@ -260,7 +260,7 @@ std::vector<uint64_t> signature(const ig_batch_item* items, int count, int devic
     key.push_back((uint64_t)device);
     key.push_back((uint64_t)g_batch_T);
     key.push_back((uint64_t)g_batch_W);
-    key.push_back((uint64_t)g_batch_Z);
+    key.push_back((uint64_t)(g_batch_persist ? g_batch_Z : 0));   // the rounds deal shares, not chunks
     key.push_back((uint64_t)g_batch_res);
     key.push_back((uint64_t)g_batch_persist);
     for (int i = 0; i < count; ++i) {
@@ -372,7 +372,6 @@ ig_status build_plan(const ig_batch_item* items, int count, int device, BatchPla
         maxnx = std::max<long>(maxnx, p.nx);
     }
     bp->W = g_batch_W;
-    bp->Z = g_batch_Z;
     bp->persist = g_batch_persist;
     bp->T = g_batch_T > 0 ? g_batch_T : std::max(1, std::min(2, maxn));
     const int T = bp->T, W = bp->W;
@@ -380,7 +379,7 @@ ig_status build_plan(const ig_batch_item* items, int count, int device, BatchPla
     int ncu = 256;
     (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device);
 
-    // per-cube plans (pieces of ~32 planes), scratch offsets, chunk tables
+    // per-cube plans (persistent launch: pieces of ~32 planes), scratch offsets, chunk tables
     std::vector<BatchCube> cubes(count);
     std::vector<Piece> pieces;
     std::vector<SumChunk> chunks;
@@ -433,7 +432,7 @@ ig_status build_plan(const ig_batch_item* items, int count, int device, BatchPla
         s.kind = IG_SCHED_BLOCKED;
         s.t_block = T;
         s.waves = W;
-        s.zchunk = g_batch_Z;
+        s.zchunk = bp->persist ? g_batch_Z : (int)p.nz;
         // 3 voxels per lane cover rows of up to 48, 96 and 192 voxels with 4, 2
         // and 1 rows per wavefront: fewer idle lanes than 4 do
         int V, R;
@@ -452,9 +451,9 @@ ig_status build_plan(const ig_batch_item* items, int count, int device, BatchPla
         const uintptr_t al = (uintptr_t)chunk_align(pp.V, 4);
         if (((uintptr_t)cb.in % al) || ((uintptr_t)cb.out % al)) cb.g.vec = 0;
         cb.V = pp.V;
-        cb.npieces = (int)pp.pieces.size();
+        cb.npieces = bp->persist ? (int)pp.pieces.size() : 0;   // (deal_rounds makes the rounds' own)
         cb.piece_off = (int)pieces.size();
-        pieces.insert(pieces.end(), pp.pieces.begin(), pp.pieces.end());
+        pieces.insert(pieces.end(), pp.pieces.begin(), pp.pieces.begin() + cb.npieces);
         // pass depths (a remainder pass is shallower); in place with an odd count: stage
         std::vector<int>& d = depths[c];
         if (p.n_iter > 0) {
@@ -616,7 +615,7 @@ ig_status build_plan(const ig_batch_item* items, int count, int device, BatchPla
 
 static bool same_as_last(const ig_batch_item* items, int count, int device) {
     return g_last.plan && g_last.device == device && (int)g_last.items.size() == count && g_last.T == g_batch_T &&
-           g_last.W == g_batch_W && g_last.Z == g_batch_Z && g_last.res == g_batch_res &&
+           g_last.W == g_batch_W && (!g_batch_persist || g_last.Z == g_batch_Z) && g_last.res == g_batch_res &&
            g_last.persist == g_batch_persist && std::memcmp(g_last.items.data(), items, (size_t)count * sizeof(ig_batch_item)) == 0;
 }
 
@@ -731,7 +730,7 @@ extern "C" ig_status ig_filter_batch(const ig_batch_item* items, int32_t count, 
             st.nonfinite = prm[c].nonfinite;
             st.monotone = (2.0 * (double)p.tau * ((double)p.C[0] + p.C[1] + p.C[2]) <= 1.0) ? 1 : 0;
             st.schedule = bp->resident[c] ? ig_schedule{IG_SCHED_BLOCKED, bp->niter[c], bp->resident[c], (int)p.nz, 1, 0, 0}
-                                          : ig_schedule{IG_SCHED_BLOCKED, bp->T, bp->W, bp->Z, 4, 0, 0};
+                                          : ig_schedule{IG_SCHED_BLOCKED, bp->T, bp->W, g_batch_Z, 4, 0, 0};
         }
         if (prm[c].abort == 2) timed_out = true;
         else if (prm[c].abort) bad = true;

@@ -384,3 +384,32 @@ def test_rounds_deal_equal_shares_bitwise(dev, cond, t_block, waves):
         ig.batch_set_resident(32768)
         ig.batch_set_schedule(0, 16, 32)
         ig.batch_cache_clear()
+
+
+def test_rounds_do_not_depend_on_the_chunk(dev):
+    """The launches per pass round deal shares of planes: another z-chunk is the same
+    plan, kept once, and gives the same bits; the persistent launch keeps one per chunk."""
+    import torch
+    import paper_1609_03782_amd as ig
+    g = torch.Generator(device=dev).manual_seed(6)
+    xs = [torch.randn(s, generator=g, device=dev) for s in ((40, 50, 60), (33, 64, 48))]
+    outs = [torch.empty_like(x) for x in xs]
+    items = [(x, o, dict(K=2.0, tau=0.05, n_iter=5, cond="pm_exp")) for x, o in zip(xs, outs)]
+    try:
+        ig.batch_set_resident(0)
+        ig.batch_cache_clear()
+        ref = None
+        for persistent, plans in ((False, 1), (True, 3)):
+            ig.batch_set_launch(persistent)
+            for z in (16, 64):
+                ig.batch_set_schedule(2, 16, z)
+                ig.batch(items)
+                torch.cuda.synchronize()
+                ref = ref or [o.clone() for o in outs]
+                assert all(torch.equal(o, r) for o, r in zip(outs, ref))
+            assert ig.lib().ig_batch_cache_size() == plans
+    finally:
+        ig.batch_set_launch(False)
+        ig.batch_set_resident(32768)
+        ig.batch_set_schedule(0, 16, 32)
+        ig.batch_cache_clear()
