@@ -191,11 +191,10 @@ hipError_t launch_conv(int cin, int cout, int epi, const void* in, const bf16x8*
         if (epi == EPI_GELU) Z(zs_launch, 2, EPI_GELU);
         Z(zs_launch, 2, EPI_BACK_GELU);
     }
-    if (NB == 2) {
+    if (NB == 2) {   // (the residual form has one output)
         if (epi == EPI_RAW) Z(zs1_launch, 2, EPI_RAW);
         if (epi == EPI_GELU) Z(zs1_launch, 2, EPI_GELU);
-        if (epi == EPI_BACK_GELU) Z(zs1_launch, 2, EPI_BACK_GELU);
-        Z(zs1_launch, 2, EPI_RESID);
+        Z(zs1_launch, 2, EPI_BACK_GELU);
     }
     if (epi == EPI_RAW) Z(zs1_launch, 1, EPI_RAW);
     Z(zs1_launch, 1, EPI_RESID);

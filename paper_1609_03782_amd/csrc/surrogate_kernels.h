@@ -143,70 +143,34 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t raw_buffer(const void* p, int 
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
 }
 
-// Epilogue of the z-stream kernels: lane (i + 16 kg) holds D[m = 4 kg + e][n = i]
-// of each (s, nb), output channels 16 nb + 4 kg + e of voxel 16 s + i of row y,
-// plane z; four consecutive channels go out in one 8- or 16-byte store.
-// Output channels are padded to 16 NB.  aux: the bf16 pre-activation
-// [v][16 NB] (EPI_GELU, optional), the pre-activation of the layer below
-// (EPI_BACK_GELU), or the FP32 input cube for the residual (EPI_RESID, output
+// FP32 epilogues of the 1-channel z-stream kernel: lane (i + 16 kg) holds D[m = 4 kg +
+// e][n = i] of each (s, nb), output channels 16 nb + 4 kg + e of voxel 16 s + i of row
+// y, plane z; four consecutive channels go out in one 16-byte store.  Output channels
+// are padded to 16 NB.  aux: the FP32 input cube for the residual (EPI_RESID, output
 // channel 0 only).
-// The four bf16 pre-activations EPI_BACK_GELU multiplies by (0 outside the cube).
-template <int NB>
-__device__ __forceinline__ uint2 zs_pre(const void* __restrict__ aux, int s, int nb, int x0, int y, int z, int nx,
-                                        int ny, int i, int kg) {
-    const int x = x0 + 16 * s + i;
-    if (y >= ny || x >= nx) return make_uint2(0, 0);
-    const long v = (long)(z * ny + y) * nx + x;
-    return *reinterpret_cast<const uint2*>(static_cast<const u16*>(aux) + v * 16 * NB + 16 * nb + 4 * kg);
-}
-
-// pb: the pre-activations of this fragment (EPI_BACK_GELU only, from zs_pre)
-template <int NB, int EPI>
-__device__ __forceinline__ void zs_store_one(const f32x4& d, uint2 pb, int s, int nb, const float* __restrict__ bias,
-                                             void* __restrict__ out, const void* __restrict__ aux, int x0, int y, int z,
-                                             int nx, int ny, int i, int kg) {
-    constexpr int COUTP = 16 * NB;
-    const int x = x0 + 16 * s + i;
-    if (y >= ny || x >= nx) return;
-    const long v = (long)(z * ny + y) * nx + x;
-    const int n0 = 16 * nb + 4 * kg;
-    if constexpr (EPI == EPI_RAW) {
-        float4 r;
-        r.x = d[0] + (bias ? bias[n0] : 0.0f);
-        r.y = d[1] + (bias ? bias[n0 + 1] : 0.0f);
-        r.z = d[2] + (bias ? bias[n0 + 2] : 0.0f);
-        r.w = d[3] + (bias ? bias[n0 + 3] : 0.0f);
-        *reinterpret_cast<float4*>(static_cast<float*>(out) + v * COUTP + n0) = r;
-    } else if constexpr (EPI == EPI_GELU) {
-        const float z0p = d[0] + bias[n0], z1p = d[1] + bias[n0 + 1];
-        const float z2p = d[2] + bias[n0 + 2], z3p = d[3] + bias[n0 + 3];
-        if (aux)
-            *reinterpret_cast<uint2*>(const_cast<u16*>(static_cast<const u16*>(aux)) + v * COUTP + n0) =
-                pack_bf16x4(z0p, z1p, z2p, z3p);
-        *reinterpret_cast<uint2*>(static_cast<u16*>(out) + v * COUTP + n0) =
-            pack_bf16x4(gelu_fast(z0p), gelu_fast(z1p), gelu_fast(z2p), gelu_fast(z3p));
-    } else if constexpr (EPI == EPI_BACK_GELU) {
-        const float g0 = gelu_grad_fast(__uint_as_float(pb.x << 16));
-        const float g1 = gelu_grad_fast(__uint_as_float(pb.x & 0xffff0000u));
-        const float g2 = gelu_grad_fast(__uint_as_float(pb.y << 16));
-        const float g3 = gelu_grad_fast(__uint_as_float(pb.y & 0xffff0000u));
-        *reinterpret_cast<uint2*>(static_cast<u16*>(out) + v * COUTP + n0) =
-            pack_bf16x4(d[0] * g0, d[1] * g1, d[2] * g2, d[3] * g3);
-    } else {   // EPI_RESID: output channel 0 only
-        if (n0 == 0) static_cast<float*>(out)[v] = static_cast<const float*>(aux)[v] + (d[0] + bias[0]);
-    }
-}
-
 template <int NB, int EPI, int MT>
 __device__ __forceinline__ void zs_store(const f32x4 (&acc)[MT][NB], const float* __restrict__ bias,
-                                         void* __restrict__ out, const void* __restrict__ aux, int x0, int y, int z,
+                                         float* __restrict__ out, const float* __restrict__ aux, int x0, int y, int z,
                                          int nx, int ny, int i, int kg) {
+    static_assert(EPI == EPI_RAW || EPI == EPI_RESID, "FP32 outputs");
 #pragma unroll
     for (int s = 0; s < MT; ++s)
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
-            const uint2 pb = EPI == EPI_BACK_GELU ? zs_pre<NB>(aux, s, nb, x0, y, z, nx, ny, i, kg) : make_uint2(0, 0);
-            zs_store_one<NB, EPI>(acc[s][nb], pb, s, nb, bias, out, aux, x0, y, z, nx, ny, i, kg);
+            const f32x4& d = acc[s][nb];
+            const int x = x0 + 16 * s + i, n0 = 16 * nb + 4 * kg;
+            if (y >= ny || x >= nx) continue;
+            const long v = (long)(z * ny + y) * nx + x;
+            if constexpr (EPI == EPI_RAW) {
+                float4 r;
+                r.x = d[0] + (bias ? bias[n0] : 0.0f);
+                r.y = d[1] + (bias ? bias[n0 + 1] : 0.0f);
+                r.z = d[2] + (bias ? bias[n0 + 2] : 0.0f);
+                r.w = d[3] + (bias ? bias[n0 + 3] : 0.0f);
+                *reinterpret_cast<float4*>(out + v * 16 * NB + n0) = r;
+            } else {
+                if (n0 == 0) out[v] = aux[v] + (d[0] + bias[0]);
+            }
         }
 }
 
@@ -521,7 +485,8 @@ k_conv1_zs(const u16* __restrict__ in, const bf16x8* __restrict__ wp, const floa
     // 32 bf16 output channels go out through a buffer over this wavefront's row of
     // the tile: no branch, and the addresses of a plane are scalar (360 x 360 x 150
     // 560 -> 452 us, the GELU of every value what is left)
-    constexpr bool BUF = NB == 2 && (EPI == EPI_GELU || EPI == EPI_BACK_GELU);
+    constexpr bool BUF = EPI == EPI_GELU || EPI == EPI_BACK_GELU;
+    static_assert(!BUF || NB == 2, "the bf16 outputs have 32 channels");
     const int lo = i * 64 + 8 * kg;
     const int row_bytes = __builtin_amdgcn_readfirstlane(y < ny ? min(nx - x0, XW) * 64 : 0);
     const int yc = __builtin_amdgcn_readfirstlane(min(y, ny - 1));
@@ -585,7 +550,7 @@ k_conv1_zs(const u16* __restrict__ in, const bf16x8* __restrict__ wp, const floa
                     }
                 }
         } else {
-            zs_store<NB, EPI, MT>(acc, bias, out, aux, x0, y, z, nx, ny, i, kg);
+            zs_store<NB, EPI, MT>(acc, bias, static_cast<float*>(out), static_cast<const float*>(aux), x0, y, z, nx, ny, i, kg);
         }
         __syncthreads();   // every wavefront is done with slot (z - 1) before it takes plane z + 2
     };
