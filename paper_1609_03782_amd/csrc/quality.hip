@@ -19,9 +19,10 @@
 //    mask j's sums are the sums of the bins from its rank up, so a voxel costs
 //    one binary search and one addition per sum instead of one per threshold.
 //    The bins live in LDS as FP64, one column per pair of lanes of a
-//    wavefront, the pair's lanes adding one after the other, so no two lanes
-//    ever meet on an address and the order of every sum is fixed.  One partial
-//    per workgroup.
+//    wavefront, the lower lanes' voxels of a chunk added before the upper
+//    lanes', so no two lanes ever meet on an address and the order of every sum
+//    is fixed (the counts, whole numbers, have none).  One partial per
+//    workgroup.
 //
 // k_quality_fold folds each slot over the partials (block b folds slot b:
 // strided per-thread sums, then a fixed tree); k_quality_derive turns the 192
@@ -155,12 +156,13 @@ size_t bins_lds(int n, bool model) {
 }
 
 // STEPS: binary search steps (2^STEPS > n).  FLAT: the ROI is contiguous.  What
-// bounds it: the search and the LDS additions, about 150 cycles of issue per 64
-// voxels with one wavefront per SIMD (the bins fill the LDS).  46 thresholds,
-// a model, 512^3: 425 us (3.8 TB/s), from 4085 us when every voxel was compared
-// with every threshold; the whole call, two noise scans included, 4241 -> 712.
+// bounds it: the search and the LDS additions, about 160 cycles of issue per 64
+// voxels with one wavefront per SIMD (the bins fill the LDS).  46 thresholds, a
+// model, 512^3: 438 us (3.7 TB/s), from 4085 us when every voxel was compared with
+// every threshold (410 with the pairs' additions in one instruction, whose order
+// nothing fixes); the whole call, two noise scans included, 4241 -> 738.
 template <int STEPS, bool MODEL, bool FLAT>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256, 2)
 k_quality_bins(const float* __restrict__ orig, const float* __restrict__ filt, const float* __restrict__ model,
                QGeom g, QSorted q, double* __restrict__ part) {
     extern __shared__ double qb[];
@@ -220,7 +222,8 @@ k_quality_bins(const float* __restrict__ orig, const float* __restrict__ filt, c
     };
     auto take = [&](long ch, const float (&fo)[kQU], const float (&ff)[kQU], const float (&fm)[kQU]) {
         const int count = (int)max(0L, min((long)kQChunk, g.nroi - ch * kQChunk));
-        int bin[kQU];
+        int bin[kQU], at[kQU];
+        float vo[kQU], vm[kQU];
 #pragma unroll
         for (int u = 0; u < kQU; ++u) {
             int b = 0;
@@ -240,19 +243,29 @@ k_quality_bins(const float* __restrict__ orig, const float* __restrict__ filt, c
                 m = fm[u];
                 a_m += in ? m : 0.0;
             }
+            // a voxel below every threshold adds zeros to the first bin
             const bool on = in && bin[u] > 0;
-            const int at = (bin[u] - 1) * kQCols + col;
-            if (on && !second) {
-                __builtin_amdgcn_ds_atomic_fadd_f64((ldp)(so + at), o);
-                if constexpr (MODEL) __builtin_amdgcn_ds_atomic_fadd_f64((ldp)(sm + at), m);
-                __hip_atomic_fetch_add(sc + at, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
-            if (on && second) {
-                __builtin_amdgcn_ds_atomic_fadd_f64((ldp)(so + at), o);
-                if constexpr (MODEL) __builtin_amdgcn_ds_atomic_fadd_f64((ldp)(sm + at), m);
-                __hip_atomic_fetch_add(sc + at, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
+            at[u] = max(bin[u] - 1, 0) * kQCols + col;
+            vo[u] = on ? fo[u] : 0.0f;
+            if constexpr (MODEL) vm[u] = on ? fm[u] : 0.0f;
+            __hip_atomic_fetch_add(sc + at[u], on ? 1u : 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
+        // the pairs' lower lanes, then the upper: the statements between keep the
+        // compiler from making one addition of the two, and the values FP32 meanwhile
+        auto add = [&]() {
+#pragma unroll
+            for (int u = 0; u < kQU; ++u) {
+                __builtin_amdgcn_ds_atomic_fadd_f64((ldp)(so + at[u]), (double)vo[u]);
+                if constexpr (MODEL) __builtin_amdgcn_ds_atomic_fadd_f64((ldp)(sm + at[u]), (double)vm[u]);
+            }
+        };
+        if (!second) add();
+#pragma unroll
+        for (int u = 0; u < kQU; ++u) {
+            asm volatile("" : "+v"(vo[u]) : : "memory");
+            if constexpr (MODEL) asm volatile("" : "+v"(vm[u]));
+        }
+        if (second) add();
     };
     float fo[2][kQU], ff[2][kQU], fm[2][kQU];
     load(blockIdx.x, fo[0], ff[0], fm[0]);
@@ -495,7 +508,9 @@ extern "C" ig_status ig_quality(const ig_quality_params* q, const float* d_orig,
             HIP_TRY(hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         // one round of workgroups: what the compute units hold with these bins
         const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(4, (kMaxLds - 2048) / lds));
-        const int blocks = (int)std::min<long>(256L * per_cu, (g.nroi + kQChunk - 1) / kQChunk);
+        int ncu = 256;
+        (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device);
+        const int blocks = (int)std::min<long>(std::min<long>((long)ncu * per_cu, kQMaxBlocks), (g.nroi + kQChunk - 1) / kQChunk);
         hipLaunchKernelGGL(k, dim3(blocks), dim3(256), lds, s, d_orig, d_filt, d_model, g, qsrt, qs.part);
         count = blocks;
     }

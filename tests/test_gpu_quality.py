@@ -192,3 +192,65 @@ def test_binned_nonfinite_and_large(dev):
     with np.errstate(invalid="ignore"):
         ref = Q.quality(orig, filt, None, thr_f=thr, rms_o=1.0, rms_f=1.0)
     _check(got, ref, orig, None, None)
+
+
+def _tree(v):
+    """A wavefront's sum: butterflies over 32, 16, .. 1 lanes."""
+    v = np.array(v, np.float64)
+    for o in (32, 16, 8, 4, 2, 1):
+        v = v + v[..., np.arange(64) ^ o]
+    return v[..., 0]
+
+
+def _binned_sums(orig, filt, model, thr, thr_o, blocks):
+    """The binned sums in their fixed order: a workgroup's chunks of 4096 voxels one
+    after another; in a chunk, each column (lanes l and l + 32 of a wavefront) takes
+    the 16 voxels of the lower lane, then those of the upper; columns, wavefronts
+    and bins in fixed trees; workgroups by the fold."""
+    n, thr = len(thr), np.sort(np.asarray(thr, np.float64))
+    o, f, m = (np.asarray(a, np.float32).ravel() for a in (orig, filt, model))
+    chunks = -(-o.size // 4096)
+    per = -(-chunks // blocks)
+
+    def lay(a, fill):
+        b = np.full(per * blocks * 4096, fill, np.float32)
+        b[:a.size] = a
+        return b.reshape(per, blocks, 16, 4, 2, 32)       # chunk turn, block, u, wavefront, half, column
+
+    bins = lay(np.searchsorted(thr, f.astype(np.float64), side="right").astype(np.float32), 0).astype(int)
+    bins[lay(np.ones_like(o), 0) == 0] = 0
+    out = []
+    bi, wi, ci = np.ix_(range(blocks), range(4), range(32))
+    for v in (lay(o, 0), lay(m, 0)):
+        acc = np.zeros((blocks, 4, 32, n + 1))
+        for t in range(per):
+            for h in range(2):
+                for u in range(16):
+                    acc[bi, wi, ci, bins[t, :, u, :, h]] += v[t, :, u, :, h].astype(np.float64)
+        lanes = np.concatenate([(0.0 + acc[:, 0]) + acc[:, 2], (0.0 + acc[:, 1]) + acc[:, 3]], axis=1)   # (block, 64, bin)
+        tot = _tree(np.moveaxis(lanes, 1, 2))[:, 1:]
+        part = np.zeros((blocks, n))
+        for j in range(n):
+            for b in range(j, n):
+                part[:, j] += tot[:, b]
+        thread = np.zeros((n, 256))
+        for k in range(blocks):
+            thread[:, k % 256] += part[k]
+        w = _tree(thread.reshape(n, 4, 64))
+        out.append(((w[:, 0] + w[:, 1]) + w[:, 2]) + w[:, 3])
+    return out
+
+
+@pytest.mark.parametrize("shape,k,blocks", [((30, 45, 70), 12, 24), ((64, 200, 300), 40, 256), ((64, 200, 300), 9, 938)])
+def test_binned_sums_in_their_order(dev, shape, k, blocks):
+    """Values over many magnitudes, so that any other order of the FP64 sums gives
+    other bits."""
+    import paper_1609_03782_amd as ig
+    rng = np.random.default_rng(k)
+    orig = (rng.standard_normal(shape) * 10.0 ** rng.uniform(-12, 12, shape)).astype(np.float32)
+    filt = rng.standard_normal(shape).astype(np.float32)
+    model = (rng.standard_normal(shape) * 10.0 ** rng.uniform(-12, 12, shape)).astype(np.float32)
+    thr = tuple(np.linspace(-1.0, 2.0, k))
+    got = ig.quality(_t(orig, dev), _t(filt, dev), _t(model, dev), thr_f=thr, thr_o=1.0, rms_o=1.0, rms_f=1.0)
+    so, sm = _binned_sums(orig, filt, model, thr, 1.0, blocks)
+    assert got["S_of"] == list(so) and got["S_mf"] == list(sm)
