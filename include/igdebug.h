@@ -49,6 +49,14 @@ int32_t ig_debug_tune_candidates(const ig_params* p, int32_t ncu, ig_schedule* o
  * handle's passes of this depth run with; zeros before the first.  Host only. */
 ig_status ig_debug_filter_layout(const ig_filter* f, int32_t depth, int32_t* layout);
 
+/* The form of ig_smooth's rotated kernel: 0 the general one, 1 and 2 columns with
+ * one and two output rows per thread, 3 columns in the least LDS.  The first
+ * fixes the form of later calls where its tile fits (-1: the library's choice;
+ * process-wide), the second returns the form chosen for half-widths radius[3] on
+ * a cube and ncu compute units (-1: refused).  Host only. */
+ig_status ig_debug_set_dense_form(int32_t form);
+int32_t ig_debug_dense_form(const int32_t* radius, int64_t nx, int64_t ny, int64_t nz, int32_t ncu);
+
 #ifdef __cplusplus
 }
 #endif

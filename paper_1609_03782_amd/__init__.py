@@ -145,6 +145,9 @@ SIGNATURES = {
     "ig_debug_live_allocations": (ctypes.c_int64, []),
     "ig_debug_release_caches": (None, []),
     "ig_debug_set_infer_piece_limit": (ctypes.c_int64, [ctypes.c_int64]),
+    "ig_debug_set_dense_form": (ctypes.c_int, [ctypes.c_int32]),
+    "ig_debug_dense_form": (ctypes.c_int32, [ctypes.POINTER(ctypes.c_int32), ctypes.c_int64, ctypes.c_int64, ctypes.c_int64,
+                                             ctypes.c_int32]),
     "ig_debug_filter_layout": (ctypes.c_int, [_P, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)]),
     "ig_debug_tune_candidates": (ctypes.c_int32, [ctypes.POINTER(IgParams), ctypes.c_int32, ctypes.POINTER(IgSchedule),
                                                   ctypes.c_int32]),

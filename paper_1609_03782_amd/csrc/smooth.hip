@@ -21,6 +21,7 @@
 #include <cmath>
 #include <type_traits>
 
+#include "igdebug.h"
 #include "igsmooth.h"
 #include "internal.h"
 
@@ -634,10 +635,18 @@ template <int RZ>
 __device__ __forceinline__ int dense_chunk(int x, int i) {
     return dense_column(RZ) == 16 ? (4 * i) ^ (x & 12) : 4 * i;
 }
-template <int RZ, int YO>
+// LEAN: for tiles that only fit without what the other forms add to them (the padding
+// of a column, the 64 floats, the sums over dz): columns of NC floats in pieces of
+// two, the sums made from the weights as they pass.  Half-widths 9, 9, 6 on 200 x 200
+// x 200 2.8 ms; the general kernel, a weight and an activation from LDS per product,
+// takes 18.1, the columns before they were padded 6.8.
+template <int RZ, int YO, bool LEAN = false>
 __global__ void __launch_bounds__(256)
 k_dense_t(const float* __restrict__ src, float* __restrict__ dst, DenseGeom g) {
-    constexpr int TZ = 8, KZ = 2 * RZ + 1, NC = TZ + 2 * RZ, TY = 4 * YO, ZS = dense_column(RZ);
+    constexpr int TZ = 8, KZ = 2 * RZ + 1, NC = TZ + 2 * RZ, TY = 4 * YO, ZS = LEAN ? NC : dense_column(RZ);
+    constexpr int CW = LEAN ? 2 : 4;            // floats of a column's chunk
+    typedef float chunk __attribute__((ext_vector_type(CW)));
+    auto place = [](int x, int i) { return LEAN ? CW * i : dense_chunk<RZ>(x, i); };
     extern __shared__ float4 sm4[];
     const int rx = g.rx, ry = g.ry;
     const int kx = 2 * rx + 1, ky = 2 * ry + 1;
@@ -646,7 +655,7 @@ k_dense_t(const float* __restrict__ src, float* __restrict__ dst, DenseGeom g) {
     const int cols = TXh * TYh;
     float* T = reinterpret_cast<float*>(sm4);   // [y][x][z]: a column's NC values together, ZS apart
     float* W = T + cols * ZS;                   // [dx][dy][dz], then 64 floats that a read of 64 may reach
-    float* S = W + nw + 64;                     // [dx][dy]: the sums over dz
+    float* S = W + nw + 64;                     // [dx][dy]: the sums over dz (not LEAN)
     __shared__ float total_sh;
     const int tx = threadIdx.x, ty = threadIdx.y, tid = ty * 64 + tx;
     const long x0 = (long)blockIdx.x * 64, y0 = (long)blockIdx.y * TY, z0 = (long)blockIdx.z * TZ;
@@ -685,8 +694,12 @@ k_dense_t(const float* __restrict__ src, float* __restrict__ dst, DenseGeom g) {
             v[i] = in && z >= 0 && z < g.nz ? f : 0.0f;
         }
 #pragma unroll
-        for (int i = 0; i < ZS / 4; ++i)
-            *reinterpret_cast<float4*>(T + q * ZS + dense_chunk<RZ>(qx, i)) = make_float4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
+        for (int i = 0; i < ZS / CW; ++i) {
+            chunk f;
+#pragma unroll
+            for (int e = 0; e < CW; ++e) f[e] = v[CW * i + e];
+            *reinterpret_cast<chunk*>(T + q * ZS + place(qx, i)) = f;
+        }
     }
     __syncthreads();
     // the total weight, in a fixed order (strided partials, then a tree), and, for
@@ -696,7 +709,7 @@ k_dense_t(const float* __restrict__ src, float* __restrict__ dst, DenseGeom g) {
         for (int t = tid; t < kx * ky; t += 64) {
             float sz = 0.0f;
             for (int k = 0; k < KZ; ++k) sz += W[t * KZ + k];
-            S[t] = sz;
+            if constexpr (!LEAN) S[t] = sz;
             s += sz;
         }
         for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
@@ -704,7 +717,7 @@ k_dense_t(const float* __restrict__ src, float* __restrict__ dst, DenseGeom g) {
     }
     const bool edge_xy = x0 - rx < 0 || x0 + 63 + rx >= g.nx || y0 - ry < 0 || y0 + TY - 1 + ry >= g.ny;
     const bool edge_z = z0 - RZ < 0 || z0 + TZ - 1 + RZ >= g.nz;
-    if (edge_xy) __syncthreads();   // S is read below (the same for the whole workgroup)
+    if (!LEAN && edge_xy) __syncthreads();   // S is read below (the same for the whole workgroup)
     float acc[YO][TZ], sw[YO][KZ];
 #pragma unroll
     for (int o = 0; o < YO; ++o) {
@@ -721,19 +734,20 @@ k_dense_t(const float* __restrict__ src, float* __restrict__ dst, DenseGeom g) {
         constexpr int EDGE = decltype(edge_c)::value;
         for (int dx = -rx; dx <= rx; ++dx) {
             const int xq = tx + rx + dx;
-            const float* col[ZS / 4];
+            const float* col[ZS / CW];
 #pragma unroll
-            for (int i = 0; i < ZS / 4; ++i) col[i] = T + (YO * ty * TXh + xq) * ZS + dense_chunk<RZ>(xq, i);
-            const float* wp = W + (dx + rx) * ky * KZ + (tid & 63);
+            for (int i = 0; i < ZS / CW; ++i) col[i] = T + (YO * ty * TXh + xq) * ZS + place(xq, i);
+            const float* wp = W + (dx + rx) * ky * KZ + (LEAN ? min(tid & 63, KZ - 1) : tid & 63);
             const float* sp = S + (dx + rx) * ky;
             const bool in_x = x0 + tx + dx >= 0 && x0 + tx + dx < g.nx;
             float ca[ZS], cb[ZS], wn, wa[KZ], wb[KZ], sa = 0.0f, sb = 0.0f;
             int yy = (int)(y0 + YO * ty) - ry;
             auto fetch = [&](float (&c)[ZS]) {               // the next row of the column
 #pragma unroll
-                for (int i = 0; i < ZS / 4; ++i) {
-                    const float4 f = *reinterpret_cast<const float4*>(col[i]);
-                    c[4 * i] = f.x; c[4 * i + 1] = f.y; c[4 * i + 2] = f.z; c[4 * i + 3] = f.w;
+                for (int i = 0; i < ZS / CW; ++i) {
+                    const chunk f = *reinterpret_cast<const chunk*>(col[i]);
+#pragma unroll
+                    for (int e = 0; e < CW; ++e) c[CW * i + e] = f[e];
                     col[i] += TXh * ZS;
                 }
             };
@@ -744,8 +758,16 @@ k_dense_t(const float* __restrict__ src, float* __restrict__ dst, DenseGeom g) {
 #pragma unroll
                     for (int k = 0; k < KZ; ++k) wa[k] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wn), k));
                     wp += KZ;
-                    wn = *wp;                                // (past the last row: the 64 floats)
-                    if constexpr (EDGE == 1) sa = *sp++;
+                    if constexpr (!LEAN || decltype(nextc)::value) wn = *wp;   // (past the last row: the 64 floats)
+                    if constexpr (EDGE == 1) {
+                        if constexpr (LEAN) {
+                            sa = 0.0f;
+#pragma unroll
+                            for (int k = 0; k < KZ; ++k) sa += wa[k];
+                        } else {
+                            sa = *sp++;
+                        }
+                    }
                 }
                 if constexpr (decltype(nextc)::value) fetch(cn);
                 const bool in = in_x && yy >= 0 && yy < (int)g.ny;
@@ -937,28 +959,36 @@ bool overlaps(const void* a, const void* b, size_t bytes) {
 using DenseKernel = void (*)(const float*, float*, DenseGeom);
 
 // the register-column kernel for z half-widths 1..8 with YO output rows per thread
-template <int YO>
+template <int YO, bool LEAN = false>
 DenseKernel dense_t_kernel(int rz) {
     switch (rz) {
-        case 1: return k_dense_t<1, YO>;
-        case 2: return k_dense_t<2, YO>;
-        case 3: return k_dense_t<3, YO>;
-        case 4: return k_dense_t<4, YO>;
-        case 5: return k_dense_t<5, YO>;
-        case 6: return k_dense_t<6, YO>;
-        case 7: return k_dense_t<7, YO>;
-        case 8: return k_dense_t<8, YO>;
+        case 1: return k_dense_t<1, YO, LEAN>;
+        case 2: return k_dense_t<2, YO, LEAN>;
+        case 3: return k_dense_t<3, YO, LEAN>;
+        case 4: return k_dense_t<4, YO, LEAN>;
+        case 5: return k_dense_t<5, YO, LEAN>;
+        case 6: return k_dense_t<6, YO, LEAN>;
+        case 7: return k_dense_t<7, YO, LEAN>;
+        case 8: return k_dense_t<8, YO, LEAN>;
         default: return nullptr;
     }
 }
 
-hipError_t launch_dense(const SmoothPlan& p, int tz, const float* in, float* out, const DenseGeom& g, hipStream_t st) {
-    int rows = 4;
-    DenseKernel k = tz == 8 ? k_dense<8> : tz == 4 ? k_dense<4> : tz == 2 ? k_dense<2> : k_dense<1>;
-    size_t lds = dense_lds(p, tz);
+// Planes of a tile of the rotated kernel: the most whose tile fits (0: none).
+int dense_planes(const SmoothPlan& p) {
+    for (int c : {8, 4, 2, 1})
+        if (dense_lds(p, c) + 256 <= kMaxLds) return c;   // + the static total slot
+    return 0;
+}
+
+// The rotated kernel's form for tiles of tz planes, and its tile's LDS.
+enum { kDenseGeneral = 0, kDenseOneRow = 1, kDenseTwoRows = 2, kDenseLean = 3 };
+int g_dense_form = -1;   // a test's choice, where its tile fits
+int dense_form(const SmoothPlan& p, int tz, const DenseGeom& g, int ncu, size_t* lds) {
+    *lds = dense_lds(p, tz);
     if (tz == 8 && g.rz >= 1 && g.rz <= 8) {
-        // the column kernel where its tile fits, with two rows per thread while
-        // two workgroups' tiles share a compute unit
+        // the column kernel, with two rows per thread while two workgroups' tiles share
+        // a compute unit, and lean where its tile does not fit otherwise
         const long kx = 2 * g.rx + 1, ky = 2 * g.ry + 1, kz = 2 * g.rz + 1;
         auto need = [&](int r) {
             return ((size_t)kx * ky * (kz + 1) + 64 +
@@ -973,8 +1003,6 @@ hipError_t launch_dense(const SmoothPlan& p, int tz, const float* in, float* out
         // unit (4, the registers' limit, against 2): half-widths 3, 2, 3 on 400 x 300 x
         // 200 459 -> 423 us, on 840 x 274 x 102 445 -> 429; 4, 2, 4 606 -> 583; with 3
         // against 2 (3, 3, 3 on 634 x 98 x 314) two rows are faster, 431 against 445.
-        int dev = 0, ncu = 256;
-        if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
         auto cost = [&](int yo) {
             const long r = 4 * yo, wgs = ((g.nx + 63) / 64) * ((g.ny + r - 1) / r) * ((g.nz + 7) / 8);
             const long work = kx * (yo * ky * 8 * kz + (ky + yo - 1) * (kz + 9)) +
@@ -984,15 +1012,30 @@ hipError_t launch_dense(const SmoothPlan& p, int tz, const float* in, float* out
         const bool two = 2 * (need(8) + 256) <= kMaxLds && g.ny > 4;
         const bool one = need(4) + 256 <= kMaxLds;
         auto resident = [&](int r) { return std::min<size_t>(4, kMaxLds / (need(r) + 256)); };
-        if (two && !(one && (cost(1) < 0.95 * cost(2) || resident(4) >= 2 * resident(8)))) {
-            rows = 8;
-            k = dense_t_kernel<2>(g.rz);
-            lds = need(8);
-        } else if (one) {
-            k = dense_t_kernel<1>(g.rz);
-            lds = need(4);
-        }
+        const bool rather_one = one && (cost(1) < 0.95 * cost(2) || resident(4) >= 2 * resident(8));
+        int form = two && !rather_one ? kDenseTwoRows : one ? kDenseOneRow : kDenseLean;
+        if (g_dense_form == kDenseGeneral || g_dense_form == kDenseLean || (g_dense_form == kDenseOneRow && one) ||
+            (g_dense_form == kDenseTwoRows && need(8) + 256 <= kMaxLds))
+            form = g_dense_form;
+        if (form == kDenseTwoRows) *lds = need(8);
+        if (form == kDenseOneRow) *lds = need(4);
+        return form;
     }
+    return kDenseGeneral;
+}
+
+hipError_t launch_dense(const SmoothPlan& p, int tz, const float* in, float* out, const DenseGeom& g, hipStream_t st) {
+    int dev = 0, ncu = 256;
+    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+    size_t lds;
+    const int form = dense_form(p, tz, g, ncu, &lds), rows = form == kDenseTwoRows ? 8 : 4;
+    const DenseKernel k = form == kDenseTwoRows ? dense_t_kernel<2>(g.rz)
+                          : form == kDenseOneRow ? dense_t_kernel<1>(g.rz)
+                          : form == kDenseLean   ? dense_t_kernel<1, true>(g.rz)
+                          : tz == 8              ? k_dense<8>
+                          : tz == 4              ? k_dense<4>
+                          : tz == 2              ? k_dense<2>
+                                                 : k_dense<1>;
     if (lds > 65536) {
         hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
@@ -1073,12 +1116,7 @@ extern "C" ig_status ig_smooth(const ig_smooth_params* s, const float* d_in, flo
         if (e != hipSuccess) return fail(IG_ERR_DEVICE, "z pass: %s", hipGetErrorString(e));
         return IG_OK;
     }
-    int tz = 0;
-    for (int c : {8, 4, 2, 1})
-        if (dense_lds(p, c) + 256 <= kMaxLds) {   // + the static total slot
-            tz = c;
-            break;
-        }
+    const int tz = dense_planes(p);
     if (!tz) return fail(IG_ERR_UNSUPPORTED, "rotated kernel half-widths %d,%d,%d need more LDS than a CU has",
                          p.r[0], p.r[1], p.r[2]);
     if ((ny + 3) / 4 > 65535 || (nz + tz - 1) / tz > 65535) return fail(IG_ERR_UNSUPPORTED, "cube too tall");
@@ -1087,6 +1125,21 @@ extern "C" ig_status ig_smooth(const ig_smooth_params* s, const float* d_in, flo
     const hipError_t e = launch_dense(p, tz, d_in, d_out, g, st_);
     if (e != hipSuccess) return fail(IG_ERR_DEVICE, "dense pass: %s", hipGetErrorString(e));
     return IG_OK;
+}
+
+extern "C" ig_status ig_debug_set_dense_form(int32_t form) {
+    if (form < -1 || form > kDenseLean) return fail(IG_ERR_INVALID_ARG, "form must be in -1..3");
+    g_dense_form = form;
+    return IG_OK;
+}
+
+extern "C" int32_t ig_debug_dense_form(const int32_t* radius, int64_t nx, int64_t ny, int64_t nz, int32_t ncu) {
+    if (!radius || nx < 1 || ny < 1 || nz < 1 || ncu < 1) return -1;
+    SmoothPlan p{};
+    for (int a = 0; a < 3; ++a) p.r[a] = std::max(0, radius[a]);
+    const int tz = dense_planes(p);
+    size_t lds;
+    return tz ? dense_form(p, tz, DenseGeom{nx, ny, nz, p.r[0], p.r[1], p.r[2]}, ncu, &lds) : -1;
 }
 
 extern "C" ig_status ig_smooth_set_path(int32_t path) {
