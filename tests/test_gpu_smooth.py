@@ -172,3 +172,33 @@ def test_rotated_column_form(dev, fz, fxy):
         ref = Sm.smooth(cube, _kernel("gauss", (fxy, 1.2 * fxy, fz), theta))
         err = np.abs(y.cpu().numpy() - ref).max()
         assert err <= _tol(cube, "gauss", theta), (shape, err)
+
+
+# the rotated kernel's forms, each forced: one row per thread, two, and the least
+# LDS, for every z half-width; whole tiles, remainders of 1, 5 and 8 rows, tiles with
+# faces in x, y and z and one without
+@pytest.mark.parametrize("fz", [0.6, 1.3, 2.0, 2.8, 3.6, 4.4, 5.2, 6.0])
+@pytest.mark.parametrize("fxy", [1.5, 3.0])
+def test_rotated_forms(dev, fz, fxy):
+    import ctypes
+    import torch
+    import paper_1609_03782_amd as ig
+    L, theta = ig.lib(), (0.0, 0.0, 30.0)
+    k = _kernel("gauss", (fxy, 1.2 * fxy, fz), theta)
+    rz, ry, rx = (n // 2 for n in np.asarray(k).shape)
+    assert 1 <= rz <= 8
+    try:
+        for shape in ((16, 16, 128), (9, 5, 70), (17, 8, 64), (10, 9, 65), (7, 3, 40), (40, 40, 200)):
+            cube = igsynth.random_cube(shape, seed=int(10 * fz) + shape[1])
+            x = torch.from_numpy(cube).to(dev)
+            ref, out = Sm.smooth(cube, k), {}
+            for form in (1, 2, 3):
+                assert L.ig_debug_set_dense_form(form) == 0
+                assert L.ig_debug_dense_form((ctypes.c_int32 * 3)(rx, ry, rz), shape[2], shape[1], shape[0], 256) == form
+                out[form] = ig.smooth(x, "gauss", (fxy, 1.2 * fxy, fz), theta)
+                err = np.abs(out[form].cpu().numpy() - ref).max()
+                assert err <= _tol(cube, "gauss", theta), (shape, form, err)
+            # the same tiles and sums (two rows: other tiles are at a face, whose divisor is summed in another order)
+            assert torch.equal(out[1], out[3])
+    finally:
+        L.ig_debug_set_dense_form(-1)
