@@ -288,3 +288,59 @@ def test_automatic_layout_follows_the_compute_units():
         differ += first[32] != first[256]
         assert first[256] == ig.schedule_auto(shape, n_iter=6)
     assert differ >= 3
+
+
+def _best_us(f, n=300, rounds=9):
+    import time
+    best = 1e9
+    for _ in range(rounds):
+        t = time.perf_counter()
+        for _ in range(n):
+            f()
+        best = min(best, (time.perf_counter() - t) / n)
+    return 1e6 * best
+
+
+def test_balanced_plan_costs_little_more_than_a_grid():
+    """A handle's first run waits for its plan: the balanced split of a small cube takes
+    at most a few times as long as a regular grid of as many pieces."""
+    import ctypes
+    L, shape = ig.lib(), (32, 64, 64)
+    p = ig.make_params(shape)
+    geom, count = (ctypes.c_int32 * 9)(), ctypes.c_int64()
+
+    def plan(s):
+        assert L.ig_schedule_plan(ctypes.byref(p), ctypes.byref(s), 2, 256, geom, None, 0, ctypes.byref(count)) == 0
+        return count.value
+
+    auto = ig.IgSchedule()
+    assert L.ig_schedule_auto(ctypes.byref(p), ctypes.byref(auto)) == 0
+    grid = ig.IgSchedule(auto.kind, auto.t_block, auto.waves, 1, auto.vec, auto.rounds, auto.rows)
+    n, m = plan(auto), plan(grid)
+    assert n == 256 and m == 256
+    assert _best_us(lambda: plan(auto)) < 3.0 * _best_us(lambda: plan(grid)) + 2.0
+
+
+@pytest.mark.parametrize("shape,kw", [((32, 64, 64), {}), ((149, 181, 187), {}), ((30, 300, 700), {}), ((5, 3, 300), {}),
+                                      ((61, 700, 1000), dict(cond="pm_rational")), ((7, 90, 40), dict(dtype="bf16"))])
+@pytest.mark.parametrize("ncu", [256, 32, 7])
+def test_balanced_plan_order(shape, kw, ncu):
+    """The pieces of the balanced split: as many a tile as the workgroups allow, the
+    first tiles one more; by the eighth of the planes that holds a piece's middle,
+    then by tile; every eighth of that order on one XCD."""
+    s = ig.schedule_auto(shape, n_iter=1, **kw)
+    g, pcs = ig.schedule_plan(shape, s, 1, ncu=ncu, n_iter=1, **kw)
+    if ig.schedule_plan_groups(shape, s, 1, ncu=ncu, n_iter=1, **kw) is not None:
+        return
+    tiles, nz, n = g["ntx"] * g["nty"], shape[0], len(pcs)
+    want = []
+    for i in range(tiles):
+        c = n // tiles + (i < n % tiles)
+        for k in range(c):
+            z0, z1 = k * nz // c, (k + 1) * nz // c
+            want.append((4 * (z0 + z1) // nz, i // g["ntx"], i % g["ntx"], z0, z1))
+    want.sort(key=lambda t: t[:3])
+    got = [tuple(int(v) for v in q) for q in pcs]
+    if n % 8 == 0:
+        got = [got[8 * (k % (n // 8)) + k // (n // 8)] for k in range(n)]
+    assert got == [(tx, ty, z0, z1) for _, ty, tx, z0, z1 in want]
