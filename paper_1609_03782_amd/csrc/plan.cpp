@@ -153,7 +153,7 @@ double step_weight(int V, int R, int waves, bool ragged) { return step_us(kCost3
 // 564 -> 756, 600 x 400 x 200 419 -> 603 Gvoxel-iter/s.  Odd chunks exist for FP32
 // only (16-bit rows move in whole 32-bit words).
 constexpr double kGain = 1.10, kGainUnsure = 1.25;
-void auto_layout(const ig_params& p, int T, int ncu, bool grouped, int* V, int* R, int* W) {
+void auto_layout(const ig_params& p, int T, int ncu, bool grouped, int* V, int* R, int* W, bool lower_gains) {
     auto_vec_rows(p.nx, V, R);
     *W = 12;
     if (stream_lds_bytes(*V, T, *W) > kMaxLds) *W = 8;
@@ -171,7 +171,8 @@ void auto_layout(const ig_params& p, int T, int ncu, bool grouped, int* V, int* 
             for (int w : {3, 4, 5, 6, 8, 10, 12, 16}) {
                 if (v == 8 && (w != 12 || !wide)) continue;
                 const double c = pass_cost(p, v, r, w, T, ncu, grouped);
-                const double gain = one_y || 64 / r * v < p.nx ? kGainUnsure : kGain;
+                const double gain = lower_gains ? (p.dtype == IG_F32 ? 1 / 0.95 : 1 / 0.90)
+                                    : one_y || 64 / r * v < p.nx ? kGainUnsure : kGain;
                 if (c * gain < base && c < best) {
                     best = c;
                     *V = v; *R = r; *W = w;
@@ -241,12 +242,13 @@ const char* plan_pass(const ig_params& p, const ig_schedule& s, int T, int ncu, 
     if (!(V == 1 || V == 2 || V == 4 || V == 8)) {
         // the other chunks only as the automatic schedule chooses them (for passes
         // of depth 1 or 2, with or without grouped plans, on this many compute units
-        // or a whole GPU's); deeper passes of a schedule that names one run the
-        // power-of-two layout
+        // or a whole GPU's) or chose them when it asked for lower gains, so that a
+        // schedule that was reported then still serves; deeper passes of a schedule that
+        // names one run the power-of-two layout
         bool ours = any_chunk;
-        for (int k = 0; k < 8 && !ours; ++k) {
+        for (int k = 0; k < 16 && !ours; ++k) {
             int av, ar, aw;
-            auto_layout(p, 1 + (k & 1), k < 4 ? ncu : kFullCus, k & 2, &av, &ar, &aw);
+            auto_layout(p, 1 + (k & 1), k & 4 ? kFullCus : ncu, k & 2, &av, &ar, &aw, k & 8);
             ours = V == av && R == ar;
         }
         if (!ours) return "vec must be 1, 2, 4 or 8";

@@ -62,7 +62,8 @@ struct PassPlan {
 void auto_vec_rows(int64_t nx, int* V, int* R);
 // voxels per lane, rows per wavefront and wavefronts of the automatic schedule's
 // passes of depth T on ncu compute units; grouped: its workgroups may take grouped plans
-void auto_layout(const ig_params& p, int T, int ncu, bool grouped, int* V, int* R, int* W);
+// (lower_gains: with the gains once asked for, whose layouts are still accepted)
+void auto_layout(const ig_params& p, int T, int ncu, bool grouped, int* V, int* R, int* W, bool lower_gains = false);
 constexpr int kFullCus = 256;   // compute units of a whole MI355X: what host-only queries plan for
 int resident_per_cu(int W, size_t lds);
 // nullptr on success, else the reason schedule s cannot serve p at depth T

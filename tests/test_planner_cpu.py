@@ -344,3 +344,13 @@ def test_balanced_plan_order(shape, kw, ncu):
     if n % 8 == 0:
         got = [got[8 * (k % (n // 8)) + k // (n // 8)] for k in range(n)]
     assert got == [(tx, ty, z0, z1) for _, ty, tx, z0, z1 in want]
+
+
+@pytest.mark.parametrize("shape,kw,vec,rows,waves", [((345, 21, 40), dict(cond="intensity"), 3, 4, 4), ((66, 8, 801), {}, 5, 1, 8),
+                                                     ((270, 12, 328), dict(n_iter=1), 6, 1, 6),
+                                                     ((17, 56, 324), dict(dtype="f16", n_iter=1), 6, 1, 6)])
+def test_schedules_once_reported_are_accepted(shape, kw, vec, rows, waves):
+    """Layouts that the automatic schedule chose when it asked for lower gains."""
+    s = dict(kind="blocked", t_block=min(2, kw.get("n_iter", 2)), waves=waves, vec=vec, rows=rows)
+    assert ig.schedule_check(shape, s, **kw) is None
+    assert ig.schedule_check(shape, dict(s, vec=7 if shape[2] > 7 * 64 else 5 if vec != 5 else 3, rows=1), **kw) is not None
