@@ -203,8 +203,8 @@ k_lift_yz(const float* __restrict__ src, float* __restrict__ dst, LiftGeom g, in
 // three levels); LANES 8, B 16 serves narrow cubes and level 4, whose blocks
 // are 16 voxels wide.  An element whose partner lies past the box is its own
 // approximation, as in the passes.  512^3, three levels, noise level
-// estimated: 2081 us with the passes, 326 us with this kernel, of which 87 us
-// are the noise scan: the cube moves at 4.5 TB/s, a plain copy's 5.1 at best.
+// estimated: 2081 us with the passes, 334 us with this kernel, which itself takes
+// 175 (one read and one write, 6.1 TB/s); the noise scan is 116 of the rest.
 constexpr int kHaarMaxLevels = 4;
 constexpr int kHaarDenoise = 0, kHaarForward = 1, kHaarInverse = 2;
 
